@@ -100,7 +100,7 @@ typedef struct ss_paged_kv {
  *                earlier call built for exactly this batch (same block_table, kv_len, q_indptr contents,
  *                same max_q_len, head counts and workspace; only q, the cache contents and the outputs
  *                may differ): the layers of one decode step share their batch, so all but the first
- *                can skip the plan kernel.  Ignored where no stored plan can serve (the vector kernel,
+ *                can skip the plan kernel.  Ignored where no stored plan can serve (the fp32 kernel,
  *                or a row bound that takes several passes).  Other calls ignore the field.
  *   tree_mask    NULL: the new tokens of a request form a chain (row i attends new tokens 0..i).
  *                Otherwise device uint32 [total rows]: the new tokens form a draft tree (the dynamic
@@ -156,7 +156,7 @@ size_t ss_spec_verify_attn_workspace(const ss_paged_kv *kv, const ss_batch *batc
  * KV head.  One pass over the cache serves up to 80 query rows per KV head (max_q_len * heads per KV head:
  * depth 9 for groups of 8, depth 19 for groups of 4, any depth for smaller groups); a larger bound is
  * served in two or three passes over equal windows of query tokens, each reading the cache again.
- * Everything else takes a plain fp32 vector kernel that has no shape limits and is far slower.
+ * Everything else takes an fp32 kernel (fp32 matrix instructions, any depth in one pass) that is slower.
  * batch == 0 or total_rows == 0 is a no-op returning SS_OK.
  */
 int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const void *q, int32_t q_dtype,
@@ -374,7 +374,7 @@ int32_t ss_route_select(const ss_worker_metrics *workers, int32_t n, const doubl
 
 /*
  * Options (process-wide, not thread-safe; meant for tests and measurement).
- *   "attn_path"     0 = automatic, 1 = force the plain fp32 vector kernel, 2 = require the MFMA kernel
+ *   "attn_path"     0 = automatic, 1 = force the fp32 kernel, 2 = require the MFMA kernel
  *   "attn_waves"    number of KV stream partitions (wavefronts) of the MFMA kernel, 0 = automatic
  *   "attn_unit_weight"  what opening a (request, KV head) unit is taken to cost a wavefront, in KV tiles, when the
  *                   KV stream is cut into partitions (default 3; 0 = partitions of equal tile counts)

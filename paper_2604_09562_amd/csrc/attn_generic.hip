@@ -1,121 +1,271 @@
-// Plain fp32 vector-ALU verify attention: the path for fp32 caches/queries, head_dim 64 and any
-// head grouping the matrix-core kernel is not built for.  One 256-lane workgroup per
-// (query row, query head); every lane walks its own tokens with a running (max, sum, output)
-// triple and the 256 triples are merged at the end.  All arithmetic is fp32.
+// fp32 verify attention: the path for fp32 caches or queries, head_dim 64 and any head grouping the bf16
+// matrix-core kernel is not built for.  All arithmetic is fp32 (fp32 matrix instructions, fp32 probabilities).
+//
+// One workgroup per (request, KV head, block of 16 query rows); its wavefronts take the request's 16-token cache
+// blocks in turn and are merged through LDS by their log-sum-exp.  A wavefront works on one block at a time:
+//   S^T[token][row] = K[token][:] . Q[row][:]    v_mfma_f32_16x16x4_f32, a lane holds D/4 consecutive d of a token
+//   O^T[d][row]    += V[token][d] * P[row][token] the same shape; step i contracts tokens {4 jq + i}, so that P is
+//                                                taken straight from the S^T accumulators
+// What bounds it: short calls are a chain of dependent reads (offsets, block table, keys, values) and the merge, so
+// many wavefronts per workgroup with the next block's tile in flight; long ones the fp32 matrix rate (D/2
+// instructions of 32 cycles per block and 16 rows).  4 requests of 64..512 tokens, 8 heads of 64, depth 4: 57 us
+// with one workgroup per (row, head) and one token per lane, 12 us (a pass among others, as the host enqueues it) with this one.
 #include "common.h"
 
 namespace ss {
 namespace {
 
-__device__ __forceinline__ float load_as_float(const void *p, int64_t i, int dtype)
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+
+constexpr float kNoRef = -1.0e30f;   // softmax reference before any visible score
+
+// Wavefronts per workgroup, as many as the registers of a compute unit hold (four on a SIMD at head_dim 64, two at 128).
+template <int D>
+constexpr int kGenericWaves = D == 64 ? 16 : 8;
+
+template <int DT, int N>
+__device__ __forceinline__ void load_run(const void *base, int64_t i, float (&x)[N])
 {
-    if (dtype == SS_F32) return static_cast<const float *>(p)[i];
-    if (dtype == SS_BF16) {
-        uint32_t w = (uint32_t) static_cast<const uint16_t *>(p)[i] << 16;
-        return __uint_as_float(w);
+    // N consecutive elements from index i (a multiple of N; every run starts on a multiple of its own size)
+    if constexpr (DT == SS_F32) {
+        const float4v *p = reinterpret_cast<const float4v *>(static_cast<const float *>(base) + i);
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j) {
+            const float4v v = p[j];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[4 * j + c] = v[c];
+        }
+    } else if constexpr (DT == SS_BF16) {
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(static_cast<const uint16_t *>(base) + i);
+        uint32_t w[N / 2];
+        __builtin_memcpy(w, __builtin_assume_aligned(p, N >= 8 ? 16 : 2 * N), 2 * N);
+#pragma unroll
+        for (int j = 0; j < N / 2; ++j) {
+            x[2 * j] = __uint_as_float(w[j] << 16);
+            x[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+        }
+    } else {
+        const uint8_t *p = static_cast<const uint8_t *>(base) + i;
+        uint32_t w[N / 4];
+        __builtin_memcpy(w, __builtin_assume_aligned(p, N >= 16 ? 16 : N), N);
+#pragma unroll
+        for (int j = 0; j < N / 4; ++j) {   // e4m3fn bytes: the gfx950 converter implements the OCP format
+            const float2v a = __builtin_amdgcn_cvt_pk_f32_fp8(w[j], false), b = __builtin_amdgcn_cvt_pk_f32_fp8(w[j], true);
+            x[4 * j] = a.x; x[4 * j + 1] = a.y; x[4 * j + 2] = b.x; x[4 * j + 3] = b.y;
+        }
     }
-    // e4m3fn byte: the gfx950 converter implements the OCP format
-    return __builtin_amdgcn_cvt_f32_fp8((uint32_t) static_cast<const uint8_t *>(p)[i], 0);
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void attn_generic_kernel(AttnArgs a)
+struct GenericTile {
+    float k[D / 4];         // key of token (lane & 15) at d = (lane >> 4) * D/4 ..
+    float v[4][D / 16];     // values of tokens 4 * (lane >> 4) + i at d = (lane & 15) * D/16 ..
+    float ks, vs;
+};
+
+template <int D, int KV, int QDT>
+__global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(AttnArgs a, int row_blocks)
 {
-    __shared__ float q_s[D];
-    __shared__ float red_m[4], red_l[4];
-    __shared__ float red_o[4][D];
+    constexpr int NW = kGenericWaves<D>, MB = D / 16;
+    __shared__ float part_o[NW][16][D + 4];
+    __shared__ float part_m[NW][16], part_l[NW][16];
 
-    const int row = blockIdx.x / a.num_q_heads;
-    const int h = blockIdx.x % a.num_q_heads;
+    const int rb = blockIdx.x % row_blocks, unit = blockIdx.x / row_blocks;
+    const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, jq = lane >> 4;
     const int G = a.num_q_heads / a.num_kv_heads;
-    const int g = h / G;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // request owning this row: largest b with q_indptr[b] <= row
-    int lo = 0, hi = a.batch;
-    while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (a.q_indptr[mid] <= row) lo = mid; else hi = mid;
-    }
-    const int b = lo;
-    const int q0 = a.q_indptr[b], q_len = a.q_indptr[b + 1] - q0;
+    const int q0 = a.q_indptr[b], q_len = a.q_indptr[b + 1] - q0, rows = q_len * G;
+    if (rb * 16 >= rows) return;
+    const int L = a.kv_len[b], ctx = L - q_len;
+    const int n = rb * 16 + n16, qi = min(n, rows - 1) / G, hh = n % G;   // this lane's query row (padding rows: the last one's mask)
     // Visible cache positions: everything before this step's new tokens, then the new tokens the
     // row's mask word names (its own node and its ancestors); for a chain those are tokens 0..i.
-    const int ctx = a.kv_len[b] - q_len;
-    const uint32_t newmask = a.tree_mask ? a.tree_mask[row] : (2u << (row - q0)) - 1u;
-    const int visible = ctx + 32 - __builtin_clz(newmask | 1u);  // one past the last visible position
-    const int64_t qoff = ((int64_t)row * a.num_q_heads + h) * D;
-
-    for (int d = tid; d < D; d += 256) q_s[d] = load_as_float(a.q, qoff + d, a.q_dtype);
-    __syncthreads();
-
-    float m = -INFINITY, l = 0.f;
-    float o[D];
-#pragma unroll
-    for (int d = 0; d < D; ++d) o[d] = 0.f;
-
+    const uint32_t newmask = a.tree_mask ? a.tree_mask[q0 + qi] : (2u << qi) - 1u;
+    // one past the last position any row of the block sees
+    const int qi_last = min(rb * 16 + 15, rows - 1) / G;
+    const int end = a.tree_mask ? L : ctx + qi_last + 1;
+    const int tiles = (end + kTile - 1) / kTile;
     const int32_t *bt = a.block_table + (int64_t)b * a.max_blocks;
-    for (int t = tid; t < visible; t += 256) {
-        if (t >= ctx && !((newmask >> (t - ctx)) & 1u)) continue;
-        const int64_t phys = bt[t / kTile];
-        const int64_t base = ((phys * a.num_kv_heads + g) * kTile + (t % kTile)) * D;
-        float s = 0.f;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d) s = fmaf(q_s[d], load_as_float(a.k, base + d, a.kv_dtype), s);
-        float vs = 1.f;
-        if (a.k_scale) {
-            s *= a.k_scale[phys * a.num_kv_heads + g];
-            vs = a.v_scale[phys * a.num_kv_heads + g];
+
+    float q[D / 4];   // B operand: lane holds its row's D/4 values at d = jq * D/4 ..
+#pragma unroll
+    for (int j = 0; j < D / 4; ++j) q[j] = 0.f;
+    if (n < rows) load_run<QDT>(a.q, ((int64_t)(q0 + qi) * a.num_q_heads + g * G + hh) * D + jq * (D / 4), q);
+
+    float m = kNoRef, l = 0.f;
+    float4v acc[MB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[mb] = float4v{0.f, 0.f, 0.f, 0.f};
+
+    // The next tile's keys are requested once this tile's scores are formed and its values once they are used, so
+    // that one tile's registers hold both and a read is always in flight under the arithmetic.
+    GenericTile<D> t;
+    auto load_k = [&](int phys) __attribute__((always_inline)) {
+        const int64_t addr = (int64_t)phys * a.num_kv_heads + g;
+        load_run<KV>(a.k, (addr * kTile + n16) * D + jq * (D / 4), t.k);
+        t.ks = KV == SS_FP8_E4M3 ? a.k_scale[addr] : 1.f;
+    };
+    auto load_v = [&](int phys) __attribute__((always_inline)) {
+        const int64_t addr = (int64_t)phys * a.num_kv_heads + g;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_run<KV>(a.v, (addr * kTile + 4 * jq + i) * D + n16 * MB, t.v[i]);
+        t.vs = KV == SS_FP8_E4M3 ? a.v_scale[addr] : 1.f;
+    };
+    // tile ti, whose keys and values are in t; `next` is the block of the wavefront's next tile, or -1
+    auto compute = [&](int ti, int next) __attribute__((always_inline)) {
+        const int tok0 = ti * kTile + 4 * jq;   // first of this lane's four positions
+        float4v s = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};   // (two chains: the instruction's latency is long)
+#pragma unroll
+        for (int j = 0; j < D / 4; j += 2) {
+            s = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[j], q[j], s, 0, 0, 0);
+            s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[j + 1], q[j + 1], s2, 0, 0, 0);
         }
-        s *= a.sm_scale;
-        const float m_new = fmaxf(m, s);
-        const float alpha = expf(m - m_new);  // exp(-inf) = 0 on the first token
-        const float p = expf(s - m_new);
-        l = l * alpha + p;
-        const float pv = p * vs;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d) o[d] = fmaf(pv, load_as_float(a.v, base + d, a.kv_dtype), o[d] * alpha);
-        m = m_new;
+        const float kscale = t.ks * a.sm_scale;
+        if (next >= 0) load_k(next);
+        const bool tail = ti * kTile + kTile > ctx;   // holds new tokens or slots past the end
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = (s[i] + s2[i]) * kscale;
+            if (tail) {
+                const int pos = tok0 + i - ctx;
+                const bool see = pos < 0 || (pos < 32 && ((newmask >> pos) & 1u));
+                p[i] = see ? p[i] : -INFINITY;
+            }
+        }
+        float mx = fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3]));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m, mx);
+        if (__any(m_new > m)) {
+            const float alpha = expf(m - m_new);
+            l *= alpha;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[mb] *= alpha;
+            m = m_new;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = expf(p[i] - m);
+        l += (p[0] + p[1]) + (p[2] + p[3]);
+        // Slots past the cache's end may hold anything; a new token some rows do not see may hold a non-finite
+        // value, which must not reach those rows through 0 * value: such a tile (rare) is added entry by entry.
+        bool odd = false;
+        if (tail) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < MB; ++c) {
+                    t.v[i][c] = tok0 + i < L ? t.v[i][c] : 0.f;
+                    odd |= !(fabsf(t.v[i][c]) <= 3.4e38f);
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] *= t.vs;
+        if (!__any(odd)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+                    acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.v[i][mb], p[i], acc[mb], 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                for (int tq = 0; tq < 4; ++tq) {   // token 4 * tq + i
+                    const float pt = __shfl(p[i], tq * 16 + n16);
+                    const bool see = __shfl(p[i] != 0.f || !(tok0 + i >= ctx), tq * 16 + n16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int mb = 0; mb < MB; ++mb) {
+                            const float vt = __shfl(t.v[i][mb], tq * 16 + 4 * jq + e);
+                            acc[mb][e] = see ? fmaf(vt, pt, acc[mb][e]) : acc[mb][e];
+                        }
+                }
+        }
+    };
+
+    // This wavefront's tiles are wave, wave + NW, ..: their block ids are read 64 at a time, one per lane.
+    for (int base = wave; base < tiles; base += 64 * NW) {
+        const int mine = base + lane * NW;
+        const int ids = bt[mine < tiles ? mine : base];
+        const int count = min(64, (tiles - base + NW - 1) / NW);
+        int cur = __builtin_amdgcn_readlane(ids, 0);
+        load_k(cur);
+        load_v(cur);
+        for (int i = 0; i < count; ++i) {
+            const int next = i + 1 < count ? __builtin_amdgcn_readlane(ids, i + 1) : -1;
+            compute(base + i * NW, next);
+            if (next >= 0) load_v(next);
+        }
     }
 
-    // merge the 256 per-lane states: common max, rescale, sum
-    float wm = m;
-    for (int off = 32; off; off >>= 1) wm = fmaxf(wm, __shfl_xor(wm, off));
-    if (lane == 0) red_m[wave] = wm;
-    __syncthreads();
-    const float gm = fmaxf(fmaxf(red_m[0], red_m[1]), fmaxf(red_m[2], red_m[3]));  // finite: visible >= 1
-    const float sc = (m == -INFINITY) ? 0.f : expf(m - gm);
-    float wl = l * sc;
-    for (int off = 32; off; off >>= 1) wl += __shfl_xor(wl, off);
-    if (lane == 0) red_l[wave] = wl;
+    // merge the wavefronts: accumulator row 4*jq+e of block mb is d = (4*jq+e) * MB + mb of row n16
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (jq == 0) {
+        part_m[wave][n16] = m;
+        part_l[wave][n16] = l;
+    }
 #pragma unroll
-    for (int d = 0; d < D; ++d) {
-        float x = o[d] * sc;
-        for (int off = 32; off; off >>= 1) x += __shfl_xor(x, off);
-        if (lane == 0) red_o[wave][d] = x;
-    }
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) part_o[wave][n16][(4 * jq + e) * MB + mb] = acc[mb][e];
     __syncthreads();
-    const float lsum = (red_l[0] + red_l[1]) + (red_l[2] + red_l[3]);
-    for (int d = tid; d < D; d += 256) {
-        const float x = ((red_o[0][d] + red_o[1][d]) + (red_o[2][d] + red_o[3][d])) / lsum;
+    const int used = min(NW, tiles);   // the other wavefronts had no tile
+    for (int i = tid; i < 16 * D; i += 64 * NW) {
+        const int r = i / D, d = i % D, nn = rb * 16 + r;
+        if (nn >= rows) continue;
+        float gm = part_m[0][r];
+        for (int w = 1; w < used; ++w) gm = fmaxf(gm, part_m[w][r]);
+        float ls = 0.f, o = 0.f;
+        for (int w = 0; w < used; ++w) {
+            const float sc = expf(part_m[w][r] - gm);
+            ls = fmaf(part_l[w][r], sc, ls);
+            o = fmaf(part_o[w][r][d], sc, o);
+        }
+        const int64_t orow = (int64_t)(q0 + nn / G) * a.num_q_heads + g * G + nn % G;
         if (a.q_dtype == SS_F32)
-            static_cast<float *>(a.out)[qoff + d] = x;
+            static_cast<float *>(a.out)[orow * D + d] = o / ls;
         else
-            static_cast<__bf16 *>(a.out)[qoff + d] = (__bf16)x;  // round to nearest even
+            static_cast<__bf16 *>(a.out)[orow * D + d] = (__bf16)(o / ls);  // round to nearest even
+        if (a.lse && d == 0) a.lse[orow] = gm + logf(ls);
     }
-    if (a.lse && tid == 0) a.lse[(int64_t)row * a.num_q_heads + h] = gm + logf(lsum);
+}
+
+template <int D, int KV>
+void launch_generic(const AttnArgs &a, int row_blocks, hipStream_t stream)
+{
+    const dim3 grid((unsigned)a.batch * a.num_kv_heads * row_blocks), wg(64 * kGenericWaves<D>);
+    if (a.q_dtype == SS_F32)
+        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_F32>), grid, wg, 0, stream, a, row_blocks);
+    else
+        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_BF16>), grid, wg, 0, stream, a, row_blocks);
+}
+
+template <int D>
+void launch_generic_kv(const AttnArgs &a, int row_blocks, hipStream_t stream)
+{
+    switch (a.kv_dtype) {
+    case SS_F32: launch_generic<D, SS_F32>(a, row_blocks, stream); break;
+    case SS_BF16: launch_generic<D, SS_BF16>(a, row_blocks, stream); break;
+    default: launch_generic<D, SS_FP8_E4M3>(a, row_blocks, stream);
+    }
 }
 
 }  // namespace
 
 int32_t attn_generic_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const unsigned grid = (unsigned)a.total_rows * (unsigned)a.num_q_heads;
+    const int row_blocks = (a.max_q_len * (a.num_q_heads / a.num_kv_heads) + 15) / 16;
+    if ((unsigned long long)a.batch * a.num_kv_heads * row_blocks > 0x7fffffffull)
+        return fail(SS_ERR_UNSUPPORTED, "batch * kv heads * rows too large for one launch");
     if (ev0) SS_HIP_CHECK(hipEventRecord(ev0, stream), "hipEventRecord");
     if (a.head_dim == 64)
-        hipLaunchKernelGGL(attn_generic_kernel<64>, dim3(grid), dim3(256), 0, stream, a);
+        launch_generic_kv<64>(a, row_blocks, stream);
     else
-        hipLaunchKernelGGL(attn_generic_kernel<128>, dim3(grid), dim3(256), 0, stream, a);
+        launch_generic_kv<128>(a, row_blocks, stream);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_generic_kernel");
     if (ev1) SS_HIP_CHECK(hipEventRecord(ev1, stream), "hipEventRecord");
     return SS_OK;

@@ -1,0 +1,55 @@
+"""GPU parity of the fp32 attention path (fp32 data, 64-wide heads, odd groupings) against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_09562_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+TINY = synth.CONFIGS[0]
+
+
+def run_gpu(inp):
+    d = binding.attention_to_device(inp)
+    mq = int(np.diff(inp["q_indptr"]).max())
+    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=mq)
+    binding.ss_set_option("attn_path", 1)
+    try:
+        binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=mq)
+        torch.cuda.synchronize()
+    finally:
+        binding.ss_set_option("attn_path", 0)
+    o = out.cpu().numpy().astype(np.float64) if inp["q_dtype"] == "f32" else binding.bf16_bits_to_float(out)
+    return o, lse.cpu().numpy().astype(np.float64)
+
+
+# row counts around a 16-row block (15, 16, 17, 21*16 rows), lengths around a tile, a round of the workgroup's
+# wavefronts (8 or 16 tiles) and a read of block ids (64 tiles per wavefront: 8192 / 16384 tokens)
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("kv,q", [("f32", "f32"), ("bf16", "bf16"), ("fp8", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("d,group,depth", [(64, 1, 14), (64, 4, 3), (64, 16, 20), (128, 1, 16), (128, 3, 4), (128, 7, 8)])
+def test_row_blocks_and_lengths(oracle, d, group, depth, kv, q, tree):
+    lens = np.array([1, 16, 17, 127, 128, 129, 255, 257, 8192, 8193, 16401], dtype=np.int32)
+    k = np.minimum(lens - 1, depth).astype(np.int32)
+    cfg = TINY.scaled(batch=len(lens), num_q_heads=2 * group, num_kv_heads=2, head_dim=d, kv_dtype=kv, q_dtype=q)
+    inp = synth.make_attention_inputs(cfg, seed=d + group, kv_len=lens, depth=k, tree=tree, nan_tail=True)
+    ref, ref_lse = oracle.verify_attn(inp)
+    got, lse = run_gpu(inp)
+    # fp32 throughout: sums of up to 16401 products, error growth sqrt(n) * 2^-24 on values of order 1, far below 1e-4;
+    # a bf16 output adds its rounding, 2^-9 relative
+    assert np.all(np.abs(got - ref) <= 1e-4 + (2.0 ** -8 if q == "bf16" else 0.0) * np.abs(ref))
+    assert np.all(np.abs(lse - ref_lse) <= 1e-4)
+
+
+def test_non_finite_value_stays_with_the_rows_that_see_it():
+    """A draft's value that is not finite reaches that draft's row and the later ones, not the rows in front of it."""
+    lens, k = np.array([50], dtype=np.int32), np.array([4], dtype=np.int32)
+    cfg = TINY.scaled(batch=1, num_q_heads=4, num_kv_heads=1)
+    inp = synth.make_attention_inputs(cfg, seed=1, kv_len=lens, depth=k)
+    clean, _ = run_gpu(inp)
+    pos = 50 - 5 + 2   # the third new token
+    inp["v_cache"][inp["block_table"][0, pos // 16], 0, pos % 16, 7] = np.inf
+    got, _ = run_gpu(inp)
+    assert np.allclose(got[:2], clean[:2], rtol=0, atol=1e-6)
+    assert np.all(np.isinf(got[2:, :, 7])) and np.all(np.isfinite(np.delete(got, 7, axis=2)))
