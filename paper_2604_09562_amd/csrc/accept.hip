@@ -28,21 +28,6 @@ namespace {
 // nothing to do).  A wave owns its chunk alone: all of its 16-byte loads go out first, then the
 // values are folded vector by vector into a per-lane running (max, sum) and reduced across the wave
 // with shuffles, so the streaming pass has no barrier and no LDS traffic.
-template <int DT>
-__device__ __forceinline__ void unpack(const uint4 &w, float (&x)[DT == SS_BF16 ? 8 : 4])
-{
-    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        if constexpr (DT == SS_BF16) {
-            x[2 * j] = __uint_as_float(ww[j] << 16);
-            x[2 * j + 1] = __uint_as_float(ww[j] & 0xffff0000u);
-        } else {
-            x[j] = __uint_as_float(ww[j]);
-        }
-    }
-}
-
 // Every logit is read exactly once by this pass: non-temporal loads keep the stream from displacing the one or
 // two rows per request that the later passes read again.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -182,7 +167,6 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
     const int t0 = a.q_indptr[b], k = a.q_indptr[b + 1] - t0 - 1, d0 = t0 - b;
     const float T = a.temperature ? a.temperature[b] : a.temperature_scalar;
     const double inv_t = a.greedy ? 1.0 : 1.0 / (double)T;
-    const int nrows = a.greedy ? k + 1 : 2 * k + 1;
 
     // Wave 0's gathers (draft token, then its two logits) depend on nothing the row merge below
     // produces: they are requested first so that their latency runs under it.
@@ -197,38 +181,27 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
         }
     }
 
-    // Sixteen rows at a time: every quarter of a wavefront (16 lanes over the chunks) merges one row, so the
-    // rows of an ordinary request are done in one trip.
-    const int quarter = lane >> 4, ql = lane & 15;
-    for (int j0 = 0; j0 < nrows; j0 += 16) {
-        const int j = j0 + wave * 4 + quarter;
-        const bool live = j < nrows;
-        const int64_t ry = !live ? 0 : (j <= k ? (int64_t)t0 + j : (int64_t)a.total_rows + d0 + (j - k - 1));
-        float m = -INFINITY;
-        if (live)
-            for (int c = ql; c < w.nchunks; c += 16) m = fmaxf(m, w.cmax[ry * w.nchunks + c]);
-        for (int off = 8; off; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));   // (stays inside the quarter)
-        if (a.greedy) {
+    if (a.greedy) {
+        // Sixteen rows at a time: every quarter of a wavefront (16 lanes over the chunks) merges one row, so the
+        // rows of an ordinary request are done in one trip.
+        const int quarter = lane >> 4, ql = lane & 15;
+        for (int j0 = 0; j0 <= k; j0 += 16) {
+            const int j = j0 + wave * 4 + quarter;
+            const bool live = j <= k;
+            const int64_t ry = live ? t0 + j : 0;
+            float m = -INFINITY;
+            if (live)
+                for (int c = ql; c < w.nchunks; c += 16) m = fmaxf(m, w.cmax[ry * w.nchunks + c]);
+            for (int off = 8; off; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));   // (stays inside the quarter)
             int best = 0x7fffffff;
             if (live)
                 for (int c = ql; c < w.nchunks; c += 16)
                     if (w.cmax[ry * w.nchunks + c] == m) best = min(best, w.carg[ry * w.nchunks + c]);
             for (int off = 8; off; off >>= 1) best = min(best, __shfl_xor(best, off));
             if (live && ql == 0) row_arg[j] = best;
-        } else {
-            double z = 0.0;
-            if (live)
-                for (int c = ql; c < w.nchunks; c += 16) {
-                    const float cm = w.cmax[ry * w.nchunks + c];
-                    if (cm != -INFINITY)
-                        z += (double)w.csum[ry * w.nchunks + c] * exp2(((double)cm - (double)m) * inv_t * kLog2eD);
-                }
-            for (int off = 8; off; off >>= 1) z += __shfl_xor(z, off);
-            if (live && ql == 0) {
-                row_m[j] = m;
-                row_z[j] = z;
-            }
         }
+    } else {
+        merge_row_stats(w, t0, (int64_t)a.total_rows + d0, k, inv_t, row_m, row_z);
     }
     __syncthreads();
     if (wave != 0) return;
@@ -300,199 +273,196 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
 }
 
 // ---- pass 2a: fp64 sums per block -------------------------------------------------------------
-// N sums in one go (fixed order): lanes, then the four waves.
-template <int N>
-__device__ __forceinline__ void block_sums(double (&v)[N], double (*sh)[N])
-{
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-        for (int off = 32; off; off >>= 1) v[i] += __shfl_xor(v[i], off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) sh[threadIdx.x >> 6][i] = v[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = (sh[0][i] + sh[1][i]) + (sh[2][i] + sh[3][i]);
-}
-
+// One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  Bound by the fp64 instructions
+// (about 34 per pair of entries at 5 cycles and the 32-bit ones around them: 16 us for 64 requests of 128256 entries), so
+// the sums cross the lanes by data-parallel moves, once.  Measured there: 22.7 us with shuffles through LDS and ldexp,
+// this form 20.2 us; two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5 against 4.9 us for 8 requests of 32000:
+// a wavefront that walks a block alone is a long chain); all 32 entries of a lane as straight-line code 27 us
+// (instruction fetch).
 template <int DT>
 __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Workspace w)
 {
-    __shared__ double sh[4];
-    __shared__ double sh5[4][5];
     __shared__ ExpTable ex;
-    ex.init();
-    const int sub = blockIdx.x % w.nsub, b = blockIdx.x / w.nsub, tid = threadIdx.x;
+    __shared__ double sum_sh[4][4];
+    __shared__ int cnt_sh[4], base_sh;
+    constexpr int WPB = kThreads / 64;
+    static_assert(kSub == kThreads * 8, "eight entries per lane");
+    const int b = blockIdx.x / w.nsub, sub = blockIdx.x % w.nsub, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const RowPick pk = w.pick[b];
+    const bool residual = pk.q_row >= 0;
+    const void *prow = row_ptr(a.target, pk.p_row, a.row_stride, DT);
+    const void *qrow = residual ? row_ptr(a.draft, pk.q_row, a.row_stride, DT) : prow;
+    const int i0 = sub * kSub + threadIdx.x * 8;   // vocabulary id of this lane's first entry
+    Raw8<DT> rp, rq;
+    load8<DT>(prow, a.vocab, i0, rp);
+    if (residual) load8<DT>(qrow, a.vocab, i0, rq);
+    ex.init();
     const double inv_t = 1.0 / (double)pk.temperature;
+    const RowArg ap(inv_t, pk.m_p), aq(inv_t, pk.m_q);
     const int64_t o = (int64_t)b * w.nsub + sub;
-    float xp[kSubPer], xq[kSubPer];
-    load_slots<DT, kSubPer, false>(row_ptr(a.target, pk.p_row, a.row_stride, DT), a.vocab, sub * kSub, tid, xp);
-    if (pk.q_row < 0) {   // bonus distribution: only the normaliser of the target row is needed
-        double z = 0.0;
+    // exponentials of all entries (zp, zq) and of those whose residual p - q is positive for certain (pp, qq):
+    // ep - rho * eq exceeds the boundary zone's half-width, kAmbEps * rho * eq
+    double zp = 0.0, zq = 0.0, pp = 0.0, qq = 0.0;
+    const double rho = pk.rho, width = pk.rho * kAmbEps;
+    unsigned near = 0;   // entries of this lane that are too close to call before Zp/Zq are exact
+    auto pair = [&](double ep, double eq, unsigned bit) __attribute__((always_inline)) {
+        zp += ep;
+        zq += eq;
+        const double t = fma(-rho, eq, ep), z = width * eq;
+        const double sure = t > z ? 1.0 : 0.0;   // (a factor costs fewer instructions than two selects of doubles)
+        pp = fma(ep, sure, pp);
+        qq = fma(eq, sure, qq);
+        if (fabs(t) <= z && ep > 0.0) near |= bit;
+    };
+    float xp[8], xq[8];
+    unpack8<DT>(rp, xp);
+    if (residual) unpack8<DT>(rq, xq);
+    // whether all of the wavefront's exponentials are normal numbers (masked logits are not) is one test
+    float low_p = xp[0], low_q = residual ? xq[0] : 0.f;
 #pragma unroll
-        for (int s = 0; s < kSubPer; ++s) z += ex(((double)xp[s] - (double)pk.m_p) * inv_t);
-        z = block_sum<double>(z, sh);
-        if (tid == 0) w.zp[o] = z;
-        return;
+    for (int s = 1; s < 8; ++s) {
+        low_p = fminf(low_p, xp[s]);
+        if (residual) low_q = fminf(low_q, xq[s]);
     }
-    load_slots<DT, kSubPer, false>(row_ptr(a.draft, pk.q_row, a.row_stride, DT), a.vocab, sub * kSub, tid, xq);
-    // v[0], v[1]: exponentials of all entries (p row, q row); v[2], v[3]: of the entries whose residual
-    // p - q is positive for certain, i.e. ep / eq above rho by more than the boundary zone
-    double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};   // [4]: how many entries of the block are too close to call
-    const double hi = pk.rho * (1.0 + kAmbEps), lo = pk.rho * (1.0 - kAmbEps);
-    unsigned near = 0;   // slots of this lane that are too close to call before Zp/Zq are exact
+    const bool normal = !__any(!(ap(low_p) >= kExpNormal) || (residual && !(aq(low_q) >= kExpNormal)));
+    if (!residual) {   // bonus distribution: only the normaliser of the target row is needed
+        if (normal) {
 #pragma unroll
-    for (int s = 0; s < kSubPer; ++s) {
-        const double ep = ex(((double)xp[s] - (double)pk.m_p) * inv_t);
-        const double eq = ex(((double)xq[s] - (double)pk.m_q) * inv_t);
-        v[0] += ep;
-        v[1] += eq;
-        if (ep > hi * eq) {
-            v[2] += ep;
-            v[3] += eq;
-        } else if (ep > 0.0 && ep >= lo * eq) {
-            near |= 1u << s;
+            for (int s = 0; s < 8; ++s) zp += ex.normal(ap(xp[s]));
+        } else {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) zp += ex(ap(xp[s]));
         }
+    } else if (normal) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) pair(ex.normal(ap(xp[s])), ex.normal(aq(xq[s])), 1u << s);
+    } else {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), 1u << s);
     }
-    // The boundary entries of this block go to the request's list as one contiguous run, in lane and
-    // slot order (so their later additions have a fixed order); one counter update per block.
-    __shared__ int wave_cnt[4], run_base;
-    const int mine = __popc(near);
-    v[4] = (double)mine;
-    block_sums<5>(v, sh5);
-    const int total = (int)v[4];
-    if (tid == 0) {
-        w.zp[o] = v[0];
-        w.zq[o] = v[1];
-        w.pp[o] = v[2];
-        w.qq[o] = v[3];
-        w.blk_cnt[o] = total;
+    zp = wave_scan(zp);
+    if (residual) {
+        zq = wave_scan(zq);
+        pp = wave_scan(pp);
+        qq = wave_scan(qq);
     }
-    if (total > 0) {
-        int incl = mine;
+    if (lane == 63) {
+        sum_sh[wave][0] = zp;
+        sum_sh[wave][1] = zq;
+        sum_sh[wave][2] = pp;
+        sum_sh[wave][3] = qq;
+    }
+    // The boundary entries of a block go to the request's list as one contiguous run, in wavefront, lane and entry
+    // order (so their later additions have a fixed order); one counter update per block.
+    int incl = __popc(near);
+    const int mine = incl;
+    const bool any = __any(near != 0);
+    if (any) {
         for (int off = 1; off < 64; off <<= 1) {
             const int t = __shfl_up(incl, off);
-            if ((tid & 63) >= off) incl += t;
-        }
-        if ((tid & 63) == 63) wave_cnt[tid >> 6] = incl;
-        __syncthreads();
-        int before = 0;
-        for (int wv = 0; wv < (tid >> 6); ++wv) before += wave_cnt[wv];
-        if (tid == 0) {
-            run_base = atomicAdd(&w.amb_cnt[b], total);
-            w.blk_base[o] = run_base;
-        }
-        __syncthreads();
-        if (run_base + total <= kAmbCap) {
-            int64_t l = (int64_t)b * kAmbCap + run_base + before + (incl - mine);
-#pragma unroll
-            for (int s = 0; s < kSubPer; ++s) {
-                if (near & (1u << s)) {
-                    // evaluated again rather than kept (the same bits): keeping sixteen doubles per lane
-                    // alive for this rare branch would halve the kernel's occupancy
-                    float yp = xp[s], yq = xq[s];
-                    asm volatile("" : "+v"(yp), "+v"(yq));
-                    w.amb_ep[l] = ex(((double)yp - (double)pk.m_p) * inv_t);
-                    w.amb_eq[l] = ex(((double)yq - (double)pk.m_q) * inv_t);
-                    ++l;
-                }
-            }
+            if (lane >= off) incl += t;
         }
     }
-}
-
-// Sum of v[0..n) with a fixed association (lane-strided partial sums, then the block tree): every
-// workgroup that calls it on the same array gets the same bits.
-__device__ __forceinline__ double block_total(const double *v, int n, double *sh)
-{
-    double s = 0.0;
-    for (int c = threadIdx.x; c < n; c += kThreads) s += v[c];
-    return block_sum<double>(s, sh);
-}
-
-// residual (or bonus) mass of one vocabulary entry
-__device__ __forceinline__ double mass(const ExpTable &ex, float lp, float lq, const RowPick &pk, double inv_t,
-                                       double inv_zp, double inv_zq)
-{
-    const double p = ex(((double)lp - (double)pk.m_p) * inv_t) * inv_zp;
-    if (pk.q_row < 0) return p;
-    const double q = ex(((double)lq - (double)pk.m_q) * inv_t) * inv_zq;
-    return p > q ? p - q : 0.0;
+    const int in_wave = __builtin_amdgcn_readlane(incl, 63);
+    int total = 0, before = 0, run_base = 0;
+    if (lane == 0) cnt_sh[wave] = in_wave;
+    __syncthreads();
+    for (int wv = 0; wv < WPB; ++wv) {
+        if (wv < wave) before += cnt_sh[wv];
+        total += cnt_sh[wv];
+    }
+    if (total > 0) {   // (the same in all of the workgroup's wavefronts)
+        if (threadIdx.x == 0) base_sh = atomicAdd(&w.amb_cnt[b], total);
+        __syncthreads();
+        run_base = base_sh;
+    }
+    if (near && run_base + total <= kAmbCap) {
+        int64_t l = (int64_t)b * kAmbCap + run_base + before + (incl - mine);
+        for (unsigned left = near; left; left &= left - 1) {
+            // read and evaluated again (the same bits) rather than kept through the loop above
+            const int v = i0 + __ffs(left) - 1;
+            w.amb_ep[l] = ex(ap(load_logit(prow, 0, 0, DT, v)));
+            w.amb_eq[l] = ex(aq(load_logit(qrow, 0, 0, DT, v)));
+            ++l;
+        }
+    }
+    if (threadIdx.x == 0) {
+        double v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = 0.0;
+#pragma unroll
+            for (int wv = 0; wv < WPB; ++wv) v[i] += sum_sh[wv][i];
+        }
+        w.zp[o] = v[0];
+        if (residual) {
+            w.zq[o] = v[1];
+            w.pp[o] = v[2];
+            w.qq[o] = v[3];
+            w.blk_cnt[o] = total;
+            if (total > 0) w.blk_base[o] = run_base;
+        }
+    }
 }
 
 // ---- pass 2b: block masses and inverse-CDF search ------------------------------------------------------------
+// A chain of dependent steps: two sums over the blocks, the running sum of the block masses, and the search inside one
+// block, each a wavefront scan plus one exchange between the four wavefronts.  Lane t owns a contiguous run of
+// blocks (one, up to vocabularies of 512k entries), so one scan of the lanes' sums serves any number of blocks.
+// 64 requests of 128256 entries: 13.4 us with shuffles through LDS and two scans, this way 7.4 us.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void accept_pick_kernel(AcceptArgs a, Workspace w)
 {
-    __shared__ double wave_tot[4];
-    __shared__ int sh_first[4], sh_last[4];
+    __shared__ double tot_sh[4][2], scan_sh[4];
+    __shared__ DrawShared draw_sh;
     __shared__ float sh_f[4];
     __shared__ ExpTable ex;
     const int b = blockIdx.x / kPickWgs, part = blockIdx.x % kPickWgs;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const RowPick pk = w.pick[b];
-    int32_t *dst = a.out_tokens + (int64_t)b * SS_OUT_WIDTH + pk.n;
-    // block masses live in LDS unless the vocabulary has more blocks than fit there
-    constexpr int kScCap = 1024;
-    __shared__ double sc_sh[kScCap];
-    __shared__ double sh4[4][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t ob = (int64_t)b * w.nsub;
-    // everything that does not depend on anything else is requested up front
+    const int per = blocks_per_lane(w.nsub);
+    const int c0 = tid * per, c1 = min(c0 + per, w.nsub);
+    // everything that does not depend on anything else is requested up front (what a bonus request has no values for
+    // is read and not used)
+    const RowPick pk = w.pick[b];
+    const int amb = w.amb_cnt[b];
     const float u_s = a.u_sample[b];
-    const int namb = pk.q_row >= 0 ? w.amb_cnt[b] : 0;
+    const int64_t o0 = ob + min(c0, w.nsub - 1);
+    const double zp0 = w.zp[o0], zq0 = w.zq[o0], pp0 = w.pp[o0], qq0 = w.qq[o0];
+    const int cnt0 = w.blk_cnt[o0], base0 = w.blk_base[o0];
+    const bool residual = pk.q_row >= 0;
+    const int namb = residual ? amb : 0;
     const bool listed = namb <= kAmbCap;
     if (listed && part != 0) return;   // one workgroup does the whole request unless the list overflowed
-    double *sc = listed && w.nsub <= kScCap ? sc_sh : w.sc + ob;
-    const bool own = tid < w.nsub;
-    const double zp0 = own ? w.zp[ob + tid] : 0.0;
-    const double zq0 = own && pk.q_row >= 0 ? w.zq[ob + tid] : 0.0;
-    const double pp0 = own && pk.q_row >= 0 ? w.pp[ob + tid] : 0.0;
-    const double qq0 = own && pk.q_row >= 0 ? w.qq[ob + tid] : 0.0;
-    const int cnt0 = own && pk.q_row >= 0 ? w.blk_cnt[ob + tid] : 0;       // this lane's block: its listed run
-    const int base0 = own && pk.q_row >= 0 ? w.blk_base[ob + tid] : 0;
+    int32_t *dst = a.out_tokens + (int64_t)b * SS_OUT_WIDTH + pk.n;
     ex.init();
 
-    // exact normalisers, then the mass of every block
-    double tot[4] = {zp0, zq0, 0.0, 0.0};
-    for (int c = tid + kThreads; c < w.nsub; c += kThreads) {
-        tot[0] += w.zp[ob + c];
-        if (pk.q_row >= 0) tot[1] += w.zq[ob + c];
+    // exact normalisers
+    double zp = c0 < c1 ? zp0 : 0.0, zq = c0 < c1 && residual ? zq0 : 0.0;
+    for (int c = c0 + 1; c < c1; ++c) {
+        zp += w.zp[ob + c];
+        if (residual) zq += w.zq[ob + c];
     }
-    block_sums<4>(tot, sh4);
-    const double zp = tot[0], zq = pk.q_row >= 0 ? tot[1] : 1.0;
+    zp = wave_scan(zp);
+    zq = wave_scan(zq);
+    if (lane == 63) {
+        tot_sh[wave][0] = zp;
+        tot_sh[wave][1] = zq;
+    }
+    __syncthreads();
+    zp = (tot_sh[0][0] + tot_sh[1][0]) + (tot_sh[2][0] + tot_sh[3][0]);
+    zq = residual ? (tot_sh[0][1] + tot_sh[1][1]) + (tot_sh[2][1] + tot_sh[3][1]) : 1.0;
     const double inv_t = 1.0 / (double)pk.temperature, inv_zp = 1.0 / zp, inv_zq = 1.0 / zq;
-    if (pk.q_row < 0) {
-        if (own) sc[tid] = zp0 / zp;
-        for (int c = tid + kThreads; c < w.nsub; c += kThreads) sc[c] = w.zp[ob + c] / zp;
-    } else if (listed) {
-        if (own) {
-            const double m = pp0 * inv_zp - qq0 * inv_zq;
-            sc[tid] = m > 0.0 ? m : 0.0;
-        }
-        for (int c = tid + kThreads; c < w.nsub; c += kThreads) {
-            const double m = w.pp[ob + c] * inv_zp - w.qq[ob + c] * inv_zq;
-            sc[c] = m > 0.0 ? m : 0.0;
-        }
-        if (namb > 0) {
-            // The listed boundary entries, now that Zp and Zq are exact: lane c adds block c's run in its stored order.
-            __syncthreads();
-            for (int c = tid; c < w.nsub; c += kThreads) {
-                const int cnt = c == tid ? cnt0 : w.blk_cnt[ob + c];
-                if (cnt > 0) {
-                    const int64_t l0 = (int64_t)b * kAmbCap + (c == tid ? base0 : w.blk_base[ob + c]);
-                    double add = 0.0;
-                    for (int e = 0; e < cnt; ++e) {
-                        const double r = w.amb_ep[l0 + e] * inv_zp - w.amb_eq[l0 + e] * inv_zq;
-                        add += r > 0.0 ? r : 0.0;
-                    }
-                    sc[c] += add;
-                }
-            }
-        }
-    } else {
+    const RowArg ap(inv_t, pk.m_p), aq(inv_t, pk.m_q);
+    // residual (or bonus) mass of one vocabulary entry
+    auto entry_mass = [&](float lp, float lq) __attribute__((always_inline)) {
+        const double p = ex(ap(lp)) * inv_zp;
+        if (!residual) return p;
+        const double q = ex(aq(lq)) * inv_zq;
+        return p > q ? p - q : 0.0;
+    };
+    if (!listed) {
         // Too many entries near p == q to list (rows that nearly coincide, or many equal logit pairs on
         // the boundary): the request's workgroups share the blocks and compute every mass entry by
         // entry; the last one to deliver (a counter in device memory) goes on to draw the token.
@@ -502,9 +472,9 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(AcceptArgs a, Wor
             load_slots<DT, kSubPer, false>(row_ptr(a.draft, pk.q_row, a.row_stride, DT), a.vocab, c * kSub, tid, yq);
             double m = 0.0;
 #pragma unroll
-            for (int i = 0; i < kSubPer; ++i) m += mass(ex, yp[i], yq[i], pk, inv_t, inv_zp, inv_zq);
-            m = block_sum<double>(m, wave_tot);
-            if (tid == 0) sc[c] = m;
+            for (int i = 0; i < kSubPer; ++i) m += entry_mass(yp[i], yq[i]);
+            m = block_sum<double>(m, scan_sh);
+            if (tid == 0) w.sc[ob + c] = m;
         }
         __shared__ int ticket_sh;
         __threadfence();   // the masses are out before the counter moves
@@ -514,130 +484,52 @@ __global__ __launch_bounds__(kThreads) void accept_pick_kernel(AcceptArgs a, Wor
         if (ticket_sh != kPickWgs - 1) return;
         __threadfence();   // and the other workgroups' masses are read from memory, not from a stale cache line
     }
-    __threadfence_block();
-    __syncthreads();
-
-    // Inclusive scan of the block masses in index order (lane c holds block c; vocabularies beyond
-    // 256 blocks take several rounds), first for the total S, then again to find the first block
-    // with mass whose running sum exceeds u * S, together with the mass in front of it.
-    __shared__ double scan_tot[4];
-    __shared__ double carry_sh, prefix_sh;
-    __shared__ int cstar_sh, lastpos_sh;
-    double S = 0.0;
-    int cand = 0x7fffffff, last = -1;
-    double cand_prefix = 0.0, last_prefix = 0.0;
-    for (int pass = 0; pass < 2; ++pass) {
-        const double thr0 = (double)u_s * S;
-        __syncthreads();
-        if (tid == 0) { carry_sh = 0.0; cstar_sh = 0x7fffffff; lastpos_sh = -1; }
-        __syncthreads();
-        for (int base = 0; base < w.nsub; base += kThreads) {
-            const int c = base + tid;
-            const double v = c < w.nsub ? sc[c] : 0.0;
-            double incl = v;
-            for (int off = 1; off < 64; off <<= 1) {
-                const double t = __shfl_up(incl, off);
-                if (lane >= off) incl += t;
+    // mass of block c, given its sums and its listed run (the boundary entries, now that Zp and Zq are exact, in
+    // their stored order)
+    auto block_mass = [&](double zpc, double ppc, double qqc, int cnt, int base) __attribute__((always_inline)) {
+        if (!residual) return zpc / zp;
+        double m = ppc * inv_zp - qqc * inv_zq;
+        m = m > 0.0 ? m : 0.0;
+        if (namb > 0 && cnt > 0) {
+            const int64_t l0 = (int64_t)b * kAmbCap + base;
+            double add = 0.0;
+            for (int e = 0; e < cnt; ++e) {
+                const double r = w.amb_ep[l0 + e] * inv_zp - w.amb_eq[l0 + e] * inv_zq;
+                add += r > 0.0 ? r : 0.0;
             }
-            if (lane == 63) scan_tot[wave] = incl;
-            __syncthreads();
-            double before = carry_sh;
-            for (int wv = 0; wv < wave; ++wv) before += scan_tot[wv];
-            const double cum = before + incl;   // running sum through block c
-            if (pass == 1 && v > 0.0) {
-                if (cum > thr0 && c < cand) { cand = c; cand_prefix = cum - v; }
-                last = c;
-                last_prefix = cum - v;
-            }
-            __syncthreads();
-            if (tid == kThreads - 1) carry_sh = cum;
-            __syncthreads();
+            m += add;
         }
-        if (pass == 0) S = carry_sh;
-        if (!(S > 0.0)) break;
-    }
-    if (!(S > 0.0)) {
+        return m;
+    };
+    auto mass_of = [&](int c) __attribute__((always_inline)) {
+        if (!listed) return w.sc[ob + c];
+        if (c == c0) return block_mass(zp0, pp0, qq0, cnt0, base0);
+        return block_mass(w.zp[ob + c], w.pp[ob + c], w.qq[ob + c], w.blk_cnt[ob + c], w.blk_base[ob + c]);
+    };
+
+    auto entries = [&](int cstar, double (&r)[kSubPer]) __attribute__((always_inline)) {
+        float xp[kSubPer], xq[kSubPer];
+        load_slots<DT, kSubPer, true>(row_ptr(a.target, pk.p_row, a.row_stride, DT), a.vocab, cstar * kSub, tid, xp);
+        if (residual)
+            load_slots<DT, kSubPer, true>(row_ptr(a.draft, pk.q_row, a.row_stride, DT), a.vocab, cstar * kSub, tid, xq);
+        else {
+#pragma unroll
+            for (int i = 0; i < kSubPer; ++i) xq[i] = 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < kSubPer; ++i) r[i] = entry_mass(xp[i], xq[i]);
+    };
+    int tok = draw_token(w.nsub, u_s, draw_sh, mass_of, entries);
+    if (tok < 0) {
         // p_n == q_n exactly: no residual mass; fall back to the lowest-index argmax of the target row
         float best = -INFINITY;
         for (int v = tid; v < a.vocab; v += kThreads)
             best = fmaxf(best, load_logit(a.target, pk.p_row, a.row_stride, DT, v));
         best = block_max(best, sh_f);
-        int arg = 0x7fffffff;
-        for (int v = tid; v < a.vocab; v += kThreads)
-            if (load_logit(a.target, pk.p_row, a.row_stride, DT, v) == best) { arg = v; break; }
-        for (int off = 32; off; off >>= 1) arg = min(arg, __shfl_xor(arg, off));
-        if (lane == 0) sh_first[wave] = arg;
-        __syncthreads();
-        if (tid == 0) *dst = min(min(sh_first[0], sh_first[1]), min(sh_first[2], sh_first[3]));
-        return;
+        tok = lowest_index_of(a.target, pk.p_row, a.row_stride, DT, a.vocab, best, draw_sh);
     }
-    atomicMin(&cstar_sh, cand);
-    atomicMax(&lastpos_sh, last);
-    __syncthreads();
-    const bool take_last = cstar_sh == 0x7fffffff;  // rounding left u*S at or past the total: last entry with mass
-    const int cstar = take_last ? lastpos_sh : cstar_sh;
-    if (!take_last && cand == cstar) prefix_sh = cand_prefix;
-    if (take_last && last == cstar) prefix_sh = last_prefix;
-    __syncthreads();   // publishes prefix_sh
-    const double thr = (double)u_s * S;
-    const double prefix = prefix_sh;
-    float xp[kSubPer], xq[kSubPer];
-    load_slots<DT, kSubPer, true>(row_ptr(a.target, pk.p_row, a.row_stride, DT), a.vocab, cstar * kSub, tid, xp);
-    if (pk.q_row >= 0)
-        load_slots<DT, kSubPer, true>(row_ptr(a.draft, pk.q_row, a.row_stride, DT), a.vocab, cstar * kSub, tid, xq);
-    else {
-#pragma unroll
-        for (int i = 0; i < kSubPer; ++i) xq[i] = 0.f;
-    }
-    double r[kSubPer];
-    double local = 0.0;
-    int my_last = -1;
-#pragma unroll
-    for (int i = 0; i < kSubPer; ++i) {
-        r[i] = mass(ex, xp[i], xq[i], pk, inv_t, inv_zp, inv_zq);
-        local += r[i];
-        if (r[i] > 0.0) my_last = cstar * kSub + tid * kSubPer + i;
-    }
-    // exclusive prefix of `local` over lanes in index order
-    double incl = local;
-    for (int off = 1; off < 64; off <<= 1) {
-        const double t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
-    if (lane == 63) wave_tot[wave] = incl;
-    __syncthreads();
-    double before = prefix;
-    for (int wv = 0; wv < wave; ++wv) before += wave_tot[wv];
-    const double excl = before + (incl - local);
-    // first lane whose running sum crosses the threshold
-    const bool crosses = !take_last && (excl + local > thr);
-    const unsigned long long bal = __ballot(crosses);
-    if (lane == 0) sh_first[wave] = bal ? wave * 64 + (__ffsll((long long)bal) - 1) : 0x7fffffff;
-    int lw = my_last;
-    for (int off = 32; off; off >>= 1) lw = max(lw, __shfl_xor(lw, off));
-    if (lane == 0) sh_last[wave] = lw;
-    __syncthreads();
-    const int first = min(min(sh_first[0], sh_first[1]), min(sh_first[2], sh_first[3]));
-    const int last_tok = max(max(sh_last[0], sh_last[1]), max(sh_last[2], sh_last[3]));
-    if (first == 0x7fffffff) {
-        if (tid == 0) *dst = last_tok;
-        return;
-    }
-    if (tid == first) {
-        double c = excl;
-        int tok = -1;
-#pragma unroll
-        for (int i = 0; i < kSubPer; ++i) {
-            if (r[i] > 0.0) {
-                c += r[i];
-                if (tok < 0 && c > thr) tok = cstar * kSub + tid * kSubPer + i;
-            }
-        }
-        // the lane total crossed but the element-wise sum may round differently: then its last entry with mass
-        *dst = tok >= 0 ? tok : my_last;
-    }
+    if (tid == 0) *dst = tok;
 }
-
 
 }  // namespace
 
@@ -655,14 +547,14 @@ size_t accept_workspace_bytes(int batch, int total_rows, int vocab)
 }
 
 template <int DT>
-static int32_t accept_launch_dt(const AcceptArgs &a, const Workspace &w, unsigned g1, unsigned g2, hipStream_t stream)
+static int32_t accept_launch_dt(const AcceptArgs &a, const Workspace &w, unsigned g1, hipStream_t stream)
 {
     hipLaunchKernelGGL(accept_rowstats_kernel<DT>, dim3(g1), dim3(kThreads), 0, stream, a, w);
     SS_HIP_CHECK(hipGetLastError(), "launch accept_rowstats_kernel");
     hipLaunchKernelGGL(accept_decide_kernel, dim3(a.batch), dim3(kThreads), 0, stream, a, w);
     SS_HIP_CHECK(hipGetLastError(), "launch accept_decide_kernel");
     if (a.greedy) return SS_OK;
-    hipLaunchKernelGGL(accept_norm_kernel<DT>, dim3(g2), dim3(kThreads), 0, stream, a, w);
+    hipLaunchKernelGGL(accept_norm_kernel<DT>, dim3((unsigned)a.batch * w.nsub), dim3(kThreads), 0, stream, a, w);
     SS_HIP_CHECK(hipGetLastError(), "launch accept_norm_kernel");
     hipLaunchKernelGGL(accept_pick_kernel<DT>, dim3((unsigned)a.batch * kPickWgs), dim3(kThreads), 0, stream, a, w);
     SS_HIP_CHECK(hipGetLastError(), "launch accept_pick_kernel");
@@ -674,11 +566,10 @@ int32_t accept_launch(const AcceptArgs &a, hipStream_t stream)
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
     const unsigned long long g1 =
         (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks + 3) / 4);
-    const unsigned long long g2 = (unsigned long long)a.batch * w.nsub;
-    if (g1 > 0x7fffffffull || g2 > 0x7fffffffull)
+    if (g1 > 0x7fffffffull || (unsigned long long)a.batch * w.nsub > 0x7fffffffull)
         return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
-    if (a.logit_dtype == SS_BF16) return accept_launch_dt<SS_BF16>(a, w, (unsigned)g1, (unsigned)g2, stream);
-    return accept_launch_dt<SS_F32>(a, w, (unsigned)g1, (unsigned)g2, stream);
+    if (a.logit_dtype == SS_BF16) return accept_launch_dt<SS_BF16>(a, w, (unsigned)g1, stream);
+    return accept_launch_dt<SS_F32>(a, w, (unsigned)g1, stream);
 }
 
 int32_t accept_rowstats_launch(const AcceptArgs &a, hipStream_t stream)

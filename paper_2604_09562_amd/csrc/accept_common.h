@@ -72,28 +72,28 @@ __host__ Workspace carve(void *ws, int batch, int total_rows, int vocab)
     return w;
 }
 
-// ---- loading one lane's share of a block of N*256 vocabulary entries -------------------------
-// Coalesced order: lane t owns entries base + it*(256*vec) + t*vec + j (vec = 8 for bf16, 4 for f32).
+// ---- loading one lane's share of a block of N*TH vocabulary entries (TH lanes share the block) ----
+// Coalesced order: lane t owns entries base + it*(TH*vec) + t*vec + j (vec = 8 for bf16, 4 for f32).
 // Sequential order (the inverse-CDF search): lane t owns base + t*N .. + N-1.
 // Out-of-vocabulary positions read as -inf.  index_of() gives the vocabulary id of slot s.
 // DT is the logit dtype (SS_BF16 or SS_F32): the kernels are compiled once per dtype.
-template <int DT, int N, bool SEQ>
+template <int DT, int N, bool SEQ, int TH = kThreads>
 __device__ __forceinline__ int index_of(int base, int tid, int s)
 {
     if (SEQ) return base + tid * N + s;
     constexpr int vec = DT == SS_BF16 ? 8 : 4;
-    return base + (s / vec) * (kThreads * vec) + tid * vec + (s % vec);
+    return base + (s / vec) * (TH * vec) + tid * vec + (s % vec);
 }
 
-template <int DT, int N, bool SEQ>
+template <int DT, int N, bool SEQ, int TH = kThreads>
 __device__ __forceinline__ void load_slots(const void *row, int vocab, int base, int tid, float (&x)[N])
 {
     constexpr int vec = DT == SS_BF16 ? 8 : 4;
-    if (base + N * kThreads <= vocab) {   // whole block inside the vocabulary (uniform): plain 16-byte loads
+    if (base + N * TH <= vocab) {   // whole block inside the vocabulary (uniform): plain 16-byte loads
         uint4 w[N / vec];
 #pragma unroll
         for (int it = 0; it < N / vec; ++it) {
-            const int i0 = index_of<DT, N, SEQ>(base, tid, it * vec);
+            const int i0 = index_of<DT, N, SEQ, TH>(base, tid, it * vec);
             if constexpr (DT == SS_BF16)
                 w[it] = *reinterpret_cast<const uint4 *>(static_cast<const uint16_t *>(row) + i0);
             else
@@ -120,7 +120,7 @@ __device__ __forceinline__ void load_slots(const void *row, int vocab, int base,
     const int last_full = vocab >= vec ? (vocab - vec) / vec * vec : -1;
 #pragma unroll
     for (int it = 0; it < N / vec; ++it) {
-        const int i0 = index_of<DT, N, SEQ>(base, tid, it * vec);
+        const int i0 = index_of<DT, N, SEQ, TH>(base, tid, it * vec);
         uint4 w = make_uint4(0, 0, 0, 0);
         if (last_full >= 0) {
             const int ic = i0 < last_full ? i0 : last_full;
@@ -150,6 +150,67 @@ __device__ __forceinline__ void load_slots(const void *row, int vocab, int base,
                         x[it * vec + j] = static_cast<const float *>(row)[i0 + j];
                 }
             }
+        }
+    }
+}
+
+template <int DT>
+__device__ __forceinline__ void unpack(const uint4 &w, float (&x)[DT == SS_BF16 ? 8 : 4])
+{
+    const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if constexpr (DT == SS_BF16) {
+            x[2 * j] = __uint_as_float(ww[j] << 16);
+            x[2 * j + 1] = __uint_as_float(ww[j] & 0xffff0000u);
+        } else {
+            x[j] = __uint_as_float(ww[j]);
+        }
+    }
+}
+
+// Eight logits of a row from vocabulary id i0 on (a multiple of 8); positions past the vocabulary read as -inf.
+template <int DT>
+struct Raw8 {
+    uint4 w[DT == SS_BF16 ? 1 : 2];
+};
+template <int DT>
+__device__ __forceinline__ void load8(const void *row, int vocab, int i0, Raw8<DT> &r)
+{
+    if (i0 + 8 <= vocab) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(static_cast<const char *>(row) + (int64_t)i0 * (DT == SS_BF16 ? 2 : 4));
+#pragma unroll
+        for (int j = 0; j < (DT == SS_BF16 ? 1 : 2); ++j) r.w[j] = p[j];
+        return;
+    }
+    uint32_t e[8];   // the end of the vocabulary, entry by entry
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if constexpr (DT == SS_BF16)
+            e[j] = i0 + j < vocab ? static_cast<const uint16_t *>(row)[i0 + j] : 0xff80u;
+        else
+            e[j] = i0 + j < vocab ? static_cast<const uint32_t *>(row)[i0 + j] : 0xff800000u;
+    }
+    if constexpr (DT == SS_BF16) {
+        r.w[0] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+    } else {
+        r.w[0] = make_uint4(e[0], e[1], e[2], e[3]);
+        r.w[1] = make_uint4(e[4], e[5], e[6], e[7]);
+    }
+}
+template <int DT>
+__device__ __forceinline__ void unpack8(const Raw8<DT> &r, float (&x)[8])
+{
+    if constexpr (DT == SS_BF16) {
+        unpack<DT>(r.w[0], x);
+    } else {
+        float lo[4], hi[4];
+        unpack<DT>(r.w[0], lo);
+        unpack<DT>(r.w[1], hi);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            x[j] = lo[j];
+            x[4 + j] = hi[j];
         }
     }
 }
@@ -185,6 +246,30 @@ __device__ __forceinline__ T block_sum(T v, T *sh)
     return (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
+// ---- sums across a wavefront in lane order, by data-parallel moves (no LDS round trips) -----------
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+    return x + __hiloint2double(hi, lo);
+}
+// Inclusive running sums of x over the lanes; lane 63 holds the total.  A fixed association.
+__device__ __forceinline__ double wave_scan(double x)
+{
+    x = dpp_add<0x111, 0xf>(x);   // row_shr 1, 2, 4, 8: running sums inside each row of 16 lanes
+    x = dpp_add<0x112, 0xf>(x);
+    x = dpp_add<0x114, 0xf>(x);
+    x = dpp_add<0x118, 0xf>(x);
+    x = dpp_add<0x142, 0xa>(x);   // row_bcast 15: the sum of row 0 to row 1, of row 2 to row 3
+    x = dpp_add<0x143, 0xc>(x);   // row_bcast 31: the sum of rows 0 and 1 to rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ double lane_value(double x, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
 // ---- fp64 exponential for non-positive arguments -----------------------------------------------
 // exp(x) = 2^e * 2^(j/64) * exp(r), x = (64 e + j) ln2/64 + r, |r| <= ln2/128, with a 64-entry
 // table of 2^(j/64) in LDS and a degree-5 Taylor polynomial (remainder < 4e-17 relative).
@@ -208,6 +293,8 @@ static __device__ const double kExp2Sixtyfourths[64] = {
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
 };
 
+constexpr double kExpNormal = -700.0;   // from here up ExpTable::normal may be used
+
 struct ExpTable {
     double t[64];
     __device__ void init()
@@ -215,18 +302,217 @@ struct ExpTable {
         if (threadIdx.x < 64) t[threadIdx.x] = kExp2Sixtyfourths[threadIdx.x];
         __syncthreads();
     }
-    __device__ __forceinline__ double operator()(double x) const
+    // the significand of exp(x), in [0.99, 2), and k with exp(x) = significand * 2^(k >> 6)
+    __device__ __forceinline__ double significand(double x, int &k) const
     {
-        x = fmax(x, -746.0);   // exp underflows to 0 from there on (also covers -inf)
-        const double kd = rint(x * 92.33248261689366);  // 64 / ln 2
+        // x * 64/ln2 to the nearest integer: added to 1.5 * 2^52 it lands in the low bits of the significand
+        const double magic = 0x1.8p52;
+        double kd = fma(x, 92.33248261689366, magic);
+        k = __double2loint(kd);
+        kd -= magic;
         double r = fma(kd, -0x1.62e42fee00000p-7, x);    // ln2/64: high part with 21 trailing zero bits
         r = fma(kd, -0x1.a39ef35793c76p-39, r);          //         low part
-        const int k = (int)kd;
         const double p = fma(fma(fma(fma(fma(r, 1.0 / 120.0, 1.0 / 24.0), r, 1.0 / 6.0), r, 0.5), r, 1.0), r, 1.0);
-        return ldexp(t[k & 63] * p, k >> 6);
+        return t[k & 63] * p;
+    }
+    __device__ __forceinline__ double operator()(double x) const
+    {
+        int k;
+        const double y = significand(fmax(x, -746.0), k);   // exp underflows to 0 from there on (also covers -inf)
+        return ldexp(y, k >> 6);
+    }
+    // the same bits for -700 <= x <= 1, where the result is normal and the power of two is an addition to its exponent
+    __device__ __forceinline__ double normal(double x) const
+    {
+        int k;
+        const double y = significand(x, k);
+        return __hiloint2double(__double2hiint(y) + ((k & ~63) << 14), __double2loint(y));
     }
 };
 
+// Argument of the exponential of a logit: (x - max) / T as one fused multiply-add.  c = -max/T is rounded once per row,
+// a factor common to all of the row's exponentials, which the normaliser takes out again.
+struct RowArg {
+    double inv_t, c;
+    __device__ __forceinline__ RowArg(double inv_t_, float m) : inv_t(inv_t_), c(-(double)m * inv_t_) {}
+    __device__ __forceinline__ double operator()(float x) const { return fma((double)x, inv_t, c); }
+};
+
+// Exponentials of eight logits.  Whether all of the wavefront's are normal numbers (those of masked logits are not) is
+// one test.
+__device__ __forceinline__ void exp8(const ExpTable &ex, const RowArg &arg, const float (&x)[8], double (&e)[8])
+{
+    float low = x[0];
+#pragma unroll
+    for (int s = 1; s < 8; ++s) low = fminf(low, x[s]);
+    if (!__any(!(arg(low) >= kExpNormal))) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) e[s] = ex.normal(arg(x[s]));
+    } else {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) e[s] = ex(arg(x[s]));
+    }
+}
+
+// ---- row statistics of one request: a 256-lane workgroup merges the chunk statistics -------------------------
+// Rows target0 .. target0 + k and draft0 .. draft0 + k - 1 (offsets into the statistics) become row_m[0 .. 2k] and
+// row_z[0 .. 2k].  Sixteen rows at a time: every quarter of a wavefront (16 lanes over the chunks) merges one row, so
+// the rows of an ordinary request are done in one trip.  The caller's barrier publishes them.
+__device__ __forceinline__ void merge_row_stats(const Workspace &w, int64_t target0, int64_t draft0, int k, double inv_t,
+                                                float *row_m, double *row_z)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, quarter = lane >> 4, ql = lane & 15;
+    const int nrows = 2 * k + 1;
+    for (int j0 = 0; j0 < nrows; j0 += 16) {
+        const int j = j0 + wave * 4 + quarter;
+        const bool live = j < nrows;
+        const int64_t ry = !live ? 0 : (j <= k ? target0 + j : draft0 + (j - k - 1));
+        const float *cmax = w.cmax + ry * w.nchunks, *csum = w.csum + ry * w.nchunks;
+        // (the lane's first chunk, usually its only one, is read once and both of its numbers together)
+        const bool has = live && ql < w.nchunks;
+        const float cm0 = has ? cmax[ql] : -INFINITY, cs0 = has ? csum[ql] : 0.f;
+        float m = cm0;
+        if (live)
+            for (int c = ql + 16; c < w.nchunks; c += 16) m = fmaxf(m, cmax[c]);
+        for (int off = 8; off; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));   // (stays inside the quarter)
+        double z = 0.0;
+        if (cm0 != -INFINITY) z = (double)cs0 * exp2(((double)cm0 - (double)m) * inv_t * kLog2eD);
+        if (live)
+            for (int c = ql + 16; c < w.nchunks; c += 16) {
+                const float cm = cmax[c];
+                if (cm != -INFINITY) z += (double)csum[c] * exp2(((double)cm - (double)m) * inv_t * kLog2eD);
+            }
+        for (int off = 8; off; off >>= 1) z += __shfl_xor(z, off);
+        if (live && ql == 0) {
+            row_m[j] = m;
+            row_z[j] = z;
+        }
+    }
+}
+
+// ---- the draw: inverse-CDF search of a 256-lane workgroup ------------------------------------------------------
+// Lane t owns a contiguous run of 2048-entry blocks (one, up to vocabularies of 512k entries), so that one scan of
+// the lanes' sums serves any number of blocks.
+__device__ __forceinline__ int blocks_per_lane(int nsub) { return (nsub + kThreads - 1) / kThreads; }
+
+struct DrawShared {
+    double scan[4], entry[4], prefix;
+    int first[4], last[4], efirst[4], elast[4], cstar, tok;
+};
+
+// mass_of(c): mass of block c, asked for the lane's own blocks only; entries(c, r): the masses of the lane's entries
+// c * 2048 + 8 * tid .. of block c.  Returns, in every lane, the first token whose running sum of masses exceeds u times
+// their total (the last one with mass if rounding leaves none), or -1 if there is no mass.
+template <class MassOf, class Entries>
+__device__ __forceinline__ int draw_token(int nsub, float u, DrawShared &sh, MassOf mass_of, Entries entries)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = blocks_per_lane(nsub), c0 = tid * per, c1 = min(c0 + per, nsub);
+    // Running sum of the lanes' masses in block order: the total S, and the first lane with mass whose running sum
+    // exceeds u * S.
+    double own = 0.0;
+    int own_last = -1;   // last block of this lane with mass
+    for (int c = c0; c < c1; ++c) {
+        const double v = mass_of(c);
+        own += v;
+        if (v > 0.0) own_last = c;
+    }
+    const double incl_w = wave_scan(own);
+    if (lane == 63) sh.scan[wave] = incl_w;
+    __syncthreads();
+    double before_w = 0.0;
+    for (int wv = 0; wv < wave; ++wv) before_w += sh.scan[wv];
+    const double S = ((sh.scan[0] + sh.scan[1]) + sh.scan[2]) + sh.scan[3];
+    if (!(S > 0.0)) return -1;
+    const double thr = (double)u * S;
+    const double cum = before_w + incl_w;   // running sum through this lane's last block
+    const unsigned long long over = __ballot(own > 0.0 && cum > thr), some = __ballot(own > 0.0);
+    if (lane == 0) {
+        sh.first[wave] = over ? wave * 64 + (__ffsll((long long)over) - 1) : 0x7fffffff;
+        sh.last[wave] = some ? wave * 64 + (63 - __clzll((long long)some)) : -1;
+    }
+    __syncthreads();
+    const int first_lane = min(min(sh.first[0], sh.first[1]), min(sh.first[2], sh.first[3]));
+    const bool take_last = first_lane == 0x7fffffff;  // rounding left u*S at or past the total: last entry with mass
+    const int owner = take_last ? max(max(sh.last[0], sh.last[1]), max(sh.last[2], sh.last[3])) : first_lane;
+    if (tid == owner) {
+        // inside the lane's run of blocks: the first with mass whose running sum crosses (rounding may leave none: then
+        // the last with mass)
+        double run = cum - own;
+        double pre = run;
+        int cs = own_last;
+        if (per > 1) {
+            bool found = false;
+            for (int c = c0; c < c1; ++c) {
+                const double v = mass_of(c);
+                if (v > 0.0 && !found) {
+                    cs = c;
+                    pre = run;
+                    found = !take_last && run + v > thr;
+                }
+                run += v;
+            }
+        }
+        sh.cstar = cs;
+        sh.prefix = pre;
+    }
+    __syncthreads();
+    const int cstar = sh.cstar;
+    double r[kSubPer];
+    entries(cstar, r);
+    double local = 0.0;
+    int my_last = -1;
+#pragma unroll
+    for (int i = 0; i < kSubPer; ++i) {
+        local += r[i];
+        if (r[i] > 0.0) my_last = cstar * kSub + tid * kSubPer + i;
+    }
+    // exclusive prefix of `local` over lanes in index order
+    const double incl = wave_scan(local);
+    if (lane == 63) sh.entry[wave] = incl;
+    int lw = my_last;
+    for (int off = 32; off; off >>= 1) lw = max(lw, __shfl_xor(lw, off));
+    if (lane == 0) sh.elast[wave] = lw;
+    __syncthreads();
+    double before = sh.prefix;
+    for (int wv = 0; wv < wave; ++wv) before += sh.entry[wv];
+    const double excl = before + (incl - local);
+    // first lane whose running sum crosses the threshold
+    const unsigned long long bal = __ballot(!take_last && excl + local > thr);
+    if (lane == 0) sh.efirst[wave] = bal ? wave * 64 + (__ffsll((long long)bal) - 1) : 0x7fffffff;
+    __syncthreads();
+    const int first = min(min(sh.efirst[0], sh.efirst[1]), min(sh.efirst[2], sh.efirst[3]));
+    if (first == 0x7fffffff) return max(max(sh.elast[0], sh.elast[1]), max(sh.elast[2], sh.elast[3]));
+    if (tid == first) {
+        double c = excl;
+        int tok = -1;
+#pragma unroll
+        for (int i = 0; i < kSubPer; ++i) {
+            if (r[i] > 0.0) {
+                c += r[i];
+                if (tok < 0 && c > thr) tok = cstar * kSub + tid * kSubPer + i;
+            }
+        }
+        // the lane total crossed but the element-wise sum may round differently: then its last entry with mass
+        sh.tok = tok >= 0 ? tok : my_last;
+    }
+    __syncthreads();
+    return sh.tok;
+}
+
+// Lowest vocabulary id of a row that holds `value` (in every lane of a 256-lane workgroup).
+__device__ __forceinline__ int lowest_index_of(const void *rows, int64_t row, int64_t stride, int dtype, int vocab, float value,
+                                               DrawShared &sh)
+{
+    int arg = 0x7fffffff;
+    for (int v = threadIdx.x; v < vocab; v += kThreads)
+        if (load_logit(rows, row, stride, dtype, v) == value) { arg = v; break; }
+    for (int off = 32; off; off >>= 1) arg = min(arg, __shfl_xor(arg, off));
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh.first[threadIdx.x >> 6] = arg;
+    __syncthreads();
+    return min(min(sh.first[0], sh.first[1]), min(sh.first[2], sh.first[3]));
+}
 
 }  // namespace
 }  // namespace ss
