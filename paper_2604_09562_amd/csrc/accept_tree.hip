@@ -7,330 +7,358 @@ namespace {
 // ---- sampled acceptance over a draft tree ------------------------------------------------------------------
 // The walk of a request is a chain of dependent steps, but only its rejections need the whole vocabulary:
 // while the running distribution r is still a node's own target distribution a child is judged from two
-// gathered logits and the row statistics of the first pass.  So the work is laid out in rounds, each a
-// short sequence of launches over all requests at once (the stream orders them, no kernel waits for
-// another workgroup):
-//   walk   one wavefront per request: finish the residual of the previous round, then offer children
-//          until one is rejected (-> a residual is due) or none is left (-> the draw is due)
-//   sums   per 2048-entry block, exact fp64 sums of the proposal's exponentials (and of the target row's,
-//          if r has not been written out yet), for the requests that are due
-//   resid  the residual max(0, r - q) with the exact normalisers, written to the request's other buffer,
-//          and its sum per block; for a request whose draw is due, r itself and its mass per block
-// A request needs one round per rejection, at most k; the launcher runs max_q_len - 1 rounds, a last
-// walk, sums and resid for the draws, and the pick.  r lives unnormalised in device memory (value / norm),
-// two fp64 vocabulary vectors per request.  All reductions have a fixed order.
+// gathered logits and the row statistics of the first pass.  So the work is laid out in launches over all
+// requests at once (the stream orders them, no kernel waits for another workgroup):
+//   prep   one workgroup per request: merges the row statistics, evaluates q(x) and p(x) of every node, and
+//          walks from the root until a child is rejected (-> a residual is due) or none is left (-> the draw)
+//   sums   per 2048-entry block, exact fp64 sums of the rejected child's proposal's exponentials, and of the
+//          target row's if r has not been written out yet; for a draw from a node's own target distribution
+//          the target row's, which are its block masses
+//   resid  the residual max(0, r - q) with the exact normalisers, written to the request's other buffer, and its
+//          sum per block (its normaliser once added up, and the block masses of a draw from it)
+//   pick   scan of the block masses, search inside one block
+// A request needs a (sums, resid) round per rejection, at most k; the sums kernel of every later round begins by
+// walking on (each of its workgroups for itself: a few loads of a record per node, cheaper than a launch), and a
+// last sums kernel ends every walk.  r lives unnormalised in device memory, two fp64 vocabulary vectors per
+// request.  All reductions have a fixed order.
+//
+// Bound by the fp64 exponentials of the rounds that have most requests pending and by the length of the launch
+// chain.  64 requests of 128256 entries, depth 4: 240 us with a walk kernel of dependent reads in every round, 2-byte
+// loads, serial sums over the blocks and a pass that wrote r out for every draw; 142 us this way.
 struct TreeScalars {
     int32_t cur, n, next, phase;       // phase: 0 walking, 1 residual due, 2 draw due
     int32_t pure, degenerate, which, rej;   // which: the buffer that holds r; rej: the child just rejected
     float mp, mq;                      // exact maxima of the current node's target row / the rejected child's draft row
-    double zp_stats;                   // normaliser of the target row from the first pass (judging only)
+    double pad;
     double norm;                       // exact normaliser of the buffer that holds r
 };
 struct TreeState {
     TreeScalars s;                     // copied to registers by the kernels
-    int32_t tok[SS_OUT_WIDTH];         // accepted tokens and nodes so far: written and read in place (a private copy
-    int32_t node[SS_MAX_DEPTH];        // indexed by a run-time value would live in scratch memory)
+    int32_t tok[SS_OUT_WIDTH];         // accepted tokens and nodes so far: written in place
+    int32_t node[SS_MAX_DEPTH];
+};
+struct TreeNode {                      // what the walk needs to know of a node
+    double qx, px;                     // its token's probability under its own proposal / its parent's target row
+    float mp, mq;                      // exact maxima of its target row / its draft row
 };
 
 enum { TS_WALK = 0, TS_RESIDUAL = 1, TS_DRAW = 2 };
 
-// maximum and (first-pass) normaliser of a row from its chunk statistics: one wavefront, lanes over chunks
-__device__ __forceinline__ void tree_row_stats(const Workspace &w, int64_t ry, double inv_t, float &m, double &z)
+// The walk reads one copy of a request's scalars while one of its workgroups writes the next: two copies in turn, in
+// arrays of the chain rule's workspace that the tree walk has no other use for (as are the node records).
+struct TreeMem {
+    TreeState *st;
+    double *arr;   // [batch][2][vocab]
+    __device__ __forceinline__ TreeScalars *scalars(const Workspace &w, int b, int copy) const
+    {
+        return copy ? reinterpret_cast<TreeScalars *>(w.amb_eq + (int64_t)b * kAmbCap) : &st[b].s;
+    }
+    __device__ __forceinline__ TreeNode *nodes(const Workspace &w, int b) const
+    {
+        return reinterpret_cast<TreeNode *>(w.amb_ep + (int64_t)b * kAmbCap);
+    }
+};
+static_assert(sizeof(TreeNode) * (SS_MAX_DEPTH + 1) <= sizeof(double) * kAmbCap, "node records fit the list");
+
+// Offers children until one is rejected or none is left: one wavefront, lane c holding node c (1..k).  `write`: this
+// workgroup records what happens.
+__device__ __forceinline__ void tree_walk(const AcceptArgs &a, const TreeNode *nodes, TreeState *st, const double *arr_b, TreeScalars &s,
+                                          int t0, int d0, int k, bool write)
 {
     const int lane = threadIdx.x & 63;
-    m = -INFINITY;
-    for (int c = lane; c < w.nchunks; c += 64) m = fmaxf(m, w.cmax[ry * w.nchunks + c]);
-    for (int off = 32; off; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    z = 0.0;
-    for (int c = lane; c < w.nchunks; c += 64) {
-        const float cm = w.cmax[ry * w.nchunks + c];
-        if (cm != -INFINITY) z += (double)w.csum[ry * w.nchunks + c] * exp2(((double)cm - (double)m) * inv_t * kLog2eD);
+    const bool is = lane >= 1 && lane <= k;
+    const int par = is ? a.tree_parent[t0 + lane] : -2;
+    const int x = is ? a.draft_tokens[d0 + lane - 1] : 0;   // (read from r only for nodes that are offered)
+    const double u = is ? (double)a.u_accept[d0 + lane - 1] : 0.0;
+    const double qx = is ? nodes[lane].qx : 0.0, px = is ? nodes[lane].px : 0.0;
+    const float mp = lane <= k ? nodes[lane].mp : 0.f, mq = is ? nodes[lane].mq : 0.f;
+    double rx = px;
+    if (!s.pure && par == s.cur && lane >= s.next) rx = arr_b[(int64_t)s.which * a.vocab + x] / s.norm;
+    const unsigned long long pure_ok = __ballot(is && u * qx < px);
+    const unsigned long long here_ok = __ballot(is && u * qx < rx);   // (s.pure: the same)
+    unsigned long long offered = 0, ok = here_ok;
+    for (;;) {   // at most k steps: every step moves to a higher-numbered node
+        const unsigned long long kids = __ballot(par == s.cur && lane >= s.next);
+        if (!kids) {
+            s.phase = TS_DRAW;
+            break;
+        }
+        const int c = __ffsll((long long)kids) - 1;
+        offered |= 1ull << c;
+        s.next = c + 1;
+        if (!((ok >> c) & 1)) {
+            s.phase = TS_RESIDUAL;
+            s.rej = c;
+            s.mq = __shfl(mq, c);
+            break;
+        }
+        if (write && lane == c) {
+            st->tok[s.n] = x;
+            st->node[s.n] = c;
+        }
+        // children of the node walked from were judged by its r; from here on r is the accepted node's own row
+        if (write && lane == c && a.ratio_out) a.ratio_out[d0 + c - 1] = (float)(rx / qx);
+        offered &= ~(1ull << c);
+        ++s.n;
+        s.cur = c;
+        s.pure = 1;
+        s.degenerate = 0;
+        s.mp = __shfl(mp, c);
+        ok = pure_ok;
+        rx = px;
     }
-    for (int off = 32; off; off >>= 1) z += __shfl_xor(z, off);   // (xor butterfly: every lane ends with the same bits)
+    if (write && a.ratio_out && ((offered >> lane) & 1)) a.ratio_out[d0 + lane - 1] = (float)(rx / qx);
 }
 
-__device__ __forceinline__ double tree_exp_at(const void *rows, int64_t row, int64_t stride, int dtype, int v, float m,
-                                              double inv_t)
+__global__ __launch_bounds__(kThreads) void tree_prep_kernel(AcceptArgs a, Workspace w, TreeMem mem)
 {
-    return exp(((double)load_logit(rows, row, stride, dtype, v) - (double)m) * inv_t);
-}
-
-template <int DT>
-__global__ __launch_bounds__(64) void tree_walk_kernel(AcceptArgs a, Workspace w, TreeState *st, double *arr, int first)
-{
-    const int b = blockIdx.x, lane = threadIdx.x;
-    const int V = a.vocab;
+    __shared__ float row_m[kMaxRows];
+    __shared__ double row_z[kMaxRows];
+    const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = a.q_indptr[b], k = a.q_indptr[b + 1] - t0 - 1, d0 = t0 - b;
     const float T = a.temperature ? a.temperature[b] : a.temperature_scalar;
     const double inv_t = 1.0 / (double)T;
+    // (gathers that depend on nothing the merge produces are requested first)
+    int par = 0;
+    float lq = 0.f, lp = 0.f;
+    const bool is = wave == 0 && lane >= 1 && lane <= k;
+    if (is) {
+        // (a node without a parent in front of it is never offered; the clamps keep its reads inside the batch)
+        par = min(max(a.tree_parent[t0 + lane], 0), lane - 1);
+        const int x = min(max(a.draft_tokens[d0 + lane - 1], 0), a.vocab - 1);
+        lq = load_logit(a.draft, d0 + lane - 1, a.row_stride, a.logit_dtype, x);
+        lp = load_logit(a.target, t0 + par, a.row_stride, a.logit_dtype, x);
+        if (a.ratio_out) a.ratio_out[d0 + lane - 1] = __builtin_nanf("");
+    }
+    merge_row_stats(w, t0, (int64_t)a.total_rows + d0, k, inv_t, row_m, row_z);
+    __syncthreads();
+    if (wave != 0) return;
+    TreeNode *nodes = mem.nodes(w, b);
+    if (lane <= k) {
+        TreeNode nd;
+        nd.mp = row_m[lane];
+        nd.mq = is ? row_m[k + lane] : 0.f;
+        nd.qx = is ? exp(((double)lq - (double)nd.mq) * inv_t) / row_z[k + lane] : 0.0;
+        nd.px = is ? exp(((double)lp - (double)row_m[par]) * inv_t) / row_z[par] : 0.0;
+        nodes[lane] = nd;
+    }
     TreeScalars s;
-    if (first) {
-        s.cur = 0; s.n = 0; s.next = 1; s.phase = TS_WALK; s.pure = 1; s.degenerate = 0; s.which = 0; s.rej = 0;
-        s.mq = 0.f; s.norm = 1.0;
-        tree_row_stats(w, t0, inv_t, s.mp, s.zp_stats);
-        if (lane < k && a.ratio_out) a.ratio_out[d0 + lane] = __builtin_nanf("");
-    } else {
-        s = st[b].s;   // (every lane reads the same record; only lane 0 writes it back)
-        if (s.phase == TS_DRAW) return;
-    }
-    if (s.phase == TS_RESIDUAL) {   // the residual of the last rejection is in the other buffer: adopt it
-        double S = 0.0;
-        for (int c = 0; c < w.nsub; ++c) S += w.sc[(int64_t)b * w.nsub + c];
-        s.degenerate = !(S > 0.0);
-        if (!s.degenerate) {
-            s.which ^= 1;
-            s.norm = S;
-            s.pure = 0;
-        }
-        s.phase = TS_WALK;
-    }
-    const double *r_arr = arr + ((int64_t)b * 2 + s.which) * V;
-    int c = s.next;
-    for (; c <= k; ++c) {
-        if (a.tree_parent[t0 + c] != s.cur) continue;
-        const int x = a.draft_tokens[d0 + c - 1];
-        const double u = (double)a.u_accept[d0 + c - 1];
-        float mq;
-        double zq;
-        tree_row_stats(w, (int64_t)a.total_rows + d0 + c - 1, inv_t, mq, zq);
-        const double qx = tree_exp_at(a.draft, d0 + c - 1, a.row_stride, DT, x, mq, inv_t) / zq;
-        const double rx = s.pure ? tree_exp_at(a.target, t0 + s.cur, a.row_stride, DT, x, s.mp, inv_t) / s.zp_stats
-                                 : r_arr[x] / s.norm;
-        if (lane == 0 && a.ratio_out) a.ratio_out[d0 + c - 1] = (float)(rx / qx);
-        if (u * qx < rx) {
-            if (lane == 0) {
-                st[b].tok[s.n] = x;
-                st[b].node[s.n] = c;
-            }
-            ++s.n;
-            s.cur = c;
-            s.pure = 1;
-            s.degenerate = 0;
-            tree_row_stats(w, (int64_t)t0 + c, inv_t, s.mp, s.zp_stats);
-        } else {
-            s.phase = TS_RESIDUAL;
-            s.rej = c;
-            s.mq = mq;
-            break;
-        }
-    }
-    s.next = c + 1;
-    if (s.phase == TS_WALK) s.phase = TS_DRAW;   // no child left
-    if (lane == 0) st[b].s = s;
+    s.cur = 0; s.n = 0; s.next = 1; s.phase = TS_WALK; s.pure = 1; s.degenerate = 0; s.which = 0; s.rej = 0;
+    s.mp = row_m[0]; s.mq = 0.f; s.pad = 0.0; s.norm = 1.0;
+    tree_walk(a, nodes, &mem.st[b], mem.arr, s, t0, d0, k, true);
+    if (lane == 0) *mem.scalars(w, b, 0) = s;
 }
 
-// Exact block sums of exponentials: of the rejected child's proposal (residual due), of the current
-// node's target row (r not written out yet and a residual or the draw is due).  grid: batch * nsub.
-template <int DT>
-__global__ __launch_bounds__(kThreads) void tree_sums_kernel(AcceptArgs a, Workspace w, const TreeState *st, int final_pass)
+// Total of a request's block sums, the same bits in every lane of every wavefront that asks.
+__device__ __forceinline__ double blocks_total(const double *v, int nsub)
 {
-    __shared__ double sh[4];
+    const int lane = threadIdx.x & 63;
+    double s = 0.0;
+    for (int c = lane; c < nsub; c += 64) s += v[c];
+    return lane_value(wave_scan(s), 63);
+}
+
+// A workgroup handles `bpw` blocks of one request; round 0 finds the walk done by the prep kernel, a later round adopts
+// the residual that the round before wrote and walks on first.  grid: batch * ceil(nsub / bpw).
+constexpr int kMaxBpw = 8;
+template <int DT>
+__global__ __launch_bounds__(kThreads) void tree_sums_kernel(AcceptArgs a, Workspace w, TreeMem mem, int round, int bpw)
+{
     __shared__ ExpTable ex;
-    const int sub = blockIdx.x % w.nsub, b = blockIdx.x / w.nsub, tid = threadIdx.x;
-    const TreeScalars s = st[b].s;
-    const bool want_q = s.phase == TS_RESIDUAL && !final_pass;
-    const bool want_p = s.pure && (want_q || (final_pass && s.phase == TS_DRAW && !s.degenerate));
+    __shared__ TreeScalars s_sh;
+    __shared__ double sum_sh[kMaxBpw][2][4];
+    const int parts = (w.nsub + bpw - 1) / bpw;
+    const int part = blockIdx.x % parts, b = blockIdx.x / parts, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t ob = (int64_t)b * w.nsub;
+    TreeScalars s = *mem.scalars(w, b, round ? (round - 1) & 1 : 0);
+    const int t0 = a.q_indptr[b], k = a.q_indptr[b + 1] - t0 - 1, d0 = t0 - b;
+    if (round) {
+        if (s.phase == TS_DRAW) {   // (its block masses are there already)
+            if (part == 0 && tid == 0) *mem.scalars(w, b, round & 1) = s;
+            return;
+        }
+        if (wave == 0) {
+            // the residual of the last rejection is in the other buffer: adopt it
+            const double S = blocks_total(w.sc + ob, w.nsub);
+            s.degenerate = !(S > 0.0);
+            if (!s.degenerate) {
+                s.which ^= 1;
+                s.norm = S;
+                s.pure = 0;
+            }
+            s.phase = TS_WALK;
+            tree_walk(a, mem.nodes(w, b), &mem.st[b], mem.arr + (int64_t)b * 2 * a.vocab, s, t0, d0, k, part == 0);
+            if (lane == 0) {
+                s_sh = s;
+                if (part == 0) *mem.scalars(w, b, round & 1) = s;
+            }
+        }
+        __syncthreads();
+        s = s_sh;
+    }
+    const bool want_q = s.phase == TS_RESIDUAL;
+    const bool want_p = s.pure && (want_q || !s.degenerate);
     if (!want_q && !want_p) return;
     ex.init();
-    const int t0 = a.q_indptr[b], d0 = t0 - b;
     const float T = a.temperature ? a.temperature[b] : a.temperature_scalar;
     const double inv_t = 1.0 / (double)T;
-    const int64_t o = (int64_t)b * w.nsub + sub;
-    double zq = 0.0, zp = 0.0;
+    const RowArg ap(inv_t, s.mp), aq(inv_t, s.mq);
+    const void *prow = row_ptr(a.target, t0 + s.cur, a.row_stride, DT);
+    const void *qrow = want_q ? row_ptr(a.draft, d0 + s.rej - 1, a.row_stride, DT) : prow;
+    const int sub0 = part * bpw, count = min(bpw, w.nsub - sub0);
+    const int i0 = sub0 * kSub + tid * 8;
+    Raw8<DT> rp, rq;
+    if (want_p) load8<DT>(prow, a.vocab, i0, rp);
+    if (want_q) load8<DT>(qrow, a.vocab, i0, rq);
+#pragma unroll 1
+    for (int j = 0; j < count; ++j) {   // (the next block's logits are requested before this one's are used)
+        float x[8];
+        double e[8];
+        if (want_p) {
+            unpack8<DT>(rp, x);
+            if (j + 1 < count) load8<DT>(prow, a.vocab, i0 + (j + 1) * kSub, rp);
+            exp8(ex, ap, x, e);
+            double z = 0.0;
 #pragma unroll
-    for (int j = 0; j < kSubPer; ++j) {
-        const int v = sub * kSub + j * kThreads + tid;
-        if (v < a.vocab) {
-            if (want_q) zq += ex(((double)load_logit(a.draft, d0 + s.rej - 1, a.row_stride, DT, v) - (double)s.mq) * inv_t);
-            if (want_p) zp += ex(((double)load_logit(a.target, t0 + s.cur, a.row_stride, DT, v) - (double)s.mp) * inv_t);
+            for (int i = 0; i < 8; ++i) z += e[i];
+            z = wave_scan(z);
+            if (lane == 63) sum_sh[j][0][wave] = z;
+        }
+        if (want_q) {
+            unpack8<DT>(rq, x);
+            if (j + 1 < count) load8<DT>(qrow, a.vocab, i0 + (j + 1) * kSub, rq);
+            exp8(ex, aq, x, e);
+            double z = 0.0;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) z += e[i];
+            z = wave_scan(z);
+            if (lane == 63) sum_sh[j][1][wave] = z;
         }
     }
-    if (want_q) {
-        zq = block_sum<double>(zq, sh);
-        if (tid == 0) w.zq[o] = zq;
-    }
-    if (want_p) {
-        zp = block_sum<double>(zp, sh);
-        if (tid == 0) w.zp[o] = zp;
+    __syncthreads();
+    if (tid < 2 * count) {
+        const int j = tid >> 1, which = tid & 1;
+        if (which ? want_q : want_p) {
+            const double *v = sum_sh[j][which];
+            (which ? w.zq : w.zp)[ob + sub0 + j] = (v[0] + v[1]) + (v[2] + v[3]);
+        }
     }
 }
 
-// Residual due: other buffer <- max(0, r - q), its block sums.  Draw due (final pass): block masses of r,
-// and r written out if it was not yet.  grid: batch * nsub.
+// Residual due: other buffer <- max(0, r - q), its block sums.  grid: batch * ceil(nsub / bpw).
 template <int DT>
-__global__ __launch_bounds__(kThreads) void tree_resid_kernel(AcceptArgs a, Workspace w, const TreeState *st, double *arr,
-                                                              int final_pass)
+__global__ __launch_bounds__(kThreads) void tree_resid_kernel(AcceptArgs a, Workspace w, TreeMem mem, int round, int bpw)
 {
-    __shared__ double sh[4];
     __shared__ ExpTable ex;
-    const int sub = blockIdx.x % w.nsub, b = blockIdx.x / w.nsub, tid = threadIdx.x;
-    const TreeScalars s = st[b].s;
-    const bool resid = s.phase == TS_RESIDUAL && !final_pass;
-    const bool draw = final_pass && s.phase == TS_DRAW && !s.degenerate;
-    if (!resid && !draw) return;
-    ex.init();
+    __shared__ double sum_sh[kMaxBpw][4];
+    const int parts = (w.nsub + bpw - 1) / bpw;
+    const int part = blockIdx.x % parts, b = blockIdx.x / parts, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t ob = (int64_t)b * w.nsub;
+    const TreeScalars s = *mem.scalars(w, b, round & 1);
+    if (s.phase != TS_RESIDUAL) return;
     const int V = a.vocab;
     const int t0 = a.q_indptr[b], d0 = t0 - b;
     const float T = a.temperature ? a.temperature[b] : a.temperature_scalar;
     const double inv_t = 1.0 / (double)T;
-    const int64_t ob = (int64_t)b * w.nsub;
-    double zq = 1.0, norm = s.norm;
-    if (resid) {
-        zq = 0.0;
-        for (int c = 0; c < w.nsub; ++c) zq += w.zq[ob + c];
-    }
-    if (s.pure) {
-        norm = 0.0;
-        for (int c = 0; c < w.nsub; ++c) norm += w.zp[ob + c];
-    }
-    double *cur_arr = arr + ((int64_t)b * 2 + s.which) * V, *alt = arr + ((int64_t)b * 2 + (s.which ^ 1)) * V;
-    const double inv_norm = 1.0 / norm, inv_zq = 1.0 / zq;   // (one division each instead of two per vocabulary entry)
-    double sum = 0.0;
-#pragma unroll
-    for (int j = 0; j < kSubPer; ++j) {
-        const int v = sub * kSub + j * kThreads + tid;
-        if (v < V) {
-            const double e = s.pure ? ex(((double)load_logit(a.target, t0 + s.cur, a.row_stride, DT, v) - (double)s.mp) * inv_t)
-                                    : cur_arr[v];
-            const double rt = e * inv_norm;
-            if (resid) {
-                const double qt = ex(((double)load_logit(a.draft, d0 + s.rej - 1, a.row_stride, DT, v) - (double)s.mq) * inv_t) * inv_zq;
-                const double res = rt > qt ? rt - qt : 0.0;
-                alt[v] = res;
-                sum += res;
+    const RowArg ap(inv_t, s.mp), aq(inv_t, s.mq);
+    const void *prow = row_ptr(a.target, t0 + s.cur, a.row_stride, DT);
+    const void *qrow = row_ptr(a.draft, d0 + s.rej - 1, a.row_stride, DT);
+    const double *cur_arr = mem.arr + ((int64_t)b * 2 + s.which) * V;
+    double *alt = mem.arr + ((int64_t)b * 2 + (s.which ^ 1)) * V;
+    const int sub0 = part * bpw, count = min(bpw, w.nsub - sub0);
+    const int i0 = sub0 * kSub + tid * 8;
+    Raw8<DT> rp, rq;
+    load8<DT>(qrow, V, i0, rq);
+    if (s.pure) load8<DT>(prow, V, i0, rp);
+    ex.init();
+    const double zq = blocks_total(w.zq + ob, w.nsub);
+    const double norm = s.pure ? blocks_total(w.zp + ob, w.nsub) : s.norm;
+    const double inv_norm = 1.0 / norm, inv_zq = 1.0 / zq;
+#pragma unroll 1
+    for (int j = 0; j < count; ++j) {
+        const int i = i0 + j * kSub;
+        float x[8];
+        double e[8], q[8];
+        unpack8<DT>(rq, x);
+        if (j + 1 < count) load8<DT>(qrow, V, i + kSub, rq);
+        if (!s.pure) {   // (rows of the buffers start 8-byte aligned)
+            if (i + 8 <= V) {
+                __builtin_memcpy(e, cur_arr + i, sizeof(e));
             } else {
-                if (s.pure) cur_arr[v] = e;
-                sum += rt;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) e[t] = i + t < V ? cur_arr[i + t] : 0.0;
             }
         }
+        exp8(ex, aq, x, q);
+        if (s.pure) {
+            unpack8<DT>(rp, x);
+            if (j + 1 < count) load8<DT>(prow, V, i + kSub, rp);
+            exp8(ex, ap, x, e);
+        }
+        double sum = 0.0;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const double rt = e[t] * inv_norm, qt = q[t] * inv_zq;
+            e[t] = rt > qt ? rt - qt : 0.0;
+            sum += e[t];
+        }
+        if (i + 8 <= V) {
+            __builtin_memcpy(alt + i, e, sizeof(e));
+        } else {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                if (i + t < V) alt[i + t] = e[t];
+        }
+        sum = wave_scan(sum);
+        if (lane == 63) sum_sh[j][wave] = sum;
     }
-    sum = block_sum<double>(sum, sh);
-    if (tid == 0) w.sc[ob + sub] = sum;
+    __syncthreads();
+    if (tid < count) w.sc[ob + sub0 + tid] = (sum_sh[tid][0] + sum_sh[tid][1]) + (sum_sh[tid][2] + sum_sh[tid][3]);
 }
 
-// The draw: scan of the block masses, search inside the block that holds u * total.  grid: batch.
+// The draw.  Masses are unnormalised: the block sums and the exponentials of the current node's target row, or those of
+// the last residual.  grid: batch.
 template <int DT>
-__global__ __launch_bounds__(kThreads) void tree_pick_kernel(AcceptArgs a, Workspace w, const TreeState *st, const double *arr)
+__global__ __launch_bounds__(kThreads) void tree_pick_kernel(AcceptArgs a, Workspace w, TreeMem mem, int copy)
 {
-    __shared__ double sh[4];
-    __shared__ int shi[4];
-    __shared__ int cstar_sh;
-    __shared__ double prefix_sh, total_sh, norm_sh;
-    __shared__ double mass_sh[kThreads];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const TreeScalars s = st[b].s;
-    const int V = a.vocab;
-    const int t0 = a.q_indptr[b];
+    __shared__ ExpTable ex;
+    __shared__ DrawShared sh;
+    const int b = blockIdx.x, tid = threadIdx.x;
+    const TreeScalars s = *mem.scalars(w, b, copy);
+    const int V = a.vocab, t0 = a.q_indptr[b];
     const int64_t ob = (int64_t)b * w.nsub;
-    int y = -1;
+    int y;
     if (s.degenerate) {   // the residual vanished: lowest-index maximum of the current node's target row
-        int best = 0x7fffffff;
-        for (int v = tid; v < V; v += kThreads)
-            if (load_logit(a.target, t0 + s.cur, a.row_stride, DT, v) == s.mp) { best = v; break; }
-        for (int off = 32; off; off >>= 1) best = min(best, __shfl_xor(best, off));
-        if (lane == 0) shi[wave] = best;
-        __syncthreads();
-        y = min(min(shi[0], shi[1]), min(shi[2], shi[3]));
+        y = lowest_index_of(a.target, t0 + s.cur, a.row_stride, DT, V, s.mp, sh);
     } else {
-        // The block masses (and, if r was only just written out, the block sums of its normaliser) are
-        // fetched by the lanes at once; lane 0 then adds them in index order, as the other kernels do.
-        double total = 0.0, zsum = 0.0;
-        for (int base = 0; base < w.nsub; base += kThreads) {
-            const int c = base + tid;
-            __syncthreads();
-            mass_sh[tid] = c < w.nsub ? (s.pure ? w.zp[ob + c] : 0.0) : 0.0;
-            __syncthreads();
-            if (tid == 0)
-                for (int j = 0; j < kThreads && base + j < w.nsub; ++j) zsum += mass_sh[j];
-        }
-        if (tid == 0) norm_sh = s.pure ? zsum : s.norm;
-        const bool one_round = w.nsub <= kThreads;   // vocabularies up to 512k entries: the masses fit the staging array
-        __syncthreads();
-        mass_sh[tid] = one_round && tid < w.nsub ? w.sc[ob + tid] : 0.0;
-        __syncthreads();
-        const double norm = norm_sh;
-        if (tid == 0) {   // block masses in index order: total, then the first block with mass whose running sum exceeds u * total
-            for (int c = 0; c < w.nsub; ++c) total += one_round ? mass_sh[c] : w.sc[ob + c];
-            const double thr = (double)a.u_sample[b] * total;
-            double cum = 0.0, pre = 0.0, last_pre = 0.0;
-            int cstar = -1, last = -1;
-            for (int c = 0; c < w.nsub; ++c) {
-                const double m = one_round ? mass_sh[c] : w.sc[ob + c];
-                if (m > 0.0) {
-                    last = c;
-                    last_pre = cum;
-                    if (cstar < 0 && cum + m > thr) {
-                        cstar = c;
-                        pre = cum;
-                    }
-                    cum += m;
-                }
-            }
-            if (cstar < 0) {   // rounding left u * total at or past the sum: the last block with mass
-                cstar = last < 0 ? 0 : last;   // (no mass at all cannot happen for a valid batch; stay in bounds anyway)
-                pre = last_pre;
-            }
-            cstar_sh = cstar;
-            prefix_sh = pre;
-            total_sh = total;
-        }
-        __syncthreads();
-        const int cstar = cstar_sh;
-        const double thr = (double)a.u_sample[b] * total_sh;
-        const double *r_arr = arr + ((int64_t)b * 2 + s.which) * V;
-        // lane t owns the block's entries t*8 .. t*8+7 in token order
-        double r[kSubPer], local = 0.0;
-        int my_last = -1;
+        ex.init();
+        const float T = a.temperature ? a.temperature[b] : a.temperature_scalar;
+        const RowArg ap(1.0 / (double)T, s.mp);
+        const void *prow = row_ptr(a.target, t0 + s.cur, a.row_stride, DT);
+        const double *r_arr = mem.arr + ((int64_t)b * 2 + s.which) * V;
+        const double *blocks = (s.pure ? w.zp : w.sc) + ob;
+        auto mass_of = [&](int c) __attribute__((always_inline)) { return blocks[c]; };
+        auto entries = [&](int cstar, double (&r)[kSubPer]) __attribute__((always_inline)) {
+            const int i = cstar * kSub + tid * kSubPer;
+            if (s.pure) {
+                Raw8<DT> raw;
+                float x[8];
+                load8<DT>(prow, V, i, raw);
+                unpack8<DT>(raw, x);
+                exp8(ex, ap, x, r);
+            } else {
 #pragma unroll
-        for (int j = 0; j < kSubPer; ++j) {
-            const int v = cstar * kSub + tid * kSubPer + j;
-            r[j] = v < V ? r_arr[v] / norm : 0.0;
-            if (r[j] > 0.0) {
-                local += r[j];
-                my_last = v;
+                for (int t = 0; t < kSubPer; ++t) r[t] = i + t < V ? r_arr[i + t] : 0.0;
             }
-        }
-        double incl = local;
-        for (int off = 1; off < 64; off <<= 1) {
-            const double t = __shfl_up(incl, off);
-            if (lane >= off) incl += t;
-        }
-        if (lane == 63) sh[wave] = incl;
-        __syncthreads();
-        double before = prefix_sh;
-        for (int wv = 0; wv < wave; ++wv) before += sh[wv];
-        const double excl = before + (incl - local);
-        const unsigned long long bal = __ballot(excl + local > thr);
-        if (lane == 0) shi[wave] = bal ? wave * 64 + (__ffsll((long long)bal) - 1) : 0x7fffffff;
-        int lw = my_last;
-        for (int off = 32; off; off >>= 1) lw = max(lw, __shfl_xor(lw, off));
-        __syncthreads();
-        const int first = min(min(shi[0], shi[1]), min(shi[2], shi[3]));
-        __syncthreads();
-        if (lane == 0) shi[wave] = lw;
-        __syncthreads();
-        const int last_tok = max(max(shi[0], shi[1]), max(shi[2], shi[3]));
-        __syncthreads();
-        int tok = -1;
-        if (tid == first) {
-            double c = excl;
-#pragma unroll
-            for (int j = 0; j < kSubPer; ++j) {
-                if (r[j] > 0.0) {
-                    c += r[j];
-                    if (tok < 0 && c > thr) tok = cstar * kSub + tid * kSubPer + j;
-                }
-            }
-            if (tok < 0) tok = my_last;   // the lane total crossed but the element-wise sum rounds differently
-        }
-        for (int off = 32; off; off >>= 1) tok = max(tok, __shfl_xor(tok, off));
-        if (lane == 0) shi[wave] = tok;
-        __syncthreads();
-        y = first == 0x7fffffff ? last_tok : max(max(shi[0], shi[1]), max(shi[2], shi[3]));
+        };
+        y = draw_token(w.nsub, a.u_sample[b], sh, mass_of, entries);
+        if (y < 0) y = 0;   // (no mass at all cannot happen for a valid batch; stay in bounds anyway)
     }
     if (tid < SS_OUT_WIDTH)
-        a.out_tokens[(int64_t)b * SS_OUT_WIDTH + tid] = tid < s.n ? st[b].tok[tid] : (tid == s.n ? y : -1);
-    if (tid < SS_MAX_DEPTH) a.accepted_nodes[(int64_t)b * SS_MAX_DEPTH + tid] = tid < s.n ? st[b].node[tid] : -1;
+        a.out_tokens[(int64_t)b * SS_OUT_WIDTH + tid] = tid < s.n ? mem.st[b].tok[tid] : (tid == s.n ? y : -1);
+    if (tid < SS_MAX_DEPTH) a.accepted_nodes[(int64_t)b * SS_MAX_DEPTH + tid] = tid < s.n ? mem.st[b].node[tid] : -1;
     if (tid == 0) a.accepted_len[b] = s.n;
 }
 
@@ -343,16 +371,22 @@ size_t accept_tree_workspace_bytes(int batch, int total_rows, int vocab)
 }
 
 template <int DT>
-static int32_t tree_sample_rounds(const AcceptArgs &a, const Workspace &w, TreeState *st, double *arr, hipStream_t stream)
+static int32_t tree_sample_rounds(const AcceptArgs &a, const Workspace &w, const TreeMem &mem, hipStream_t stream)
 {
-    const dim3 per_request((unsigned)a.batch), per_block((unsigned)a.batch * w.nsub);
-    for (int round = 0; round < a.max_q_len; ++round) {   // a request has at most max_q_len - 1 rejections
-        hipLaunchKernelGGL(tree_walk_kernel<DT>, per_request, dim3(64), 0, stream, a, w, st, arr, round == 0 ? 1 : 0);
-        const int final_pass = round == a.max_q_len - 1;   // by now every request is waiting for its draw
-        hipLaunchKernelGGL(tree_sums_kernel<DT>, per_block, dim3(kThreads), 0, stream, a, w, st, final_pass);
-        hipLaunchKernelGGL(tree_resid_kernel<DT>, per_block, dim3(kThreads), 0, stream, a, w, st, arr, final_pass);
+    // Blocks per workgroup: one as long as that leaves no more than four wavefronts for each of the chip's 1024 SIMDs,
+    // then as many as keep it there, so that a large batch pays the walk and the totals once for several blocks and an
+    // idle round stays a small launch.
+    const long long blocks = (long long)a.batch * w.nsub;
+    const int bpw = (int)(blocks <= 1024 ? 1 : blocks >= 1024 * kMaxBpw ? kMaxBpw : (blocks + 1023) / 1024);
+    const dim3 per_request((unsigned)a.batch), per_part((unsigned)a.batch * ((w.nsub + bpw - 1) / bpw));
+    hipLaunchKernelGGL(tree_prep_kernel, per_request, dim3(kThreads), 0, stream, a, w, mem);
+    // a request has at most max_q_len - 1 rejections; the last sums kernel only walks on and prepares draws
+    const int rounds = a.max_q_len - 1;
+    for (int round = 0; round <= rounds; ++round) {
+        hipLaunchKernelGGL(tree_sums_kernel<DT>, per_part, dim3(kThreads), 0, stream, a, w, mem, round, bpw);
+        if (round < rounds) hipLaunchKernelGGL(tree_resid_kernel<DT>, per_part, dim3(kThreads), 0, stream, a, w, mem, round, bpw);
     }
-    hipLaunchKernelGGL(tree_pick_kernel<DT>, per_request, dim3(kThreads), 0, stream, a, w, st, arr);
+    hipLaunchKernelGGL(tree_pick_kernel<DT>, per_request, dim3(kThreads), 0, stream, a, w, mem, rounds & 1);
     SS_HIP_CHECK(hipGetLastError(), "launch of the sampled tree walk");
     return SS_OK;
 }
@@ -361,13 +395,14 @@ int32_t accept_tree_sample_launch(const AcceptArgs &a, hipStream_t stream)
 {
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
     char *p = static_cast<char *>(a.workspace) + accept_workspace_bytes(a.batch, a.total_rows, a.vocab);
-    TreeState *st = reinterpret_cast<TreeState *>(p);
-    double *arr = reinterpret_cast<double *>(p + align_up(sizeof(TreeState) * (size_t)a.batch, 256));
+    TreeMem mem;
+    mem.st = reinterpret_cast<TreeState *>(p);
+    mem.arr = reinterpret_cast<double *>(p + align_up(sizeof(TreeState) * (size_t)a.batch, 256));
     if ((unsigned long long)a.batch * w.nsub > 0x7fffffffull) return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
     const int32_t rc = accept_rowstats_launch(a, stream);
     if (rc != SS_OK) return rc;
-    if (a.logit_dtype == SS_BF16) return tree_sample_rounds<SS_BF16>(a, w, st, arr, stream);
-    return tree_sample_rounds<SS_F32>(a, w, st, arr, stream);
+    if (a.logit_dtype == SS_BF16) return tree_sample_rounds<SS_BF16>(a, w, mem, stream);
+    return tree_sample_rounds<SS_F32>(a, w, mem, stream);
 }
 
 }  // namespace ss
