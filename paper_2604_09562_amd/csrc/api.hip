@@ -29,7 +29,7 @@ int32_t hip_fail(hipError_t e, const char *what)
 static int64_t g_attn_path = 0;
 static int64_t g_attn_waves = 0;
 static int64_t g_validate = 0;
-static int64_t g_unit_weight = kUnitWeight;
+static int64_t g_unit_weight = -1;        // -1: by the instance's row blocks
 static std::vector<hipEvent_t> g_events;  // pairs
 static int g_prof_cap = 0, g_prof_used = 0;
 
@@ -219,17 +219,17 @@ int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const 
     a.q_lo = 0;
     a.q_win = max_q_len;
     a.reuse_plan = (batch->flags & SS_BATCH_REUSE_PLAN) ? 1 : 0;
-    a.unit_weight = (int32_t)g_unit_weight;
+    a.unit_weight = g_unit_weight < 0 ? -1 : ((int32_t)g_unit_weight + 1) / 2;   // tiles -> pairs
     // carve the workspace
     char *w = static_cast<char *>(workspace);
     a.plan = reinterpret_cast<AttnPlan *>(w);
     w += 256;
-    a.tile_prefix = reinterpret_cast<int32_t *>(w);
+    a.pair_prefix = reinterpret_cast<int32_t *>(w);
     w += align_up(sizeof(int32_t) * ((size_t)batch->batch + 1), 256);
     a.wave_desc = reinterpret_cast<int32_t *>(w);
     w += align_up(sizeof(int32_t) * kDescInts * (size_t)launch_waves, 256);
-    a.tile_addr = reinterpret_cast<int32_t *>(w);
-    w += align_up(sizeof(int32_t) * (size_t)batch->batch * batch->max_blocks_per_seq * kv->num_kv_heads, 256);
+    a.pair_addr = reinterpret_cast<int2 *>(w);
+    w += align_up(sizeof(int2) * (size_t)batch->batch * (((size_t)batch->max_blocks_per_seq + 1) / 2) * kv->num_kv_heads, 256);
     const size_t slots = (size_t)launch_waves + (size_t)batch->batch * kv->num_kv_heads;
     a.part_ml = reinterpret_cast<float *>(w);
     w += align_up(slots * a.rows_pad * 2 * sizeof(float), 256);

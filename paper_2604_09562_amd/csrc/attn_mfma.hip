@@ -1,27 +1,7 @@
 // Verify attention on the matrix cores (gfx950), head_dim 128, bf16 queries, bf16 or e4m3 cache.
 //
-// Work decomposition.  The KV cache of one (request, KV head) pair ("unit") is a run of
-// 16-token tiles, one per cache block.  All tiles of all units form one flat sequence (unit
-// major).  A plan kernel writes that sequence out as a flat list of tile addresses (physical
-// block * kv heads + kv head) and cuts it into `num_waves` contiguous spans of equal cost (a
-// tile costs one, opening a unit a fixed number of tiles; span_cuts.h); every wavefront streams
-// one span, so the load is balanced whatever the mix of context lengths, and the load side of
-// the kernel is a plain linear walk that never stops at a unit boundary.  A span may cover the
-// tail of one unit, several whole units and the head of another; for every unit it touches the
-// wave has one partial result (softmax reference, sum, unnormalised output).  What the streaming
-// kernel cannot finish itself (attn_mfma_kernels.h) goes to a partial slot, `wave + unit` or
-// `workgroup + unit` (unique along the sequence), and a last kernel merges the partials of each
-// such unit by their log-sum-exp and writes the rounded output.
-//
-// Per tile, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
-//   S^T[token][row] = K[token][:] . Q[row][:]   v_mfma_f32_16x16x32_bf16, K tile as A operand
-//   online softmax on S^T in registers (a row's 16 scores sit in 4 lanes x 4 registers)
-//   O^T[d][row]    += V[token][d] * P[row][token]   v_mfma_f32_16x16x16_bf16, P taken straight
-//                     from the S^T accumulator layout, V as A operand
-// Both K and V are read from HBM directly in operand layout with 16-byte loads: for K a lane
-// holds 8 consecutive d of one token; for V a lane holds d = 8*i .. 8*i+7 of four tokens and
-// the eight M-blocks of O^T are the eight interleaved d-phases, so no transpose through LDS is
-// needed (only a 16-bit pack per operand register).
+// The work decomposition and the tile arithmetic are described in attn_mfma_kernels.h; here are the plan kernel,
+// the workspace layout and the dispatch.
 #include "common.h"
 #include "span_cuts.h"
 
@@ -29,15 +9,15 @@ namespace ss {
 namespace {
 
 // ---------------------------------------------------------------------------------------------
-// plan: workgroup (b, g) writes the flat tile address list of its unit and the descriptors of the waves
+// plan: workgroup (b, g) writes the flat list of tile pair addresses of its unit and the descriptors of the waves
 // whose span starts inside it; (b, 0) / the last one publish the prefix and the partition count.
 //
 // Where the spans are cut.  A wave pays a fixed price for every unit it opens (query loads, a drained
 // tile pipeline, the partial of the unit before: about the time of kUnitWeight tiles), so equal tile
 // counts do not finish together: on a ragged batch the waves that cross ten short units were 10 % late.
-// The cuts are therefore equal in a weighted coordinate in which every unit is kUnitWeight virtual
-// tiles followed by its real ones; a cut that falls into a unit's virtual part becomes the unit's first
-// tile.  The cuts depend on the batch's lengths only, so results do not vary from run to run.
+// The cuts are therefore equal in a weighted coordinate in which every unit is `unit_weight` virtual
+// pairs followed by its real ones; a cut that falls into a unit's virtual part becomes the unit's first
+// pair.  The cuts depend on the batch's lengths only, so results do not vary from run to run.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPlanMaxBatch = 4096;   // requests whose tile prefix fits the plan kernel's LDS; beyond that the cuts are unweighted
 
@@ -57,7 +37,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         int carry = 0;
         for (int base = 0; base < a.batch; base += 256) {
             const int i = base + tid;
-            const int t = i < a.batch ? window_tiles(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo) : 0;
+            const int t = i < a.batch ? window_pairs(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo) : 0;
             int incl = t;
             for (int off = 1; off < 64; off <<= 1) {
                 const int o = __shfl_up(incl, off);
@@ -79,7 +59,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     } else {
         int before = 0, rest = 0;
         for (int i = tid; i < a.batch; i += 256) {
-            const int t = window_tiles(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo);
+            const int t = window_pairs(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo);
             if (i < b) before += t; else rest += t;
         }
         for (int off = 32; off; off >>= 1) {
@@ -95,17 +75,29 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         pre = sh2[0] + sh2[1] + sh2[2] + sh2[3];
         total = (long long)(pre + sh2[4] + sh2[5] + sh2[6] + sh2[7]) * a.num_kv_heads;
     }
-    long long nw = total / kMinTilesPerWave;
+    long long nw = total / kMinPairsPerWave;
     if (nw < 1) nw = 1;
     if (nw > a.launch_waves) nw = a.launch_waves;
+    // A chip that is full combines the spans of a workgroup in LDS, which saves partials.  A batch too small for that is
+    // bound by latency, and the hand-over is a chain of up to four unit ends (1.2 us each, 3.8 us for the output): there
+    // every wavefront leaves its partial at once and the merge kernel, which runs anyway, combines them
+    // (4 requests of 40..600 tokens, 8 KV heads: streaming kernel 16.4 -> 14.2 us, with spans of two pairs instead of
+    // four 11.4 us; merge kernel 4.0 -> 4.2 us).
+    const int chain = nw == a.launch_waves;
     const int weight = weighted ? a.unit_weight : 0;
     const long long total_w = total + (long long)weight * a.batch * a.num_kv_heads;
 
-    const int n = window_tiles(a.kv_len[b], a.q_indptr[b + 1] - a.q_indptr[b], a.q_lo);
+    const int n = window_pairs(a.kv_len[b], a.q_indptr[b + 1] - a.q_indptr[b], a.q_lo);
     const long long off = (long long)pre * a.num_kv_heads + (long long)g * n;   // this unit's place in the flat list
     const int32_t *bt = a.block_table + (long long)b * a.max_blocks;
-    int32_t *dst = a.tile_addr + off;
-    for (int t = tid; t < n; t += 256) dst[t] = bt[t] * a.num_kv_heads + g;
+    const int blocks = (a.kv_len[b] + kTile - 1) / kTile;
+    // (a pair whose second tile lies past the cache's end repeats the first; its slots are never visible)
+    auto pair_at = [](const int32_t *table, int t, int nblk, int hkv, int gg) {
+        const int b0 = table[2 * t], b1 = 2 * t + 1 < nblk ? table[2 * t + 1] : b0;
+        return make_int2(b0 * hkv + gg, b1 * hkv + gg);
+    };
+    int2 *dst = a.pair_addr + off;
+    for (int t = tid; t < n; t += 256) dst[t] = pair_at(bt, t, blocks, a.num_kv_heads, g);
 
     // waves whose cut falls into this unit's stretch [ya, ya + weight + n) of the weighted coordinate
     SpanCuts cuts;
@@ -120,7 +112,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     const long long w_lo = cuts.first_cut_at_or_after(ya);                // first w with w*total_w/nw >= ya
     const long long w_hi = cuts.first_cut_at_or_after(ya + weight + n);   // first w at or past the unit's end
     // Descriptor: {request, kv head, first tile, tiles of the unit, span begin, span end, kv_len,
-    // first query row, end query row, addresses of the span's first kDescAddrs tiles}: everything
+    // first query row, end query row, addresses of the span's first kDescPairs tile pairs}: everything
     // the wave's first loads depend on, so that they go out after a single read.
     for (long long w = w_lo + tid; w < w_hi && w < nw; w += 256) {
         const int t0 = cuts.first_tile(cuts.cut(w), ya);
@@ -129,23 +121,27 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         int32_t *d = a.wave_desc + w * kDescInts;
         d[0] = b; d[1] = g; d[2] = t0; d[3] = n;
         d[4] = (int)x0; d[5] = (int)x1;
+        d[15] = chain;
         d[6] = a.kv_len[b]; d[7] = a.q_indptr[b]; d[8] = a.q_indptr[b + 1];
-        // walk forward from (b, g, tile) over unit boundaries; past the last unit repeat the last tile
-        int bb = b, gg = g, tt = t0, nn = n, last = 0;
+        // walk forward from (b, g, pair) over unit boundaries; past the last unit repeat the last pair
+        int bb = b, gg = g, tt = t0, nn = n, nblk = blocks;
+        int2 last = make_int2(0, 0);
         const int32_t *tb = bt;
-        for (int j = 0; j < kDescAddrs; ++j) {
+        for (int j = 0; j < kDescPairs; ++j) {
             while (bb < a.batch && tt >= nn) {
                 tt -= nn;
                 if (++gg == a.num_kv_heads) {
                     gg = 0;
                     if (++bb < a.batch) {
-                        nn = window_tiles(a.kv_len[bb], a.q_indptr[bb + 1] - a.q_indptr[bb], a.q_lo);
+                        nn = window_pairs(a.kv_len[bb], a.q_indptr[bb + 1] - a.q_indptr[bb], a.q_lo);
+                        nblk = (a.kv_len[bb] + kTile - 1) / kTile;
                         tb = a.block_table + (long long)bb * a.max_blocks;
                     }
                 }
             }
-            if (bb < a.batch) last = tb[tt] * a.num_kv_heads + gg;
-            d[9 + j] = last;
+            if (bb < a.batch) last = pair_at(tb, tt, nblk, a.num_kv_heads, gg);
+            d[9 + 2 * j] = last.x;
+            d[10 + 2 * j] = last.y;
             ++tt;
         }
     }
@@ -157,12 +153,13 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         }
     }
     if (g == 0 && tid == 0) {
-        a.tile_prefix[b] = pre;
+        a.pair_prefix[b] = pre;
         if (b == a.batch - 1) {
-            a.tile_prefix[a.batch] = pre + n;
-            a.plan->total_tiles = (int)total;
+            a.pair_prefix[a.batch] = pre + n;
+            a.plan->total_pairs = (int)total;
             a.plan->num_waves = (int)nw;
             a.plan->unit_weight = weight;
+            a.plan->chain = chain;
         }
     }
 }
@@ -178,7 +175,7 @@ size_t attn_workspace_bytes(int batch, int max_blocks, int num_q_heads, int num_
     size_t n = 256;
     n += align_up(sizeof(int32_t) * ((size_t)batch + 1), 256);
     n += align_up(sizeof(int32_t) * kDescInts * (size_t)launch_waves, 256);
-    n += align_up(sizeof(int32_t) * (size_t)batch * max_blocks * num_kv_heads, 256);
+    n += align_up(sizeof(int2) * (size_t)batch * (((size_t)max_blocks + 1) / 2) * num_kv_heads, 256);
     n += align_up(slots * rows_pad * 2 * sizeof(float), 256);
     n += align_up(slots * rows_pad * (size_t)head_dim * sizeof(float), 256);
     return n;
@@ -202,6 +199,7 @@ int32_t attn_mfma_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, 
     const int passes = (a.max_q_len + win_max - 1) / win_max;
     AttnArgs p = a;
     p.q_win = (a.max_q_len + passes - 1) / passes;
+    if (p.unit_weight < 0) p.unit_weight = (p.q_win * G + 15) / 16 >= 4 ? kUnitWeightDeep : kUnitWeight;
     for (p.q_lo = 0; p.q_lo < a.max_q_len; p.q_lo += p.q_win) {
         if (!(a.reuse_plan && passes == 1)) {   // a stored plan describes one window only
             hipLaunchKernelGGL(attn_plan_kernel, dim3((unsigned)a.batch * a.num_kv_heads), dim3(256), 0, stream, p);

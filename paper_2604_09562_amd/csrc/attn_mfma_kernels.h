@@ -3,15 +3,15 @@
 // instances compile in parallel; attn_mfma.hip holds the plan kernel and the dispatch.
 //
 // Work decomposition.  The KV cache of one (request, KV head) pair ("unit") is a run of
-// 16-token tiles, one per cache block.  All tiles of all units form one flat sequence (unit
-// major).  A plan kernel writes that sequence out as a flat list of tile addresses (physical
+// 16-token tiles, one per cache block, taken two at a time ("pair").  All pairs of all units form one flat
+// sequence (unit major).  A plan kernel writes that sequence out as a flat list of tile addresses (physical
 // block * kv heads + kv head) and cuts it into `num_waves` contiguous spans of equal cost (a
-// tile costs one, opening a unit costs a fixed number of tiles); every wavefront streams one
+// pair costs one, opening a unit costs a fixed number of pairs); every wavefront streams one
 // span, so the load is balanced whatever the mix of context lengths, and the load side of the
 // kernel is a plain linear walk that never stops at a unit boundary.  A span may cover the tail
 // of one unit, several whole units and the head of another; for every unit it touches the wave
 // has one partial result (softmax reference, sum, unnormalised output).  In the instances with
-// at most two row blocks the four wavefronts of a workgroup, whose spans are consecutive, hand
+// at most two row blocks, when the batch fills the chip, the four wavefronts of a workgroup, whose spans are consecutive, hand
 // the partials of a shared unit from right to left through LDS and combine them by their
 // log-sum-exp; a unit that lies inside one workgroup's spans is normalised, rounded and
 // written by that workgroup.  What is left (a unit that crosses workgroups; every split unit
@@ -19,15 +19,30 @@
 // (`wave + unit` without the LDS hand-over; unique along the sequence either way), and a last
 // kernel merges those partials in span order and writes the rounded output.
 //
-// Per tile, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
-//   S^T[token][row] = K[token][:] . Q[row][:]   v_mfma_f32_16x16x32_bf16, K tile as A operand
-//   online softmax on S^T in registers (a row's 16 scores sit in 4 lanes x 4 registers)
-//   O^T[d][row]    += V[token][d] * P[row][token]   v_mfma_f32_16x16x16_bf16, P taken straight
-//                     from the S^T accumulator layout, V as A operand
+// Per pair, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
+//   S^T[token][row] = K[token][:] . Q[row][:]   v_mfma_f32_16x16x32_bf16, each K tile as A operand
+//   online softmax on S^T in registers (a row's 16 scores of a tile sit in 4 lanes x 4 registers)
+//   O^T[d][row]    += V[token][d] * P[row][token]   v_mfma_f32_16x16x32_bf16 over both tiles' tokens, V as A
+//                     operand.  Which token stands at which place of the contraction is free as long as both operands
+//                     agree: lane group jq brings tokens 4 jq .. 4 jq + 3 of the first tile and of the second, so that P
+//                     is taken straight from the two S^T accumulators.
 // Both K and V are read from HBM directly in operand layout with 16-byte loads: for K a lane
-// holds 8 consecutive d of one token; for V a lane holds d = 8*i .. 8*i+7 of four tokens and
+// holds 8 consecutive d of one token; for V a lane holds d = 8*i .. 8*i+7 of four tokens of each tile and
 // the eight M-blocks of O^T are the eight interleaved d-phases, so no transpose through LDS is
 // needed (only a 16-bit pack per operand register).
+//
+// Why pairs: contracting over 32 tokens the output product runs at the full matrix rate (the 16-token shape takes the
+// same 16 cycles for half of the work), and matrix and vector instructions of a wavefront hardly overlap on this
+// chip (16 cycles and 5 cycles take 18.9 together), so every matrix instruction less is time.
+//
+// Why the code is written to be small (one copy of a unit's beginning and end outside the ring, which is rotated in
+// registers instead): the instances took up to 150 KB of code with those inlined into every step of an unrolled ring and its
+// epilogue, more than the 64 KB instruction cache that two compute units share; now 14 to 28 KB.
+//
+// Measured (a whole call, before / after: single tiles, 16-token output products, query loads under a branch per row
+// block, one unit weight): 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 / 249 us; 32 requests of
+// 256..4096, trees of 8..16 nodes, 32 heads over 8: 101 / 80; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 / 107.2; four
+// requests of 40..600: 26.0 / 20.1.
 #pragma once
 
 #include <type_traits>
@@ -52,7 +67,6 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kSlack = 8.0f;       // log2 headroom of the lagging softmax reference
 constexpr float kNoMax = -1.0e30f;   // reference before any score was seen (finite, so that -inf - ref stays -inf)
-constexpr int kIdWindow = 512;       // tile addresses a wave stages in LDS at a time
 constexpr int kMaxFlagPolls = 1 << 23;   // polls of a neighbour's deposit flag before giving up (each at least 128 cycles)
 constexpr int kPartRowStride = 33;   // float4 per staged partial row in LDS (32 of data + 1 of padding)
 template <int NB>
@@ -74,35 +88,19 @@ __device__ __forceinline__ uint32_t pack_lo16(uint32_t lo_src, uint32_t hi_src)
     return __builtin_amdgcn_perm(hi_src, lo_src, 0x05040100u);
 }
 
-// 8 e4m3 bytes (two words) -> 8 bf16 (exact: e4m3 has 4 significant bits)
+// Two e4m3 bytes (the lower or upper half of a word) -> two bf16 (exact: e4m3 has 4 significant bits; the scale is 1)
+template <bool HI>
+__device__ __forceinline__ uint32_t fp8x2_to_bf16x2(uint32_t w)
+{
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, HI));
+}
 __device__ __forceinline__ uint4 fp8x8_to_bf16x8(uint32_t w0, uint32_t w1)
 {
-    const float2v a = __builtin_amdgcn_cvt_pk_f32_fp8(w0, false);
-    const float2v b = __builtin_amdgcn_cvt_pk_f32_fp8(w0, true);
-    const float2v c = __builtin_amdgcn_cvt_pk_f32_fp8(w1, false);
-    const float2v d = __builtin_amdgcn_cvt_pk_f32_fp8(w1, true);
-    uint4 r;
-    r.x = pack_hi16(__float_as_uint(a.x), __float_as_uint(a.y));
-    r.y = pack_hi16(__float_as_uint(b.x), __float_as_uint(b.y));
-    r.z = pack_hi16(__float_as_uint(c.x), __float_as_uint(c.y));
-    r.w = pack_hi16(__float_as_uint(d.x), __float_as_uint(d.y));
-    return r;
+    return make_uint4(fp8x2_to_bf16x2<false>(w0), fp8x2_to_bf16x2<true>(w0), fp8x2_to_bf16x2<false>(w1), fp8x2_to_bf16x2<true>(w1));
 }
 
-// KV tiles are read exactly once per call: non-temporal loads keep them from displacing what is reused
-// (partials, queries, the tile list) in the caches.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint4 stream_load16(const char *p)
-{
-    const u32x4 r = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(r.x, r.y, r.z, r.w);
-}
-__device__ __forceinline__ uint2 stream_load8(const char *p)
-{
-    const u32x2 r = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
-    return make_uint2(r.x, r.y);
-}
 
 // Output accumulators live in the accumulator registers (the matrix instructions are selected in that form
 // once a kernel needs more than 256 registers).  A value that ordinary vector arithmetic produced -- the zero
@@ -127,65 +125,85 @@ template <bool FP8>
 struct TileRegs {
     // bf16: k[ks] = 8 bf16 of token (lane&15) at d = 32*ks + 8*(lane>>4)
     // fp8 : k[kk] = 16 bytes of token (lane&15) at d = 64*kk + 16*(lane>>4)   (kk = 0,1)
-    uint4 k[FP8 ? 2 : 4];
+    u32x4 k[FP8 ? 2 : 4];
     // bf16: v[e] = 8 bf16 of token 4*(lane>>4)+e at d = 8*(lane&15)
     // fp8 : v[e] = 8 bytes of the same
-    typename std::conditional<FP8, uint2, uint4>::type v[4];
+    typename std::conditional<FP8, u32x2, u32x4>::type v[4];
     float ks, vs;  // block scales (fp8), 1 otherwise
+};
+template <bool FP8>
+struct PairRegs {
+    TileRegs<FP8> t[2];
 };
 
 // All loads of one tile are vector loads issued back to back, so one counter orders them and the
 // consumer can wait for exactly this tile.  `addr` = physical block * kv heads + kv head indexes
-// both the 4 KB (2 KB for e4m3) tile and its scale.  `vzero` is a lane register holding 0 that the
-// compiler cannot see through: it keeps the (wave-uniform) scale reads on the vector path too.
+// both the 4 KB (2 KB for e4m3) tile and its scale.  Buffer loads through a descriptor of exactly the tile: a
+// load with `live` false (past the span's end) has a descriptor of no bytes, returns zeros and moves nothing, so the ring's
+// last steps need no code of their own.  KV tiles are read exactly once per call: non-temporal loads keep them from
+// displacing what is reused (partials, queries, the pair list) in the caches.
+// The keys of both tiles come first: they are used first.
+constexpr int kNonTemporal = 2;
 template <bool FP8>
-__device__ __forceinline__ void load_tile(TileRegs<FP8> &t, const AttnArgs &a, const float *__restrict__ k_scale,
-                                          const float *__restrict__ v_scale, int addr, int lane, int vzero)
+__device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs &a, const float *__restrict__ k_scale,
+                                                const float *__restrict__ v_scale, int2 addr, bool live, int lane)
 {
-    constexpr int ES = FP8 ? 1 : 2;
-    const int64_t blk = (int64_t)addr * (kTile * D * ES);
-    const char *kp = static_cast<const char *>(a.k) + blk + (lane & 15) * (D * ES) + (lane >> 4) * 16;
-    const char *vp = static_cast<const char *>(a.v) + blk + (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
+    constexpr int ES = FP8 ? 1 : 2, BYTES = kTile * D * ES;
+    const int bytes = live ? BYTES : 0;
+    const int ko = (lane & 15) * (D * ES) + (lane >> 4) * 16, vo = (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
 #pragma unroll
-    for (int i = 0; i < (FP8 ? 2 : 4); ++i) t.k[i] = stream_load16(kp + i * 64);
+    for (int h = 0; h < 2; ++h) {
+        const int64_t blk = (int64_t)(h ? addr.y : addr.x) * BYTES;
+        const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(static_cast<const char *>(a.k)) + blk, 0, bytes, 0x00020000);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        if constexpr (FP8)
-            t.v[e] = stream_load8(vp + e * (D * ES));
-        else
-            t.v[e] = stream_load16(vp + e * (D * ES));
+        for (int i = 0; i < (FP8 ? 2 : 4); ++i)
+            p.t[h].k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, ko + i * 64, 0, kNonTemporal);
     }
-    if constexpr (FP8) {
-        t.ks = k_scale[addr + vzero];
-        t.vs = v_scale[addr + vzero];
-    } else {
-        t.ks = 1.f;
-        t.vs = 1.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int ad = h ? addr.y : addr.x;
+        const int64_t blk = (int64_t)ad * BYTES;
+        const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(static_cast<const char *>(a.v)) + blk, 0, bytes, 0x00020000);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if constexpr (FP8)
+                p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b64(vr, vo + e * (D * ES), 0, kNonTemporal);
+            else
+                p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b128(vr, vo + e * (D * ES), 0, kNonTemporal);
+        }
+        if constexpr (FP8) {
+            p.t[h].ks = k_scale[ad];   // wave-uniform: scalar loads
+            p.t[h].vs = v_scale[ad];
+        } else {
+            p.t[h].ks = 1.f;
+            p.t[h].vs = 1.f;
+        }
     }
 }
 
 // NB    16-row blocks of query rows the kernel is compiled for (covers max_q_len * G rows)
-// NBUF  KV tiles resident per wave: one being consumed, NBUF-1 in flight from HBM
+// NBUF  tile pairs resident per wave; a pair's registers are refilled as soon as its operands have been taken
 // QLDS  keep the query operands in LDS (in operand order, one 1 KB line per row block and k-step)
 //       instead of registers: for many row blocks the registers are needed for the accumulators
 // TREE  the new tokens of a request form a draft tree: a row's visibility among them comes from its
 //       mask word instead of the chain's "tokens up to my own"
 template <int G, int NB, bool FP8, int NBUF, bool QLDS, bool TREE>
 __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
-    AttnArgs a, const int32_t *__restrict__ tile_addr, const int32_t *__restrict__ wave_desc,
-    const int32_t *__restrict__ tile_prefix,
+    AttnArgs a, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
+    const int32_t *__restrict__ pair_prefix,
     const int32_t *__restrict__ kv_len, const int32_t *__restrict__ q_indptr, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale)
 {
     // The metadata arrays come in as separate no-alias arguments so that their wave-uniform reads
     // become scalar loads (own counter, no ordering against the vector KV loads).
-    __shared__ int32_t id_lds[kWavesPerWg][kIdWindow];
     __shared__ uint4 q_lds[QLDS ? kWavesPerWg * NB * 4 * 64 : 1];
     // one 16-row block of a partial per wave, rows 33 float4 apart (the odd stride spreads the rows over the banks)
     __shared__ float4v o_lds[kStageRows<NB> ? kWavesPerWg : 1][kStageRows<NB> ? 16 * kPartRowStride : 1];
     __shared__ float2 ml_lds[kWavesPerWg][16];
-    // CHAIN: the wavefronts of a workgroup own consecutive spans, so a unit that runs on from one span into the
-    // next is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit
+    // CHAIN (with the plan's consent): the wavefronts of a workgroup own consecutive spans, so a unit that runs on from
+    // one span into the next is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit
     // slot, the left-hand one folds it into its own.  Only what crosses a workgroup's edge goes to memory as a
     // partial; a unit that lies inside one workgroup is finished here.
     // (Only for one or two row blocks: with three the deposit slots take 100 KB and the ragged workload, the one
@@ -198,33 +216,31 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = blockIdx.x * kWavesPerWg + wslot;
     const int r16 = lane & 15, jq = lane >> 4;
-    int vzero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(vzero));
-    int32_t *ids = id_lds[wslot];
     uint4 *qs = q_lds + (QLDS ? wslot * NB * 4 * 64 : 0) + (QLDS ? lane : 0);
 
     // where this wave's span starts: written by the plan kernel (waves past the partition count get x0 == x1)
-    int b, g, tile, nb_tiles;
+    int b, g, tile, nb_tiles;   // request, KV head, pair within the unit, pairs of the unit
     long long x0, x1;
-    int meta_L, meta_q0, meta_q1, meta_nbt;   // kv_len / q_indptr / tile count of the next unit to open
-    int desc_addr[kDescAddrs];
+    bool chain;                 // combine the spans of the workgroup (the plan's choice)
+    int meta_L, meta_q0, meta_q1, meta_nbt;   // kv_len / q_indptr / pair count of the next unit to open
+    int2 desc_addr[kDescPairs];
     {
         const int32_t *d = wave_desc + (long long)wave * kDescInts;
         b = d[0]; g = d[1]; tile = d[2]; nb_tiles = d[3];
         x0 = d[4]; x1 = d[5];
         meta_L = d[6]; meta_q0 = d[7]; meta_q1 = d[8]; meta_nbt = nb_tiles;
 #pragma unroll
-        for (int j = 0; j < kDescAddrs; ++j) desc_addr[j] = d[9 + j];
+        for (int j = 0; j < kDescPairs; ++j) desc_addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
+        chain = CHAIN && d[15] != 0;
     }
-    static_assert(NBUF - 1 <= kDescAddrs, "descriptor carries too few tile addresses");
     if (lane == 0) dep_flag[wslot] = 0;
     __syncthreads();   // the only barrier: every wave's flag is clear before any neighbour can look at it
     if (x0 >= x1) return;
 
     // ---- state of the unit being computed ----
-    int span_left = (int)(x1 - x0);   // tiles of the span not yet computed
-    int seg_left = 0;                 // of those, tiles that still belong to the current unit
-    int seg_tile0 = 0;                // the unit's tile the current segment began with
+    int span_left = (int)(x1 - x0);   // pairs of the span not yet computed
+    int seg_left = 0;                 // of those, pairs that still belong to the current unit
+    int seg_tile0 = 0;                // the unit's pair the current segment began with
     int L = 0, q0 = 0, q_len = 0, rows = 0, nbu = 0;   // nbu: 16-row blocks the unit really has (for its partial)
     bf16x8 qreg[QLDS ? 1 : NB][4];    // Q as B operand: lane holds row 16*nb + r16, 8 consecutive d per k-step
     int lim[TREE ? 1 : NB];           // chain: last visible cache position of this lane's row in block nb
@@ -250,31 +266,40 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 meta_L = kv_len[nb_];
                 meta_q0 = q_indptr[nb_];
                 meta_q1 = q_indptr[nb_ + 1];
-                meta_nbt = tile_prefix[nb_ + 1] - tile_prefix[nb_];
+                meta_nbt = pair_prefix[nb_ + 1] - pair_prefix[nb_];
             }
         }
         seg_left = nb_tiles - tile < span_left ? nb_tiles - tile : span_left;
         seg_tile0 = tile;
+        // All query loads go out before any of them is waited for: buffer loads over the request's rows, whose
+        // offset is out of range (zeros) for a row the unit does not have, so there is no branch between them.  (Under a branch
+        // per block the LDS instances waited for every block's loads in turn, 7 us at the start of a span.)
+        const long long q_row = (long long)a.num_q_heads * D * 2;   // bytes from one query token to the next
+        const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char *>(static_cast<const char *>(a.q)) + (q0 * q_row + (long long)g * (G * D * 2)), 0, (int)(q_len * q_row),
+            0x00020000);
+        u32x4 qw[NB][4];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int n = nb * 16 + r16;
             const bool ok = n < rows;
             const int qi = a.q_lo + n / G, hh = n % G;   // query token within the request, head within the group
             if constexpr (TREE)   // padding rows see every new token: harmless, and no row is empty
-                newmask[nb] = ok ? a.tree_mask[q0 + qi] : (2u << (q_len - 1)) - 1u;
+                newmask[nb] = a.tree_mask[q0 + (ok ? qi : 0)];
             else
                 lim[nb] = ok ? L - q_len + qi : L - 1;
-            const char *qp = static_cast<const char *>(a.q) +
-                             (((long long)(q0 + qi) * a.num_q_heads + g * G + hh) * D) * 2;
+            const int off = ok ? qi * (int)q_row + hh * (D * 2) : 0x7fffff00;
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 const int d0 = FP8 ? ((ks >> 1) * 64 + jq * 16 + (ks & 1) * 8) : (ks * 32 + jq * 8);
-                uint4 w = make_uint4(0, 0, 0, 0);
-                if (ok) w = *reinterpret_cast<const uint4 *>(qp + d0 * 2);
-                if constexpr (QLDS)
-                    qs[(nb * 4 + ks) * 64] = w;
-                else
-                    qreg[nb][ks] = __builtin_bit_cast(bf16x8, w);
+                qw[nb][ks] = __builtin_amdgcn_raw_buffer_load_b128(qr, off + d0 * 2, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                if constexpr (!QLDS) qreg[nb][ks] = __builtin_bit_cast(bf16x8, qw[nb][ks]);
             }
             m_run[nb] = kNoMax;
             l_run[nb] = 0.f;
@@ -283,6 +308,12 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 acc[mb][nb] = float4v{0.f, 0.f, 0.f, 0.f};
                 to_accumulator_file(acc[mb][nb]);
             }
+        }
+        if constexpr (QLDS) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) qs[(nb * 4 + ks) * 64] = __builtin_bit_cast(uint4, qw[nb][ks]);
         }
     };
     // Have the queries arrive here, inside the rarely taken branch, so that the steady-state path
@@ -296,7 +327,10 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
         if constexpr (TREE) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+v"(newmask[nb]));
+            for (int nb = 0; nb < NB; ++nb) {
+                if (nb * 16 + r16 >= rows) newmask[nb] = (2u << (q_len - 1)) - 1u;
+                asm volatile("" : "+v"(newmask[nb]));
+            }
         }
     };
 
@@ -317,7 +351,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
         bool to_end = ends;   // does the result held here reach the unit's last tile?
         if constexpr (CHAIN) {
-            if (!ends && wslot + 1 < kWavesPerWg) {
+            if (chain && !ends && wslot + 1 < kWavesPerWg) {
                 // The unit runs on into the right-hand neighbour's span, where it is that wave's first
                 // segment: finished long ago unless the spans are very short.  Fold its result into mine
                 // (mine first: a fixed order, so the bits do not depend on timing).
@@ -360,7 +394,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                     }
                 }
             }
-            if (!starts && wslot > 0) {
+            if (chain && !starts && wslot > 0) {
                 // The unit began in the left-hand neighbour's span: leave the result for it.
                 float4v *dq = dep_o[wslot];
 #pragma unroll
@@ -387,9 +421,9 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             }
         }
         // What is held here goes to memory: as the finished output if it covers the whole unit, else as a
-        // partial in slot (workgroup, or wave without CHAIN) + unit, unique along the tile sequence.
+        // partial in slot (workgroup, or wave without the hand-over) + unit, unique along the pair sequence.
         const bool whole = CHAIN && starts && to_end;
-        const long long slot = (long long)(CHAIN ? (int)blockIdx.x : wave) + (long long)b * a.num_kv_heads + g;
+        const long long slot = (long long)(chain ? (int)blockIdx.x : wave) + (long long)b * a.num_kv_heads + g;
         float *po = a.part_o + slot * a.rows_pad * D;
         float *pml = a.part_ml + slot * a.rows_pad * 2;
         // A lane holds 32 consecutive d of one row (d = 32*jq + 8*e + mb), in registers that are 16 bytes
@@ -473,286 +507,264 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
     };
 
-    // One tile: S^T = K Q^T for all row blocks, softmax, O^T += V^T P^T.  Row blocks beyond the
-    // unit's rows hold zero queries; they are computed anyway (cheaper than branching, which was
-    // measured) and never stored.  Three wave-uniform branches leave the straight line: the mask
-    // selects (only tiles that reach into the request's new tokens), the clearing of V slots past the
-    // end of the cache (e4m3 instances: only a cache's last tile) and the rare rescale.  The compiler
+    // ---- load side: a linear walk over the span's pairs, the address of the next one read a step ahead ----
+    long long next_x = x0;            // next pair to load
+    int2 next_addr = desc_addr[0];    // its addresses
+    auto load_pair = [&](PairRegs<FP8> &t, int2 addr) __attribute__((always_inline)) {
+        const bool live = next_x < x1;
+        load_pair_tiles<FP8>(t, a, k_scale, v_scale, addr, live, lane);
+        ++next_x;
+    };
+    auto issue = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
+        const int2 addr = next_addr;
+        load_pair(t, addr);
+        next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
+    };
+
+    // One pair: S^T = K Q^T for both tiles and all row blocks, softmax, O^T += V^T P^T.  Row blocks beyond the
+    // unit's rows hold zero queries; they are computed anyway and never stored (skipping them by wave-uniform branches was
+    // measured again: the blocks' values then live across the branches, the compiler spills, and the spans are cut for
+    // pairs of equal cost).  Three wave-uniform branches leave the straight line: the mask
+    // selects (only pairs that reach into the request's new tokens), the clearing of V slots past the
+    // end of the cache (only a cache's last pair) and the rare rescale.  The compiler
     // keeps the wait states between a matrix instruction and the first read of its result, also across
     // these branches; where the read is written out by hand (the rescale, from_accumulator_file) or
     // follows a scheduling barrier (the end of a unit), explicit wait states stand in front of it.
-    // The order of the pieces is chosen so that vector work that does not depend on a matrix result
-    // follows each group of MFMAs: the V operands are built while S^T is in the matrix pipeline, and
-    // a row block's exponentials while the previous block's output MFMAs run.
-    auto compute = [&](const TileRegs<FP8> &t, int ti) __attribute__((always_inline)) {
-        const int tok0 = ti * kTile + jq * 4;   // first of this lane's four cache positions
+    // Once the scores are formed and the V operands packed, the pair's registers are free and the next
+    // pair's loads go out into them, ahead of the softmax and the output product.
+    auto compute = [&](PairRegs<FP8> &t, int ti) __attribute__((always_inline)) {
+        const int tok0 = ti * kPairTokens + jq * 4;   // first of this lane's four cache positions in the first tile
+        const float kscale[2] = {sc2 * t.t[0].ks, sc2 * t.t[1].ks}, vscale[2] = {t.t[0].vs, t.t[1].vs};
 
-        bf16x8 kop[4];
-        if constexpr (FP8) {
-            kop[0] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(t.k[0].x, t.k[0].y));
-            kop[1] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(t.k[0].z, t.k[0].w));
-            kop[2] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(t.k[1].x, t.k[1].y));
-            kop[3] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(t.k[1].z, t.k[1].w));
-        } else {
+        bf16x8 kop[2][4];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kop[ks] = __builtin_bit_cast(bf16x8, t.k[ks]);
+        for (int h = 0; h < 2; ++h) {
+            const TileRegs<FP8> &tt = t.t[h];
+            if constexpr (FP8) {
+                kop[h][0] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[0].x, tt.k[0].y));
+                kop[h][1] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[0].z, tt.k[0].w));
+                kop[h][2] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[1].x, tt.k[1].y));
+                kop[h][3] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[1].z, tt.k[1].w));
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) kop[h][ks] = __builtin_bit_cast(bf16x8, tt.k[ks]);
+            }
         }
-        float4v s[NB];
+        float4v s[NB][2];
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) s[nb] = float4v{0.f, 0.f, 0.f, 0.f};
-        if constexpr (QLDS) {
-            // operands come from LDS a few MFMAs ahead of their use, so that its latency is covered
-            constexpr int NOPS = 4 * NB, AHEAD = NOPS < 6 ? NOPS : 6;
+        for (int nb = 0; nb < NB; ++nb) s[nb][0] = s[nb][1] = float4v{0.f, 0.f, 0.f, 0.f};
+        {
+            // (operands from LDS are requested a few MFMAs ahead of their use, so that its latency is covered)
+            constexpr int NOPS = 4 * NB, AHEAD = QLDS ? (NOPS < 4 ? NOPS : 4) : 1;
             uint4 qb[AHEAD];
+            if constexpr (QLDS) {
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i) qb[i] = qs[((i % NB) * 4 + i / NB) * 64];
+                for (int i = 0; i < AHEAD; ++i) qb[i] = qs[((i % NB) * 4 + i / NB) * 64];
+            }
 #pragma unroll
             for (int i = 0; i < NOPS; ++i) {
                 const int ks = i / NB, nb = i % NB;
-                const bf16x8 qop = __builtin_bit_cast(bf16x8, qb[i % AHEAD]);
-                if (i + AHEAD < NOPS) {
-                    const int i2 = i + AHEAD;
-                    qb[i % AHEAD] = qs[((i2 % NB) * 4 + i2 / NB) * 64];
+                bf16x8 qop;
+                if constexpr (QLDS) {
+                    qop = __builtin_bit_cast(bf16x8, qb[i % AHEAD]);
+                    if (i + AHEAD < NOPS) {
+                        const int i2 = i + AHEAD;
+                        qb[i % AHEAD] = qs[((i2 % NB) * 4 + i2 / NB) * 64];
+                    }
+                } else {
+                    qop = qreg[nb][ks];
                 }
-                s[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], qop, s[nb], 0, 0, 0);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) s[nb][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[h][ks], qop, s[nb][h], 0, 0, 0);
             }
-        } else {
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    s[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[ks], qreg[nb][ks], s[nb], 0, 0, 0);
         }
 
-        // V operand registers: vop[mb] = d-phase mb of tokens tok0 .. tok0+3.
-        short4v vop[8];
+        // V operand registers: vop[mb] = d-phase mb of tokens tok0 .. tok0+3 (words 0, 1) and tok0+16 .. tok0+19 (2, 3).
+        uint32_t vop[8][4];
+        {
 #pragma unroll
-        for (int h = 0; h < 4; ++h) {   // word h of each token's 8 values holds d-phases 2h and 2h+1
-            uint32_t w[4];
+            for (int t2 = 0; t2 < 2; ++t2) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if constexpr (FP8) {
-                    const uint32_t src = (h < 2) ? t.v[e].x : t.v[e].y;   // two e4m3 bytes -> two bf16, exact
-                    const float2v f = (h & 1) ? __builtin_amdgcn_cvt_pk_f32_fp8(src, true)
-                                              : __builtin_amdgcn_cvt_pk_f32_fp8(src, false);
-                    w[e] = pack_hi16(__float_as_uint(f.x), __float_as_uint(f.y));
-                } else {
-                    w[e] = (&t.v[e].x)[h];
+                for (int h = 0; h < 4; ++h) {   // word h of each token's 8 values holds d-phases 2h and 2h+1
+                    uint32_t w[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (FP8) {
+                            const uint32_t src = (h < 2) ? t.t[t2].v[e].x : t.t[t2].v[e].y;   // two e4m3 bytes -> two bf16, exact
+                            w[e] = (h & 1) ? fp8x2_to_bf16x2<true>(src) : fp8x2_to_bf16x2<false>(src);
+                        } else {
+                            w[e] = t.t[t2].v[e][h];
+                        }
+                    }
+                    vop[2 * h][2 * t2] = pack_lo16(w[0], w[1]);
+                    vop[2 * h][2 * t2 + 1] = pack_lo16(w[2], w[3]);
+                    vop[2 * h + 1][2 * t2] = pack_hi16(w[0], w[1]);
+                    vop[2 * h + 1][2 * t2 + 1] = pack_hi16(w[2], w[3]);
                 }
             }
-            uint2 lo, hi;
-            lo.x = pack_lo16(w[0], w[1]);
-            lo.y = pack_lo16(w[2], w[3]);
-            hi.x = pack_hi16(w[0], w[1]);
-            hi.y = pack_hi16(w[2], w[3]);
-            vop[2 * h] = __builtin_bit_cast(short4v, lo);
-            vop[2 * h + 1] = __builtin_bit_cast(short4v, hi);
-        }
-        // Slots at or past kv_len may hold anything (NaN, inf): they are cleared so that 0 * garbage cannot
-        // occur.  Only the last tile of a cache has such slots; the e4m3 instances, which are bound by their
-        // vector instructions, test for it (wave-uniform), the others clear unconditionally (measured: there the
-        // branch costs more than the sixteen ANDs).
-        if (!FP8 || ti * kTile + kTile > L) {
-            const uint32_t m01 = (tok0 + 0 < L ? 0x0000ffffu : 0u) | (tok0 + 1 < L ? 0xffff0000u : 0u);
-            const uint32_t m23 = (tok0 + 2 < L ? 0x0000ffffu : 0u) | (tok0 + 3 < L ? 0xffff0000u : 0u);
+            __builtin_amdgcn_sched_barrier(0);
+            issue(t);
+            __builtin_amdgcn_sched_barrier(0);
+            // Slots at or past kv_len may hold anything (NaN, inf): they are cleared so that 0 * garbage cannot
+            // occur.  Only the last pair of a cache has such slots.
+            if (ti * kPairTokens + kPairTokens > L) {
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb) {
-                uint2 w = __builtin_bit_cast(uint2, vop[mb]);
-                w.x &= m01;
-                w.y &= m23;
-                vop[mb] = __builtin_bit_cast(short4v, w);
+                for (int t2 = 0; t2 < 2; ++t2) {
+                    const int p0 = tok0 + t2 * kTile;
+                    const uint32_t m01 = (p0 + 0 < L ? 0x0000ffffu : 0u) | (p0 + 1 < L ? 0xffff0000u : 0u);
+                    const uint32_t m23 = (p0 + 2 < L ? 0x0000ffffu : 0u) | (p0 + 3 < L ? 0xffff0000u : 0u);
+#pragma unroll
+                    for (int mb = 0; mb < 8; ++mb) {
+                        vop[mb][2 * t2] &= m01;
+                        vop[mb][2 * t2 + 1] &= m23;
+                    }
+                }
             }
         }
 
         // Online softmax with a lagging reference: p = 2^(s - m_ref).  The reference only moves
         // (and the accumulators are rescaled) when some score exceeds it by more than kSlack, so
-        // p <= 2^kSlack and the common tile needs no cross-lane traffic and no rescale.  The common path forms
+        // p <= 2^kSlack and the common pair needs no cross-lane traffic and no rescale.  The common path forms
         // the exponent's argument with one fused multiply-add per score and tests all of them against the slack
-        // at once; the scores themselves are only formed on the rare path (before a unit's first tile the
+        // at once; the scores themselves are only formed on the rare path (before a unit's first pair the
         // reference is so low that the argument has absorbed them).
-        const float kscale = sc2 * t.ks;
-        float pd[NB][4];
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) pd[nb][e] = __builtin_fmaf(s[nb][e], kscale, -m_run[nb]);
-        // Every row sees all of the context before the request's new tokens, so only the last tile or two of a
+        // Every row sees all of the context before the request's new tokens, so only the last pair or two of a
         // unit need the selects: the wave-uniform test skips them for the rest.
-        const bool tail = ti * kTile + kTile > ctx;
-        if (tail) {
+        const bool tail = ti * kPairTokens + kPairTokens > ctx;
+        auto arguments = [&](int nb, const float4v (&s)[2], float (&pd)[2][4]) __attribute__((always_inline)) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) pd[h][e] = __builtin_fmaf(s[h][e], kscale[h], -m_run[nb]);
+        };
+        auto mask = [&](int nb, float (&pd)[2][4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int p0 = tok0 + h * kTile;
                 if constexpr (TREE) {
                     // Positions past the cache end are past the mask's last set bit.
-                    const uint32_t vis = tree_visible4(newmask[nb], tok0 - ctx);
+                    const uint32_t vis = tree_visible4(newmask[nb], p0 - ctx);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) pd[nb][e] = ((vis >> e) & 1u) ? pd[nb][e] : -INFINITY;
+                    for (int e = 0; e < 4; ++e) pd[h][e] = ((vis >> e) & 1u) ? pd[h][e] : -INFINITY;
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)   // causal limit among the new tokens / end of the cache
-                        pd[nb][e] = (tok0 + e > lim[nb]) ? -INFINITY : pd[nb][e];
+                        pd[h][e] = (p0 + e > lim[nb]) ? -INFINITY : pd[h][e];
                 }
             }
-        }
-        float top = pd[0][0];
+        };
+        auto top8 = [](const float (&pd)[2][4]) __attribute__((always_inline)) {
+            return fmaxf(fmaxf(fmaxf(pd[0][0], pd[0][1]), fmaxf(pd[0][2], pd[0][3])),
+                         fmaxf(fmaxf(pd[1][0], pd[1][1]), fmaxf(pd[1][2], pd[1][3])));
+        };
+        auto rescale = [&](int nb, const float4v (&s)[2], float (&pd)[2][4]) __attribute__((always_inline)) {
+            float sv[2][4];   // the scores, masked where the argument was
+            float mx = -INFINITY;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) top = fmaxf(top, pd[nb][e]);
-        if (__any(top > kSlack)) {
-            accumulator_read_guard();
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                float sv[4];   // the scores, masked where the argument was
-#pragma unroll
-                for (int e = 0; e < 4; ++e) sv[e] = pd[nb][e] == -INFINITY ? -INFINITY : s[nb][e] * kscale;
-                float mx = fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3]));
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m_run[nb], mx);
-                const float alpha = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
-                l_run[nb] *= alpha;
-#pragma unroll
-                for (int mb = 0; mb < 8; ++mb) {
-                    const float4v c = acc[mb][nb];
-                    float4v r = {from_accumulator_file(c[0]) * alpha, from_accumulator_file(c[1]) * alpha,
-                                 from_accumulator_file(c[2]) * alpha, from_accumulator_file(c[3]) * alpha};
-                    to_accumulator_file(r);
-                    acc[mb][nb] = r;
+                for (int e = 0; e < 4; ++e) {
+                    sv[h][e] = pd[h][e] == -INFINITY ? -INFINITY : s[h][e] * kscale[h];
+                    mx = fmaxf(mx, sv[h][e]);
                 }
-                m_run[nb] = m_new;
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m_run[nb], mx);
+            const float alpha = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
+            l_run[nb] *= alpha;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) pd[nb][e] = sv[e] - m_new;
+            for (int mb = 0; mb < 8; ++mb) {
+                const float4v c = acc[mb][nb];
+                float4v r = {from_accumulator_file(c[0]) * alpha, from_accumulator_file(c[1]) * alpha,
+                             from_accumulator_file(c[2]) * alpha, from_accumulator_file(c[3]) * alpha};
+                to_accumulator_file(r);
+                acc[mb][nb] = r;
             }
-        }
-        if constexpr (NB >= 3) {
-            // A wavefront issues in order: matrix instructions that stand back to back leave the vector ALU idle
-            // while they run, and the vector work of a row block leaves the matrix pipeline idle.  With many row
-            // blocks the kernel is bound by that, not by memory, so the blocks are software-pipelined by hand: the
-            // exponentials and the packing of block nb+1 are cut into pieces of two or three instructions, one after
-            // each of block nb's eight output MFMAs, and a scheduling barrier after every piece keeps the compiler
-            // from gathering the matrix instructions together again.
-            float pe[4];
-            uint2 pk;
-            auto piece = [&](int nb, int i) __attribute__((always_inline)) {
-                if (i == 0) pe[0] = __builtin_amdgcn_exp2f(pd[nb][0]);
-                if (i == 1) pe[1] = __builtin_amdgcn_exp2f(pd[nb][1]);
-                if (i == 2) pe[2] = __builtin_amdgcn_exp2f(pd[nb][2]);
-                if (i == 3) pe[3] = __builtin_amdgcn_exp2f(pd[nb][3]);
-                if (i == 4) l_run[nb] += (pe[0] + pe[1]) + (pe[2] + pe[3]);
-                if (i == 5) {
-                    const float2v lo = {pe[0] * t.vs, pe[1] * t.vs};
-                    pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
-                }
-                if (i == 6) {
-                    const float2v hi = {pe[2] * t.vs, pe[3] * t.vs};
-                    pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-                }
-            };
+            m_run[nb] = m_new;
 #pragma unroll
-            for (int i = 0; i < 7; ++i) piece(0, i);
-            short4v pop = __builtin_bit_cast(short4v, pk);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
+                for (int e = 0; e < 4; ++e) pd[h][e] = sv[h][e] - m_new;
+        };
+        auto output = [&](int nb, const float (&pd)[2][4]) __attribute__((always_inline)) {
+            uint32_t pw[4];
+            float sum[2];
 #pragma unroll
-                for (int mb = 0; mb < 8; ++mb) {
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vop[mb], pop, acc[mb][nb], 0, 0, 0);
-                    if (nb + 1 < NB) {
-                        piece(nb + 1, mb);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                if (nb + 1 < NB) pop = __builtin_bit_cast(short4v, pk);
-            }
-        } else {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
+            for (int h = 0; h < 2; ++h) {
                 float p[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(pd[nb][e]);
-                l_run[nb] += (p[0] + p[1]) + (p[2] + p[3]);
-                const float2v lo = {p[0] * t.vs, p[1] * t.vs}, hi = {p[2] * t.vs, p[3] * t.vs};
-                uint2 pk;
-                pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
-                pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-                const short4v pop = __builtin_bit_cast(short4v, pk);
-#pragma unroll
-                for (int mb = 0; mb < 8; ++mb)
-                    acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vop[mb], pop, acc[mb][nb], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) p[e] = __builtin_amdgcn_exp2f(pd[h][e]);
+                sum[h] = (p[0] + p[1]) + (p[2] + p[3]);
+                const float2v lo = {p[0] * vscale[h], p[1] * vscale[h]}, hi = {p[2] * vscale[h], p[3] * vscale[h]};
+                pw[2 * h] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+                pw[2 * h + 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
             }
-        }
-    };
-
-    // one step of the compute side: consume a tile; at the end of a unit segment write its partial
-    // and open the next segment (its query loads go out ahead of the next KV prefetch)
-    auto step = [&](const TileRegs<FP8> &t) __attribute__((always_inline)) {
-        compute(t, tile);
-        ++tile;
-        --span_left;
-        if (--seg_left == 0) {
-            end_unit(seg_tile0 == 0, tile == nb_tiles);
-            next_unit();
-            if (span_left > 0) {
-                begin_unit_issue();
-                begin_unit_wait();
-            }
-        }
-    };
-
-    // ---- load side: a linear walk over the span's tile addresses, staged in LDS a window at a time ----
-    bool first_window = true;
-    for (long long c0 = x0; c0 < x1; c0 += kIdWindow) {
-        const int n = (int)(x1 - c0 < kIdWindow ? x1 - c0 : kIdWindow);
-        // the window's addresses: vector reads now, into LDS once they have arrived
-        int idtmp[kIdWindow / 64];
+            l_run[nb] += sum[0] + sum[1];
+            const bf16x8 pop = __builtin_bit_cast(bf16x8, make_uint4(pw[0], pw[1], pw[2], pw[3]));
 #pragma unroll
-        for (int i = 0; i < kIdWindow / 64; ++i) idtmp[i] = (i * 64 + lane < n) ? tile_addr[c0 + i * 64 + lane] : 0;
-        // the first NBUF-1 tiles do not wait for that: their addresses come by scalar reads
-        int first_addr[NBUF - 1];
-#pragma unroll
-        for (int j = 0; j < NBUF - 1; ++j)
-            first_addr[j] = first_window ? desc_addr[j] : tile_addr[c0 + (j < n ? j : n - 1)];
-        if (first_window) begin_unit_issue();   // queries of the first unit go out before any KV tile
-
-        TileRegs<FP8> buf[NBUF];
-#pragma unroll
-        for (int j = 0; j < NBUF - 1; ++j)
-            if (j < n) load_tile<FP8>(buf[j], a, k_scale, v_scale, first_addr[j], lane, vzero);
-        if (first_window) begin_unit_wait();
-        first_window = false;
-#pragma unroll
-        for (int i = 0; i < kIdWindow / 64; ++i) ids[i * 64 + lane] = idtmp[i];
-
-        int p_load = NBUF - 1;   // next tile of the window to load
-        int id_v = ids[p_load < n ? p_load : n - 1];   // its address, read from LDS one step ahead of its use
-        auto issue = [&](TileRegs<FP8> &t) __attribute__((always_inline)) {
-            const int addr = __builtin_amdgcn_readfirstlane(id_v);
-            ++p_load;
-            id_v = ids[p_load < n ? p_load : n - 1];
-            load_tile<FP8>(t, a, k_scale, v_scale, addr, lane, vzero);
+            for (int mb = 0; mb < 8; ++mb)
+                acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    __builtin_bit_cast(bf16x8, make_uint4(vop[mb][0], vop[mb][1], vop[mb][2], vop[mb][3])), pop, acc[mb][nb], 0, 0, 0);
         };
 
-        // Software pipeline over a ring of NBUF tile buffers (fully unrolled: static registers).
-        // The steady-state loop issues its prefetch unconditionally, so the wait before each
-        // compute only covers the tile it needs and NBUF-1 tiles stay in flight; the last few
-        // tiles of a window (and short windows) run through a conditional epilogue.
-        int p = 0;
-        for (; p + 2 * NBUF - 2 < n; p += NBUF) {
+        {
+            float pd[NB][2][4];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) arguments(nb, s[nb], pd[nb]);
+            if (tail) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) mask(nb, pd[nb]);
+            }
+            float top = top8(pd[0]);
+#pragma unroll
+            for (int nb = 1; nb < NB; ++nb) top = fmaxf(top, top8(pd[nb]));
+            if (__any(top > kSlack)) {
+                accumulator_read_guard();
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) rescale(nb, s[nb], pd[nb]);
+            }
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) output(nb, pd[nb]);
+        }
+    };
+
+    // ---- the walk: a ring of NBUF pairs in registers (static indices: the loop over it is unrolled) ----
+    begin_unit_issue();   // queries of the first unit go out before any KV tile
+    PairRegs<FP8> buf[NBUF];
+#pragma unroll
+    for (int j = 0; j < NBUF; ++j) {
+        // the first pairs' addresses come with the descriptor
+        load_pair(buf[j], j < kDescPairs ? desc_addr[j] : pair_addr[x0 + j < x1 ? x0 + j : x1 - 1]);
+    }
+    next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
+    begin_unit_wait();
+    for (;;) {
+        int turn = 0;   // where in the ring the segment ended
+        for (;;) {
+            bool done = false;
 #pragma unroll
             for (int j = 0; j < NBUF; ++j) {
-                issue(buf[(j + NBUF - 1) % NBUF]);
-                __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of every use of the current tile
-                step(buf[j]);
+                if (!done) {
+                    compute(buf[j], tile);
+                    ++tile;
+                    done = --seg_left == 0;
+                    turn = j + 1;
+                }
             }
+            if (done) break;
         }
-        // here buf[j] holds tile p + j for j < NBUF-1 (as far as such tiles exist)
+        span_left -= tile - seg_tile0;
+        end_unit(seg_tile0 == 0, tile == nb_tiles);
+        if (span_left <= 0) break;
+        next_unit();
+        begin_unit_issue();
+        begin_unit_wait();
+        // the next pair back to the ring's front (everything in the ring has arrived by now)
+        for (; turn < NBUF; ++turn) {
+            const PairRegs<FP8> last = buf[NBUF - 1];
 #pragma unroll
-        for (int j = 0; j < 2 * NBUF - 2; ++j) {
-            if (p + j < n) {
-                if (p + j + NBUF - 1 < n) issue(buf[(j + NBUF - 1) % NBUF]);
-                step(buf[j % NBUF]);
-            }
+            for (int j = NBUF - 1; j > 0; --j) buf[j] = buf[j - 1];
+            buf[0] = last;
         }
     }
 }
@@ -772,17 +784,17 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     const int rows = window_q_len(a.q_indptr[b + 1] - q0, a.q_lo, a.q_win) * G;   // rows of this pass's window
     const int n = slab * kMergeRows + (threadIdx.x >> 5), d4 = threadIdx.x & 31;
     if (n >= rows) return;
-    const long long total = a.plan->total_tiles;
+    const long long total = a.plan->total_pairs;
     const long long nw = a.plan->num_waves;
-    const int pre = a.tile_prefix[b];
-    const int nb_tiles = a.tile_prefix[b + 1] - pre;
+    const int pre = a.pair_prefix[b];
+    const int nb_tiles = a.pair_prefix[b + 1] - pre;
     const long long off = (long long)pre * a.num_kv_heads + (long long)g * nb_tiles;
     // The spans were cut at w*total_w/nw in the weighted coordinate (every unit: `weight` virtual tiles, then
     // its own); the last wave whose cut lies at or before coordinate t is ((t+1)*nw - 1) / total_w.  A cut
     // inside the unit's virtual part starts at its first tile, so the unit's first wave is the last one at
     // or before the end of that part, its last wave the last one before the next unit's stretch.
     SpanCuts cuts;
-    cuts.prefix = a.tile_prefix;
+    cuts.prefix = a.pair_prefix;
     cuts.batch = a.batch;
     cuts.hkv = a.num_kv_heads;
     cuts.weight = a.plan->unit_weight;
@@ -791,7 +803,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     cuts.nw = nw;
     int w_first, w_last;
     cuts.unit_waves(off + (long long)cuts.weight * unit, nb_tiles, w_first, w_last);
-    if (a.chain) {
+    if (a.chain && !a.plan->chain) {   // one partial per wavefront, but a unit that one held alone is finished
+        if (w_first == w_last) return;
+    } else if (a.chain) {
         // the streaming kernel has combined the spans of each workgroup: one partial per workgroup the unit
         // touches, and a unit inside a single workgroup is already finished
         w_first /= kWavesPerWg;
@@ -827,17 +841,17 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 template <int G, int NB, bool FP8, bool TREE>
 int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
-    // One wavefront per SIMD (the whole register file, a ring of NBUF tiles): two waves on a SIMD
+    // One wavefront per SIMD (the whole register file, a ring of NBUF pairs): two waves on a SIMD
     // do not share the memory pipeline fairly under saturation (the older one wins), which turns
     // into a long tail.
     constexpr bool QLDS = NB >= 4;
-    constexpr int NBUF = NB <= 3 ? 4 : (NB == 5 && !FP8) ? 2 : 3;
+    constexpr int NBUF = 2;   // (three or four pairs spill in most instances: 104 us instead of 97 where they just fit)
     AttnArgs b = a;   // (the plan kernel has been enqueued by the caller)
     b.chain = kChainMerge<NB> ? 1 : 0;
     // When a profile is being taken the two events are attached to the dispatch itself, so that
     // their difference is the kernel's own duration on this stream (what a kernel trace shows).
     hipExtLaunchKernelGGL((attn_stream_kernel<G, NB, FP8, NBUF, QLDS, TREE>), dim3((unsigned)(b.launch_waves / kWavesPerWg)),
-                          dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, b, b.tile_addr, b.wave_desc, b.tile_prefix,
+                          dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, b, b.pair_addr, b.wave_desc, b.pair_prefix,
                           b.kv_len, b.q_indptr, b.k_scale, b.v_scale);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_stream_kernel");
     hipLaunchKernelGGL(attn_merge_kernel<G>, dim3((unsigned)a.batch * a.num_kv_heads * (a.rows_pad / kMergeRows)), dim3(256),

@@ -23,16 +23,20 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // ---- attention -----------------------------------------------------------------------------
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
+constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
 constexpr int kWavesPerWg = 4;
-constexpr int kMinTilesPerWave = 8;      // below this a KV partition is not worth its partial write
+constexpr int kMinPairsPerWave = 2;      // below this a KV partition is not worth its partial write
 constexpr int kDescInts = 16;            // ints per wave descriptor
-constexpr int kDescAddrs = 4;            // tile addresses a descriptor carries for the span's first tiles
+constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
 constexpr int kMaxRowBlocks = 5;         // 16-row blocks of query rows one wavefront can keep accumulators for
-constexpr int kUnitWeight = 3;           // default cost of opening a unit, in tiles, for the span cuts
+// What opening a unit costs a wavefront, in pairs, for the span cuts.  With up to three row blocks 2 (1 to 3 are level);
+// with four or five the query rows go through LDS and a unit's partial is 32 or 40 KB: 6 to 10 are level (96 requests of
+// 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 260 us a call at 2, 243 at 8; 128 requests of 64..1024: 87 and 80).
+constexpr int kUnitWeight = 2, kUnitWeightDeep = 8;
 
-// Query tokens of a request that fall into the pass's window, and the KV tiles its units stream in this
-// pass: a request without rows in the window keeps one tile so that no unit of the flat tile space is empty.
+// Query tokens of a request that fall into the pass's window, and the tile pairs its units stream in this
+// pass: a request without rows in the window keeps one pair so that no unit of the flat pair space is empty.
 __host__ __device__ inline int window_q_len(int q_len, int q_lo, int q_win)
 {
     const int n = q_len - q_lo;
@@ -46,17 +50,17 @@ inline int attn_rows_pad(int max_q_len, int G)
     const int win_max = cap / G, passes = (max_q_len + win_max - 1) / win_max;
     return (int)align_up((size_t)((max_q_len + passes - 1) / passes) * G, 16);
 }
-__host__ __device__ inline int window_tiles(int kv_len, int q_len, int q_lo)
+__host__ __device__ inline int window_pairs(int kv_len, int q_len, int q_lo)
 {
-    return q_len > q_lo ? (kv_len + kTile - 1) / kTile : 1;
+    return q_len > q_lo ? (kv_len + kPairTokens - 1) / kPairTokens : 1;
 }
 
 // Written by the plan kernel, read by the streaming and merge kernels.
 struct AttnPlan {
-    int32_t total_tiles;   // sum over requests of ceil(kv_len/16) * num_kv_heads
+    int32_t total_pairs;   // sum over requests of ceil(kv_len/32) * num_kv_heads
     int32_t num_waves;     // partitions actually used (<= launched wavefronts)
-    int32_t unit_weight;   // virtual tiles per unit in the coordinate the spans were cut in (0: plain tile counts)
-    int32_t pad;
+    int32_t unit_weight;   // virtual pairs per unit in the coordinate the spans were cut in (0: plain pair counts)
+    int32_t chain;         // the spans of a workgroup are combined in LDS (instances that can)
 };
 
 struct AttnArgs {
@@ -81,14 +85,14 @@ struct AttnArgs {
     float sm_scale;
     // workspace carve-up
     AttnPlan *plan;
-    int32_t *tile_prefix;  // [batch+1] exclusive prefix of ceil(kv_len/16)
-    int32_t *tile_addr;    // [batch*max_blocks*kv_heads] flat tile list: physical block * kv_heads + kv head
+    int32_t *pair_prefix;  // [batch+1] exclusive prefix of the requests' pair counts
+    int2 *pair_addr;       // [batch*ceil(max_blocks/2)*kv_heads] flat pair list: per tile, physical block * kv_heads + kv head
     int32_t *wave_desc;    // [launch_waves][kDescInts]: where each wave's span starts and what its first loads need
     float *part_o;         // [slots][rows_pad][head_dim]
     float *part_ml;        // [slots][rows_pad][2]  (log2-domain max, sum)
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
-    int32_t unit_weight;   // what opening a unit costs a wave, in tiles (weights the span cuts; 0 = equal tile counts)
+    int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts, -1 = default)
     int32_t chain;         // set by the launcher: partials are per (workgroup, unit), units inside one workgroup are final
 };
 
