@@ -23,11 +23,16 @@ namespace ss {
 namespace {
 
 // ---- pass 1 ---------------------------------------------------------------------------------
-// grid: batch * rows_max * ceil(nchunks / 4), rows_max from the caller's bound of k+1; workgroup (b, j, group): wave wv of it streams chunk
-// 4 * group + wv of request b's row j (j <= k: target row j; k < j <= 2k: draft row j-k-1; larger j:
-// nothing to do).  A wave owns its chunk alone: all of its 16-byte loads go out first, then the
+// grid: batch * rows_max * ceil(nchunks / 2), rows_max from the caller's bound of k+1; workgroup (b, j, group): its wavefronts
+// stream chunks 2 * group and 2 * group + 1 of request b's row j (j <= k: target row j; k < j <= 2k: draft row j-k-1; larger j:
+// nothing to do), two wavefronts to a chunk.  A wavefront's 16-byte loads all go out first, then the
 // values are folded vector by vector into a per-lane running (max, sum) and reduced across the wave
-// with shuffles, so the streaming pass has no barrier and no LDS traffic.
+// with shuffles; the two halves of a chunk meet in LDS at the end.  Bound by memory: 147.7 MB (64 requests, depth 4,
+// 128256 entries) take 28 us, 182 MB of target rows 31 us.  With a wavefront per chunk (twice the registers, five
+// instead of eight wavefronts on a SIMD, a coarser tail) 30 and 33 us, 8.0 against 6.3 us for 8 requests of 32000; four
+// wavefronts per chunk are level with two.
+constexpr int kRowWaves = 2;   // wavefronts per chunk
+
 // Every logit is read exactly once by this pass: non-temporal loads keep the stream from displacing the one or
 // two rows per request that the later passes read again.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -41,27 +46,31 @@ template <int DT>
 __global__ __launch_bounds__(kThreads) void accept_rowstats_kernel(AcceptArgs a, Workspace w)
 {
     constexpr int vec = DT == SS_BF16 ? 8 : 4;       // logits per 16-byte load
-    constexpr int NV = kChunk / (64 * vec);          // loads per lane and chunk
+    constexpr int WPC = kRowWaves;                   // wavefronts per chunk
+    constexpr int PART = kChunk / WPC, CPG = 4 / WPC;   // entries of a wavefront, chunks of a workgroup
+    constexpr int NV = PART / (64 * vec);            // loads per lane
     constexpr int STEP = 4;                          // vectors folded per update of the running maximum
+    __shared__ float part_m[4], part_z[4];
+    __shared__ int part_arg[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int groups = (w.nchunks + 3) / 4;
-    const int chunk = (blockIdx.x % groups) * 4 + wv;
+    const int groups = (w.nchunks + CPG - 1) / CPG;
+    const int chunk = (blockIdx.x % groups) * CPG + wv / WPC;
     const int rows_max = a.greedy ? a.max_q_len : 2 * a.max_q_len - 1;   // rows a request can have
     const int bj = blockIdx.x / groups, b = bj / rows_max, j = bj % rows_max;
     const int t0 = a.q_indptr[b], k = a.q_indptr[b + 1] - t0 - 1;
-    if (j > (a.greedy ? k : 2 * k) || chunk >= w.nchunks) return;
+    if (j > (a.greedy ? k : 2 * k)) return;   // (the whole workgroup)
     const bool is_draft = j > k;
     const int r = is_draft ? t0 - b + (j - k - 1) : t0 + j;
     const int64_t ry = is_draft ? (int64_t)a.total_rows + r : r;
     const void *row = row_ptr(is_draft ? a.draft : a.target, r, a.row_stride, DT);
-    const int base = chunk * kChunk;
+    const int base = chunk * kChunk + (wv % WPC) * PART;
     const int64_t o = ry * w.nchunks + chunk;
     const float T = a.greedy ? 1.f : (a.temperature ? a.temperature[b] : a.temperature_scalar);
     const float sc = 1.4426950408889634f / T;
 
     // vector v of this lane starts at vocabulary id base + v * (64 * vec) + lane * vec
     uint4 raw[NV];
-    const bool full = base + kChunk <= a.vocab;       // uniform: the chunk lies inside the vocabulary
+    const bool full = base + PART <= a.vocab;         // uniform: the part lies inside the vocabulary
     const int last_full = a.vocab >= vec ? (a.vocab - vec) / vec * vec : -1;
     if (full) {
 #pragma unroll
@@ -134,13 +143,24 @@ __global__ __launch_bounds__(kThreads) void accept_rowstats_kernel(AcceptArgs a,
             }
         }
     }
-    // across the wave
+    // across the wave, then across the chunk's wavefronts
     float cm = m;
     for (int off = 32; off; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off));
     if (a.greedy) {
-        int arg = m == cm ? best : 0x7fffffff;   // lowest vocabulary id holding the chunk maximum
+        int arg = m == cm ? best : 0x7fffffff;   // lowest vocabulary id holding the part's maximum
         for (int off = 32; off; off >>= 1) arg = min(arg, __shfl_xor(arg, off));
         if (lane == 0) {
+            part_m[wv] = cm;
+            part_arg[wv] = arg;
+        }
+        __syncthreads();
+        if (lane == 0 && wv % WPC == 0 && chunk < w.nchunks) {
+#pragma unroll
+            for (int i = 1; i < WPC; ++i)   // (ids ascend with the wavefront: the first holder of the maximum wins)
+                if (part_m[wv + i] > cm) {
+                    cm = part_m[wv + i];
+                    arg = part_arg[wv + i];
+                }
             w.cmax[o] = cm;
             w.carg[o] = arg;
         }
@@ -149,8 +169,20 @@ __global__ __launch_bounds__(kThreads) void accept_rowstats_kernel(AcceptArgs a,
     if (m != -INFINITY) z *= __builtin_amdgcn_exp2f((m - cm) * sc);
     for (int off = 32; off; off >>= 1) z += __shfl_xor(z, off);
     if (lane == 0) {
-        w.cmax[o] = cm;
-        w.csum[o] = z;
+        part_m[wv] = cm;
+        part_z[wv] = z;
+    }
+    __syncthreads();
+    if (lane == 0 && wv % WPC == 0 && chunk < w.nchunks) {
+        float all = cm;
+#pragma unroll
+        for (int i = 1; i < WPC; ++i) all = fmaxf(all, part_m[wv + i]);
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < WPC; ++i)
+            if (part_m[wv + i] != -INFINITY) sum += part_z[wv + i] * __builtin_amdgcn_exp2f((part_m[wv + i] - all) * sc);
+        w.cmax[o] = all;
+        w.csum[o] = sum;
     }
 }
 
@@ -565,7 +597,7 @@ int32_t accept_launch(const AcceptArgs &a, hipStream_t stream)
 {
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
     const unsigned long long g1 =
-        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks + 3) / 4);
+        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks * kRowWaves + 3) / 4);
     if (g1 > 0x7fffffffull || (unsigned long long)a.batch * w.nsub > 0x7fffffffull)
         return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
     if (a.logit_dtype == SS_BF16) return accept_launch_dt<SS_BF16>(a, w, (unsigned)g1, stream);
@@ -576,7 +608,7 @@ int32_t accept_rowstats_launch(const AcceptArgs &a, hipStream_t stream)
 {
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
     const unsigned long long g1 =
-        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks + 3) / 4);
+        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks * kRowWaves + 3) / 4);
     if (g1 > 0x7fffffffull) return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
     if (a.logit_dtype == SS_BF16)
         hipLaunchKernelGGL(accept_rowstats_kernel<SS_BF16>, dim3((unsigned)g1), dim3(kThreads), 0, stream, a, w);
