@@ -40,8 +40,8 @@
 // epilogue, more than the 64 KB instruction cache that two compute units share; now 14 to 28 KB.
 //
 // Measured (a whole call, before / after: single tiles, 16-token output products, query loads under a branch per row
-// block, one unit weight): 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 / 249 us; 32 requests of
-// 256..4096, trees of 8..16 nodes, 32 heads over 8: 101 / 80; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 / 107.2; four
+// block, one unit weight): 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 / 245 us; 32 requests of
+// 256..4096, trees of 8..16 nodes, 32 heads over 8: 98 / 75; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 / 107.2; four
 // requests of 40..600: 26.0 / 20.1.
 #pragma once
 
@@ -184,12 +184,11 @@ __device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs
 }
 
 // NB    16-row blocks of query rows the kernel is compiled for (covers max_q_len * G rows)
-// NBUF  tile pairs resident per wave; a pair's registers are refilled as soon as its operands have been taken
 // QLDS  keep the query operands in LDS (in operand order, one 1 KB line per row block and k-step)
 //       instead of registers: for many row blocks the registers are needed for the accumulators
 // TREE  the new tokens of a request form a draft tree: a row's visibility among them comes from its
 //       mask word instead of the chain's "tokens up to my own"
-template <int G, int NB, bool FP8, int NBUF, bool QLDS, bool TREE>
+template <int G, int NB, bool FP8, bool QLDS, bool TREE>
 __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     AttnArgs a, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
     const int32_t *__restrict__ pair_prefix,
@@ -237,6 +236,10 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     __syncthreads();   // the only barrier: every wave's flag is clear before any neighbour can look at it
     if (x0 >= x1) return;
 
+    // SINGLE: with many row blocks a step is longer than a read's latency, and one buffer that is refilled as soon as its
+    // operands have been copied out keeps a pair in flight all the time, where two spill (32 requests of 256..4096, trees
+    // of 8..16 nodes: 80 us a call with two buffers, 75 with one; with three row blocks both are level).
+    constexpr bool SINGLE = NB >= 4;
     // ---- state of the unit being computed ----
     int span_left = (int)(x1 - x0);   // pairs of the span not yet computed
     int seg_left = 0;                 // of those, pairs that still belong to the current unit
@@ -250,6 +253,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     float4v acc[8][NB];
     const float sc2 = a.sm_scale * kLog2e;
 
+    u32x4 qw[NB][4];   // a unit's queries on their way (between begin_unit_issue and begin_unit_wait)
     // (the metadata of the unit after the current one is fetched a unit ahead)
     auto begin_unit_issue = [&]() __attribute__((always_inline)) {
         L = meta_L;
@@ -278,7 +282,6 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         const __amdgpu_buffer_rsrc_t qr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(static_cast<const char *>(a.q)) + (q0 * q_row + (long long)g * (G * D * 2)), 0, (int)(q_len * q_row),
             0x00020000);
-        u32x4 qw[NB][4];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int n = nb * 16 + r16;
@@ -297,10 +300,6 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                if constexpr (!QLDS) qreg[nb][ks] = __builtin_bit_cast(bf16x8, qw[nb][ks]);
-            }
             m_run[nb] = kNoMax;
             l_run[nb] = 0.f;
 #pragma unroll
@@ -309,22 +308,21 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 to_accumulator_file(acc[mb][nb]);
             }
         }
-        if constexpr (QLDS) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) qs[(nb * 4 + ks) * 64] = __builtin_bit_cast(uint4, qw[nb][ks]);
-        }
     };
     // Have the queries arrive here, inside the rarely taken branch, so that the steady-state path
     // never carries a pending load of them.
     auto begin_unit_wait = [&]() __attribute__((always_inline)) {
-        if constexpr (!QLDS) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(qreg[nb][ks]));
-        }
+            for (int ks = 0; ks < 4; ++ks) {
+                if constexpr (QLDS) {
+                    qs[(nb * 4 + ks) * 64] = __builtin_bit_cast(uint4, qw[nb][ks]);
+                } else {
+                    qreg[nb][ks] = __builtin_bit_cast(bf16x8, qw[nb][ks]);
+                    asm volatile("" : "+v"(qreg[nb][ks]));
+                }
+            }
         if constexpr (TREE) {
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
@@ -530,9 +528,9 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     // keeps the wait states between a matrix instruction and the first read of its result, also across
     // these branches; where the read is written out by hand (the rescale, from_accumulator_file) or
     // follows a scheduling barrier (the end of a unit), explicit wait states stand in front of it.
-    // Once the scores are formed and the V operands packed, the pair's registers are free and the next
+    // Once the scores are formed and the V operands packed, the pair's registers are free and (refill) the next
     // pair's loads go out into them, ahead of the softmax and the output product.
-    auto compute = [&](PairRegs<FP8> &t, int ti) __attribute__((always_inline)) {
+    auto compute = [&](PairRegs<FP8> &t, int ti, auto refill) __attribute__((always_inline)) {
         const int tok0 = ti * kPairTokens + jq * 4;   // first of this lane's four cache positions in the first tile
         const float kscale[2] = {sc2 * t.t[0].ks, sc2 * t.t[1].ks}, vscale[2] = {t.t[0].vs, t.t[1].vs};
 
@@ -547,9 +545,51 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 kop[h][3] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[1].z, tt.k[1].w));
             } else {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) kop[h][ks] = __builtin_bit_cast(bf16x8, tt.k[ks]);
+                for (int ks = 0; ks < 4; ++ks) {
+                    u32x4 w = tt.k[ks];
+                    if constexpr (SINGLE) {   // a copy, so that the registers it came in are free for the refill
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) {
+                            uint32_t x;
+                            asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(w[c]));
+                            w[c] = x;
+                        }
+                    }
+                    kop[h][ks] = __builtin_bit_cast(bf16x8, w);
+                }
             }
         }
+        // V operand registers: vop[mb] = d-phase mb of tokens tok0 .. tok0+3 (words 0, 1) and tok0+16 .. tok0+19 (2, 3).
+        uint32_t vop[8][4];
+        auto pack_values = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int t2 = 0; t2 < 2; ++t2) {
+#pragma unroll
+                for (int h = 0; h < 4; ++h) {   // word h of each token's 8 values holds d-phases 2h and 2h+1
+                    uint32_t w[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if constexpr (FP8) {
+                            const uint32_t src = (h < 2) ? t.t[t2].v[e].x : t.t[t2].v[e].y;   // two e4m3 bytes -> two bf16, exact
+                            w[e] = (h & 1) ? fp8x2_to_bf16x2<true>(src) : fp8x2_to_bf16x2<false>(src);
+                        } else {
+                            w[e] = t.t[t2].v[e][h];
+                        }
+                    }
+                    vop[2 * h][2 * t2] = pack_lo16(w[0], w[1]);
+                    vop[2 * h][2 * t2 + 1] = pack_lo16(w[2], w[3]);
+                    vop[2 * h + 1][2 * t2] = pack_hi16(w[0], w[1]);
+                    vop[2 * h + 1][2 * t2 + 1] = pack_hi16(w[2], w[3]);
+                }
+            }
+        };
+        if constexpr (SINGLE) {
+            pack_values();
+            __builtin_amdgcn_sched_barrier(0);
+            issue(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+
         float4v s[NB][2];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) s[nb][0] = s[nb][1] = float4v{0.f, 0.f, 0.f, 0.f};
@@ -579,32 +619,13 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             }
         }
 
-        // V operand registers: vop[mb] = d-phase mb of tokens tok0 .. tok0+3 (words 0, 1) and tok0+16 .. tok0+19 (2, 3).
-        uint32_t vop[8][4];
         {
-#pragma unroll
-            for (int t2 = 0; t2 < 2; ++t2) {
-#pragma unroll
-                for (int h = 0; h < 4; ++h) {   // word h of each token's 8 values holds d-phases 2h and 2h+1
-                    uint32_t w[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if constexpr (FP8) {
-                            const uint32_t src = (h < 2) ? t.t[t2].v[e].x : t.t[t2].v[e].y;   // two e4m3 bytes -> two bf16, exact
-                            w[e] = (h & 1) ? fp8x2_to_bf16x2<true>(src) : fp8x2_to_bf16x2<false>(src);
-                        } else {
-                            w[e] = t.t[t2].v[e][h];
-                        }
-                    }
-                    vop[2 * h][2 * t2] = pack_lo16(w[0], w[1]);
-                    vop[2 * h][2 * t2 + 1] = pack_lo16(w[2], w[3]);
-                    vop[2 * h + 1][2 * t2] = pack_hi16(w[0], w[1]);
-                    vop[2 * h + 1][2 * t2 + 1] = pack_hi16(w[2], w[3]);
-                }
+            if constexpr (!SINGLE) {
+                pack_values();
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (decltype(refill)::value) issue(t);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            __builtin_amdgcn_sched_barrier(0);
-            issue(t);
-            __builtin_amdgcn_sched_barrier(0);
             // Slots at or past kv_len may hold anything (NaN, inf): they are cleared so that 0 * garbage cannot
             // occur.  Only the last pair of a cache has such slots.
             if (ti * kPairTokens + kPairTokens > L) {
@@ -728,30 +749,32 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
     };
 
-    // ---- the walk: a ring of NBUF pairs in registers (static indices: the loop over it is unrolled) ----
+    // ---- the walk: a ring of two pairs in registers ----
     begin_unit_issue();   // queries of the first unit go out before any KV tile
-    PairRegs<FP8> buf[NBUF];
-#pragma unroll
-    for (int j = 0; j < NBUF; ++j) {
-        // the first pairs' addresses come with the descriptor
-        load_pair(buf[j], j < kDescPairs ? desc_addr[j] : pair_addr[x0 + j < x1 ? x0 + j : x1 - 1]);
-    }
-    next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
+    PairRegs<FP8> buf[SINGLE ? 1 : 2];
+    load_pair(buf[0], desc_addr[0]);   // the first pairs' addresses come with the descriptor
+    if constexpr (!SINGLE) load_pair(buf[1], desc_addr[1]);
+    next_addr = desc_addr[SINGLE ? 1 : 2];
     begin_unit_wait();
     for (;;) {
-        int turn = 0;   // where in the ring the segment ended
-        for (;;) {
-            bool done = false;
-#pragma unroll
-            for (int j = 0; j < NBUF; ++j) {
-                if (!done) {
-                    compute(buf[j], tile);
-                    ++tile;
-                    done = --seg_left == 0;
-                    turn = j + 1;
-                }
+        if constexpr (SINGLE) {
+            for (; seg_left > 0; --seg_left) compute(buf[0], tile++, std::true_type{});
+        } else {
+            // A segment of odd length begins with a step of its own, so that the loop takes both buffers in turn with one way
+            // out: with an exit after either buffer the compiler either sees a path on which the first buffer's loads are the
+            // newest, and drains the whole ring at the top, or spills.
+            if (seg_left & 1) {
+                compute(buf[0], tile, std::false_type{});
+                ++tile;
+                --seg_left;
+                buf[0] = buf[SINGLE ? 0 : 1];
+                issue(buf[SINGLE ? 0 : 1]);
             }
-            if (done) break;
+            for (; seg_left > 0; seg_left -= 2) {
+                compute(buf[0], tile, std::true_type{});
+                compute(buf[SINGLE ? 0 : 1], tile + 1, std::true_type{});
+                tile += 2;
+            }
         }
         span_left -= tile - seg_tile0;
         end_unit(seg_tile0 == 0, tile == nb_tiles);
@@ -759,13 +782,6 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         next_unit();
         begin_unit_issue();
         begin_unit_wait();
-        // the next pair back to the ring's front (everything in the ring has arrived by now)
-        for (; turn < NBUF; ++turn) {
-            const PairRegs<FP8> last = buf[NBUF - 1];
-#pragma unroll
-            for (int j = NBUF - 1; j > 0; --j) buf[j] = buf[j - 1];
-            buf[0] = last;
-        }
     }
 }
 
@@ -841,16 +857,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 template <int G, int NB, bool FP8, bool TREE>
 int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
-    // One wavefront per SIMD (the whole register file, a ring of NBUF pairs): two waves on a SIMD
+    // One wavefront per SIMD (the whole register file; a ring of two pairs, three or four spill in most instances and
+    // were slower where they just fit): two waves on a SIMD
     // do not share the memory pipeline fairly under saturation (the older one wins), which turns
     // into a long tail.
     constexpr bool QLDS = NB >= 4;
-    constexpr int NBUF = 2;   // (three or four pairs spill in most instances: 104 us instead of 97 where they just fit)
     AttnArgs b = a;   // (the plan kernel has been enqueued by the caller)
     b.chain = kChainMerge<NB> ? 1 : 0;
     // When a profile is being taken the two events are attached to the dispatch itself, so that
     // their difference is the kernel's own duration on this stream (what a kernel trace shows).
-    hipExtLaunchKernelGGL((attn_stream_kernel<G, NB, FP8, NBUF, QLDS, TREE>), dim3((unsigned)(b.launch_waves / kWavesPerWg)),
+    hipExtLaunchKernelGGL((attn_stream_kernel<G, NB, FP8, QLDS, TREE>), dim3((unsigned)(b.launch_waves / kWavesPerWg)),
                           dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, b, b.pair_addr, b.wave_desc, b.pair_prefix,
                           b.kv_len, b.q_indptr, b.k_scale, b.v_scale);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_stream_kernel");
