@@ -4,8 +4,7 @@ Every source is compiled to an object of its own, several at a time, then linked
 in ``_build/`` next to this file.  The compiler's per-kernel resource remarks are collected into
 ``_build/resources.txt`` (registers, scratch bytes per lane, LDS per kernel): the place to look when a change
 to the streaming attention kernel makes an instance an order of magnitude slower, which is what happens when
-its tile ring or accumulators no longer fit the register file.  (The instances with four and five row blocks
-spill some values at entry that only the end of a unit reloads; their tile bodies touch no scratch.)
+its pairs of tiles in flight or accumulators no longer fit the register file.
 """
 from __future__ import annotations
 

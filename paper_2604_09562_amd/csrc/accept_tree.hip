@@ -26,7 +26,7 @@ namespace {
 //
 // Bound by the fp64 exponentials of the rounds that have most requests pending and by the length of the launch
 // chain.  64 requests of 128256 entries, depth 4: 240 us with a walk kernel of dependent reads in every round, 2-byte
-// loads, serial sums over the blocks and a pass that wrote r out for every draw; 142 us this way.
+// loads, serial sums over the blocks and a pass that wrote r out for every draw; 125 to 132 us this way.
 struct TreeScalars {
     int32_t cur, n, next, phase;       // phase: 0 walking, 1 residual due, 2 draw due
     int32_t pure, degenerate, which, rej;   // which: the buffer that holds r; rej: the child just rejected
