@@ -357,18 +357,19 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
         low_p = fminf(low_p, xp[s]);
         if (residual) low_q = fminf(low_q, xq[s]);
     }
-    const bool normal = !__any(!(ap(low_p) >= kExpNormal) || (residual && !(aq(low_q) >= kExpNormal)));
+    const bool normal = ap.fused && (!residual || aq.fused) &&
+                        !__any(!(ap.fma_form(low_p) >= kExpNormal) || (residual && !(aq.fma_form(low_q) >= kExpNormal)));
     if (!residual) {   // bonus distribution: only the normaliser of the target row is needed
         if (normal) {
 #pragma unroll
-            for (int s = 0; s < 8; ++s) zp += ex.normal(ap(xp[s]));
+            for (int s = 0; s < 8; ++s) zp += ex.normal(ap.fma_form(xp[s]));
         } else {
 #pragma unroll
             for (int s = 0; s < 8; ++s) zp += ex(ap(xp[s]));
         }
     } else if (normal) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) pair(ex.normal(ap(xp[s])), ex.normal(aq(xq[s])), 1u << s);
+        for (int s = 0; s < 8; ++s) pair(ex.normal(ap.fma_form(xp[s])), ex.normal(aq.fma_form(xq[s])), 1u << s);
     } else {
 #pragma unroll
         for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), 1u << s);

@@ -330,12 +330,26 @@ struct ExpTable {
     }
 };
 
-// Argument of the exponential of a logit: (x - max) / T as one fused multiply-add.  c = -max/T is rounded once per row,
-// a factor common to all of the row's exponentials, which the normaliser takes out again.
+// Argument of the exponential of a logit, (x - max) / T.  As one fused multiply-add x / T - max / T where max / T is small
+// enough: its rounding (below 1.2e-10 there) is a factor common to all of the row's exponentials, which the normaliser takes
+// out again, and far inside the boundary zone of p == q.  Beyond that (a tiny temperature, enormous logits) the rounding would
+// be as large as the arguments themselves -- at T = 1e-18 every exponential of a row underflowed or overflowed -- so there
+// the difference is formed first, which is exactly 0 at the row's maximum.
+constexpr double kFusedArgMax = 0x1p20;
 struct RowArg {
     double inv_t, c;
-    __device__ __forceinline__ RowArg(double inv_t_, float m) : inv_t(inv_t_), c(-(double)m * inv_t_) {}
-    __device__ __forceinline__ double operator()(float x) const { return fma((double)x, inv_t, c); }
+    float sub;
+    bool fused;   // uniform: all lanes of a workgroup hold the same row
+    __device__ __forceinline__ RowArg(double inv_t_, float m) : inv_t(inv_t_)
+    {
+        const double mt = (double)m * inv_t_;
+        const bool f = fabs(mt) < kFusedArgMax;   // (false for a row without a finite maximum)
+        c = f ? -mt : 0.0;
+        fused = __builtin_amdgcn_readfirstlane(f);
+        sub = fused ? 0.f : m;
+    }
+    __device__ __forceinline__ double operator()(float x) const { return fma((double)x - (double)sub, inv_t, c); }
+    __device__ __forceinline__ double fma_form(float x) const { return fma((double)x, inv_t, c); }   // the same bits if `fused`
 };
 
 // Exponentials of eight logits.  Whether all of the wavefront's are normal numbers (those of masked logits are not) is
@@ -345,9 +359,9 @@ __device__ __forceinline__ void exp8(const ExpTable &ex, const RowArg &arg, cons
     float low = x[0];
 #pragma unroll
     for (int s = 1; s < 8; ++s) low = fminf(low, x[s]);
-    if (!__any(!(arg(low) >= kExpNormal))) {
+    if (arg.fused && !__any(!(arg.fma_form(low) >= kExpNormal))) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) e[s] = ex.normal(arg(x[s]));
+        for (int s = 0; s < 8; ++s) e[s] = ex.normal(arg.fma_form(x[s]));
     } else {
 #pragma unroll
         for (int s = 0; s < 8; ++s) e[s] = ex(arg(x[s]));

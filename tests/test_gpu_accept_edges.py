@@ -1,0 +1,38 @@
+"""GPU parity of sampled acceptance at the edges of its arithmetic: temperatures so small that a row's distribution is its
+arg-maxima.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance tests."""
+import numpy as np
+import pytest
+
+from paper_2604_09562_amd import synth
+from tests.test_gpu_accept import compare as compare_chain
+from tests.test_gpu_tree_sample import compare as compare_tree
+
+pytestmark = pytest.mark.gpu
+
+TINY = synth.CONFIGS[0]
+
+
+def make(tree, cfg, seed, pad=0, **kw):
+    return (synth.make_tree_sample_inputs if tree else synth.make_accept_inputs)(cfg, seed=seed, row_pad=pad, **kw)
+
+
+def check(tree, inp, oracle, label):
+    (compare_tree if tree else compare_chain)(inp, oracle, label=label)
+
+
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("temperature", [1e-3, 1e-5, 1e-9, 1e-15, 1e-18, 1e-20, 1e-30])
+def test_tiny_temperatures(oracle, tree, dtype, temperature):
+    """max / T beyond the range in which it can be rounded: every row's exponentials are 1 at the maximum and 0 elsewhere."""
+    cfg = TINY.scaled(batch=24, vocab=3000, logit_dtype=dtype, temperature=temperature, depth=("uniform", 0, 3),
+                      sigma_draft=("fixed", 0.2))
+    inp = make(tree, cfg, 4)
+    # requests without drafts: two equal maxima, so that the uniform decides between them
+    rows = inp["target_logits"]
+    lone = [b for b in range(24) if inp["depth"][b] == 0]
+    assert lone
+    for i, b in enumerate(lone):
+        rows[inp["q_indptr"][b], [700, 2500]] = synth.store(np.array([20.0 + 3 * i], np.float32), dtype)[0]
+        inp["u_sample"][b] = 0.25 if i % 2 else 0.75
+    check(tree, inp, oracle, f"T {temperature} {dtype}")
