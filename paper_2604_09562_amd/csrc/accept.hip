@@ -354,8 +354,8 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
     float low_p = xp[0], low_q = residual ? xq[0] : 0.f;
 #pragma unroll
     for (int s = 1; s < 8; ++s) {
-        low_p = fminf(low_p, xp[s]);
-        if (residual) low_q = fminf(low_q, xq[s]);
+        low_p = min_or_nan(low_p, xp[s]);
+        if (residual) low_q = min_or_nan(low_q, xq[s]);
     }
     const bool normal = ap.fused && (!residual || aq.fused) &&
                         !__any(!(ap.fma_form(low_p) >= kExpNormal) || (residual && !(aq.fma_form(low_q) >= kExpNormal)));

@@ -352,13 +352,17 @@ struct RowArg {
     __device__ __forceinline__ double fma_form(float x) const { return fma((double)x, inv_t, c); }   // the same bits if `fused`
 };
 
+// The smaller of two logits, NaN if either is (one instruction for three operands): the tests that admit a wavefront to
+// ExpTable::normal must see a NaN, which the general form takes as no mass.
+__device__ __forceinline__ float min_or_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
+
 // Exponentials of eight logits.  Whether all of the wavefront's are normal numbers (those of masked logits are not) is
 // one test.
 __device__ __forceinline__ void exp8(const ExpTable &ex, const RowArg &arg, const float (&x)[8], double (&e)[8])
 {
     float low = x[0];
 #pragma unroll
-    for (int s = 1; s < 8; ++s) low = fminf(low, x[s]);
+    for (int s = 1; s < 8; ++s) low = min_or_nan(low, x[s]);
     if (arg.fused && !__any(!(arg.fma_form(low) >= kExpNormal))) {
 #pragma unroll
         for (int s = 0; s < 8; ++s) e[s] = ex.normal(arg.fma_form(x[s]));

@@ -1,11 +1,12 @@
 """GPU parity of sampled acceptance at the edges of its arithmetic: temperatures so small that a row's distribution is its
-arg-maxima.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance tests."""
+arg-maxima, and logits that are NaN.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance
+tests."""
 import numpy as np
 import pytest
 
 from paper_2604_09562_amd import synth
-from tests.test_gpu_accept import compare as compare_chain
-from tests.test_gpu_tree_sample import compare as compare_tree
+from tests.test_gpu_accept import compare as compare_chain, run_gpu as run_chain
+from tests.test_gpu_tree_sample import compare as compare_tree, run_gpu as run_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +37,23 @@ def test_tiny_temperatures(oracle, tree, dtype, temperature):
         rows[inp["q_indptr"][b], [700, 2500]] = synth.store(np.array([20.0 + 3 * i], np.float32), dtype)[0]
         inp["u_sample"][b] = 0.25 if i % 2 else 0.75
     check(tree, inp, oracle, f"T {temperature} {dtype}")
+
+
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("share", [1, 40, 2990])   # NaN entries of each row
+def test_nan_logits_carry_no_mass(oracle, tree, dtype, share):
+    """A NaN logit counts as masked: requests without drafts draw what they draw with -inf in its place."""
+    cfg = TINY.scaled(batch=16, vocab=3000, logit_dtype=dtype, depth=("fixed", 0))
+    inp = make(tree, cfg, 6)
+    rng = np.random.default_rng(share)
+    at = [rng.choice(3000, share, replace=False) for _ in range(16)]
+    for value in (-np.inf, np.nan):
+        for b in range(16):
+            inp["target_logits"][b, at[b]] = synth.store(np.array([value], np.float32), dtype)[0]
+        if value != value:
+            got = (run_tree if tree else run_chain)(inp)[1]
+            assert np.array_equal(got, masked)
+        else:
+            check(tree, inp, oracle, f"{share} masked, {dtype}")
+            masked = (run_tree if tree else run_chain)(inp)[1]
