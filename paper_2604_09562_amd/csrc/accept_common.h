@@ -495,8 +495,9 @@ __device__ __forceinline__ int draw_token(int nsub, float u, DrawShared &sh, Mas
     double before = sh.prefix;
     for (int wv = 0; wv < wave; ++wv) before += sh.entry[wv];
     const double excl = before + (incl - local);
-    // first lane whose running sum crosses the threshold
-    const unsigned long long bal = __ballot(!take_last && excl + local > thr);
+    // first lane with mass whose running sum crosses the threshold (the scan groups its additions differently for every lane,
+    // so the sum at a lane without mass may lie an ulp above that of the lane in front of it)
+    const unsigned long long bal = __ballot(!take_last && local > 0.0 && excl + local > thr);
     if (lane == 0) sh.efirst[wave] = bal ? wave * 64 + (__ffsll((long long)bal) - 1) : 0x7fffffff;
     __syncthreads();
     const int first = min(min(sh.efirst[0], sh.efirst[1]), min(sh.efirst[2], sh.efirst[3]));

@@ -1,5 +1,5 @@
 """GPU parity of sampled acceptance at the edges of its arithmetic: temperatures so small that a row's distribution is its
-arg-maxima, and logits that are NaN.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance
+arg-maxima, logits that are NaN, uniforms that fall on a boundary of the distribution.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance
 tests."""
 import numpy as np
 import pytest
@@ -57,3 +57,30 @@ def test_nan_logits_carry_no_mass(oracle, tree, dtype, share):
         else:
             check(tree, inp, oracle, f"{share} masked, {dtype}")
             masked = (run_tree if tree else run_chain)(inp)[1]
+
+
+@pytest.mark.parametrize("tree", [False, True])
+def test_uniform_on_a_boundary_next_to_masked_runs(tree):
+    """Equal masses 1/n with runs of masked entries between them, and u = j/8 where u * n is a whole number: the running sum
+    meets the threshold but for its rounding, at a place where lanes without any mass follow.  The token is one of the two
+    entries at the boundary, whichever way the sums round."""
+    requests = 400
+    rows = np.full((requests, 2048), -np.inf, np.float32)
+    want = []
+    for seed in range(requests):
+        rng = np.random.default_rng(seed)
+        n = 2 * int(rng.integers(300, 900))
+        idx = np.flatnonzero(np.repeat(rng.random(256) < 0.5, 8))
+        n = min(n, len(idx) // 2 * 2)
+        idx = np.sort(rng.choice(idx, n, replace=False))
+        rows[seed, idx] = 0.0
+        want.append(idx)
+    cfg = TINY.scaled(batch=requests * 7, vocab=2048, logit_dtype="f32", depth=("fixed", 0), temperature=1.0)
+    inp = make(tree, cfg, 0)
+    inp["target_logits"][:] = synth.store(np.repeat(rows, 7, axis=0), "f32")
+    inp["u_sample"][:] = np.tile(np.arange(1, 8, dtype=np.float32) / 8.0, requests)
+    got = (run_tree if tree else run_chain)(inp)[1][:, 0]
+    for r in range(requests * 7):
+        idx, j = want[r // 7], (r % 7 + 1) * len(want[r // 7])
+        ok = idx[[j // 8 - 1, j // 8]] if j % 8 == 0 else idx[[j // 8]]
+        assert got[r] in ok, (r, int(got[r]), ok)
