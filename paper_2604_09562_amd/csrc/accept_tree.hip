@@ -70,12 +70,13 @@ __device__ __forceinline__ void tree_walk(const AcceptArgs &a, const TreeNode *n
     const int lane = threadIdx.x & 63;
     const bool is = lane >= 1 && lane <= k;
     const int par = is ? a.tree_parent[t0 + lane] : -2;
-    const int x = is ? a.draft_tokens[d0 + lane - 1] : 0;   // (read from r only for nodes that are offered)
+    const int x = is ? a.draft_tokens[d0 + lane - 1] : 0;
+    const int x_in = min(max(x, 0), a.vocab - 1);   // where r is read: inside the request's buffer, as the prep kernel's gathers
     const double u = is ? (double)a.u_accept[d0 + lane - 1] : 0.0;
     const double qx = is ? nodes[lane].qx : 0.0, px = is ? nodes[lane].px : 0.0;
     const float mp = lane <= k ? nodes[lane].mp : 0.f, mq = is ? nodes[lane].mq : 0.f;
     double rx = px;
-    if (!s.pure && par == s.cur && lane >= s.next) rx = arr_b[(int64_t)s.which * a.vocab + x] / s.norm;
+    if (!s.pure && par == s.cur && lane >= s.next) rx = arr_b[(int64_t)s.which * a.vocab + x_in] / s.norm;
     const unsigned long long pure_ok = __ballot(is && u * qx < px);
     const unsigned long long here_ok = __ballot(is && u * qx < rx);   // (s.pure: the same)
     unsigned long long offered = 0, ok = here_ok;

@@ -84,3 +84,25 @@ def test_uniform_on_a_boundary_next_to_masked_runs(tree):
         idx, j = want[r // 7], (r % 7 + 1) * len(want[r // 7])
         ok = idx[[j // 8 - 1, j // 8]] if j % 8 == 0 else idx[[j // 8]]
         assert got[r] in ok, (r, int(got[r]), ok)
+
+
+@pytest.mark.parametrize("bad", [-1, -70000, 3000, 70000])
+def test_tree_walk_reads_residuals_inside_the_vocabulary(oracle, bad):
+    """A draft token outside the vocabulary is a caller's error; the walk that judges it by a residual still reads inside
+    the request's own buffer (of the nearest token, as the other reads do) and the rest of the batch is as it would be."""
+    cfg = TINY.scaled(batch=6, vocab=3000, logit_dtype="bf16", depth=("fixed", 4), sigma_draft=("fixed", 2.0))
+    inp = make(True, cfg, 9)
+    inp["tree_parent"] = np.tile(np.concatenate([[-1], np.zeros(4)]), 6).astype(np.int32)
+    inp["u_accept"][:] = np.float32(0.999999)
+    last, t0 = 5 * 4, int(inp["q_indptr"][5])
+    inp["target_logits"][t0, [0, 2999]] = synth.store(np.array([-30.0], np.float32), "bf16")[0]
+    gap = (synth.decode_storage(inp["draft_logits"], "bf16")[last:last + 4, :3000]
+           - synth.decode_storage(inp["target_logits"], "bf16")[t0, :3000])
+    inp["draft_tokens"][last:last + 4] = gap.argmax(axis=1)       # tokens the target likes far less than their proposals
+    inp["draft_tokens"][last + 2] = min(max(bad, 0), 2999)
+    ref = oracle.tree_accept_sample(inp)
+    assert ref["accepted_len"][5] == 0 and np.isfinite(ref["ratio"][last:last + 4]).all()   # all offered, all rejected
+    inp["draft_tokens"][last + 2] = bad
+    acc, toks, nodes, _ = run_tree(inp)
+    assert np.array_equal(acc, ref["accepted_len"]) and np.array_equal(toks, ref["out_tokens"])
+    assert np.array_equal(nodes, ref["accepted_nodes"])
