@@ -404,7 +404,10 @@ __global__ __launch_bounds__(kThreads) void tree_pick_kernel(AcceptArgs a, Works
             }
         };
         y = draw_token(w.nsub, a.u_sample[b], sh, mass_of, entries);
-        if (y < 0) y = 0;   // (no mass at all cannot happen for a valid batch; stay in bounds anyway)
+        if (y < 0) {   // no mass at all, as with an infinite logit: the arg-maximum, as in the chain rule
+            y = lowest_index_of(a.target, t0 + s.cur, a.row_stride, DT, V, s.mp, sh);
+            if (y >= V) y = 0;   // (a row of NaN)
+        }
     }
     if (tid < SS_OUT_WIDTH)
         a.out_tokens[(int64_t)b * SS_OUT_WIDTH + tid] = tid < s.n ? mem.st[b].tok[tid] : (tid == s.n ? y : -1);

@@ -106,3 +106,17 @@ def test_tree_walk_reads_residuals_inside_the_vocabulary(oracle, bad):
     acc, toks, nodes, _ = run_tree(inp)
     assert np.array_equal(acc, ref["accepted_len"]) and np.array_equal(toks, ref["out_tokens"])
     assert np.array_equal(nodes, ref["accepted_nodes"])
+
+
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_rows_without_mass_give_the_arg_maximum(tree, dtype):
+    """An infinite logit, or a row with every entry masked: no entry has a finite share, the lowest arg-maximum is emitted."""
+    cfg = TINY.scaled(batch=3, vocab=3000, logit_dtype=dtype, depth=("fixed", 0))
+    inp = make(tree, cfg, 8)
+    inf = synth.store(np.array([np.inf, -np.inf], np.float32), dtype)
+    inp["target_logits"][0, 1234] = inf[0]
+    inp["target_logits"][1, [2999, 77]] = inf[0]
+    inp["target_logits"][2, :3000] = inf[1]
+    got = (run_tree if tree else run_chain)(inp)[1][:, 0]
+    assert got.tolist() == [1234, 77, 0]
