@@ -29,7 +29,8 @@ int32_t hip_fail(hipError_t e, const char *what)
 static int64_t g_attn_path = 0;
 static int64_t g_attn_waves = 0;
 static int64_t g_validate = 0;
-static int64_t g_unit_weight = -1;        // -1: by the instance's row blocks
+constexpr int64_t kUnitWeightAuto = 3;    // the option's default: by the instance's row blocks (3 or 16 tiles)
+static int64_t g_unit_weight = kUnitWeightAuto;
 static std::vector<hipEvent_t> g_events;  // pairs
 static int g_prof_cap = 0, g_prof_used = 0;
 
@@ -219,7 +220,7 @@ int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const 
     a.q_lo = 0;
     a.q_win = max_q_len;
     a.reuse_plan = (batch->flags & SS_BATCH_REUSE_PLAN) ? 1 : 0;
-    a.unit_weight = g_unit_weight < 0 ? -1 : ((int32_t)g_unit_weight + 1) / 2;   // tiles -> pairs
+    a.unit_weight = g_unit_weight == kUnitWeightAuto ? -1 : ((int32_t)g_unit_weight + 1) / 2;   // tiles -> pairs
     // carve the workspace
     char *w = static_cast<char *>(workspace);
     a.plan = reinterpret_cast<AttnPlan *>(w);

@@ -3,6 +3,7 @@ tile and a pair, units of one pair, spans from one wavefront to more than the ba
 inside a workgroup), one to five row blocks, chains and trees."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2604_09562_amd import binding, synth
 from tests.test_gpu_attn import check
@@ -27,4 +28,44 @@ def test_pairs(oracle, hq, depth, kv, tree, waves):
         check(inp, oracle, label=f"{kv} {hq} heads depth {depth} tree {tree} waves {waves}")
     finally:
         binding.ss_set_option("attn_path", 0)
+        binding.ss_set_option("attn_waves", 0)
+
+
+@pytest.mark.parametrize("weight,pairs,pairs_deep", [(0, 0, 0), (1, 1, 1), (4, 2, 2), (17, 9, 9), (64, 32, 32), (3, 2, 8)])
+def test_unit_weight_option(weight, pairs, pairs_deep):
+    """The plan record (four int32 at the start of the workspace: pairs, spans, unit weight, hand-over) carries the weight the
+    spans were cut with: as given, or by the row blocks for the default, also after the option had another value."""
+    for hq, depth, want in ((8, 4, pairs), (16, 9, pairs_deep)):
+        cfg = LLAMA8B.scaled(batch=4, num_q_heads=hq, num_kv_heads=2, depth=("fixed", depth))
+        d = binding.attention_to_device(synth.make_attention_inputs(cfg, seed=1, kv_len=np.full(4, 900, np.int32)))
+        out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=depth + 1)
+        binding.ss_set_option("attn_unit_weight", 64)
+        binding.ss_set_option("attn_unit_weight", weight)
+        try:
+            binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=depth + 1)
+        finally:
+            binding.ss_set_option("attn_unit_weight", 3)
+        torch.cuda.synchronize()
+        assert ws[:16].view(torch.int32)[2].item() == want, (hq, weight)
+
+
+@pytest.mark.parametrize("weight", [0, 3, 16, 64])
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("hq,depth", [(8, 15), (16, 9)])   # 4 and 5 row blocks
+def test_many_short_units_over_weights(oracle, hq, depth, kv, tree, weight):
+    """Many short units and a few long ones: with the larger weights most spans are empty or hold several whole units."""
+    lens = np.array([40] * 30 + [1500, 21, 3000, 33], dtype=np.int32)
+    cfg = (LLAMA8B if kv == "bf16" else FP8_70B).scaled(batch=len(lens), num_q_heads=hq, num_kv_heads=2)
+    inp = synth.make_attention_inputs(cfg, seed=weight, kv_len=lens, depth=np.minimum(lens - 1, depth).astype(np.int32), tree=tree,
+                                      nan_tail=True)
+    binding.ss_set_option("attn_path", 2)
+    binding.ss_set_option("attn_unit_weight", weight)
+    try:
+        for waves in (8, 64, 0):
+            binding.ss_set_option("attn_waves", waves)
+            check(inp, oracle, label=f"{kv} {hq} heads depth {depth} tree {tree} weight {weight} waves {waves}")
+    finally:
+        binding.ss_set_option("attn_path", 0)
+        binding.ss_set_option("attn_unit_weight", 3)
         binding.ss_set_option("attn_waves", 0)
