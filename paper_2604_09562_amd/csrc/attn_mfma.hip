@@ -19,7 +19,22 @@ namespace {
 // pairs followed by its real ones; a cut that falls into a unit's virtual part becomes the unit's first
 // pair.  The cuts depend on the batch's lengths only, so results do not vary from run to run.
 // ---------------------------------------------------------------------------------------------
+static_assert(kSpansPerWg == kWavesPerWg, "one span per wavefront");
 constexpr int kPlanMaxBatch = 4096;   // requests whose tile prefix fits the plan kernel's LDS; beyond that the cuts are unweighted
+
+// Inclusive scan over a wavefront's lanes (values >= 0, 0 is neutral for `op`) by data-parallel moves: a scan by shuffles is six
+// LDS round trips, 0.3 us of the plan's 5.
+template <class Op>
+__device__ __forceinline__ int wave_scan_int(int x, Op op)
+{
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));   // row_shr 1, 2, 4, 8: inside each row of 16 lanes
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));   // row_bcast 15: row 0 to row 1, row 2 to row 3
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));   // row_bcast 31: rows 0 and 1 to rows 2 and 3
+    return x;
+}
 
 __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
 {
@@ -31,18 +46,20 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
 
     // exclusive prefix of the tile counts of all requests (every workgroup builds its own copy), or,
     // for a batch too large for that, just the sums in front of and from request b on
-    int pre = 0;
+    int pre = 0, longest = 0;   // (pairs of the longest unit)
     long long total = 0;
+    __shared__ int longest_sh[4];
+    auto note_longest = [&](int n) {
+        n = wave_scan_int(n, [](int x, int y) { return max(x, y); });
+        if ((tid & 63) == 63) longest_sh[tid >> 6] = n;
+    };
     if (a.batch <= kPlanMaxBatch) {
         int carry = 0;
         for (int base = 0; base < a.batch; base += 256) {
             const int i = base + tid;
             const int t = i < a.batch ? window_pairs(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo) : 0;
-            int incl = t;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int o = __shfl_up(incl, off);
-                if ((tid & 63) >= off) incl += o;
-            }
+            longest = max(longest, t);
+            const int incl = wave_scan_int(t, [](int x, int y) { return x + y; });
             if ((tid & 63) == 63) sh[tid >> 6] = incl;
             __syncthreads();
             int before = carry;
@@ -53,19 +70,22 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
             carry += chunk_total;
         }
         if (tid == 0) prefix[a.batch] = carry;
+        note_longest(longest);
         __syncthreads();
         pre = prefix[b];
-        total = (long long)prefix[a.batch] * a.num_kv_heads;
+        total = (long long)__builtin_amdgcn_readfirstlane(prefix[a.batch]) * a.num_kv_heads;   // (uniform: scalar arithmetic below)
     } else {
         int before = 0, rest = 0;
         for (int i = tid; i < a.batch; i += 256) {
             const int t = window_pairs(a.kv_len[i], a.q_indptr[i + 1] - a.q_indptr[i], a.q_lo);
+            longest = max(longest, t);
             if (i < b) before += t; else rest += t;
         }
         for (int off = 32; off; off >>= 1) {
             before += __shfl_xor(before, off);
             rest += __shfl_xor(rest, off);
         }
+        note_longest(longest);
         __shared__ int sh2[8];
         if ((tid & 63) == 0) {
             sh2[tid >> 6] = before;
@@ -75,15 +95,11 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         pre = sh2[0] + sh2[1] + sh2[2] + sh2[3];
         total = (long long)(pre + sh2[4] + sh2[5] + sh2[6] + sh2[7]) * a.num_kv_heads;
     }
-    long long nw = total / kMinPairsPerWave;
-    if (nw < 1) nw = 1;
-    if (nw > a.launch_waves) nw = a.launch_waves;
-    // A chip that is full combines the spans of a workgroup in LDS, which saves partials.  A batch too small for that is
-    // bound by latency, and the hand-over is a chain of up to four unit ends (1.2 us each, 3.8 us for the output): there
-    // every wavefront leaves its partial at once and the merge kernel, which runs anyway, combines them
-    // (4 requests of 40..600 tokens, 8 KV heads: streaming kernel 16.4 -> 14.2 us, with spans of two pairs instead of
-    // four 11.4 us; merge kernel 4.0 -> 4.2 us).
-    const int chain = nw == a.launch_waves;
+    longest = __builtin_amdgcn_readfirstlane(max(max(longest_sh[0], longest_sh[1]), max(longest_sh[2], longest_sh[3])));
+    const bool can_chain = (a.q_win * (a.num_q_heads / a.num_kv_heads) + 15) / 16 <= kChainRowBlocks;
+    const SpanCount count = count_spans(total, longest, a.launch_waves, can_chain);
+    const long long nw = count.spans;
+    const int chain = count.chain;
     const int weight = weighted ? a.unit_weight : 0;
     const long long total_w = total + (long long)weight * a.batch * a.num_kv_heads;
 

@@ -11,8 +11,8 @@
 // kernel is a plain linear walk that never stops at a unit boundary.  A span may cover the tail
 // of one unit, several whole units and the head of another; for every unit it touches the wave
 // has one partial result (softmax reference, sum, unnormalised output).  In the instances with
-// at most two row blocks, when the batch fills the chip, the four wavefronts of a workgroup, whose spans are consecutive, hand
-// the partials of a shared unit from right to left through LDS and combine them by their
+// at most two row blocks, when the batch fills the chip or has units of many spans (count_spans), the four wavefronts of a
+// workgroup, whose spans are consecutive, hand the partials of a shared unit from right to left through LDS and combine them by their
 // log-sum-exp; a unit that lies inside one workgroup's spans is normalised, rounded and
 // written by that workgroup.  What is left (a unit that crosses workgroups; every split unit
 // in the other instances) goes to device memory as a partial in slot `workgroup + unit`
@@ -70,7 +70,7 @@ constexpr float kNoMax = -1.0e30f;   // reference before any score was seen (fin
 constexpr int kMaxFlagPolls = 1 << 23;   // polls of a neighbour's deposit flag before giving up (each at least 128 cycles)
 constexpr int kPartRowStride = 33;   // float4 per staged partial row in LDS (32 of data + 1 of padding)
 template <int NB>
-constexpr bool kChainMerge = NB <= 2;   // instances that combine the spans of a workgroup in LDS
+constexpr bool kChainMerge = NB <= kChainRowBlocks;   // instances that combine the spans of a workgroup in LDS
 template <int NB>
 constexpr bool kStageRows = NB <= 4;    // instances that write partials as whole rows through LDS (measured: with five
                                         // row blocks the staging costs more than the scattered stores it replaces)

@@ -25,10 +25,10 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
 constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
 constexpr int kWavesPerWg = 4;
-constexpr int kMinPairsPerWave = 2;      // below this a KV partition is not worth its partial write
 constexpr int kDescInts = 16;            // ints per wave descriptor
 constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
+constexpr int kChainRowBlocks = 2;       // up to here the spans of a workgroup can be combined in LDS
 constexpr int kMaxRowBlocks = 5;         // 16-row blocks of query rows one wavefront can keep accumulators for
 // What opening a unit costs a wavefront, in pairs, for the span cuts.  With up to three row blocks 2 (1 to 3 are level);
 // with four or five the query rows go through LDS and a unit's partial is 32 or 40 KB: 6 to 10 are level (96 requests of

@@ -69,3 +69,21 @@ def test_many_short_units_over_weights(oracle, hq, depth, kv, tree, weight):
         binding.ss_set_option("attn_path", 0)
         binding.ss_set_option("attn_unit_weight", 3)
         binding.ss_set_option("attn_waves", 0)
+
+
+@pytest.mark.parametrize("tokens,hkv,hq,depth,spans,chain", [
+    (1000, 8, 32, 4, 128, 0), (1100, 8, 32, 4, 140, 1), (4000, 8, 32, 4, 500, 1),      # two row blocks: the hand-over comes in
+    (8200, 8, 32, 4, 1024, 1), (8100, 4, 16, 4, 508, 1),                               # (a full chip)
+    (8200, 4, 16, 4, 257, 1), (32000, 1, 4, 4, 250, 1),                                # then spans of four pairs
+    (2000, 8, 32, 8, 252, 0), (2200, 8, 32, 8, 138, 0), (20000, 1, 8, 8, 156, 0)])     # three and five row blocks
+def test_single_long_requests(oracle, tokens, hkv, hq, depth, spans, chain):
+    """One request: the plan record (pairs, spans, unit weight, hand-over) on both sides of its rules, and the result."""
+    cfg = LLAMA8B.scaled(batch=1, num_q_heads=hq, num_kv_heads=hkv)
+    inp = synth.make_attention_inputs(cfg, seed=tokens, kv_len=np.array([tokens], np.int32), depth=np.array([depth], np.int32))
+    check(inp, oracle, max_q_len=depth + 1, label=f"{tokens} tokens over {hkv} KV heads")
+    d = binding.attention_to_device(inp)
+    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=depth + 1)
+    binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=depth + 1)
+    torch.cuda.synchronize()
+    plan = ws[:16].view(torch.int32).tolist()
+    assert (plan[1], plan[3]) == (spans, chain), plan

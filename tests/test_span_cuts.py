@@ -45,6 +45,12 @@ extern "C" void plan_spans(const int32_t *prefix, int batch, int hkv, int weight
             }
         }
 }
+extern "C" long long count_spans(long long total, int longest, long long launch_waves, int can_chain, int *chain)
+{
+    const ss::SpanCount c = ss::count_spans(total, longest, launch_waves, can_chain != 0);
+    *chain = c.chain;
+    return c.spans;
+}
 extern "C" void merge_waves(const int32_t *prefix, int batch, int hkv, int weight, long long nw, int *first, int *last)
 {
     const SpanCuts c = SpanCuts::make(prefix, batch, hkv, weight, nw);
@@ -142,3 +148,38 @@ def test_bench_workload_shape(shim):
     rng = np.random.default_rng(2)
     tiles = (rng.integers(256, 4097, 64) + 5 + 15) // 16
     _check(shim, tiles, 8, 3, 1024)
+
+
+@pytest.mark.parametrize("can_chain", [False, True])
+def test_the_merge_adds_few_partials(shim, can_chain):
+    """A unit's partials are added one after the other: at most about 32 of them, or what spans of four pairs leave (with the
+    hand-over, where the instance has it) on a call of long units.  One request, a few equal ones, one long among short ones."""
+    shim.count_spans.restype = ctypes.c_longlong
+    worst = 0
+    for hkv in (1, 2, 8):
+        for batch in (1, 2, 4, 16, 64):
+            for n in (1, 2, 9, 31, 32, 33, 63, 64, 65, 125, 128, 129, 250, 500, 1000, 4000):
+                for rest in (n, 3):
+                    pairs = np.array([n] + [min(rest, n)] * (batch - 1))
+                    total = int(pairs.sum()) * hkv
+                    chain = ctypes.c_int()
+                    nw = shim.count_spans(ctypes.c_longlong(total), n, ctypes.c_longlong(1024), int(can_chain),
+                                          ctypes.byref(chain))
+                    label = (hkv, batch, n, rest, nw, chain.value)
+                    assert 1 <= nw <= 1024 and (nw == 1 or total >= 2 * nw), label
+                    assert can_chain or not chain.value, label
+                    assert not can_chain or chain.value or nw < 1024, label    # a full chip hands over
+                    _check(shim, pairs, hkv, 2, nw)
+                    prefix = np.concatenate([[0], np.cumsum(pairs)]).astype(np.int32)
+                    first, last = np.zeros(batch * hkv, np.int32), np.zeros(batch * hkv, np.int32)
+                    as_int = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+                    shim.merge_waves(as_int(prefix), batch, hkv, 2, ctypes.c_longlong(nw), as_int(first), as_int(last))
+                    per = 4 if chain.value else 1
+                    partials = int((last // per - first // per).max()) + 1
+                    coarse = min(1024, max(1, total // 4))       # spans of four pairs
+                    before = -(-n * coarse // total) // (4 if can_chain else 1) + 2
+                    assert partials <= max(34, before), (label, partials, before)
+                    if not chain.value and can_chain:
+                        assert partials <= 18, label
+                    worst = max(worst, partials)
+    assert worst > 200 or can_chain
