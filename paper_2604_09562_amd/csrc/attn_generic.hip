@@ -18,7 +18,7 @@ namespace {
 typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 
-constexpr float kNoRef = -1.0e30f;   // softmax reference before any visible score
+constexpr float kNoRef = -3.4028234663852886e38f;   // softmax reference before any visible score: no finite score lies below it
 
 // Wavefronts per workgroup, as many as the registers of a compute unit hold (four on a SIMD at head_dim 64, two at 128).
 template <int D>

@@ -53,3 +53,25 @@ def test_non_finite_value_stays_with_the_rows_that_see_it():
     got, _ = run_gpu(inp)
     assert np.allclose(got[:2], clean[:2], rtol=0, atol=1e-6)
     assert np.all(np.isinf(got[2:, :, 7])) and np.all(np.isfinite(np.delete(got, 7, axis=2)))
+
+
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("sign", [-1.0, 1.0])
+@pytest.mark.parametrize("d,kv", [(64, "f32"), (128, "f32"), (64, "bf16")])
+def test_scores_of_the_whole_fp32_range(oracle, d, kv, sign, tree):
+    """Scores from +-1e32 to +-2e37, products to 1.6e38: the largest takes all of the weight, whatever its sign."""
+    lens, k = np.array([3, 40, 300, 1000], dtype=np.int32), np.array([2, 4, 6, 5], dtype=np.int32)
+    cfg = TINY.scaled(batch=4, num_q_heads=4, num_kv_heads=2, head_dim=d, kv_dtype=kv, q_dtype="f32")
+    inp = synth.make_attention_inputs(cfg, seed=3, kv_len=lens, depth=k, tree=tree)
+    rng = np.random.default_rng(5)
+    size = 10.0 ** rng.uniform(14.0, 19.0, inp["k_cache"].shape[:-1])
+    keys = np.zeros(inp["k_cache"].shape, np.float32)
+    keys[..., 5] = sign * size                      # one product per score: its rounding cannot reorder distinct scores
+    inp["k_cache"] = synth.store(keys, kv)
+    inp["q"] = np.zeros_like(inp["q"])
+    inp["q"][..., 5] = np.float32(1.6e19)
+    ref, ref_lse = oracle.verify_attn(inp)
+    got, lse = run_gpu(inp)
+    assert np.abs(ref_lse).min() > 1e32 and np.abs(ref_lse).max() > 9e35
+    assert np.all(np.abs(got - ref) <= 1e-6 * np.abs(ref) + 1e-6)
+    assert np.all(np.abs(lse - ref_lse) <= 1e-6 * np.abs(ref_lse))
