@@ -256,17 +256,29 @@ void launch_generic_kv(const AttnArgs &a, int row_blocks, hipStream_t stream)
 
 }  // namespace
 
-int32_t attn_generic_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
+int32_t attn_generic_launch(const AttnArgs &args, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
+    AttnArgs a = args;
     const int row_blocks = (a.max_q_len * (a.num_q_heads / a.num_kv_heads) + 15) / 16;
-    if ((unsigned long long)a.batch * a.num_kv_heads * row_blocks > 0x7fffffffull)
-        return fail(SS_ERR_UNSUPPORTED, "batch * kv heads * rows too large for one launch");
+    const long long per_request = (long long)a.num_kv_heads * row_blocks;   // workgroups
+    // A grid has fewer than 2^32 work items (beyond that the runtime drops workgroups without an error): a larger batch goes out
+    // in several launches over runs of requests.
+    constexpr long long kMaxGrid = 1 << 21;   // workgroups of up to 1024 work items
+    if (per_request > kMaxGrid) return fail(SS_ERR_UNSUPPORTED, "kv heads * rows too large for one launch");
+    const int run = (int)(kMaxGrid / per_request);
     if (ev0) SS_HIP_CHECK(hipEventRecord(ev0, stream), "hipEventRecord");
-    if (a.head_dim == 64)
-        launch_generic_kv<64>(a, row_blocks, stream);
-    else
-        launch_generic_kv<128>(a, row_blocks, stream);
-    SS_HIP_CHECK(hipGetLastError(), "launch attn_generic_kernel");
+    for (int first = 0; first < args.batch; first += run) {
+        a.batch = args.batch - first < run ? args.batch - first : run;
+        a.block_table = args.block_table + (int64_t)first * args.max_blocks;
+        a.kv_len = args.kv_len + first;
+        a.q_indptr = args.q_indptr + first;   // (rows are numbered over the whole batch)
+        if (a.head_dim == 64)
+            launch_generic_kv<64>(a, row_blocks, stream);
+        else
+            launch_generic_kv<128>(a, row_blocks, stream);
+        SS_HIP_CHECK(hipGetLastError(), "launch attn_generic_kernel");
+        if (args.batch - first <= run) break;
+    }
     if (ev1) SS_HIP_CHECK(hipEventRecord(ev1, stream), "hipEventRecord");
     return SS_OK;
 }

@@ -75,3 +75,24 @@ def test_scores_of_the_whole_fp32_range(oracle, d, kv, sign, tree):
     assert np.abs(ref_lse).min() > 1e32 and np.abs(ref_lse).max() > 9e35
     assert np.all(np.abs(got - ref) <= 1e-6 * np.abs(ref) + 1e-6)
     assert np.all(np.abs(lse - ref_lse) <= 1e-6 * np.abs(ref_lse))
+
+
+def test_more_units_than_a_grid_holds():
+    """70000 requests of one token over 64 heads: 4.48 million units, more than one workgroup each would fit a launch.  A row
+    that sees one token gives that token's value."""
+    B, H = 70000, 64
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+    blocks = 40
+    cache = [torch.randn((blocks, H, 16, 64), device="cuda:0", generator=gen).to(torch.bfloat16) for _ in range(2)]
+    table = torch.randint(0, blocks, (B, 1), device="cuda:0", generator=gen, dtype=torch.int32)
+    q = torch.randn((B, H, 64), device="cuda:0", generator=gen).to(torch.bfloat16)
+    d = dict(batch=B, num_q_heads=H, num_kv_heads=H, head_dim=64, block_size=16, num_blocks=blocks, max_blocks_per_seq=1,
+             total_rows=B, kv_dtype="bf16", q_dtype="bf16", kv_len=torch.ones(B, dtype=torch.int32, device="cuda:0"),
+             q_indptr=torch.arange(B + 1, dtype=torch.int32, device="cuda:0"), block_table=table,
+             k_cache=cache[0].view(torch.int16), v_cache=cache[1].view(torch.int16), k_scale=None, v_scale=None,
+             q=q.view(torch.int16), sm_scale=0.125)
+    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=1)
+    out.fill_(0x7fc0)
+    binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, cache[1][table[:, 0].long(), :, 0].view(torch.int16))
