@@ -579,11 +579,36 @@ size_t accept_workspace_bytes(int batch, int total_rows, int vocab)
     return n + 256;
 }
 
+// The first pass over the whole batch.  A grid has fewer than 2^32 work items (beyond that the runtime drops workgroups
+// without an error), and the bound of the rows, 41 per request if the caller gives none, counts for every request: a larger
+// batch goes out in several launches over runs of requests.
 template <int DT>
-static int32_t accept_launch_dt(const AcceptArgs &a, const Workspace &w, unsigned g1, hipStream_t stream)
+static int32_t rowstats_launch_dt(const AcceptArgs &args, const Workspace &w, hipStream_t stream)
 {
-    hipLaunchKernelGGL(accept_rowstats_kernel<DT>, dim3(g1), dim3(kThreads), 0, stream, a, w);
-    SS_HIP_CHECK(hipGetLastError(), "launch accept_rowstats_kernel");
+    constexpr long long kMaxGrid = 1 << 23;   // workgroups of 256 work items
+    const long long per_request = (long long)(args.greedy ? args.max_q_len : 2 * args.max_q_len - 1) * ((w.nchunks * kRowWaves + 3) / 4);
+    if (per_request > kMaxGrid) return fail(SS_ERR_UNSUPPORTED, "vocab too large for one launch");
+    const int run = (int)(kMaxGrid / per_request);
+    AcceptArgs a = args;
+    for (int first = 0; first < args.batch; first += run) {
+        a.batch = args.batch - first < run ? args.batch - first : run;
+        a.q_indptr = args.q_indptr + first;   // (target rows are numbered over the whole batch)
+        if (args.temperature) a.temperature = args.temperature + first;
+        // A request's draft rows start at its first target row less its number, which counts from `first` here.
+        if (args.draft) a.draft = static_cast<const char *>(args.draft) - first * args.row_stride * (DT == SS_BF16 ? 2 : 4);
+        a.total_rows = args.total_rows - first;
+        hipLaunchKernelGGL(accept_rowstats_kernel<DT>, dim3((unsigned)(a.batch * per_request)), dim3(kThreads), 0, stream, a, w);
+        SS_HIP_CHECK(hipGetLastError(), "launch accept_rowstats_kernel");
+        if (args.batch - first <= run) break;
+    }
+    return SS_OK;
+}
+
+template <int DT>
+static int32_t accept_launch_dt(const AcceptArgs &a, const Workspace &w, hipStream_t stream)
+{
+    const int32_t rc = rowstats_launch_dt<DT>(a, w, stream);
+    if (rc != SS_OK) return rc;
     hipLaunchKernelGGL(accept_decide_kernel, dim3(a.batch), dim3(kThreads), 0, stream, a, w);
     SS_HIP_CHECK(hipGetLastError(), "launch accept_decide_kernel");
     if (a.greedy) return SS_OK;
@@ -597,26 +622,17 @@ static int32_t accept_launch_dt(const AcceptArgs &a, const Workspace &w, unsigne
 int32_t accept_launch(const AcceptArgs &a, hipStream_t stream)
 {
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
-    const unsigned long long g1 =
-        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks * kRowWaves + 3) / 4);
-    if (g1 > 0x7fffffffull || (unsigned long long)a.batch * w.nsub > 0x7fffffffull)
+    if ((unsigned long long)a.batch * w.nsub > 0x7fffffffull)
         return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
-    if (a.logit_dtype == SS_BF16) return accept_launch_dt<SS_BF16>(a, w, (unsigned)g1, stream);
-    return accept_launch_dt<SS_F32>(a, w, (unsigned)g1, stream);
+    if (a.logit_dtype == SS_BF16) return accept_launch_dt<SS_BF16>(a, w, stream);
+    return accept_launch_dt<SS_F32>(a, w, stream);
 }
 
 int32_t accept_rowstats_launch(const AcceptArgs &a, hipStream_t stream)
 {
     const Workspace w = carve(a.workspace, a.batch, a.total_rows, a.vocab);
-    const unsigned long long g1 =
-        (unsigned long long)a.batch * (a.greedy ? a.max_q_len : 2 * a.max_q_len - 1) * ((w.nchunks * kRowWaves + 3) / 4);
-    if (g1 > 0x7fffffffull) return fail(SS_ERR_UNSUPPORTED, "batch * vocab too large for one launch");
-    if (a.logit_dtype == SS_BF16)
-        hipLaunchKernelGGL(accept_rowstats_kernel<SS_BF16>, dim3((unsigned)g1), dim3(kThreads), 0, stream, a, w);
-    else
-        hipLaunchKernelGGL(accept_rowstats_kernel<SS_F32>, dim3((unsigned)g1), dim3(kThreads), 0, stream, a, w);
-    SS_HIP_CHECK(hipGetLastError(), "launch accept_rowstats_kernel");
-    return SS_OK;
+    if (a.logit_dtype == SS_BF16) return rowstats_launch_dt<SS_BF16>(a, w, stream);
+    return rowstats_launch_dt<SS_F32>(a, w, stream);
 }
 
 }  // namespace ss

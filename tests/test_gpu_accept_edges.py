@@ -1,10 +1,12 @@
 """GPU parity of sampled acceptance at the edges of its arithmetic: temperatures so small that a row's distribution is its
-arg-maxima, logits that are NaN, uniforms that fall on a boundary of the distribution.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance
+arg-maxima, logits that are NaN, uniforms that fall on a boundary of the distribution, and batches
+beyond one grid.  Chain and tree walk against the CPU oracle; tokens equal, as in the other acceptance
 tests."""
 import numpy as np
 import pytest
+import torch
 
-from paper_2604_09562_amd import synth
+from paper_2604_09562_amd import binding, synth
 from tests.test_gpu_accept import compare as compare_chain, run_gpu as run_chain
 from tests.test_gpu_tree_sample import compare as compare_tree, run_gpu as run_tree
 
@@ -120,3 +122,41 @@ def test_rows_without_mass_give_the_arg_maximum(tree, dtype):
     inp["target_logits"][2, :3000] = inf[1]
     got = (run_tree if tree else run_chain)(inp)[1][:, 0]
     assert got.tolist() == [1234, 77, 0]
+
+
+def test_more_workgroups_than_a_grid_holds():
+    """210000 requests of an unknown row bound (41 rows each at most) and three chunks of vocabulary: 17.2 million workgroups of
+    the first pass, more than one launch takes.  The first and the last requests have drafts, whose rows are offset by the
+    requests in front of them; every row's mass sits on one token."""
+    B, V = 210000, 16392
+    dev = "cuda:0"
+    k = torch.zeros(B, dtype=torch.int64, device=dev)
+    k[:3], k[-300:] = 2, 1
+    q_indptr = torch.cat([torch.zeros(1, dtype=torch.int64, device=dev), torch.cumsum(k + 1, 0)])
+    R = int(q_indptr[-1])
+    Rd = R - B
+    gen = torch.Generator(device=dev).manual_seed(3)
+    hot = torch.randint(0, V, (R,), device=dev, generator=gen)
+    target = torch.zeros((R, V), dtype=torch.bfloat16, device=dev)
+    target.scatter_(1, hot[:, None], 60.0)
+    # draft i of request b is judged by its target row i: every second draft proposes that row's token, the others another one
+    owner = torch.repeat_interleave(torch.arange(B, device=dev), k)
+    index = torch.arange(Rd, device=dev) - (q_indptr[:-1] - torch.arange(B, device=dev))[owner]
+    judge = q_indptr[:-1][owner] + index
+    agree = torch.arange(Rd, device=dev) % 2 == 0
+    tokens = torch.where(agree, hot[judge], (hot[judge] + 1) % V)
+    draft = torch.zeros((Rd, V), dtype=torch.bfloat16, device=dev)
+    draft.scatter_(1, tokens[:, None], 60.0)
+    d = dict(batch=B, vocab=V, row_stride=V, logit_dtype="bf16", total_rows=R, q_indptr=q_indptr.to(torch.int32),
+             target_logits=target.view(torch.int16), draft_logits=draft.view(torch.int16), draft_tokens=tokens.to(torch.int32),
+             u_accept=torch.full((Rd,), 0.5, device=dev), u_sample=torch.rand(B, device=dev, generator=gen),
+             temperature=torch.ones(B, device=dev), greedy=0)
+    acc, toks, ratio, ws = binding.alloc_accept_outputs(d)
+    ws.fill_(0xFF)
+    binding.ss_spec_accept(d, acc, toks, ratio, ws)
+    torch.cuda.synchronize()
+    agree, k, first = agree.cpu().numpy(), k.cpu().numpy(), (q_indptr[:-1].cpu().numpy() - np.arange(B))
+    n = np.array([next((i for i in range(k[b]) if not agree[first[b] + i]), k[b]) for b in range(B)])
+    assert np.array_equal(acc.cpu().numpy(), n)
+    last = toks.cpu().numpy()[np.arange(B), n]
+    assert np.array_equal(last, hot.cpu().numpy()[q_indptr[:-1].cpu().numpy() + n])
