@@ -261,7 +261,7 @@ int32_t ss_spec_accept_tree_greedy(int32_t batch, int32_t vocab, int64_t row_str
  *   workspace   >= ss_spec_accept_tree_sample_workspace(...) bytes (it holds two fp64 vocabulary vectors
  *               per request besides the row statistics)
  *   max_q_len   also bounds the number of rejections a request can have, hence the number of rounds the
- *               call enqueues (a walk, block sums and a residual pass per round): a tight bound saves launches
+ *               call enqueues (block sums, whose kernel walks on first, and a residual pass per round): a tight bound saves launches
  * Children are judged from two gathered logits and the row statistics (fp32 chunk sums, relative error
  * below 1e-6, as in ss_spec_accept); residuals, their normalisers and the draw are fp64 with fixed reduction
  * orders.  Other arguments and errors as for ss_spec_accept.

@@ -8,8 +8,11 @@
 //                                                taken straight from the S^T accumulators
 // What bounds it: short calls are a chain of dependent reads (offsets, block table, keys, values) and the merge, so
 // many wavefronts per workgroup with the next block's tile in flight; long ones the fp32 matrix rate (D/2
-// instructions of 32 cycles per block and 16 rows).  4 requests of 64..512 tokens, 8 heads of 64, depth 4: 57 us
-// with one workgroup per (row, head) and one token per lane, 12 us (a pass among others, as the host enqueues it) with this one.
+// instructions of 32 cycles per block and 16 rows) where there are workgroups enough to fill the chip.  The cache of a
+// request is not split over workgroups: one request of 65536 tokens, 32 heads of 64 over 8, is 8 to 24 workgroups at depth
+// 0 to 8 and takes 0.67 ms at any of them (4.0 to 8.6 ms with one workgroup per (row, head) and one token per lane); its
+// bytes alone would take about 0.04 ms.  4 requests of 64..512 tokens, 8 heads of 64, depth 4: 57 us with that form, 12 us
+// (a pass among others, as the host enqueues it) with this one.
 #include "common.h"
 
 namespace ss {

@@ -13,14 +13,14 @@ namespace {
 // whose span starts inside it; (b, 0) / the last one publish the prefix and the partition count.
 //
 // Where the spans are cut.  A wave pays a fixed price for every unit it opens (query loads, a drained
-// tile pipeline, the partial of the unit before: about the time of kUnitWeight tiles), so equal tile
-// counts do not finish together: on a ragged batch the waves that cross ten short units were 10 % late.
+// ring of pairs, the partial of the unit before: about the time of kUnitWeight pairs, of kUnitWeightDeep with four or five row
+// blocks), so equal pair counts do not finish together: on a ragged batch the waves that cross ten short units were 10 % late.
 // The cuts are therefore equal in a weighted coordinate in which every unit is `unit_weight` virtual
 // pairs followed by its real ones; a cut that falls into a unit's virtual part becomes the unit's first
 // pair.  The cuts depend on the batch's lengths only, so results do not vary from run to run.
 // ---------------------------------------------------------------------------------------------
 static_assert(kSpansPerWg == kWavesPerWg, "one span per wavefront");
-constexpr int kPlanMaxBatch = 4096;   // requests whose tile prefix fits the plan kernel's LDS; beyond that the cuts are unweighted
+constexpr int kPlanMaxBatch = 4096;   // requests whose pair prefix fits the plan kernel's LDS; beyond that the cuts are unweighted
 
 // Inclusive scan over a wavefront's lanes (values >= 0, 0 is neutral for `op`) by data-parallel moves: a scan by shuffles is six
 // LDS round trips, 0.3 us of the plan's 5.
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     const int tid = threadIdx.x;
     const bool weighted = a.batch <= kPlanMaxBatch && a.unit_weight > 0;
 
-    // exclusive prefix of the tile counts of all requests (every workgroup builds its own copy), or,
+    // exclusive prefix of the pair counts of all requests (every workgroup builds its own copy), or,
     // for a batch too large for that, just the sums in front of and from request b on
     int pre = 0, longest = 0;   // (pairs of the longest unit)
     long long total = 0;
@@ -127,11 +127,11 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     const long long ya = off + (long long)weight * ((long long)b * a.num_kv_heads + g);
     const long long w_lo = cuts.first_cut_at_or_after(ya);                // first w with w*total_w/nw >= ya
     const long long w_hi = cuts.first_cut_at_or_after(ya + weight + n);   // first w at or past the unit's end
-    // Descriptor: {request, kv head, first tile, tiles of the unit, span begin, span end, kv_len,
+    // Descriptor: {request, kv head, first pair, pairs of the unit, span begin, span end, kv_len,
     // first query row, end query row, addresses of the span's first kDescPairs tile pairs}: everything
     // the wave's first loads depend on, so that they go out after a single read.
     for (long long w = w_lo + tid; w < w_hi && w < nw; w += 256) {
-        const int t0 = cuts.first_tile(cuts.cut(w), ya);
+        const int t0 = cuts.first_pair(cuts.cut(w), ya);
         const long long x0 = off + t0;
         const long long x1 = cuts.span_end(w);
         int32_t *d = a.wave_desc + w * kDescInts;

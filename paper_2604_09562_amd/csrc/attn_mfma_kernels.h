@@ -333,7 +333,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     };
 
     // A segment (the part of a unit that lies in this span) has ended: `starts` / `ends` say whether it holds
-    // the unit's first / last tile.
+    // the unit's first / last pair.
     auto end_unit = [&](bool starts, bool ends) __attribute__((always_inline)) {
         // The accumulators were last written by MFMAs in another basic block: give them the wait
         // states a read needs before anything below touches them.
@@ -805,9 +805,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     const int pre = a.pair_prefix[b];
     const int nb_tiles = a.pair_prefix[b + 1] - pre;
     const long long off = (long long)pre * a.num_kv_heads + (long long)g * nb_tiles;
-    // The spans were cut at w*total_w/nw in the weighted coordinate (every unit: `weight` virtual tiles, then
+    // The spans were cut at w*total_w/nw in the weighted coordinate (every unit: `weight` virtual pairs, then
     // its own); the last wave whose cut lies at or before coordinate t is ((t+1)*nw - 1) / total_w.  A cut
-    // inside the unit's virtual part starts at its first tile, so the unit's first wave is the last one at
+    // inside the unit's virtual part starts at its first pair, so the unit's first wave is the last one at
     // or before the end of that part, its last wave the last one before the next unit's stretch.
     SpanCuts cuts;
     cuts.prefix = a.pair_prefix;

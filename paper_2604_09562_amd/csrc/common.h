@@ -108,7 +108,7 @@ int32_t attn_generic_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev
 int attn_default_waves();
 
 // ---- accept --------------------------------------------------------------------------------
-constexpr int kChunk = 8192;  // vocabulary entries per workgroup in the streaming passes
+constexpr int kChunk = 8192;  // vocabulary entries per chunk of the row statistics (two chunks to a workgroup)
 
 struct AcceptArgs {
     int32_t batch, vocab, logit_dtype, total_rows, greedy;

@@ -1,10 +1,10 @@
-// Where the flat KV tile sequence is cut into the spans of the streaming attention kernel.
+// Where the flat sequence of KV tile pairs is cut into the spans of the streaming attention kernel.
 //
-// The tiles of all (request, KV head) units lie end to end, unit major: request b contributes hkv units of
-// n_b tiles each.  Spans are equal in a "weighted" coordinate in which every unit is preceded by `weight`
-// virtual tiles (what opening a unit costs a wavefront): unit u = b * hkv + g occupies the stretch
-// [ya, ya + weight + n_b), ya = (flat index of its first tile) + weight * u, and wave w starts at the cut
-// w * total_w / nw.  A cut inside a unit's virtual part starts the span at the unit's first tile.  The plan
+// The pairs of all (request, KV head) units lie end to end, unit major: request b contributes hkv units of
+// n_b pairs each.  Spans are equal in a "weighted" coordinate in which every unit is preceded by `weight`
+// virtual pairs (what opening a unit costs a wavefront): unit u = b * hkv + g occupies the stretch
+// [ya, ya + weight + n_b), ya = (flat index of its first pair) + weight * u, and wave w starts at the cut
+// w * total_w / nw.  A cut inside a unit's virtual part starts the span at the unit's first pair.  The plan
 // kernel (which writes the spans) and the merge kernel (which has to know which waves hold a part of a unit)
 // both use the functions below; plain integer code with no device dependency, so that a host test can check
 // them against each other over many shapes.
@@ -53,10 +53,10 @@ SS_HOST_DEVICE inline SpanCount count_spans(long long total, int longest, long l
 }
 
 struct SpanCuts {
-    const int32_t *prefix;   // [batch + 1] exclusive prefix of the tiles per KV head of the requests
+    const int32_t *prefix;   // [batch + 1] exclusive prefix of the pairs per KV head of the requests
     int batch, hkv, weight;
-    long long total;         // tiles of all units
-    long long total_w;       // tiles of all units plus `weight` per unit
+    long long total;         // pairs of all units
+    long long total_w;       // pairs of all units plus `weight` per unit
     long long nw;            // number of spans
 
     SS_HOST_DEVICE static SpanCuts make(const int32_t *prefix, int batch, int hkv, int weight, long long nw)
@@ -73,7 +73,7 @@ struct SpanCuts {
     }
     // weighted coordinate of wave w's cut
     SS_HOST_DEVICE long long cut(long long w) const { return w * total_w / nw; }
-    // flat index of unit (b, g)'s first tile, and the weighted coordinate where its stretch begins
+    // flat index of unit (b, g)'s first pair, and the weighted coordinate where its stretch begins
     SS_HOST_DEVICE long long unit_offset(int b, int g) const
     {
         return (long long)prefix[b] * hkv + (long long)g * (prefix[b + 1] - prefix[b]);
@@ -81,14 +81,14 @@ struct SpanCuts {
     SS_HOST_DEVICE long long unit_coord(int b, int g) const { return unit_offset(b, g) + (long long)weight * ((long long)b * hkv + g); }
     // the waves whose cut falls into the stretch [ya, ya + weight + n): w_lo <= w < w_hi (w_hi may exceed nw)
     SS_HOST_DEVICE long long first_cut_at_or_after(long long y) const { return (y * nw + total_w - 1) / total_w; }
-    // tile of the unit at which a span begins whose cut lies `ya <= cut < ya + weight + n`
-    SS_HOST_DEVICE int first_tile(long long cut_y, long long ya) const
+    // pair of the unit at which a span begins whose cut lies `ya <= cut < ya + weight + n`
+    SS_HOST_DEVICE int first_pair(long long cut_y, long long ya) const
     {
         const long long in_unit = cut_y - ya - weight;
         return in_unit > 0 ? (int)in_unit : 0;
     }
-    // unit and tile that weighted coordinate y (< total_w) falls on; returns the flat tile index
-    SS_HOST_DEVICE long long locate(long long y, int &b, int &g, int &tile) const
+    // unit and pair that weighted coordinate y (< total_w) falls on; returns the flat pair index
+    SS_HOST_DEVICE long long locate(long long y, int &b, int &g, int &pair) const
     {
         int lo = 0, hi = batch - 1;   // last request whose first unit starts at or before y
         while (lo < hi) {
@@ -103,10 +103,10 @@ struct SpanCuts {
         const long long r = y - ((long long)prefix[b] + (long long)weight * b) * hkv;
         g = (int)(r / (n + weight));
         const int in_unit = (int)(r - (long long)g * (n + weight)) - weight;
-        tile = in_unit > 0 ? in_unit : 0;
-        return (long long)prefix[b] * hkv + (long long)g * n + tile;
+        pair = in_unit > 0 ? in_unit : 0;
+        return (long long)prefix[b] * hkv + (long long)g * n + pair;
     }
-    // flat index one past wave w's last tile
+    // flat index one past wave w's last pair
     SS_HOST_DEVICE long long span_end(long long w) const
     {
         if (w + 1 >= nw) return total;
@@ -114,8 +114,8 @@ struct SpanCuts {
         int b, g, t;
         return locate(cut(w + 1), b, g, t);
     }
-    // The waves that hold tiles of a unit with n >= 1 tiles whose stretch begins at ya: the last wave whose cut
-    // lies at or before the unit's first tile ... the last wave whose cut lies at or before its last tile.
+    // The waves that hold pairs of a unit with n >= 1 pairs whose stretch begins at ya: the last wave whose cut
+    // lies at or before the unit's first pair ... the last wave whose cut lies at or before its last pair.
     SS_HOST_DEVICE void unit_waves(long long ya, int n, int &w_first, int &w_last) const
     {
         w_first = (int)(((ya + weight + 1) * nw - 1) / total_w);

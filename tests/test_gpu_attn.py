@@ -54,7 +54,7 @@ def test_config0_tiny_fp32(oracle):
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("hq,hkv", [(8, 8), (8, 4), (16, 4), (16, 2)])
 def test_small_shapes_all_groupings(oracle, path, kv_dtype, hq, hkv):
-    # several tiles, ragged tails, ragged depths; path 1 forces the fp32 vector kernel
+    # several tiles, ragged tails, ragged depths; path 1 forces the fp32 kernel
     cfg = LLAMA8B.scaled(batch=6, num_q_heads=hq, num_kv_heads=hkv, kv_dtype=kv_dtype,
                          ctx=("uniform", 9, 700), depth=("uniform", 0, 8))
     inp = synth.make_attention_inputs(cfg, seed=hq + hkv)

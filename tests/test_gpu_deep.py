@@ -19,7 +19,7 @@ TINY, LLAMA8B, RAGGED, LONG, FP8_70B = synth.CONFIGS
                          ids=["g1", "g2", "g4_one_pass", "g4_two_passes", "g8_three_passes", "g8_two_passes", "g8_vector"])
 def test_attention_up_to_depth_20(oracle, kv_dtype, hq, hkv, kmax, path):
     # path 2 demands the matrix-core kernel: up to 80 query rows per KV head in one pass, more in
-    # several passes over windows of query tokens; path 1 is the vector kernel
+    # several passes over windows of query tokens; path 1 is the fp32 kernel
     cfg = LLAMA8B.scaled(batch=7, num_q_heads=hq, num_kv_heads=hkv, kv_dtype=kv_dtype, ctx=("uniform", 30, 900))
     depth = np.array([kmax, 0, 9, 13, kmax, 8, 17][:7], np.int32)
     depth = np.minimum(depth, kmax)
