@@ -220,13 +220,14 @@ int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const 
     a.q_lo = 0;
     a.q_win = max_q_len;
     a.reuse_plan = (batch->flags & SS_BATCH_REUSE_PLAN) ? 1 : 0;
-    a.unit_weight = g_unit_weight == kUnitWeightAuto ? -1 : ((int32_t)g_unit_weight + 1) / 2;   // tiles -> pairs
+    a.auto_weight = g_unit_weight == kUnitWeightAuto;
+    a.unit_weight = ((int32_t)g_unit_weight + 1) / 2;   // tiles -> pairs
     // carve the workspace
     char *w = static_cast<char *>(workspace);
     a.plan = reinterpret_cast<AttnPlan *>(w);
     w += 256;
-    a.pair_prefix = reinterpret_cast<int32_t *>(w);
-    w += align_up(sizeof(int32_t) * ((size_t)batch->batch + 1), 256);
+    a.req = reinterpret_cast<AttnReq *>(w);
+    w += align_up(sizeof(AttnReq) * (size_t)batch->batch, 256);
     a.wave_desc = reinterpret_cast<int32_t *>(w);
     w += align_up(sizeof(int32_t) * kDescInts * (size_t)launch_waves, 256);
     a.pair_addr = reinterpret_cast<int2 *>(w);

@@ -5,18 +5,25 @@
 // Work decomposition.  The KV cache of one (request, KV head) pair ("unit") is a run of
 // 16-token tiles, one per cache block, taken two at a time ("pair").  All pairs of all units form one flat
 // sequence (unit major).  A plan kernel writes that sequence out as a flat list of tile addresses (physical
-// block * kv heads + kv head) and cuts it into `num_waves` contiguous spans of equal cost (a
-// pair costs one, opening a unit costs a fixed number of pairs); every wavefront streams one
-// span, so the load is balanced whatever the mix of context lengths, and the load side of the
+// block * kv heads + kv head) and cuts it into contiguous spans of equal cost (opening a unit costs as much as
+// some pairs), so the load is balanced whatever the mix of context lengths, and the load side of the
 // kernel is a plain linear walk that never stops at a unit boundary.  A span may cover the tail
-// of one unit, several whole units and the head of another; for every unit it touches the wave
-// has one partial result (softmax reference, sum, unnormalised output).  In the instances with
-// at most two row blocks, when the batch fills the chip or has units of many spans (count_spans), the four wavefronts of a
-// workgroup, whose spans are consecutive, hand the partials of a shared unit from right to left through LDS and combine them by their
-// log-sum-exp; a unit that lies inside one workgroup's spans is normalised, rounded and
-// written by that workgroup.  What is left (a unit that crosses workgroups; every split unit
-// in the other instances) goes to device memory as a partial in slot `workgroup + unit`
-// (`wave + unit` without the LDS hand-over; unique along the sequence either way), and a last
+// of one unit, several whole units and the head of another; for every unit it touches there is
+// one partial result (softmax reference, sum, unnormalised output).
+//
+// Units of one or two row blocks only: a span per wavefront.  When the batch fills the chip or has units of many spans (count_spans),
+// the four wavefronts of a workgroup, whose spans are consecutive, hand the partials of a shared unit from right to left through LDS and
+// combine them by their log-sum-exp; a unit that lies inside one workgroup's spans is normalised, rounded and written by that workgroup.
+//
+// Calls with units of three row blocks or more: a span per workgroup, whose wavefronts are a team and take its pairs in turn (every
+// fourth), so that they reach the end of a unit together and add their results block by block through LDS: one
+// partial per workgroup instead of four (with five row blocks a partial is 40 KB: 52 MB of them and as much read again by the merge
+// for 281 MB of keys and values, 32 requests of 256..4096 with trees of 8..16 nodes; the call 76.5 us with a span per wavefront,
+// 72 with teams).  The requests are laid out by row blocks, and each run of units is walked by the code for its own number
+// of them (see the plan kernel).
+//
+// What is left (a unit that crosses spans that are not combined) goes to device memory as a partial in slot
+// `workgroup + unit` (`wave + unit` without the LDS hand-over; unique along the sequence either way), and a last
 // kernel merges those partials in span order and writes the rounded output.
 //
 // Per pair, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
@@ -37,12 +44,12 @@
 //
 // Why the code is written to be small (one copy of a unit's beginning and end outside the ring, which is rotated in
 // registers instead): the instances took up to 150 KB of code with those inlined into every step of an unrolled ring and its
-// epilogue, more than the 64 KB instruction cache that two compute units share; now 14 to 28 KB.
+// epilogue, more than the 64 KB instruction cache that two compute units share; now 14 to 28 KB per number of row blocks.
 //
-// Measured (a whole call, before / after: single tiles, 16-token output products, query loads under a branch per row
-// block, one unit weight): 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 / 245 us; 32 requests of
-// 256..4096, trees of 8..16 nodes, 32 heads over 8: 98 / 75; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 / 107.2; four
-// requests of 40..600: 26.0 / 20.1.
+// Measured, a whole call: 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 us as single tiles with 16-token output
+// products, 247 as pairs, 221 in teams by classes; 32 requests of 256..4096, trees of 8..16 nodes, 32 heads over 8: 98 / 76.5 / 72;
+// 128 requests of 128..16384, depth 0..8, 32 heads over 8: 292 / 291 / 279; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 /
+// 107.2 / 107.7; four requests of 40..600: 26.0 / 20.1 / 20.1.
 #pragma once
 
 #include <type_traits>
@@ -70,10 +77,9 @@ constexpr float kNoMax = -1.0e30f;   // reference before any score was seen (fin
 constexpr int kMaxFlagPolls = 1 << 23;   // polls of a neighbour's deposit flag before giving up (each at least 128 cycles)
 constexpr int kPartRowStride = 33;   // float4 per staged partial row in LDS (32 of data + 1 of padding)
 template <int NB>
-constexpr bool kChainMerge = NB <= kChainRowBlocks;   // instances that combine the spans of a workgroup in LDS
+constexpr bool kTeam = NB > kChainRowBlocks;   // kernels whose workgroups share a span pair by pair
 template <int NB>
-constexpr bool kStageRows = NB <= 4;    // instances that write partials as whole rows through LDS (measured: with five
-                                        // row blocks the staging costs more than the scattered stores it replaces)
+constexpr bool kQueriesInLds = NB >= 4;        // for many row blocks the registers are needed for the accumulators
 
 // ---------------------------------------------------------------------------------------------
 // streaming kernel
@@ -183,67 +189,71 @@ __device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs
     }
 }
 
-// NB    16-row blocks of query rows the kernel is compiled for (covers max_q_len * G rows)
-// QLDS  keep the query operands in LDS (in operand order, one 1 KB line per row block and k-step)
-//       instead of registers: for many row blocks the registers are needed for the accumulators
-// TREE  the new tokens of a request form a draft tree: a row's visibility among them comes from its
-//       mask word instead of the chain's "tokens up to my own"
-template <int G, int NB, bool FP8, bool QLDS, bool TREE>
-__global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
-    AttnArgs a, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
-    const int32_t *__restrict__ pair_prefix,
-    const int32_t *__restrict__ kv_len, const int32_t *__restrict__ q_indptr, const float *__restrict__ k_scale,
-    const float *__restrict__ v_scale)
+// A workgroup's LDS.  BLOCKS: the most row blocks of the kernel.
+//   q    query operands, in operand order, one 1 KB line per row block and k-step of each wavefront (kQueriesInLds)
+//   o    one 16-row block of a partial per wavefront, rows 33 float4 apart (the odd stride spreads the rows over the banks); teams
+//        exchange blocks through it: two buffers, one barrier per block
+//   ml   references and sums of the rows
+//   dep  CHAIN: the deposits.  The wavefronts of a workgroup own consecutive spans, so a unit that runs on from one span into the next
+//        is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit slot, the left-hand one
+//        folds it into its own.  Only what crosses a workgroup's edge goes to memory as a partial; a unit that lies inside one
+//        workgroup is finished here.
+template <int BLOCKS, bool TEAM>
+struct StreamLds {
+    uint4 q[kQueriesInLds<BLOCKS> ? kWavesPerWg * BLOCKS * 4 * 64 : 1];
+    float4v o[(TEAM ? 2 : 1) * kWavesPerWg][16 * kPartRowStride];
+    float2 ml[kWavesPerWg][BLOCKS * 16];
+    float4v dep_o[TEAM ? 1 : kWavesPerWg][TEAM ? 1 : BLOCKS * 16 * kPartRowStride];
+    float2 dep_ml[TEAM ? 1 : kWavesPerWg][TEAM ? 1 : BLOCKS * 16];
+    int dep_flag[kWavesPerWg];   // 0 nothing yet; 1 deposited; 2 deposited and it reaches the unit's last tile
+};
+
+// Where a run (units of one class inside a span) starts, and what the wave's first loads need.
+struct Run {
+    int p, g, b, n;       // place in the layout, KV head, request, pairs of the unit
+    int unit_x;           // flat index of the unit's first pair
+    int x0, x1;           // the run, flat
+    int L, q0, q1;        // kv_len and query rows of the request
+    int2 addr[kDescPairs];   // of the wave's first pairs
+    bool chain;           // combine the spans of the workgroup (the plan's choice)
+};
+
+// NB      16-row blocks of query rows the code is compiled for
+// BLOCKS  those of the kernel
+// TREE    the new tokens of a request form a draft tree: a row's visibility among them comes from its
+//         mask word instead of the chain's "tokens up to my own"
+// TEAM    the run is the workgroup's: its wavefronts take the pairs in turn; else it is the wavefront's own
+template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool TEAM>
+__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> &lds, const Run &run, const int2 *__restrict__ pair_addr,
+                                     const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
+                                     const float *__restrict__ v_scale)
 {
-    // The metadata arrays come in as separate no-alias arguments so that their wave-uniform reads
-    // become scalar loads (own counter, no ordering against the vector KV loads).
-    __shared__ uint4 q_lds[QLDS ? kWavesPerWg * NB * 4 * 64 : 1];
-    // one 16-row block of a partial per wave, rows 33 float4 apart (the odd stride spreads the rows over the banks)
-    __shared__ float4v o_lds[kStageRows<NB> ? kWavesPerWg : 1][kStageRows<NB> ? 16 * kPartRowStride : 1];
-    __shared__ float2 ml_lds[kWavesPerWg][16];
-    // CHAIN (with the plan's consent): the wavefronts of a workgroup own consecutive spans, so a unit that runs on from
-    // one span into the next is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit
-    // slot, the left-hand one folds it into its own.  Only what crosses a workgroup's edge goes to memory as a
-    // partial; a unit that lies inside one workgroup is finished here.
-    // (Only for one or two row blocks: with three the deposit slots take 100 KB and the ragged workload, the one
-    // that uses them, ran 7 % slower; beyond that the queries live in LDS and there is no room.)
-    constexpr bool CHAIN = kChainMerge<NB>;
-    __shared__ float4v dep_o[CHAIN ? kWavesPerWg : 1][CHAIN ? NB * 16 * kPartRowStride : 1];
-    __shared__ float2 dep_ml[CHAIN ? kWavesPerWg : 1][CHAIN ? NB * 16 : 1];
-    __shared__ int dep_flag[kWavesPerWg];   // 0 nothing yet; 1 deposited; 2 deposited and it reaches the unit's last tile
+    constexpr bool QLDS = kQueriesInLds<NB>, CHAIN = !TEAM;
     const int lane = threadIdx.x & 63;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = blockIdx.x * kWavesPerWg + wslot;
     const int r16 = lane & 15, jq = lane >> 4;
-    uint4 *qs = q_lds + (QLDS ? wslot * NB * 4 * 64 : 0) + (QLDS ? lane : 0);
-
-    // where this wave's span starts: written by the plan kernel (waves past the partition count get x0 == x1)
-    int b, g, tile, nb_tiles;   // request, KV head, pair within the unit, pairs of the unit
-    long long x0, x1;
-    bool chain;                 // combine the spans of the workgroup (the plan's choice)
-    int meta_L, meta_q0, meta_q1, meta_nbt;   // kv_len / q_indptr / pair count of the next unit to open
-    int2 desc_addr[kDescPairs];
-    {
-        const int32_t *d = wave_desc + (long long)wave * kDescInts;
-        b = d[0]; g = d[1]; tile = d[2]; nb_tiles = d[3];
-        x0 = d[4]; x1 = d[5];
-        meta_L = d[6]; meta_q0 = d[7]; meta_q1 = d[8]; meta_nbt = nb_tiles;
-#pragma unroll
-        for (int j = 0; j < kDescPairs; ++j) desc_addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
-        chain = CHAIN && d[15] != 0;
-    }
-    if (lane == 0) dep_flag[wslot] = 0;
-    __syncthreads();   // the only barrier: every wave's flag is clear before any neighbour can look at it
-    if (x0 >= x1) return;
+    uint4 *qs = lds.q + (QLDS ? wslot * NB * 4 * 64 + lane : 0);
+    auto &o_lds = lds.o;
+    auto &ml_lds = lds.ml;
+    auto &dep_o = lds.dep_o;
+    auto &dep_ml = lds.dep_ml;
+    auto &dep_flag = lds.dep_flag;
+    int p = run.p, b = run.b, g = run.g, nb_tiles = run.n, unit_x = run.unit_x;
+    const int x0 = run.x0, x1 = run.x1;
+    const bool chain = CHAIN && run.chain;
+    int meta_b = b, meta_L = run.L, meta_q0 = run.q0, meta_q1 = run.q1, meta_nbt = nb_tiles;   // of the next unit to open
 
     // SINGLE: with many row blocks a step is longer than a read's latency, and one buffer that is refilled as soon as its
     // operands have been copied out keeps a pair in flight all the time, where two spill (32 requests of 256..4096, trees
     // of 8..16 nodes: 80 us a call with two buffers, 75 with one; with three row blocks both are level).
     constexpr bool SINGLE = NB >= 4;
     // ---- state of the unit being computed ----
-    int span_left = (int)(x1 - x0);   // pairs of the span not yet computed
-    int seg_left = 0;                 // of those, pairs that still belong to the current unit
-    int seg_tile0 = 0;                // the unit's pair the current segment began with
+    // A team takes the pairs of its span in turn: wavefront w every fourth from the w-th on, whatever units they belong to.
+    constexpr int STRIDE = TEAM ? kWavesPerWg : 1;
+    int pos = x0 + (TEAM ? wslot : 0);   // flat index of this wave's next pair
+    int seg_x0 = x0, seg_x1 = x0;     // the current segment (the part of the unit inside the span), flat
+    int seg_left = 0;                 // this wave's pairs of it that are left
     int L = 0, q0 = 0, q_len = 0, rows = 0, nbu = 0;   // nbu: 16-row blocks the unit really has (for its partial)
     bf16x8 qreg[QLDS ? 1 : NB][4];    // Q as B operand: lane holds row 16*nb + r16, 8 consecutive d per k-step
     int lim[TREE ? 1 : NB];           // chain: last visible cache position of this lane's row in block nb
@@ -256,6 +266,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     u32x4 qw[NB][4];   // a unit's queries on their way (between begin_unit_issue and begin_unit_wait)
     // (the metadata of the unit after the current one is fetched a unit ahead)
     auto begin_unit_issue = [&]() __attribute__((always_inline)) {
+        b = meta_b;
         L = meta_L;
         q0 = meta_q0;
         q_len = meta_q1 - meta_q0;
@@ -265,16 +276,18 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         nbu = (rows + 15) >> 4;
         ctx = L - q_len;
         {
-            const int nb_ = (g + 1 == a.num_kv_heads) ? b + 1 : b;   // request of the next unit
-            if (nb_ != b && nb_ < a.batch) {
-                meta_L = kv_len[nb_];
-                meta_q0 = q_indptr[nb_];
-                meta_q1 = q_indptr[nb_ + 1];
-                meta_nbt = pair_prefix[nb_ + 1] - pair_prefix[nb_];
+            const int np = (g + 1 == a.num_kv_heads) ? p + 1 : p;   // place of the next unit's request
+            if (np != p && np < a.batch) {
+                const AttnReq r = req[np];
+                meta_b = r.b;
+                meta_L = r.L;
+                meta_q0 = r.q0;
+                meta_q1 = r.q1;
+                meta_nbt = r.n;
             }
         }
-        seg_left = nb_tiles - tile < span_left ? nb_tiles - tile : span_left;
-        seg_tile0 = tile;
+        seg_x1 = unit_x + nb_tiles < x1 ? unit_x + nb_tiles : x1;
+        seg_left = pos < seg_x1 ? (seg_x1 - pos + STRIDE - 1) / STRIDE : 0;
         // All query loads go out before any of them is waited for: buffer loads over the request's rows, whose
         // offset is out of range (zeros) for a row the unit does not have, so there is no branch between them.  (Under a branch
         // per block the LDS instances waited for every block's loads in turn, 7 us at the start of a span.)
@@ -332,6 +345,100 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         }
     };
 
+    // Output row of the unit's row nn, and four of a finished row's values: normalised, rounded to bf16 (nearest even), 256 bytes
+    // per half-wavefront.
+    auto row_of = [&](int nn) __attribute__((always_inline)) {
+        return (long long)(q0 + a.q_lo + nn / G) * a.num_q_heads + g * G + nn % G;
+    };
+    auto write_row = [&](long long orow, float4v v, float inv) __attribute__((always_inline)) {
+        const float2v lo2 = {v[0] * inv, v[1] * inv}, hi2 = {v[2] * inv, v[3] * inv};
+        uint2 pk;
+        pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, bf16x2));
+        pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, bf16x2));
+        *reinterpret_cast<uint2 *>(static_cast<__bf16 *>(a.out) + orow * D + (lane & 31) * 4) = pk;
+    };
+
+    // The end of a team's segment: the four wavefronts' results are brought to a common reference and added, block by block
+    // through LDS, each wavefront adding (in a fixed order) and writing four of a block's sixteen rows: as finished output if the
+    // segment is the `whole` unit, else as one partial of the workgroup.  The barriers wait for LDS only, not for the pairs in
+    // flight.  Two block buffers: a wavefront that writes block nb + 2 has passed the barrier of block nb + 1, which the others
+    // reach after reading block nb.
+    auto team_barrier = []() __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto end_team = [&](bool whole, const float (&lsum)[NB]) __attribute__((always_inline)) {
+        if (nbu == 0) return;   // (a request without rows in this window)
+        if (jq == 0) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) ml_lds[wslot][nb * 16 + r16] = make_float2(m_run[nb], lsum[nb]);
+        }
+        team_barrier();
+        float m_all[NB], l_all[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            float2 ml[kWavesPerWg];
+#pragma unroll
+            for (int w = 0; w < kWavesPerWg; ++w) ml[w] = ml_lds[w][nb * 16 + r16];
+            m_all[nb] = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+            l_all[nb] = 0.f;
+#pragma unroll
+            for (int w = 0; w < kWavesPerWg; ++w) l_all[nb] += ml[w].y * __builtin_amdgcn_exp2f(ml[w].x - m_all[nb]);
+        }
+        auto deposit = [&](int nb) __attribute__((always_inline)) {
+            const float mine = __builtin_amdgcn_exp2f(m_run[nb] - m_all[nb]);   // (0 for a wave without a pair of this segment)
+            float4v *ol = o_lds[(TEAM ? nb & 1 : 0) * kWavesPerWg + wslot];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {   // accumulator row 4*jq+e of M-block mb is d = 8*(4*jq+e) + mb
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float4v x;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[c] = from_accumulator_file(acc[4 * h + c][nb][e]) * mine;
+                    ol[r16 * kPartRowStride + jq * 8 + e * 2 + h] = x;
+                }
+            }
+        };
+        const long long slot = (long long)blockIdx.x + (long long)p * a.num_kv_heads + g;
+        float *po = a.part_o + slot * a.rows_pad * D;
+        float2 *pml = reinterpret_cast<float2 *>(a.part_ml) + slot * a.rows_pad;
+        deposit(0);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            if (nb < nbu) {
+                team_barrier();
+                float4v v[2][kWavesPerWg];
+#pragma unroll
+                for (int it = 0; it < 2; ++it)
+#pragma unroll
+                    for (int w = 0; w < kWavesPerWg; ++w)
+                        v[it][w] = o_lds[(TEAM ? nb & 1 : 0) * kWavesPerWg + w][(wslot * 4 + it * 2 + (lane >> 5)) * kPartRowStride + (lane & 31)];
+                if (nb + 1 < NB) deposit(nb + 1 < NB ? nb + 1 : 0);   // (under the latency of the reads)
+                const bool mine = jq == 0 && (r16 >> 2) == wslot && nb * 16 + r16 < rows;   // lanes that hold (m, l) of the rows written here
+                float inv = 1.f;
+                if (whole) {
+                    inv = 1.f / l_all[nb];
+                    if (mine && a.lse) a.lse[row_of(nb * 16 + r16)] = (m_all[nb] + log2f(l_all[nb])) * kLn2;
+                } else if (mine) {
+                    pml[nb * 16 + r16] = make_float2(m_all[nb], l_all[nb]);
+                }
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const int row = wslot * 4 + it * 2 + (lane >> 5), nn = nb * 16 + row;
+                    const float4v sum = ((v[it][0] + v[it][1]) + v[it][2]) + v[it][3];
+                    if (whole) {
+                        const float iv = __shfl(inv, row);
+                        if (nn < rows) write_row(row_of(nn), sum, iv);
+                    } else if (nn < rows) {
+                        *reinterpret_cast<float4v *>(po + nn * D + (lane & 31) * 4) = sum;
+                    }
+                }
+            }
+        }
+    };
+
     // A segment (the part of a unit that lies in this span) has ended: `starts` / `ends` say whether it holds
     // the unit's first / last pair.
     auto end_unit = [&](bool starts, bool ends) __attribute__((always_inline)) {
@@ -346,6 +453,10 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             l += __shfl_xor(l, 16);
             l += __shfl_xor(l, 32);
             lsum[nb] = l;
+        }
+        if constexpr (TEAM) {
+            end_team(starts && ends, lsum);
+            return;
         }
         bool to_end = ends;   // does the result held here reach the unit's last tile?
         if constexpr (CHAIN) {
@@ -421,13 +532,13 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         // What is held here goes to memory: as the finished output if it covers the whole unit, else as a
         // partial in slot (workgroup, or wave without the hand-over) + unit, unique along the pair sequence.
         const bool whole = CHAIN && starts && to_end;
-        const long long slot = (long long)(chain ? (int)blockIdx.x : wave) + (long long)b * a.num_kv_heads + g;
+        const long long slot = (long long)(chain ? (int)blockIdx.x : wave) + (long long)p * a.num_kv_heads + g;
         float *po = a.part_o + slot * a.rows_pad * D;
         float *pml = a.part_ml + slot * a.rows_pad * 2;
         // A lane holds 32 consecutive d of one row (d = 32*jq + 8*e + mb), in registers that are 16 bytes
         // apart in memory: written directly, every store would scatter 16-byte pieces over 64 cache lines.
-        // The block goes through LDS instead and leaves as whole rows, two per store (kStageRows).
-        float4v *ol = o_lds[kStageRows<NB> ? wslot : 0];
+        // The block goes through LDS instead and leaves as whole rows, two per store.
+        float4v *ol = o_lds[wslot];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             if (nb < nbu) {
@@ -437,19 +548,6 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 } else if (n < rows && jq == 0) {
                     pml[n * 2 + 0] = m_run[nb];
                     pml[n * 2 + 1] = lsum[nb];
-                }
-                if constexpr (!kStageRows<NB>) {
-                    if (n < rows) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {   // accumulator row 4*jq+e of M-block mb is d = 8*(4*jq+e) + mb
-                            float *dst = po + n * D + (jq * 4 + e) * 8;
-                            const float4v lo = {acc[0][nb][e], acc[1][nb][e], acc[2][nb][e], acc[3][nb][e]};
-                            const float4v hi = {acc[4][nb][e], acc[5][nb][e], acc[6][nb][e], acc[7][nb][e]};
-                            *reinterpret_cast<float4v *>(dst) = lo;
-                            *reinterpret_cast<float4v *>(dst + 4) = hi;
-                        }
-                    }
-                    continue;
                 }
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -475,18 +573,10 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                     const int row = it * 2 + (lane >> 5), nn = nb * 16 + row;
                     const float4v v = rowv[it];
                     if (whole) {
-                        // normalise, round to bf16 (nearest even), 256-byte output rows; lse from the row's (m, l)
                         const float2 ml = rowml[it];
-                        const float inv = 1.f / ml.y;
-                        const int qi = a.q_lo + nn / G, hh = nn % G;
-                        const long long orow = (long long)(q0 + qi) * a.num_q_heads + g * G + hh;
-                        const float2v lo2 = {v[0] * inv, v[1] * inv}, hi2 = {v[2] * inv, v[3] * inv};
-                        uint2 pk;
-                        pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, bf16x2));
-                        pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, bf16x2));
                         if (nn < rows) {
-                            *reinterpret_cast<uint2 *>(static_cast<__bf16 *>(a.out) + orow * D + (lane & 31) * 4) = pk;
-                            if (a.lse && (lane & 31) == 0) a.lse[orow] = (ml.x + log2f(ml.y)) * kLn2;
+                            write_row(row_of(nn), v, 1.f / ml.y);
+                            if (a.lse && (lane & 31) == 0) a.lse[row_of(nn)] = (ml.x + log2f(ml.y)) * kLn2;
                         }
                     } else if (nn < rows) {
                         *reinterpret_cast<float4v *>(po + nn * D + (lane & 31) * 4) = v;
@@ -496,22 +586,23 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             }
         }
     };
-    // (b, g) <- the unit after it (its metadata is already in meta_*)
+    // (p, g) <- the unit after it (its metadata is already in meta_*)
     auto next_unit = [&]() __attribute__((always_inline)) {
-        tile = 0;
+        unit_x += nb_tiles;
+        seg_x0 = unit_x;
         if (++g == a.num_kv_heads) {
             g = 0;
-            ++b;
+            ++p;
         }
     };
 
     // ---- load side: a linear walk over the span's pairs, the address of the next one read a step ahead ----
-    long long next_x = x0;            // next pair to load
-    int2 next_addr = desc_addr[0];    // its addresses
+    int next_x = pos;                 // next pair to load
+    int2 next_addr = run.addr[0];    // its addresses
     auto load_pair = [&](PairRegs<FP8> &t, int2 addr) __attribute__((always_inline)) {
         const bool live = next_x < x1;
         load_pair_tiles<FP8>(t, a, k_scale, v_scale, addr, live, lane);
-        ++next_x;
+        next_x += STRIDE;
     };
     auto issue = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
         const int2 addr = next_addr;
@@ -691,15 +782,17 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new = fmaxf(m_run[nb], mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
-            l_run[nb] *= alpha;
+            if (__any(m_run[nb] > kNoMax)) {   // (before a unit's first pair there is nothing to rescale)
+                const float alpha = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
+                l_run[nb] *= alpha;
 #pragma unroll
-            for (int mb = 0; mb < 8; ++mb) {
-                const float4v c = acc[mb][nb];
-                float4v r = {from_accumulator_file(c[0]) * alpha, from_accumulator_file(c[1]) * alpha,
-                             from_accumulator_file(c[2]) * alpha, from_accumulator_file(c[3]) * alpha};
-                to_accumulator_file(r);
-                acc[mb][nb] = r;
+                for (int mb = 0; mb < 8; ++mb) {
+                    const float4v c = acc[mb][nb];
+                    float4v r = {from_accumulator_file(c[0]) * alpha, from_accumulator_file(c[1]) * alpha,
+                                 from_accumulator_file(c[2]) * alpha, from_accumulator_file(c[3]) * alpha};
+                    to_accumulator_file(r);
+                    acc[mb][nb] = r;
+                }
             }
             m_run[nb] = m_new;
 #pragma unroll
@@ -742,7 +835,8 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             if (__any(top > kSlack)) {
                 accumulator_read_guard();
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) rescale(nb, s[nb], pd[nb]);
+                for (int nb = 0; nb < NB; ++nb)
+                    if (__any(top8(pd[nb]) > kSlack)) rescale(nb, s[nb], pd[nb]);
             }
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) output(nb, pd[nb]);
@@ -752,36 +846,103 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     // ---- the walk: a ring of two pairs in registers ----
     begin_unit_issue();   // queries of the first unit go out before any KV tile
     PairRegs<FP8> buf[SINGLE ? 1 : 2];
-    load_pair(buf[0], desc_addr[0]);   // the first pairs' addresses come with the descriptor
-    if constexpr (!SINGLE) load_pair(buf[1], desc_addr[1]);
-    next_addr = desc_addr[SINGLE ? 1 : 2];
+    load_pair(buf[0], run.addr[0]);   // the first pairs' addresses come with the descriptor
+    if constexpr (!SINGLE) load_pair(buf[1], run.addr[1]);
+    next_addr = run.addr[SINGLE ? 1 : 2];
     begin_unit_wait();
     for (;;) {
+        int tile = pos - unit_x;
         if constexpr (SINGLE) {
-            for (; seg_left > 0; --seg_left) compute(buf[0], tile++, std::true_type{});
+            for (; seg_left > 0; --seg_left) {
+                compute(buf[0], tile, std::true_type{});
+                tile += STRIDE;
+            }
         } else {
             // A segment of odd length begins with a step of its own, so that the loop takes both buffers in turn with one way
             // out: with an exit after either buffer the compiler either sees a path on which the first buffer's loads are the
             // newest, and drains the whole ring at the top, or spills.
             if (seg_left & 1) {
                 compute(buf[0], tile, std::false_type{});
-                ++tile;
+                tile += STRIDE;
                 --seg_left;
                 buf[0] = buf[SINGLE ? 0 : 1];
                 issue(buf[SINGLE ? 0 : 1]);
             }
             for (; seg_left > 0; seg_left -= 2) {
                 compute(buf[0], tile, std::true_type{});
-                compute(buf[SINGLE ? 0 : 1], tile + 1, std::true_type{});
-                tile += 2;
+                compute(buf[SINGLE ? 0 : 1], tile + STRIDE, std::true_type{});
+                tile += 2 * STRIDE;
             }
         }
-        span_left -= tile - seg_tile0;
-        end_unit(seg_tile0 == 0, tile == nb_tiles);
-        if (span_left <= 0) break;
+        pos = unit_x + tile;
+        end_unit(seg_x0 == unit_x, seg_x1 == unit_x + nb_tiles);
+        if (seg_x1 >= x1) break;
         next_unit();
         begin_unit_issue();
         begin_unit_wait();
+    }
+}
+
+// BLOCKS  the most 16-row blocks of query rows a unit can have
+template <int G, int BLOCKS, bool FP8, bool TREE>
+__global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
+    AttnArgs a, const AttnPlan *__restrict__ plan, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
+    const AttnReq *__restrict__ req, const float *__restrict__ k_scale, const float *__restrict__ v_scale)
+{
+    // The metadata arrays come in as separate no-alias arguments so that their wave-uniform reads
+    // become scalar loads (own counter, no ordering against the vector KV loads).
+    constexpr bool TEAM = kTeam<BLOCKS>;
+    __shared__ StreamLds<BLOCKS, TEAM> lds;
+    const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // where this wave's span starts: written by the plan kernel (waves past the partition count get x0 == x1)
+    const int32_t *d = wave_desc + (long long)(blockIdx.x * kWavesPerWg + wslot) * kDescInts;
+    Run run;
+    run.p = d[0]; run.g = d[1]; run.b = d[16]; run.n = d[17];
+    run.x0 = d[4]; run.x1 = d[5];
+    run.unit_x = run.x0 - d[2];
+    run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
+#pragma unroll
+    for (int j = 0; j < kDescPairs; ++j) run.addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
+    run.chain = d[15] != 0;
+    if constexpr (!TEAM) {
+        if ((threadIdx.x & 63) == 0) lds.dep_flag[wslot] = 0;
+        __syncthreads();   // every wave's flag is clear before any neighbour can look at it
+        if (run.x0 >= run.x1) return;
+        walk<G, BLOCKS, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+    } else {
+        // The span of the workgroup, class by class: units of k row blocks are walked by the code for k.
+        if (run.x0 >= run.x1) return;
+        const int end = run.x1;
+        for (int c = d[3];;) {
+            const int class_end = plan->class_x[c];
+            run.x1 = class_end < end ? class_end : end;
+            if (run.x0 < run.x1) {
+                const int blocks = BLOCKS - c;
+                if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                else {
+                    if constexpr (BLOCKS >= 5) {
+                        if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                        else walk<G, 4, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                    }
+                }
+            }
+            if (run.x1 >= end) break;
+            // the next class begins with its first request
+            const int place = plan->class_req[c];
+            ++c;
+            if (place >= a.batch) break;
+            const AttnReq r = req[place];
+            run.p = place; run.g = 0; run.b = r.b; run.n = r.n;
+            run.x0 = run.unit_x = run.x1;
+            run.L = r.L; run.q0 = r.q0; run.q1 = r.q1;
+#pragma unroll
+            for (int j = 0; j < kDescPairs; ++j) {
+                const int x = run.x0 + wslot + j * kWavesPerWg;
+                run.addr[j] = pair_addr[x < end ? x : end - 1];
+            }
+        }
     }
 }
 
@@ -795,39 +956,27 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 {
     const int slabs = a.rows_pad / kMergeRows;
     const int unit = blockIdx.x / slabs, slab = blockIdx.x % slabs;
-    const int b = unit / a.num_kv_heads, g = unit % a.num_kv_heads;
-    const int q0 = a.q_indptr[b];
-    const int rows = window_q_len(a.q_indptr[b + 1] - q0, a.q_lo, a.q_win) * G;   // rows of this pass's window
+    const int g = unit % a.num_kv_heads;
+    const AttnReq r = a.req[unit / a.num_kv_heads];
+    const int q0 = r.q0;
+    const int rows = window_q_len(r.q1 - q0, a.q_lo, a.q_win) * G;   // rows of this pass's window
     const int n = slab * kMergeRows + (threadIdx.x >> 5), d4 = threadIdx.x & 31;
     if (n >= rows) return;
-    const long long total = a.plan->total_pairs;
-    const long long nw = a.plan->num_waves;
-    const int pre = a.pair_prefix[b];
-    const int nb_tiles = a.pair_prefix[b + 1] - pre;
-    const long long off = (long long)pre * a.num_kv_heads + (long long)g * nb_tiles;
-    // The spans were cut at w*total_w/nw in the weighted coordinate (every unit: `weight` virtual pairs, then
-    // its own); the last wave whose cut lies at or before coordinate t is ((t+1)*nw - 1) / total_w.  A cut
-    // inside the unit's virtual part starts at its first pair, so the unit's first wave is the last one at
-    // or before the end of that part, its last wave the last one before the next unit's stretch.
+    // The spans were cut at w*total_cost/cuts in the weighted coordinate (every unit: what opening it costs, then its
+    // pairs); the last wave whose cut lies at or before coordinate t is ((t+1)*cuts - 1) / total_cost.  A cut
+    // inside the opening's part starts at the unit's first pair, so the unit's first wave is the last one at
+    // or before the end of that part and the first pair, its last wave the last one before the next unit's stretch.
+    const int cost = a.plan->class_cost[r.cls], weight = a.plan->class_weight[r.cls];
     SpanCuts cuts;
-    cuts.prefix = a.pair_prefix;
-    cuts.batch = a.batch;
-    cuts.hkv = a.num_kv_heads;
-    cuts.weight = a.plan->unit_weight;
-    cuts.total = total;
-    cuts.total_w = total + (long long)cuts.weight * a.batch * a.num_kv_heads;
-    cuts.nw = nw;
+    cuts.total_w = a.plan->total_cost;
+    cuts.nw = a.plan->cuts;
     int w_first, w_last;
-    cuts.unit_waves(off + (long long)cuts.weight * unit, nb_tiles, w_first, w_last);
-    if (a.chain && !a.plan->chain) {   // one partial per wavefront, but a unit that one held alone is finished
-        if (w_first == w_last) return;
-    } else if (a.chain) {
-        // the streaming kernel has combined the spans of each workgroup: one partial per workgroup the unit
-        // touches, and a unit inside a single workgroup is already finished
+    cuts.unit_waves((long long)r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
+    if (a.plan->chain) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
         w_first /= kWavesPerWg;
         w_last /= kWavesPerWg;
-        if (w_first == w_last) return;
     }
+    if (w_first == w_last) return;   // the unit lies in one span (of a wavefront, of a workgroup): finished there
 
     // running merge: (m, l, o) <- (m, l, o) (+) partial, both relative to their own reference m
     float m_all = kNoMax, l_all = 0.f;
@@ -854,48 +1003,43 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     if (a.lse && d4 == 0) a.lse[orow] = (m_all + log2f(l_all)) * kLn2;
 }
 
-template <int G, int NB, bool FP8, bool TREE>
+template <int G, int BLOCKS, bool FP8, bool TREE>
 int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
     // One wavefront per SIMD (the whole register file; a ring of two pairs, three or four spill in most instances and
     // were slower where they just fit): two waves on a SIMD
     // do not share the memory pipeline fairly under saturation (the older one wins), which turns
     // into a long tail.
-    constexpr bool QLDS = NB >= 4;
-    AttnArgs b = a;   // (the plan kernel has been enqueued by the caller)
-    b.chain = kChainMerge<NB> ? 1 : 0;
     // When a profile is being taken the two events are attached to the dispatch itself, so that
     // their difference is the kernel's own duration on this stream (what a kernel trace shows).
-    hipExtLaunchKernelGGL((attn_stream_kernel<G, NB, FP8, QLDS, TREE>), dim3((unsigned)(b.launch_waves / kWavesPerWg)),
-                          dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, b, b.pair_addr, b.wave_desc, b.pair_prefix,
-                          b.kv_len, b.q_indptr, b.k_scale, b.v_scale);
+    hipExtLaunchKernelGGL((attn_stream_kernel<G, BLOCKS, FP8, TREE>), dim3((unsigned)(a.launch_waves / kWavesPerWg)),
+                          dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, a, a.plan, a.pair_addr, a.wave_desc, a.req, a.k_scale,
+                          a.v_scale);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_stream_kernel");
     hipLaunchKernelGGL(attn_merge_kernel<G>, dim3((unsigned)a.batch * a.num_kv_heads * (a.rows_pad / kMergeRows)), dim3(256),
-                       0, stream, b);
+                       0, stream, a);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_merge_kernel");
     return SS_OK;
 }
 
-template <int G, int NB>
+template <int G, int BLOCKS>
 int32_t launch_nb(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
     if (a.tree_mask) {
-        if (a.kv_dtype == SS_FP8_E4M3) return launch_stream<G, NB, true, true>(a, stream, ev0, ev1);
-        return launch_stream<G, NB, false, true>(a, stream, ev0, ev1);
+        if (a.kv_dtype == SS_FP8_E4M3) return launch_stream<G, BLOCKS, true, true>(a, stream, ev0, ev1);
+        return launch_stream<G, BLOCKS, false, true>(a, stream, ev0, ev1);
     }
-    if (a.kv_dtype == SS_FP8_E4M3) return launch_stream<G, NB, true, false>(a, stream, ev0, ev1);
-    return launch_stream<G, NB, false, false>(a, stream, ev0, ev1);
+    if (a.kv_dtype == SS_FP8_E4M3) return launch_stream<G, BLOCKS, true, false>(a, stream, ev0, ev1);
+    return launch_stream<G, BLOCKS, false, false>(a, stream, ev0, ev1);
 }
 
 template <int G>
 int32_t launch_for_group(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)
 {
-    constexpr int NBMAX = (SS_OUT_WIDTH * G + 15) / 16 < kMaxRowBlocks ? (SS_OUT_WIDTH * G + 15) / 16 : kMaxRowBlocks;
     const int nb = (a.q_win * G + 15) / 16;   // row blocks of one pass's window
-    if constexpr (NBMAX >= 5) if (nb == 5) return launch_nb<G, 5>(a, stream, ev0, ev1);
-    if constexpr (NBMAX >= 4) if (nb == 4) return launch_nb<G, 4>(a, stream, ev0, ev1);
-    if constexpr (NBMAX >= 3) if (nb == 3) return launch_nb<G, 3>(a, stream, ev0, ev1);
-    if constexpr (NBMAX >= 2) if (nb == 2) return launch_nb<G, 2>(a, stream, ev0, ev1);
+    if constexpr (attn_team_blocks(G) > kChainRowBlocks)
+        if (nb > kChainRowBlocks) return launch_nb<G, attn_team_blocks(G)>(a, stream, ev0, ev1);
+    if (nb == 2) return launch_nb<G, 2>(a, stream, ev0, ev1);
     return launch_nb<G, 1>(a, stream, ev0, ev1);
 }
 

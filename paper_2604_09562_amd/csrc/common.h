@@ -6,6 +6,7 @@
 #include <stddef.h>
 
 #include "specverify.h"
+#include "span_cuts.h"
 
 namespace ss {
 
@@ -25,14 +26,13 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
 constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
 constexpr int kWavesPerWg = 4;
-constexpr int kDescInts = 16;            // ints per wave descriptor
+constexpr int kDescInts = 32;            // ints per wave descriptor (18 in use)
 constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
 constexpr int kChainRowBlocks = 2;       // up to here the spans of a workgroup can be combined in LDS
 constexpr int kMaxRowBlocks = 5;         // 16-row blocks of query rows one wavefront can keep accumulators for
-// What opening a unit costs a wavefront, in pairs, for the span cuts.  With up to three row blocks 2 (1 to 3 are level);
-// with four or five the query rows go through LDS and a unit's partial is 32 or 40 KB: 6 to 10 are level (96 requests of
-// 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 260 us a call at 2, 243 at 8; 128 requests of 64..1024: 87 and 80).
+// What opening a unit is taken to cost a wavefront, in pairs, for the span cuts: with one or two row blocks 2 (1 to 3 are level).
+// The team kernels have costs of their own by row blocks (attn_mfma.hip); the plan's record still names 8 for four and five.
 constexpr int kUnitWeight = 2, kUnitWeightDeep = 8;
 
 // Query tokens of a request that fall into the pass's window, and the tile pairs its units stream in this
@@ -59,8 +59,24 @@ __host__ __device__ inline int window_pairs(int kv_len, int q_len, int q_lo)
 struct AttnPlan {
     int32_t total_pairs;   // sum over requests of ceil(kv_len/32) * num_kv_heads
     int32_t num_waves;     // partitions actually used (<= launched wavefronts)
-    int32_t unit_weight;   // virtual pairs per unit in the coordinate the spans were cut in (0: plain pair counts)
+    int32_t unit_weight;   // what opening a unit costs a wavefront, in pairs (0: spans of equal pair counts)
     int32_t chain;         // the spans of a workgroup are combined in LDS (instances that can)
+    int32_t cuts;          // spans that were cut: num_waves, or a quarter of that where a workgroup shares a span
+    int32_t pad;
+    int64_t total_cost;                  // the end of the coordinate they were cut in
+    int32_t class_req[kMaxClasses];      // requests, in layout order, before the end of each class
+    int32_t class_x[kMaxClasses];        // pairs of the flat sequence before the end of each class
+    int32_t class_cost[kMaxClasses], class_weight[kMaxClasses];
+};
+static_assert(kMaxClasses >= kMaxRowBlocks, "a class per number of row blocks");
+static_assert(sizeof(AttnPlan) <= 256, "the plan record's place in the workspace");
+// One per request, in the order in which the flat sequence holds them.
+struct AttnReq {
+    int32_t b;             // the request
+    int32_t L, q0, q1;     // its kv_len, its query rows
+    int32_t n, cls;        // pairs per KV head, class
+    int32_t pre;           // pairs per KV head in front of it
+    uint32_t cpre;         // cost per KV head in front of it
 };
 
 struct AttnArgs {
@@ -85,21 +101,29 @@ struct AttnArgs {
     float sm_scale;
     // workspace carve-up
     AttnPlan *plan;
-    int32_t *pair_prefix;  // [batch+1] exclusive prefix of the requests' pair counts
+    AttnReq *req;          // [batch] the requests in the order of the flat sequence
     int2 *pair_addr;       // [batch*ceil(max_blocks/2)*kv_heads] flat pair list: per tile, physical block * kv_heads + kv head
     int32_t *wave_desc;    // [launch_waves][kDescInts]: where each wave's span starts and what its first loads need
     float *part_o;         // [slots][rows_pad][head_dim]
     float *part_ml;        // [slots][rows_pad][2]  (log2-domain max, sum)
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
-    int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts, -1 = default)
-    int32_t chain;         // set by the launcher: partials are per (workgroup, unit), units inside one workgroup are final
+    int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts)
+    int32_t auto_weight;   // unit_weight is the default: teams take the weights measured for their row blocks
+    int32_t plan_fits;     // the plan's prefixes fit LDS and 32 bits: the cuts are weighted, the requests laid out by class
+    int32_t team_blocks;   // row blocks of the team kernel that is launched, 0 for the kernels of one or two
 };
 
 size_t attn_workspace_bytes(int batch, int max_blocks, int num_q_heads, int num_kv_heads, int head_dim,
                             int launch_waves, int max_q_len);
 bool attn_mfma_supported(const AttnArgs &a);
 int32_t attn_mfma_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
+// Row blocks of a grouping's team kernel: it serves every call whose windows have more than kChainRowBlocks.
+constexpr int attn_team_blocks(int G)
+{
+    const int nb = (SS_OUT_WIDTH * G + 15) / 16;
+    return nb < kMaxRowBlocks ? nb : kMaxRowBlocks;
+}
 int32_t attn_mfma_launch_g1(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);   // per head grouping,
 int32_t attn_mfma_launch_g2(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);   // after the plan kernel
 int32_t attn_mfma_launch_g4(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);

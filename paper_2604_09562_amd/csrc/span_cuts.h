@@ -15,6 +15,7 @@
 #ifndef SS_HOST_DEVICE
 #define SS_HOST_DEVICE __host__ __device__
 #endif
+#define SS_INLINE __attribute__((always_inline))   // (a call would put the struct into scratch memory)
 
 namespace ss {
 
@@ -52,12 +53,59 @@ SS_HOST_DEVICE inline SpanCount count_spans(long long total, int longest, long l
     return c;
 }
 
+// Spans of a team kernel, whose four wavefronts take a span's pairs in turn and write one partial: of two pairs as long as the chip
+// is not full (then half of the wavefronts have none, but the span is over sooner), of sixteen where a unit would leave more
+// than kMaxUnitPartials partials.  A whole call, in us, with a span per wavefront and no team / spans of 8 / 4 / 2 pairs:
+//   24 requests of 30..200 tokens, 8 KV heads, three row blocks  24.1 / 31.9 / 26.5 / 23.7     4 of 40..600, four and five  25.7 / 28.9 / 24.6 / 23.6
+//   4 of 1000..3000, e4m3  27.8 / 26.5 / 24.7 / 24.7      one of 60000 over one KV head, five row blocks  108 / 53 (spans of 16) / 74 (spans of 8)
+constexpr int kMinTeamPairs = 2, kMinTeamPairsLongUnits = 16;
+SS_HOST_DEVICE inline long long count_team_spans(long long total, int longest, long long most)
+{
+    auto bounded = [&](long long n) { return n < 1 ? 1 : n > most ? most : n; };
+    const long long n = bounded(total / kMinTeamPairs);
+    return longest * n > kMaxUnitPartials * total ? bounded(total / kMinTeamPairsLongUnits) : n;
+}
+
+// Requests of different row blocks in one call are laid out class by class (most row blocks first, so that a run of units
+// is streamed by the code for just their row blocks), and a pair of a class costs `cost` and opening one of its units `weight`.
+constexpr int kMaxClasses = 5;
+struct SpanClasses {
+    int end[kMaxClasses];    // requests (in layout order) of class 0, classes 0 and 1, ...: the last one is the batch
+    uint64_t cost, weight;   // of a pair (8 bits a class), of opening a unit (12 bits a class): packed, as arrays indexed by a
+                             // variable would live in scratch memory
+    SS_HOST_DEVICE SS_INLINE int of(int i) const
+    {
+        int c = 0;
+#pragma unroll
+        for (int k = 0; k + 1 < kMaxClasses; ++k) c += i >= end[k];
+        return c;
+    }
+    SS_HOST_DEVICE SS_INLINE int cost_of(int c) const { return (int)(cost >> (8 * c)) & 0xff; }
+    SS_HOST_DEVICE SS_INLINE int weight_of(int c) const { return (int)(weight >> (12 * c)) & 0xfff; }
+};
+
+// a / b for 0 <= a < 2^62, b >= 1 and a quotient below 2^31: by a reciprocal in fp64 and one correction (the integer division is
+// about 150 instructions, and a descriptor takes five of them).
+SS_HOST_DEVICE SS_INLINE inline long long quotient(long long a, long long b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    long long q = (long long)((double)a / (double)b);
+    const long long r = a - q * b;
+    q += r < 0 ? -1 : r >= b ? 1 : 0;
+    return q;
+#else
+    return a / b;
+#endif
+}
+
 struct SpanCuts {
-    const int32_t *prefix;   // [batch + 1] exclusive prefix of the pairs per KV head of the requests
-    int batch, hkv, weight;
-    long long total;         // pairs of all units
-    long long total_w;       // pairs of all units plus `weight` per unit
-    long long nw;            // number of spans
+    const int32_t *prefix;    // [batch + 1] exclusive prefix of the pairs per KV head of the requests
+    int batch, hkv, weight;   // (weight: of every unit, without classes)
+    long long total;          // pairs of all units
+    long long total_w;        // the coordinate's end: what all units cost
+    long long nw;             // number of spans
+    const uint32_t *cprefix;  // [batch + 1] exclusive prefix of the units' costs, or nullptr: every pair costs one
+    SpanClasses classes;      // (with cprefix)
 
     SS_HOST_DEVICE static SpanCuts make(const int32_t *prefix, int batch, int hkv, int weight, long long nw)
     {
@@ -69,58 +117,64 @@ struct SpanCuts {
         c.total = (long long)prefix[batch] * hkv;
         c.total_w = c.total + (long long)weight * batch * hkv;
         c.nw = nw;
+        c.cprefix = nullptr;
         return c;
     }
     // weighted coordinate of wave w's cut
-    SS_HOST_DEVICE long long cut(long long w) const { return w * total_w / nw; }
+    SS_HOST_DEVICE long long cut(long long w) const { return quotient(w * total_w, nw); }
+    // where request i's stretch begins in the coordinate, per KV head; what opening a unit and a pair of it cost
+    SS_HOST_DEVICE SS_INLINE long long start(int i) const { return cprefix ? (long long)cprefix[i] : (long long)prefix[i] + (long long)weight * i; }
+    SS_HOST_DEVICE SS_INLINE int weight_of(int i) const { return cprefix ? classes.weight_of(classes.of(i)) : weight; }
+    SS_HOST_DEVICE SS_INLINE int cost_of(int i) const { return cprefix ? classes.cost_of(classes.of(i)) : 1; }
     // flat index of unit (b, g)'s first pair, and the weighted coordinate where its stretch begins
     SS_HOST_DEVICE long long unit_offset(int b, int g) const
     {
         return (long long)prefix[b] * hkv + (long long)g * (prefix[b + 1] - prefix[b]);
     }
-    SS_HOST_DEVICE long long unit_coord(int b, int g) const { return unit_offset(b, g) + (long long)weight * ((long long)b * hkv + g); }
+    SS_HOST_DEVICE long long unit_coord(int b, int g) const { return start(b) * hkv + (long long)g * (start(b + 1) - start(b)); }
     // the waves whose cut falls into the stretch [ya, ya + weight + n): w_lo <= w < w_hi (w_hi may exceed nw)
-    SS_HOST_DEVICE long long first_cut_at_or_after(long long y) const { return (y * nw + total_w - 1) / total_w; }
-    // pair of the unit at which a span begins whose cut lies `ya <= cut < ya + weight + n`
-    SS_HOST_DEVICE int first_pair(long long cut_y, long long ya) const
+    SS_HOST_DEVICE long long first_cut_at_or_after(long long y) const { return quotient(y * nw + total_w - 1, total_w); }
+    // pair of the unit at which a span begins whose cut lies in the unit's stretch
+    SS_HOST_DEVICE static int first_pair(long long cut_y, long long ya, int weight, int cost)
     {
         const long long in_unit = cut_y - ya - weight;
-        return in_unit > 0 ? (int)in_unit : 0;
+        return in_unit > 0 ? (int)((uint32_t)in_unit / (uint32_t)cost) : 0;   // (a unit's stretch fits 32 bits)
     }
+    SS_HOST_DEVICE int first_pair(long long cut_y, long long ya) const { return first_pair(cut_y, ya, weight, 1); }
     // unit and pair that weighted coordinate y (< total_w) falls on; returns the flat pair index
-    SS_HOST_DEVICE long long locate(long long y, int &b, int &g, int &pair) const
+    SS_HOST_DEVICE SS_INLINE long long locate(long long y, int &b, int &g, int &pair) const
     {
         int lo = 0, hi = batch - 1;   // last request whose first unit starts at or before y
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (((long long)prefix[mid] + (long long)weight * mid) * hkv <= y)
+            if (start(mid) * hkv <= y)
                 lo = mid;
             else
                 hi = mid - 1;
         }
         b = lo;
         const int n = prefix[b + 1] - prefix[b];
-        const long long r = y - ((long long)prefix[b] + (long long)weight * b) * hkv;
-        g = (int)(r / (n + weight));
-        const int in_unit = (int)(r - (long long)g * (n + weight)) - weight;
-        pair = in_unit > 0 ? in_unit : 0;
+        const long long r = y - start(b) * hkv, unit = start(b + 1) - start(b);
+        g = (int)quotient(r, unit);
+        pair = first_pair(r, (long long)g * unit, weight_of(b), cost_of(b));
         return (long long)prefix[b] * hkv + (long long)g * n + pair;
     }
     // flat index one past wave w's last pair
-    SS_HOST_DEVICE long long span_end(long long w) const
+    SS_HOST_DEVICE SS_INLINE long long span_end(long long w) const
     {
         if (w + 1 >= nw) return total;
-        if (weight == 0) return (w + 1) * total / nw;
+        if (!cprefix && weight == 0) return (w + 1) * total / nw;
         int b, g, t;
         return locate(cut(w + 1), b, g, t);
     }
     // The waves that hold pairs of a unit with n >= 1 pairs whose stretch begins at ya: the last wave whose cut
     // lies at or before the unit's first pair ... the last wave whose cut lies at or before its last pair.
-    SS_HOST_DEVICE void unit_waves(long long ya, int n, int &w_first, int &w_last) const
+    SS_HOST_DEVICE void unit_waves(long long ya, int n, int weight, int cost, int &w_first, int &w_last) const
     {
-        w_first = (int)(((ya + weight + 1) * nw - 1) / total_w);
-        w_last = (int)(((ya + weight + n) * nw - 1) / total_w);
+        w_first = (int)quotient((ya + weight + cost) * nw - 1, total_w);
+        w_last = (int)quotient((ya + weight + (long long)n * cost) * nw - 1, total_w);
     }
+    SS_HOST_DEVICE void unit_waves(long long ya, int n, int &w_first, int &w_last) const { unit_waves(ya, n, weight, 1, w_first, w_last); }
 };
 
 }  // namespace ss

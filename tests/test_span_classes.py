@@ -1,0 +1,102 @@
+"""Host check of the span cuts with classes (`csrc/span_cuts.h`): requests laid out by class, a pair and the opening of a unit
+costing what their class says.  The spans have to tile the flat sequence, and the spans that hold pairs of a unit have to be the
+ones the merge kernel's formula names."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HEADER_DIR = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2604_09562_amd", "csrc")
+
+SHIM = r"""
+#define SS_HOST_DEVICE
+#include "span_cuts.h"
+using namespace ss;
+// out[w] = {unit, first pair, x0, x1} of every span, as the plan kernel finds them unit by unit; first/last: the merge's formula
+extern "C" long long spans(const int32_t *n, const int32_t *cls, int batch, int hkv, const int32_t *cost, const int32_t *weight, long long nw,
+                           int32_t *prefix, uint32_t *cprefix, long long *out, int *count, int *first, int *last)
+{
+    SpanCuts c = SpanCuts::make(prefix, batch, hkv, 0, nw);
+    c.classes.cost = c.classes.weight = 0;
+    for (int k = 0; k < kMaxClasses; ++k) {
+        c.classes.end[k] = 0;
+        for (int i = 0; i < batch; ++i) c.classes.end[k] += cls[i] <= k;
+        c.classes.cost |= (uint64_t)cost[k] << (8 * k);
+        c.classes.weight |= (uint64_t)weight[k] << (12 * k);
+    }
+    prefix[0] = 0;
+    cprefix[0] = 0;
+    for (int i = 0; i < batch; ++i) {
+        if (c.classes.of(i) != cls[i]) return -1;
+        prefix[i + 1] = prefix[i] + n[i];
+        cprefix[i + 1] = cprefix[i] + n[i] * c.classes.cost_of(cls[i]) + c.classes.weight_of(cls[i]);
+    }
+    c.cprefix = cprefix;
+    c.total = (long long)prefix[batch] * hkv;
+    c.total_w = (long long)cprefix[batch] * hkv;
+    for (int p = 0; p < batch; ++p)
+        for (int g = 0; g < hkv; ++g) {
+            const int co = c.cost_of(p), we = c.weight_of(p);
+            const long long off = c.unit_offset(p, g), ya = c.unit_coord(p, g), ye = ya + we + (long long)n[p] * co;
+            for (long long w = c.first_cut_at_or_after(ya); w < c.first_cut_at_or_after(ye) && w < nw; ++w) {
+                const int t0 = SpanCuts::first_pair(c.cut(w), ya, we, co);
+                out[4 * w] = (long long)p * hkv + g;
+                out[4 * w + 1] = t0;
+                out[4 * w + 2] = off + t0;
+                out[4 * w + 3] = c.span_end(w);
+                ++count[w];
+            }
+            c.unit_waves(ya, n[p], we, co, first[p * hkv + g], last[p * hkv + g]);
+        }
+    return c.total;
+}
+extern "C" long long team_spans(long long total, int longest, long long most) { return count_team_spans(total, longest, most); }
+"""
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    d = tmp_path_factory.mktemp("span_classes")
+    (d / "shim.cpp").write_text(SHIM)
+    subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I", HEADER_DIR, str(d / "shim.cpp"), "-o", str(d / "shim.so")], check=True)
+    lib = ctypes.CDLL(str(d / "shim.so"))
+    lib.spans.restype = lib.team_spans.restype = ctypes.c_longlong
+    return lib
+
+
+def _p(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_spans_by_class(shim, seed):
+    rng = np.random.default_rng(seed)
+    for _ in range(60):
+        batch, hkv = int(rng.integers(1, 50)), int(rng.choice([1, 2, 8]))
+        cls = np.sort(rng.integers(0, 5, batch)).astype(np.int32)
+        n = (np.exp(rng.uniform(0, np.log(rng.choice([4, 60, 700])), batch)).astype(np.int32) + 1).astype(np.int32)
+        if rng.random() < 0.5:
+            cost, weight = np.array([10, 9, 9, 8, 8], np.int32), np.array([280, 220, 160, 96, 64], np.int32)
+        else:
+            cost, weight = rng.integers(1, 17, 5).astype(np.int32), rng.integers(0, 1025, 5).astype(np.int32)
+        total = int(n.sum()) * hkv
+        nw = int(min(rng.choice([1, 3, 16, 256]), max(1, total // 2)))
+        out, count = np.full((nw, 4), -1, np.int64), np.zeros(nw, np.int32)
+        first, last = np.zeros(batch * hkv, np.int32), np.zeros(batch * hkv, np.int32)
+        prefix, cprefix = np.zeros(batch + 1, np.int32), np.zeros(batch + 1, np.uint32)
+        assert shim.spans(_p(n), _p(cls), batch, hkv, _p(cost), _p(weight), ctypes.c_longlong(nw), _p(prefix), _p(cprefix), _p(out),
+                          _p(count), _p(first), _p(last)) == total
+        assert np.all(count == 1)
+        x0, x1 = out[:, 2], out[:, 3]
+        assert x0[0] == 0 and x1[-1] == total and np.all(x1[:-1] == x0[1:]) and np.all(x1 >= x0)
+        off = np.concatenate([[0], np.cumsum(np.repeat(n, hkv))])
+        for u in range(batch * hkv):
+            holders = [w for w in range(nw) if max(x0[w], off[u]) < min(x1[w], off[u + 1])]
+            assert holders == list(range(first[u], last[u] + 1)), (u, holders, first[u], last[u])
+
+
+def test_team_spans(shim):
+    for total, longest, want in [(1, 1, 1), (8, 8, 4), (64, 64, 32), (66, 66, 4), (700, 4, 256), (625, 625, 39), (100000, 400, 256), (8000, 8000, 256)]:
+        assert shim.team_spans(ctypes.c_longlong(total), longest, ctypes.c_longlong(256)) == want, (total, longest)
