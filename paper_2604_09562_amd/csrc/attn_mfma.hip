@@ -63,27 +63,24 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     // (for a batch whose prefix fits LDS: pairs and costs per KV head in front of each request of the layout, and the order)
     extern __shared__ int32_t plan_lds[];
     int32_t *prefix = plan_lds;
-    uint32_t *cprefix = reinterpret_cast<uint32_t *>(plan_lds + a.batch + 1);
+    uint32_t *cprefix = reinterpret_cast<uint32_t *>(plan_lds + a.batch + 1);   // (SORTED)
     uint16_t *order = reinterpret_cast<uint16_t *>(plan_lds + 2 * (a.batch + 1));
     __shared__ int sh[4], csh[4], longest_sh[4], counts[4][kMaxClasses];
     const int p = blockIdx.x / a.num_kv_heads, g = blockIdx.x % a.num_kv_heads;   // place in the layout, KV head
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = a.num_q_heads / a.num_kv_heads;
     const bool fits = a.plan_fits;
-    const bool team = a.team_blocks > 0;
-    const int per = team ? kWavesPerWg : 1;   // wavefronts that share a span
 
     SpanCuts cuts;
 #pragma unroll
     for (int c = 0; c < kMaxClasses; ++c) cuts.classes.end[c] = a.batch;
-    cuts.classes.cost = 1;
-    cuts.classes.weight = fits ? a.unit_weight * per : 0;   // (a team's wavefronts open a unit together)
+    cuts.classes.cost = cuts.classes.weight = 0;
     if constexpr (SORTED) {
         const bool kv8 = a.kv_dtype == SS_FP8_E4M3;
         const int skip = kMaxClasses - a.team_blocks;   // classes with more row blocks than the kernel has
         cuts.classes.cost = (kv8 ? pack_costs(kPairCost[1], 8) : pack_costs(kPairCost[0], 8)) >> (8 * skip);
         cuts.classes.weight = a.auto_weight ? (kv8 ? pack_costs(kOpenCost[1], 12) : pack_costs(kOpenCost[0], 12)) >> (12 * skip)
-                                            : 0x001001001001001ull * (uint64_t)(a.unit_weight * per * 8);
+                                            : 0x001001001001001ull * (uint64_t)(a.unit_weight * kWavesPerWg * 8);
     }
     // request i: pairs per KV head, and its class (the most row blocks first)
     auto request = [&](int i, int &n, int &cls) __attribute__((always_inline)) {
@@ -192,8 +189,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
             }
             if (i < a.batch) {
                 prefix[i] = before + incl - t;
-                // (without classes a pair costs one)
-                cprefix[i] = SORTED ? (uint32_t)(cbefore + cincl - u) : (uint32_t)(before + incl - t) + (uint32_t)(a.unit_weight * per) * i;
+                if constexpr (SORTED) cprefix[i] = (uint32_t)(cbefore + cincl - u);
             }
             const int chunk_total = sh[0] + sh[1] + sh[2] + sh[3], cchunk = csh[0] + csh[1] + csh[2] + csh[3];
             __syncthreads();
@@ -202,7 +198,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         }
         if (tid == 0) {
             prefix[a.batch] = carry;
-            cprefix[a.batch] = SORTED ? (uint32_t)ccarry : (uint32_t)carry + (uint32_t)(a.unit_weight * per) * a.batch;
+            if constexpr (SORTED) cprefix[a.batch] = (uint32_t)ccarry;
         }
         note_longest(longest);
         __syncthreads();
@@ -231,7 +227,9 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         total = (long long)(pre + csh[0] + csh[1] + csh[2] + csh[3]) * a.num_kv_heads;
     }
     longest = __builtin_amdgcn_readfirstlane(max(max(longest_sh[0], longest_sh[1]), max(longest_sh[2], longest_sh[3])));
-    const SpanCount count = count_spans(total, longest, a.launch_waves, !team);
+    const SpanCount count = count_spans(total, longest, a.launch_waves, a.team_blocks == 0);
+    const bool team = a.team_blocks > 0 || count.spans < a.launch_waves;   // (kernels of one or two row blocks: when the chip is not full)
+    const int per = team ? kWavesPerWg : 1;   // wavefronts that share a span
     const long long nw = team ? count_team_spans(total, longest, a.launch_waves / kWavesPerWg) : count.spans;   // spans to cut
 
     const int L = a.kv_len[b], q0 = a.q_indptr[b], q1 = a.q_indptr[b + 1];
@@ -249,19 +247,23 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
 
     // waves (or teams) whose cut falls into this unit's stretch [ya, ye) of the weighted coordinate
     cuts.prefix = prefix;   // (read only if they were built)
-    cuts.cprefix = fits ? cprefix : nullptr;
+    cuts.cprefix = SORTED ? cprefix : nullptr;
     cuts.batch = a.batch;
     cuts.hkv = a.num_kv_heads;
-    cuts.weight = 0;
+    // Without classes a pair costs one.  What a team pays for opening a unit: 4 to 8 pairs are level with one or two row blocks.
+    cuts.weight = !fits ? 0 : !team ? a.unit_weight : a.team_blocks ? a.unit_weight * kWavesPerWg : a.unit_weight * 2;
     cuts.total = total;
-    cuts.total_w = fits ? (long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)cprefix[a.batch]) * a.num_kv_heads : total;
+    cuts.total_w = SORTED ? (long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)cprefix[a.batch]) * a.num_kv_heads
+                          : total + (long long)cuts.weight * a.batch * a.num_kv_heads;
     cuts.nw = nw;
-    const int cls = cuts.classes.of(p), cost = cuts.classes.cost_of(cls), weight = cuts.classes.weight_of(cls);
-    const long long ya = fits ? cuts.unit_coord(p, g) : off, ye = ya + weight + (long long)n * cost;
+    const int cls = SORTED ? cuts.classes.of(p) : 0, cost = SORTED ? cuts.classes.cost_of(cls) : 1;
+    const int weight = SORTED ? cuts.classes.weight_of(cls) : cuts.weight;
+    const uint32_t cpre = SORTED ? cprefix[p] : (uint32_t)pre + (uint32_t)weight * (uint32_t)p;
+    const long long ya = (long long)cpre * a.num_kv_heads + (long long)g * (weight + (long long)n * cost), ye = ya + weight + (long long)n * cost;
     const long long w_lo = cuts.first_cut_at_or_after(ya);   // first w with w*total_w/nw >= ya
     const long long w_hi = cuts.first_cut_at_or_after(ye);   // first w at or past the unit's end
     // Descriptor: {place in the layout, kv head, first pair, class, span begin, span end, kv_len, first query row, end query
-    // row, addresses of the first kDescPairs tile pairs the wave reads, hand-over, request, pairs of the unit}: everything
+    // row, addresses of the first kDescPairs tile pairs the wave reads, team, request, pairs of the unit}: everything
     // the wave's first loads depend on, so that they go out after a single read.
     for (long long i = w_lo * per + tid; i < w_hi * per && i < nw * per; i += 256) {
         const long long w = i / per;
@@ -272,7 +274,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         d[0] = p; d[1] = g; d[2] = t0; d[3] = cls;
         d[4] = (int)x0; d[5] = (int)x1;
         d[6] = L; d[7] = q0; d[8] = q1;
-        d[15] = count.chain; d[16] = b; d[17] = n;
+        d[15] = team; d[16] = b; d[17] = n;
         // walk forward from (p, g, pair) over unit boundaries; past the last unit repeat the last pair
         int pp = p, gg = g, tt = t0 + (int)(i - w * per), nn = n, nblk = blocks;
         int2 last = pair_at(bt, t0, blocks, a.num_kv_heads, g);
@@ -306,7 +308,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     if (g == 0 && tid == 0) {
         AttnReq r;
         r.b = b; r.L = L; r.q0 = q0; r.q1 = q1; r.n = n; r.cls = cls; r.pre = pre;
-        r.cpre = fits ? cprefix[p] : (uint32_t)pre;
+        r.cpre = cpre;
         a.req[p] = r;
         if (p == a.batch - 1) {
             a.plan->total_pairs = (int)total;
@@ -314,13 +316,14 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
             a.plan->unit_weight = fits ? a.unit_weight : 0;
             a.plan->chain = count.chain;
             a.plan->cuts = (int)nw;
+            a.plan->team = team;
             a.plan->total_cost = cuts.total_w;
 #pragma unroll
             for (int c = 0; c < kMaxClasses; ++c) {
                 a.plan->class_req[c] = cuts.classes.end[c];
-                a.plan->class_x[c] = fits ? prefix[cuts.classes.end[c]] * a.num_kv_heads : (int)total;
-                a.plan->class_cost[c] = cuts.classes.cost_of(c);
-                a.plan->class_weight[c] = cuts.classes.weight_of(c);
+                a.plan->class_x[c] = SORTED ? prefix[cuts.classes.end[c]] * a.num_kv_heads : (int)total;
+                a.plan->class_cost[c] = SORTED ? cuts.classes.cost_of(c) : 1;
+                a.plan->class_weight[c] = SORTED ? cuts.classes.weight_of(c) : weight;
             }
         }
     }
@@ -367,7 +370,8 @@ int32_t attn_mfma_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, 
     // (the costs per KV head are summed in 32 bits)
     p.plan_fits = a.batch <= kPlanMaxBatch &&
                   (uint64_t)a.batch * (((uint64_t)a.max_blocks + 1) / 2 * kMaxPairCost + kMaxOpenCost) < (1ull << 32);
-    const size_t lds = p.plan_fits ? 2 * sizeof(int32_t) * ((size_t)a.batch + 1) + sizeof(uint16_t) * a.batch : 0;
+    const size_t prefix_bytes = sizeof(int32_t) * ((size_t)a.batch + 1);
+    const size_t lds = !p.plan_fits ? 0 : p.team_blocks ? 2 * prefix_bytes + sizeof(uint16_t) * a.batch : prefix_bytes;
     for (p.q_lo = 0; p.q_lo < a.max_q_len; p.q_lo += p.q_win) {
         if (!(a.reuse_plan && passes == 1)) {   // a stored plan describes one window only
             const dim3 grid((unsigned)a.batch * a.num_kv_heads);

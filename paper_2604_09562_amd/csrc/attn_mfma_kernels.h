@@ -11,19 +11,20 @@
 // of one unit, several whole units and the head of another; for every unit it touches there is
 // one partial result (softmax reference, sum, unnormalised output).
 //
-// Units of one or two row blocks only: a span per wavefront.  When the batch fills the chip or has units of many spans (count_spans),
-// the four wavefronts of a workgroup, whose spans are consecutive, hand the partials of a shared unit from right to left through LDS and
-// combine them by their log-sum-exp; a unit that lies inside one workgroup's spans is normalised, rounded and written by that workgroup.
+// A full chip and units of one or two row blocks only: a span per wavefront.  The four wavefronts of a workgroup, whose spans are
+// consecutive, hand the partials of a shared unit from right to left through LDS and combine them by their log-sum-exp; a unit that
+// lies inside one workgroup's spans is normalised, rounded and written by that workgroup.
 //
-// Calls with units of three row blocks or more: a span per workgroup, whose wavefronts are a team and take its pairs in turn (every
-// fourth), so that they reach the end of a unit together and add their results block by block through LDS: one
-// partial per workgroup instead of four (with five row blocks a partial is 40 KB: 52 MB of them and as much read again by the merge
-// for 281 MB of keys and values, 32 requests of 256..4096 with trees of 8..16 nodes; the call 76.5 us with a span per wavefront,
-// 72 with teams).  The requests are laid out by row blocks, and each run of units is walked by the code for its own number
-// of them (see the plan kernel).
+// Otherwise a span per workgroup, whose wavefronts are a team and take its pairs in turn (every fourth), so that they reach the
+// end of a unit together and add their results block by block through LDS.  One partial per workgroup instead of four: with five row
+// blocks a partial is 40 KB (52 MB of them and as much read again by the merge for 281 MB of keys and values, 32 requests of 256..4096
+// with trees of 8..16 nodes; the call 76.5 us with a span per wavefront, 72 with teams).  On a chip that is not full the team ends
+// sooner than a chain of hand-overs (one request of 8000 tokens 29.5 us and 27.3, four of 40..600 21.2 and 20.2), on a full one with one or
+// two row blocks the chain is ahead (64 requests of 256..4096: 108 and 112).  In the kernels for three row blocks and more the requests are
+// laid out by row blocks, and each run of units is walked by the code for its own number of them (see the plan kernel).
 //
 // What is left (a unit that crosses spans that are not combined) goes to device memory as a partial in slot
-// `workgroup + unit` (`wave + unit` without the LDS hand-over; unique along the sequence either way), and a last
+// `workgroup + unit` (unique along the sequence), and a last
 // kernel merges those partials in span order and writes the rounded output.
 //
 // Per pair, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
@@ -76,8 +77,6 @@ constexpr float kSlack = 8.0f;       // log2 headroom of the lagging softmax ref
 constexpr float kNoMax = -1.0e30f;   // reference before any score was seen (finite, so that -inf - ref stays -inf)
 constexpr int kMaxFlagPolls = 1 << 23;   // polls of a neighbour's deposit flag before giving up (each at least 128 cycles)
 constexpr int kPartRowStride = 33;   // float4 per staged partial row in LDS (32 of data + 1 of padding)
-template <int NB>
-constexpr bool kTeam = NB > kChainRowBlocks;   // kernels whose workgroups share a span pair by pair
 template <int NB>
 constexpr bool kQueriesInLds = NB >= 4;        // for many row blocks the registers are needed for the accumulators
 
@@ -198,13 +197,14 @@ __device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs
 //        is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit slot, the left-hand one
 //        folds it into its own.  Only what crosses a workgroup's edge goes to memory as a partial; a unit that lies inside one
 //        workgroup is finished here.
-template <int BLOCKS, bool TEAM>
+template <int BLOCKS>
 struct StreamLds {
+    static constexpr bool CHAIN = BLOCKS <= kChainRowBlocks;
     uint4 q[kQueriesInLds<BLOCKS> ? kWavesPerWg * BLOCKS * 4 * 64 : 1];
-    float4v o[(TEAM ? 2 : 1) * kWavesPerWg][16 * kPartRowStride];
+    float4v o[2 * kWavesPerWg][16 * kPartRowStride];
     float2 ml[kWavesPerWg][BLOCKS * 16];
-    float4v dep_o[TEAM ? 1 : kWavesPerWg][TEAM ? 1 : BLOCKS * 16 * kPartRowStride];
-    float2 dep_ml[TEAM ? 1 : kWavesPerWg][TEAM ? 1 : BLOCKS * 16];
+    float4v dep_o[CHAIN ? kWavesPerWg : 1][CHAIN ? BLOCKS * 16 * kPartRowStride : 1];
+    float2 dep_ml[CHAIN ? kWavesPerWg : 1][CHAIN ? BLOCKS * 16 : 1];
     int dep_flag[kWavesPerWg];   // 0 nothing yet; 1 deposited; 2 deposited and it reaches the unit's last tile
 };
 
@@ -215,7 +215,6 @@ struct Run {
     int x0, x1;           // the run, flat
     int L, q0, q1;        // kv_len and query rows of the request
     int2 addr[kDescPairs];   // of the wave's first pairs
-    bool chain;           // combine the spans of the workgroup (the plan's choice)
 };
 
 // NB      16-row blocks of query rows the code is compiled for
@@ -224,14 +223,13 @@ struct Run {
 //         mask word instead of the chain's "tokens up to my own"
 // TEAM    the run is the workgroup's: its wavefronts take the pairs in turn; else it is the wavefront's own
 template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool TEAM>
-__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> &lds, const Run &run, const int2 *__restrict__ pair_addr,
+__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, const Run &run, const int2 *__restrict__ pair_addr,
                                      const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
                                      const float *__restrict__ v_scale)
 {
     constexpr bool QLDS = kQueriesInLds<NB>, CHAIN = !TEAM;
     const int lane = threadIdx.x & 63;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = blockIdx.x * kWavesPerWg + wslot;
     const int r16 = lane & 15, jq = lane >> 4;
     uint4 *qs = lds.q + (QLDS ? wslot * NB * 4 * 64 + lane : 0);
     auto &o_lds = lds.o;
@@ -241,7 +239,6 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> 
     auto &dep_flag = lds.dep_flag;
     int p = run.p, b = run.b, g = run.g, nb_tiles = run.n, unit_x = run.unit_x;
     const int x0 = run.x0, x1 = run.x1;
-    const bool chain = CHAIN && run.chain;
     int meta_b = b, meta_L = run.L, meta_q0 = run.q0, meta_q1 = run.q1, meta_nbt = nb_tiles;   // of the next unit to open
 
     // SINGLE: with many row blocks a step is longer than a read's latency, and one buffer that is refilled as soon as its
@@ -460,7 +457,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> 
         }
         bool to_end = ends;   // does the result held here reach the unit's last tile?
         if constexpr (CHAIN) {
-            if (chain && !ends && wslot + 1 < kWavesPerWg) {
+            if (!ends && wslot + 1 < kWavesPerWg) {
                 // The unit runs on into the right-hand neighbour's span, where it is that wave's first
                 // segment: finished long ago unless the spans are very short.  Fold its result into mine
                 // (mine first: a fixed order, so the bits do not depend on timing).
@@ -503,7 +500,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> 
                     }
                 }
             }
-            if (chain && !starts && wslot > 0) {
+            if (!starts && wslot > 0) {
                 // The unit began in the left-hand neighbour's span: leave the result for it.
                 float4v *dq = dep_o[wslot];
 #pragma unroll
@@ -532,7 +529,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS, TEAM> 
         // What is held here goes to memory: as the finished output if it covers the whole unit, else as a
         // partial in slot (workgroup, or wave without the hand-over) + unit, unique along the pair sequence.
         const bool whole = CHAIN && starts && to_end;
-        const long long slot = (long long)(chain ? (int)blockIdx.x : wave) + (long long)p * a.num_kv_heads + g;
+        const long long slot = (long long)blockIdx.x + (long long)p * a.num_kv_heads + g;
         float *po = a.part_o + slot * a.rows_pad * D;
         float *pml = a.part_ml + slot * a.rows_pad * 2;
         // A lane holds 32 consecutive d of one row (d = 32*jq + 8*e + mb), in registers that are 16 bytes
@@ -891,8 +888,8 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
 {
     // The metadata arrays come in as separate no-alias arguments so that their wave-uniform reads
     // become scalar loads (own counter, no ordering against the vector KV loads).
-    constexpr bool TEAM = kTeam<BLOCKS>;
-    __shared__ StreamLds<BLOCKS, TEAM> lds;
+    constexpr bool CLASSES = BLOCKS > kChainRowBlocks;
+    __shared__ StreamLds<BLOCKS> lds;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // where this wave's span starts: written by the plan kernel (waves past the partition count get x0 == x1)
     const int32_t *d = wave_desc + (long long)(blockIdx.x * kWavesPerWg + wslot) * kDescInts;
@@ -903,12 +900,16 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
 #pragma unroll
     for (int j = 0; j < kDescPairs; ++j) run.addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
-    run.chain = d[15] != 0;
-    if constexpr (!TEAM) {
-        if ((threadIdx.x & 63) == 0) lds.dep_flag[wslot] = 0;
-        __syncthreads();   // every wave's flag is clear before any neighbour can look at it
-        if (run.x0 >= run.x1) return;
-        walk<G, BLOCKS, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+    if constexpr (!CLASSES) {
+        if (d[15]) {   // (the same for the whole workgroup)
+            if (run.x0 >= run.x1) return;
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
+        } else {
+            if ((threadIdx.x & 63) == 0) lds.dep_flag[wslot] = 0;
+            __syncthreads();   // every wave's flag is clear before any neighbour can look at it
+            if (run.x0 >= run.x1) return;
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, false>(a, lds, run, pair_addr, req, k_scale, v_scale);
+        }
     } else {
         // The span of the workgroup, class by class: units of k row blocks are walked by the code for k.
         if (run.x0 >= run.x1) return;
@@ -918,13 +919,13 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             run.x1 = class_end < end ? class_end : end;
             if (run.x0 < run.x1) {
                 const int blocks = BLOCKS - c;
-                if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
                 else {
                     if constexpr (BLOCKS >= 5) {
-                        if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                        else walk<G, 4, BLOCKS, FP8, TREE, TEAM>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                        if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
+                        else walk<G, 4, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
                     }
                 }
             }
@@ -972,7 +973,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     cuts.nw = a.plan->cuts;
     int w_first, w_last;
     cuts.unit_waves((long long)r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
-    if (a.plan->chain) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
+    if (!a.plan->team) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
         w_first /= kWavesPerWg;
         w_last /= kWavesPerWg;
     }

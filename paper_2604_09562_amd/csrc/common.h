@@ -60,9 +60,9 @@ struct AttnPlan {
     int32_t total_pairs;   // sum over requests of ceil(kv_len/32) * num_kv_heads
     int32_t num_waves;     // partitions actually used (<= launched wavefronts)
     int32_t unit_weight;   // what opening a unit costs a wavefront, in pairs (0: spans of equal pair counts)
-    int32_t chain;         // the spans of a workgroup are combined in LDS (instances that can)
+    int32_t chain;         // count_spans' choice to combine the results of a workgroup in LDS
     int32_t cuts;          // spans that were cut: num_waves, or a quarter of that where a workgroup shares a span
-    int32_t pad;
+    int32_t team;          // the spans are workgroups', whose wavefronts take the pairs in turn
     int64_t total_cost;                  // the end of the coordinate they were cut in
     int32_t class_req[kMaxClasses];      // requests, in layout order, before the end of each class
     int32_t class_x[kMaxClasses];        // pairs of the flat sequence before the end of each class

@@ -21,18 +21,9 @@ namespace ss {
 
 // How many spans, and whether the spans of a workgroup are combined in LDS (`can_chain`: the instance is able to).
 //
-// A call that does not fill the chip is bound by latency: spans of two pairs, and every wavefront leaves its partial at once
-// (the hand-over is a chain of up to four unit ends, 1.2 us each, 3.8 us for the output), as the merge kernel runs anyway: 4 requests
-// of 40..600 tokens over 8 KV heads 16.4 -> 11.4 us in the streaming kernel, against spans of four pairs with the hand-over.
-// But the merge kernel adds a unit's partials one after the other, so that holds only while they are few.  A whole call, in us,
-// with spans of two pairs / the same and the hand-over / four pairs and the hand-over (one request, 8 KV heads, depth 4):
-//   1000 tokens (16 spans a unit)  20.5 / 22.2 / 23.9      2000 (31)  24.1 / 23.3 / 24.8      4000 (63)  30.8 / 25.1 / 25.9
-//   8000 (125)  41.7 / 28.9 / 28.3      32000 tokens over one KV head (500)  103 / 45.6 / 36.3
-// and without a hand-over (three row blocks and more), with spans of two / four pairs:
-//   4 requests of 2000, 8 KV heads (31): 29.8 / 28.8 (three row blocks), 32.1 / 32.4 (four, tree)      4000 (63): 34.1 / 30.0
-//   60000 tokens over one KV head, five row blocks (937): 184 / 109
-// So the hand-over comes in from kMaxLooseSpans spans per unit on, the longer spans from kMaxUnitPartials partials on, both for
-// the longest unit.
+// The spans of a call with one or two row blocks on a full chip are these, a wavefront's each, handed over in LDS.  A call that does not
+// fill the chip is served by teams instead (count_team_spans); what is counted here then only says so (fewer spans than
+// launched wavefronts) and stands in the plan's record.
 constexpr int kMinPairsPerSpan = 2, kMinPairsLongUnits = 4;
 constexpr int kMaxLooseSpans = 16, kMaxUnitPartials = 32;
 constexpr int kSpansPerWg = 4;   // wavefronts of a workgroup
