@@ -682,8 +682,11 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) s[nb][0] = s[nb][1] = float4v{0.f, 0.f, 0.f, 0.f};
         {
-            // (operands from LDS are requested a few MFMAs ahead of their use, so that its latency is covered)
-            constexpr int NOPS = 4 * NB, AHEAD = QLDS ? (NOPS < 4 ? NOPS : 4) : 1;
+            // Operands from LDS are requested eight steps (16 matrix instructions) ahead of their use, so that its latency is covered;
+            // the barriers keep the compiler from gathering the reads in pairs right in front of their use, where each pair
+            // waited for LDS (96 requests e4m3 at depth 8, five row blocks: 234 us a call and 227; decode step of two layers of e4m3
+            // trees 138 and 130).
+            constexpr int NOPS = 4 * NB, AHEAD = QLDS ? (NOPS < 8 ? NOPS : 8) : 1;
             uint4 qb[AHEAD];
             if constexpr (QLDS) {
 #pragma unroll
@@ -704,6 +707,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
                 }
 #pragma unroll
                 for (int h = 0; h < 2; ++h) s[nb][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[h][ks], qop, s[nb][h], 0, 0, 0);
+                if constexpr (QLDS) __builtin_amdgcn_sched_barrier(0);
             }
         }
 
