@@ -296,7 +296,10 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
             pk.m_q = n < k ? row_m[k + 1 + n] : 0.f;
             pk.temperature = T;
             pk.n = n;
-            pk.rho = n < k ? row_z[n] / row_z[k + 1 + n] : 1.0;
+            // kAmbEps wide in e_p / e_q is kAmbEps * T in the difference; rounding moves a difference by 2^-24 of it and of theta
+            // (near the boundary it is about theta)
+            pk.theta = n < k ? (float)((double)T * (double)logf((float)(row_z[n] / row_z[k + 1 + n])) + ((double)pk.m_p - (double)pk.m_q)) : 0.f;
+            pk.width = (float)(kAmbEps * (double)T) + 4.0e-7f * fabsf(pk.theta);
             w.pick[b] = pk;
             w.amb_cnt[b] = 0;
             w.done[b] = 0;
@@ -306,11 +309,11 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
 
 // ---- pass 2a: fp64 sums per block -------------------------------------------------------------
 // One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  Bound by the fp64 instructions
-// (about 34 per pair of entries at 5 cycles and the 32-bit ones around them: 16 us for 64 requests of 128256 entries), so
-// the sums cross the lanes by data-parallel moves, once.  Measured there: 22.7 us with shuffles through LDS and ldexp,
-// this form 20.2 us; two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5 against 4.9 us for 8 requests of 32000:
-// a wavefront that walks a block alone is a long chain); all 32 entries of a lane as straight-line code 27 us
-// (instruction fetch).
+// (26 per pair of entries and the 32-bit ones around them), so the sums cross the lanes by data-parallel moves, once.  Measured for
+// 64 requests of 128256 entries: 22.7 us with shuffles through LDS and ldexp, 20.3 with data-parallel moves and 32 fp64 instructions per
+// pair, 19.0 this way; two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5 against 4.9 us for 8 requests of 32000: a wavefront that
+// walks a block alone is a long chain); all 32 entries of a lane as straight-line code 27 us (instruction fetch).  Exponentials of bf16
+// logits by a table of all values in LDS (64 KB, 1024-lane workgroups): 17.3 us, 58.0 -> 56.7 for the call; not kept for its size.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Workspace w)
 {
@@ -333,19 +336,19 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
     const double inv_t = 1.0 / (double)pk.temperature;
     const RowArg ap(inv_t, pk.m_p), aq(inv_t, pk.m_q);
     const int64_t o = (int64_t)b * w.nsub + sub;
-    // exponentials of all entries (zp, zq) and of those whose residual p - q is positive for certain (pp, qq):
-    // ep - rho * eq exceeds the boundary zone's half-width, kAmbEps * rho * eq
+    // exponentials of all entries (zp, zq) and of those whose residual p - q is positive for certain (pp, qq): the difference of an
+    // entry's logits decides that in 32 bits (before, two fp64 instructions and two fp64 comparisons did)
     double zp = 0.0, zq = 0.0, pp = 0.0, qq = 0.0;
-    const double rho = pk.rho, width = pk.rho * kAmbEps;
+    const float theta = pk.theta, width = pk.width;
     unsigned near = 0;   // entries of this lane that are too close to call before Zp/Zq are exact
-    auto pair = [&](double ep, double eq, unsigned bit) __attribute__((always_inline)) {
+    auto pair = [&](double ep, double eq, float d, unsigned bit) __attribute__((always_inline)) {
+        const float t = d - theta;
         zp += ep;
         zq += eq;
-        const double t = fma(-rho, eq, ep), z = width * eq;
-        const double sure = t > z ? 1.0 : 0.0;   // (a factor costs fewer instructions than two selects of doubles)
+        const double sure = t > width ? 1.0 : 0.0;   // (a factor costs fewer instructions than two selects of doubles)
         pp = fma(ep, sure, pp);
         qq = fma(eq, sure, qq);
-        if (fabs(t) <= z && ep > 0.0) near |= bit;
+        if (fabsf(t) <= width && __double2hiint(ep) != 0) near |= bit;   // (an entry without mass is not worth a place)
     };
     float xp[8], xq[8];
     unpack8<DT>(rp, xp);
@@ -369,10 +372,10 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
         }
     } else if (normal) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) pair(ex.normal(ap.fma_form(xp[s])), ex.normal(aq.fma_form(xq[s])), 1u << s);
+        for (int s = 0; s < 8; ++s) pair(ex.normal(ap.fma_form(xp[s])), ex.normal(aq.fma_form(xq[s])), xp[s] - xq[s], 1u << s);
     } else {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), 1u << s);
+        for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), xp[s] - xq[s], 1u << s);
     }
     zp = wave_scan(zp);
     if (residual) {

@@ -20,7 +20,9 @@ struct RowPick {      // written by decide, read by the resampling passes
     float m_p, m_q;   // exact row maxima
     float temperature;
     int32_t n;        // accepted length
-    double rho;       // Zp/Zq as known from the fp32 row statistics (relative error below 2e-5)
+    // The difference of the two logits at which p == q, T log(Zp/Zq) + m_p - m_q with Zp/Zq as known from the fp32 row statistics
+    // (relative error below 2e-5), and the half-width of the zone around it that is left to the exact normalisers.
+    float theta, width;
 };
 
 constexpr int kAmbCap = 4096;       // listed boundary entries per request; beyond that the slow exact path runs
@@ -271,8 +273,10 @@ __device__ __forceinline__ double lane_value(double x, int lane)
 }
 
 // ---- fp64 exponential for non-positive arguments -----------------------------------------------
-// exp(x) = 2^e * 2^(j/64) * exp(r), x = (64 e + j) ln2/64 + r, |r| <= ln2/128, with a 64-entry
-// table of 2^(j/64) in LDS and a degree-5 Taylor polynomial (remainder < 4e-17 relative).
+// Arguments come in steps of the table, y = x * 64/ln2 (RowArg folds the factor into 1 / T): exp(x) = 2^e * 2^(j/64) * exp(f ln2/64) with
+// y = 64 e + j + f, |f| <= 1/2 and exact, a 64-entry table of 2^(j/64) in LDS and a degree-5 Taylor polynomial in f (remainder <
+// 4e-17 relative).  Reducing x itself takes a two-part ln2/64 and one instruction more: 11 fp64 ones with the conversion and the
+// argument, instead of 12.
 // 2^(j/64), j = 0..63, each the double nearest to the exact value (tests/test_exp_table.py recomputes them)
 static __device__ const double kExp2Sixtyfourths[64] = {
     0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
@@ -293,7 +297,8 @@ static __device__ const double kExp2Sixtyfourths[64] = {
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0,
 };
 
-constexpr double kExpNormal = -700.0;   // from here up ExpTable::normal may be used
+constexpr double kExpSteps = 92.33248261689366;   // 64 / ln2
+constexpr double kExpNormal = -700.0 * kExpSteps;   // from here up ExpTable::normal may be used
 
 struct ExpTable {
     double t[64];
@@ -302,35 +307,35 @@ struct ExpTable {
         if (threadIdx.x < 64) t[threadIdx.x] = kExp2Sixtyfourths[threadIdx.x];
         __syncthreads();
     }
-    // the significand of exp(x), in [0.99, 2), and k with exp(x) = significand * 2^(k >> 6)
-    __device__ __forceinline__ double significand(double x, int &k) const
+    // the significand of exp, in [0.99, 2), and k with exp = significand * 2^(k >> 6)
+    __device__ __forceinline__ double significand(double y, int &k) const
     {
-        // x * 64/ln2 to the nearest integer: added to 1.5 * 2^52 it lands in the low bits of the significand
-        const double magic = 0x1.8p52;
-        double kd = fma(x, 92.33248261689366, magic);
+        // y to the nearest integer: added to 1.5 * 2^52 it lands in the low bits of the significand
+        constexpr double magic = 0x1.8p52, step = 0.010830424696249145;   // ln2 / 64
+        const double kd = y + magic;
         k = __double2loint(kd);
-        kd -= magic;
-        double r = fma(kd, -0x1.62e42fee00000p-7, x);    // ln2/64: high part with 21 trailing zero bits
-        r = fma(kd, -0x1.a39ef35793c76p-39, r);          //         low part
-        const double p = fma(fma(fma(fma(fma(r, 1.0 / 120.0, 1.0 / 24.0), r, 1.0 / 6.0), r, 0.5), r, 1.0), r, 1.0);
+        const double f = y - (kd - magic);
+        constexpr double c1 = step, c2 = step * step / 2, c3 = step * step * step / 6, c4 = step * step * step * step / 24,
+                         c5 = step * step * step * step * step / 120;
+        const double p = fma(fma(fma(fma(fma(f, c5, c4), f, c3), f, c2), f, c1), f, 1.0);
         return t[k & 63] * p;
     }
-    __device__ __forceinline__ double operator()(double x) const
+    __device__ __forceinline__ double operator()(double y) const
     {
         int k;
-        const double y = significand(fmax(x, -746.0), k);   // exp underflows to 0 from there on (also covers -inf)
-        return ldexp(y, k >> 6);
+        const double s = significand(fmax(y, -746.0 * kExpSteps), k);   // exp underflows to 0 from there on (also covers -inf)
+        return ldexp(s, k >> 6);
     }
     // the same bits for -700 <= x <= 1, where the result is normal and the power of two is an addition to its exponent
-    __device__ __forceinline__ double normal(double x) const
+    __device__ __forceinline__ double normal(double y) const
     {
         int k;
-        const double y = significand(x, k);
-        return __hiloint2double(__double2hiint(y) + ((k & ~63) << 14), __double2loint(y));
+        const double s = significand(y, k);
+        return __hiloint2double(__double2hiint(s) + ((k & ~63) << 14), __double2loint(s));
     }
 };
 
-// Argument of the exponential of a logit, (x - max) / T.  As one fused multiply-add x / T - max / T where max / T is small
+// Argument of the exponential of a logit, (x - max) / T, in steps of the table.  As one fused multiply-add x / T - max / T where max / T is small
 // enough: its rounding (below 1.2e-10 there) is a factor common to all of the row's exponentials, which the normaliser takes
 // out again, and far inside the boundary zone of p == q.  Beyond that (a tiny temperature, enormous logits) the rounding would
 // be as large as the arguments themselves -- at T = 1e-18 every exponential of a row underflowed or overflowed -- so there
@@ -340,10 +345,10 @@ struct RowArg {
     double inv_t, c;
     float sub;
     bool fused;   // uniform: all lanes of a workgroup hold the same row
-    __device__ __forceinline__ RowArg(double inv_t_, float m) : inv_t(inv_t_)
+    __device__ __forceinline__ RowArg(double inv_t_, float m) : inv_t(inv_t_ * kExpSteps)
     {
-        const double mt = (double)m * inv_t_;
-        const bool f = fabs(mt) < kFusedArgMax;   // (false for a row without a finite maximum)
+        const double mt = (double)m * inv_t;
+        const bool f = fabs(mt) < kFusedArgMax * kExpSteps;   // (false for a row without a finite maximum)
         c = f ? -mt : 0.0;
         fused = __builtin_amdgcn_readfirstlane(f);
         sub = fused ? 0.f : m;
