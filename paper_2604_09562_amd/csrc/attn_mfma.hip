@@ -303,6 +303,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
             int32_t *d = a.wave_desc + w * kDescInts;
             d[4] = 0;
             d[5] = 0;
+            d[15] = team;   // (read before the span is seen to be empty)
         }
     }
     if (g == 0 && tid == 0) {

@@ -75,7 +75,7 @@ struct SpanClasses {
     SS_HOST_DEVICE SS_INLINE int weight_of(int c) const { return (int)(weight >> (12 * c)) & 0xfff; }
 };
 
-// a / b for 0 <= a < 2^62, b >= 1 and a quotient below 2^31: by a reciprocal in fp64 and one correction (the integer division is
+// a / b for 0 <= a < 2^62, b >= 1 and a quotient below 2^50: by a division in fp64 and one correction (the integer division is
 // about 150 instructions, and a descriptor takes five of them).
 SS_HOST_DEVICE SS_INLINE inline long long quotient(long long a, long long b)
 {
