@@ -952,20 +952,24 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// merge: workgroup (unit, slab) combines the partials of 8 query rows of one unit
+// merge: workgroup (unit, slab) combines the partials of 8 * PER query rows of one unit, PER rows to a lane.  Most workgroups find
+// their unit finished or their rows past its own and end at once, so a call with more of them than the chip holds is better off with
+// half as many (PER 2; 96 requests of up to 72 rows over 8 KV heads 9.8 -> 7.9 us, 128 of up to 36 7.8 -> 5.7, 128 short ones of
+// up to 72 81.8 -> 78.5 a whole call); below that a lane's second row only lengthens its chain of additions (one request of 8000
+// tokens 25.3 -> 28.2 a call).
 // ---------------------------------------------------------------------------------------------
-constexpr int kMergeRows = 8;
+constexpr int kMergeBusy = 2048;   // workgroups of 8 rows that the chip holds at once (eight to a compute unit)
 
-template <int G>
+template <int G, int PER>
 __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
 {
-    const int slabs = a.rows_pad / kMergeRows;
+    const int slabs = a.rows_pad / (8 * PER);
     const int unit = blockIdx.x / slabs, slab = blockIdx.x % slabs;
     const int g = unit % a.num_kv_heads;
     const AttnReq r = a.req[unit / a.num_kv_heads];
     const int q0 = r.q0;
     const int rows = window_q_len(r.q1 - q0, a.q_lo, a.q_win) * G;   // rows of this pass's window
-    const int n = slab * kMergeRows + (threadIdx.x >> 5), d4 = threadIdx.x & 31;
+    const int n = slab * (8 * PER) + (threadIdx.x >> 5), d4 = threadIdx.x & 31;
     if (n >= rows) return;
     // The spans were cut at w*total_cost/cuts in the weighted coordinate (every unit: what opening it costs, then its
     // pairs); the last wave whose cut lies at or before coordinate t is ((t+1)*cuts - 1) / total_cost.  A cut
@@ -984,28 +988,43 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     if (w_first == w_last) return;   // the unit lies in one span (of a wavefront, of a workgroup): finished there
 
     // running merge: (m, l, o) <- (m, l, o) (+) partial, both relative to their own reference m
-    float m_all = kNoMax, l_all = 0.f;
-    float4v o = {0.f, 0.f, 0.f, 0.f};
+    float m_all[PER], l_all[PER];
+    float4v o[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        m_all[i] = kNoMax;
+        l_all[i] = 0.f;
+        o[i] = float4v{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll 4
     for (int w = w_first; w <= w_last; ++w) {
-        const long long row = ((long long)w + unit) * a.rows_pad + n;
-        const float2 ml = *reinterpret_cast<const float2 *>(a.part_ml + row * 2);
-        const float4v op = *reinterpret_cast<const float4v *>(a.part_o + row * D + d4 * 4);
-        const float m_new = fmaxf(m_all, ml.x);
-        const float wa = exp2f(m_all - m_new), wb = exp2f(ml.x - m_new);  // a partial without visible tokens has l = 0
-        l_all = l_all * wa + ml.y * wb;
-        o = o * wa + op * wb;
-        m_all = m_new;
+        const long long first = ((long long)w + unit) * a.rows_pad + n;   // (rows past the unit's are inside its slot: rows_pad)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const long long row = first + i * 8;
+            const float2 ml = *reinterpret_cast<const float2 *>(a.part_ml + row * 2);
+            const float4v op = *reinterpret_cast<const float4v *>(a.part_o + row * D + d4 * 4);
+            const float m_new = fmaxf(m_all[i], ml.x);
+            const float wa = exp2f(m_all[i] - m_new), wb = exp2f(ml.x - m_new);  // a partial without visible tokens has l = 0
+            l_all[i] = l_all[i] * wa + ml.y * wb;
+            o[i] = o[i] * wa + op * wb;
+            m_all[i] = m_new;
+        }
     }
-    const float inv = 1.f / l_all;
-    const int qi = a.q_lo + n / G, hh = n % G;
-    const long long orow = (long long)(q0 + qi) * a.num_q_heads + g * G + hh;
-    const float2v lo = {o.x * inv, o.y * inv}, hi = {o.z * inv, o.w * inv};
-    uint2 pk;
-    pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
-    pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-    *reinterpret_cast<uint2 *>(static_cast<__bf16 *>(a.out) + orow * D + d4 * 4) = pk;
-    if (a.lse && d4 == 0) a.lse[orow] = (m_all + log2f(l_all)) * kLn2;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const int nn = n + i * 8;
+        if (nn >= rows) return;
+        const float inv = 1.f / l_all[i];
+        const int qi = a.q_lo + nn / G, hh = nn % G;
+        const long long orow = (long long)(q0 + qi) * a.num_q_heads + g * G + hh;
+        const float2v lo = {o[i].x * inv, o[i].y * inv}, hi = {o[i].z * inv, o[i].w * inv};
+        uint2 pk;
+        pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+        pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
+        *reinterpret_cast<uint2 *>(static_cast<__bf16 *>(a.out) + orow * D + d4 * 4) = pk;
+        if (a.lse && d4 == 0) a.lse[orow] = (m_all[i] + log2f(l_all[i])) * kLn2;
+    }
 }
 
 template <int G, int BLOCKS, bool FP8, bool TREE>
@@ -1021,8 +1040,11 @@ int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hip
                           dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, a, a.plan, a.pair_addr, a.wave_desc, a.req, a.k_scale,
                           a.v_scale);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_stream_kernel");
-    hipLaunchKernelGGL(attn_merge_kernel<G>, dim3((unsigned)a.batch * a.num_kv_heads * (a.rows_pad / kMergeRows)), dim3(256),
-                       0, stream, a);
+    const long long slabs = (long long)a.batch * a.num_kv_heads * (a.rows_pad / 8);   // of 8 rows
+    if (slabs >= kMergeBusy)
+        hipLaunchKernelGGL((attn_merge_kernel<G, 2>), dim3((unsigned)(slabs / 2)), dim3(256), 0, stream, a);
+    else
+        hipLaunchKernelGGL((attn_merge_kernel<G, 1>), dim3((unsigned)slabs), dim3(256), 0, stream, a);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_merge_kernel");
     return SS_OK;
 }
