@@ -263,7 +263,8 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     const long long w_lo = cuts.first_cut_at_or_after(ya);   // first w with w*total_w/nw >= ya
     const long long w_hi = cuts.first_cut_at_or_after(ye);   // first w at or past the unit's end
     // Descriptor: {place in the layout, kv head, first pair, class, span begin, span end, kv_len, first query row, end query
-    // row, addresses of the first kDescPairs tile pairs the wave reads, team, request, pairs of the unit}: everything
+    // row, addresses of the first kDescPairs tile pairs the wave reads, team, request, pairs of the unit,
+    // end of the span's first class}: everything
     // the wave's first loads depend on, so that they go out after a single read.
     for (long long i = w_lo * per + tid; i < w_hi * per && i < nw * per; i += 256) {
         const long long w = i / per;
@@ -275,6 +276,8 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
         d[4] = (int)x0; d[5] = (int)x1;
         d[6] = L; d[7] = q0; d[8] = q1;
         d[15] = team; d[16] = b; d[17] = n;
+        if constexpr (SORTED) d[18] = min((int)x1, prefix[cuts.classes.end_of(cls)] * a.num_kv_heads);
+        else d[18] = (int)x1;
         // walk forward from (p, g, pair) over unit boundaries; past the last unit repeat the last pair
         int pp = p, gg = g, tt = t0 + (int)(i - w * per), nn = n, nblk = blocks;
         int2 last = pair_at(bt, t0, blocks, a.num_kv_heads, g);

@@ -918,9 +918,10 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         // The span of the workgroup, class by class: units of k row blocks are walked by the code for k.
         if (run.x0 >= run.x1) return;
         const int end = run.x1;
+        // (the first class's end comes with the descriptor: the plan's record would be one more read in a row before the
+        // first pair, 0.5 % of the whole call: 221.8 -> 220.5 us with 96 e4m3 requests, 278.8 -> 277.4 with 128 ragged ones)
+        run.x1 = d[18];
         for (int c = d[3];;) {
-            const int class_end = plan->class_x[c];
-            run.x1 = class_end < end ? class_end : end;
             if (run.x0 < run.x1) {
                 const int blocks = BLOCKS - c;
                 if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
@@ -947,6 +948,8 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
                 const int x = run.x0 + wslot + j * kWavesPerWg;
                 run.addr[j] = pair_addr[x < end ? x : end - 1];
             }
+            const int class_end = plan->class_x[c];
+            run.x1 = class_end < end ? class_end : end;
         }
     }
 }

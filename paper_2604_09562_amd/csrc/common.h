@@ -26,7 +26,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
 constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
 constexpr int kWavesPerWg = 4;
-constexpr int kDescInts = 32;            // ints per wave descriptor (18 in use)
+constexpr int kDescInts = 32;            // ints per wave descriptor (19 in use)
 constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
 constexpr int kChainRowBlocks = 2;       // up to here the spans of a workgroup can be combined in LDS

@@ -71,6 +71,7 @@ struct SpanClasses {
         for (int k = 0; k + 1 < kMaxClasses; ++k) c += i >= end[k];
         return c;
     }
+    SS_HOST_DEVICE SS_INLINE int end_of(int c) const { return c == 0 ? end[0] : c == 1 ? end[1] : c == 2 ? end[2] : c == 3 ? end[3] : end[4]; }
     SS_HOST_DEVICE SS_INLINE int cost_of(int c) const { return (int)(cost >> (8 * c)) & 0xff; }
     SS_HOST_DEVICE SS_INLINE int weight_of(int c) const { return (int)(weight >> (12 * c)) & 0xfff; }
 };
