@@ -97,7 +97,46 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a)
     };
     int b = p, pre = 0;
     long long total = 0;
-    if (fits) {
+    if (fits && a.batch <= 64) {
+        // A request to a lane: each wavefront does all of it by itself and waits once, for the prefixes in LDS, where the loops
+        // below wait five times (three times without classes) and read the other wavefronts' counts in between.  A call is 0.6 us
+        // shorter with classes (16 requests of 20..60 tokens 31.9 -> 31.3 us, 32 trees 69.4 -> 68.7) and 0.3 without (110.3 -> 110.0).
+        const bool real = lane < a.batch;
+        int t = 0, c = 0, req = lane;
+        if (real) request(lane, t, c);
+        if constexpr (SORTED) {
+            int place = lane, end = 0;
+#pragma unroll
+            for (int k = 0; k < kMaxClasses; ++k) {
+                const unsigned long long m = __ballot(real && c == k);
+                if (real && c == k) place = end + __popcll(m & ((1ull << lane) - 1));
+                end += __popcll(m);
+                cuts.classes.end[k] = end;
+            }
+            t = __builtin_amdgcn_ds_permute(place << 2, t);   // (`place` is a permutation of the lanes)
+            req = __builtin_amdgcn_ds_permute(place << 2, lane);
+        }
+        longest = t;
+        auto add = [](int x, int y) { return x + y; };
+        const int incl = wave_scan_int(t, add);
+        if (wave == 0 && real) prefix[lane] = incl - t;
+        if (wave == 0 && lane == 63) prefix[a.batch] = incl;
+        if constexpr (SORTED) {
+            const int cls = cuts.classes.of(lane);
+            const int u = real ? t * cuts.classes.cost_of(cls) + cuts.classes.weight_of(cls) : 0;
+            const int cincl = wave_scan_int(u, add);
+            if (wave == 0 && real) {
+                cprefix[lane] = (uint32_t)(cincl - u);
+                order[lane] = (uint16_t)req;
+            }
+            if (wave == 0 && lane == 63) cprefix[a.batch] = (uint32_t)cincl;
+        }
+        note_longest(longest);
+        __syncthreads();
+        pre = prefix[p];
+        if constexpr (SORTED) b = order[p];
+        total = (long long)__builtin_amdgcn_readfirstlane(prefix[a.batch]) * a.num_kv_heads;
+    } else if (fits) {
         // the first 256 requests stay in registers between the passes
         int n0 = 0, c0 = 0;
         if (tid < a.batch) request(tid, n0, c0);

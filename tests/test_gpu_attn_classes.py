@@ -45,6 +45,15 @@ def test_large_batches(oracle, batch):
     check(_inputs("bf16", 8, 1, lens, depth, seed=1), oracle, max_q_len=10, label=f"{batch} requests")
 
 
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])   # a request to a lane of the plan up to 64, loops from 65 on
+@pytest.mark.parametrize("hq,top", [(4, 3), (8, 9)])     # one row block (no classes); one to five
+def test_batches_of_a_lane_each(oracle, hq, top, batch):
+    rng = np.random.default_rng(batch)
+    depth = rng.integers(0, top + 1, batch)
+    lens = np.maximum(depth + 1, rng.integers(1, 300, batch))
+    check(_inputs("bf16", hq, 1, lens, depth, seed=2), oracle, max_q_len=top + 1, label=f"{batch} requests, {hq} heads")
+
+
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_repeated_calls_give_the_same_bits(kv):
     rng = np.random.default_rng(3)
