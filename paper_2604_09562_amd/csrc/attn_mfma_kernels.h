@@ -783,7 +783,9 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             const float m_new = fmaxf(m_run[nb], mx);
-            if (__any(m_run[nb] > kNoMax)) {   // (before a unit's first pair there is nothing to rescale)
+            // (Before a unit's first pair there is nothing to rescale.  Not by the reference: scores of exactly kNoMax leave
+            // it where it was, and their mass has to go with the first larger score.)
+            if (__any(l_run[nb] != 0.f)) {
                 const float alpha = __builtin_amdgcn_exp2f(m_run[nb] - m_new);
                 l_run[nb] *= alpha;
 #pragma unroll

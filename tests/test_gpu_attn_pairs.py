@@ -87,3 +87,25 @@ def test_single_long_requests(oracle, tokens, hkv, hq, depth, spans, chain):
     torch.cuda.synchronize()
     plan = ws[:16].view(torch.int32).tolist()
     assert (plan[1], plan[3]) == (spans, chain), plan
+
+
+@pytest.mark.parametrize("waves", [4, 0])
+@pytest.mark.parametrize("hq,depth", [(8, 1), (4, 7), (8, 5), (4, 15), (8, 9)])   # 1 to 5 row blocks, all of them full
+def test_scores_at_the_first_reference(oracle, hq, depth, waves):
+    """Scores of exactly -1e30, the reference before any score was seen, have mass until a larger score comes: none of it may stay."""
+    cfg = LLAMA8B.scaled(batch=1, num_q_heads=hq, num_kv_heads=1)
+    inp = synth.make_attention_inputs(cfg, seed=depth, kv_len=np.array([256], np.int32), depth=np.array([depth], np.int32))
+    inp["sm_scale"] = float.fromhex("0x1.17f5bep-1")       # times log2(e) in float32: 1e30 / 2^100
+    one = synth.to_bf16_bits(np.array([2.0 ** 50, -2.0 ** 50], np.float32))
+    inp["q"][:] = 0
+    inp["q"][:, :, 0] = one[0]
+    inp["k_cache"][:] = 0
+    for pair in (0, 2):                                    # each the first of some wavefront, alone or in a team
+        inp["k_cache"][inp["block_table"][0, 2 * pair:2 * pair + 2], :, :, 0] = one[1]
+    binding.ss_set_option("attn_path", 2)
+    binding.ss_set_option("attn_waves", waves)
+    try:
+        check(inp, oracle, label=f"{hq} heads depth {depth} waves {waves}")
+    finally:
+        binding.ss_set_option("attn_path", 0)
+        binding.ss_set_option("attn_waves", 0)
