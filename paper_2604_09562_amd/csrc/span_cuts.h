@@ -6,8 +6,8 @@
 // [ya, ya + weight + n_b), ya = (flat index of its first pair) + weight * u, and wave w starts at the cut
 // w * total_w / nw.  A cut inside a unit's virtual part starts the span at the unit's first pair.  The plan
 // kernel (which writes the spans) and the merge kernel (which has to know which waves hold a part of a unit)
-// both use the functions below; plain integer code with no device dependency, so that a host test can check
-// them against each other over many shapes.
+// both use the functions below; they depend on nothing of the device, so that a host test can check
+// them against each other over many shapes: the same arithmetic, the division of `quotient` included.
 #pragma once
 
 #include <stdint.h>
@@ -77,17 +77,12 @@ struct SpanClasses {
 };
 
 // a / b for 0 <= a < 2^62, b >= 1 and a quotient below 2^50: by a division in fp64 and one correction (the integer division is
-// about 150 instructions, and a descriptor takes five of them).
+// about 150 instructions on the GPU, and a descriptor takes five of them).
 SS_HOST_DEVICE SS_INLINE inline long long quotient(long long a, long long b)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    long long q = (long long)((double)a / (double)b);
+    const long long q = (long long)((double)a / (double)b);   // off by less than one: 2^50 * 3 * 2^-53
     const long long r = a - q * b;
-    q += r < 0 ? -1 : r >= b ? 1 : 0;
-    return q;
-#else
-    return a / b;
-#endif
+    return q + (r < 0 ? -1 : r >= b ? 1 : 0);
 }
 
 struct SpanCuts {

@@ -51,6 +51,10 @@ extern "C" long long count_spans(long long total, int longest, long long launch_
     *chain = c.chain;
     return c.spans;
 }
+extern "C" void quotients(const long long *a, const long long *b, int n, long long *out)
+{
+    for (int i = 0; i < n; ++i) out[i] = ss::quotient(a[i], b[i]);
+}
 extern "C" void merge_waves(const int32_t *prefix, int batch, int hkv, int weight, long long nw, int *first, int *last)
 {
     const SpanCuts c = SpanCuts::make(prefix, batch, hkv, weight, nw);
@@ -109,6 +113,27 @@ def _check(shim, pairs, hkv, weight, nw):
             wg_slots.add(wg + unit)
         # a unit whose holders share one workgroup is finished inside the streaming kernel: the merge kernel skips it
         assert (first[unit] // 4 == last[unit] // 4) == (len({w // 4 for w in holders}) == 1)
+
+
+def test_quotient(shim):
+    """Floor division at exact multiples and one to either side, up to its limits: dividend below 2^62, quotient below 2^50."""
+    rng = np.random.default_rng(3)
+    pairs = []
+    for _ in range(20000):
+        b = int(2 ** rng.uniform(0, 61.9))
+        q = int(2 ** rng.uniform(0, min(50.0, 61.99 - np.log2(b)))) if b < 2 ** 61 else 1
+        for a in (q * b - 1, q * b, q * b + 1, q * b + b - 1):
+            if 0 <= a < 2 ** 62 and a // b < 2 ** 50:
+                pairs.append((a, b))
+    for b in (1, 2, 3, 2 ** 12 - 1, 2 ** 12, 2 ** 12 + 1):
+        for q in (0, 1, 2 ** 50 - 1):
+            pairs += [(q * b, b), (q * b + b - 1, b)]
+    pairs += [(2 ** 62 - 1, 2 ** 12 + 1), (2 ** 62 - 1, 2 ** 62), (0, 1), (0, 2 ** 62)]
+    a, b = (np.array(x, np.int64) for x in zip(*pairs))
+    out = np.empty_like(a)
+    p64 = ctypes.POINTER(ctypes.c_longlong)
+    shim.quotients(a.ctypes.data_as(p64), b.ctypes.data_as(p64), len(a), out.ctypes.data_as(p64))
+    assert len(a) > 50000 and np.array_equal(out, a // b)
 
 
 def test_small_shapes_exhaustively(shim):
