@@ -229,7 +229,7 @@ int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const 
     a.req = reinterpret_cast<AttnReq *>(w);
     w += align_up(sizeof(AttnReq) * (size_t)batch->batch, 256);
     a.wave_desc = reinterpret_cast<int32_t *>(w);
-    w += align_up(sizeof(int32_t) * kDescInts * (size_t)launch_waves, 256);
+    w += align_up(sizeof(int32_t) * kDescInts * ((size_t)launch_waves + 1), 256);
     a.pair_addr = reinterpret_cast<int2 *>(w);
     w += align_up(sizeof(int2) * (size_t)batch->batch * (((size_t)batch->max_blocks_per_seq + 1) / 2) * kv->num_kv_heads, 256);
     const size_t slots = (size_t)launch_waves + (size_t)batch->batch * kv->num_kv_heads;

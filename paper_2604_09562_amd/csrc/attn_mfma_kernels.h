@@ -897,11 +897,14 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     constexpr bool CLASSES = BLOCKS > kChainRowBlocks;
     __shared__ StreamLds<BLOCKS> lds;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // where this wave's span starts: written by the plan kernel (waves past the partition count get x0 == x1)
+    // where this wave's span starts: written by the plan kernel (waves past the partition count start at the end of all pairs).  It
+    // ends where the next one starts.
     const int32_t *d = wave_desc + (long long)(blockIdx.x * kWavesPerWg + wslot) * kDescInts;
     Run run;
     run.p = d[0]; run.g = d[1]; run.b = d[16]; run.n = d[17];
-    run.x0 = d[4]; run.x1 = d[5];
+    run.x0 = d[4];
+    const int next_team = wave_desc[(long long)(blockIdx.x + 1) * kWavesPerWg * kDescInts + 4], next_wave = d[kDescInts + 4];
+    run.x1 = CLASSES || d[15] ? next_team : next_wave;
     run.unit_x = run.x0 - d[2];
     run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
 #pragma unroll
@@ -922,7 +925,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         const int end = run.x1;
         // (the first class's end comes with the descriptor: the plan's record would be one more read in a row before the
         // first pair, 0.5 % of the whole call: 221.8 -> 220.5 us with 96 e4m3 requests, 278.8 -> 277.4 with 128 ragged ones)
-        run.x1 = d[18];
+        run.x1 = d[5] < end ? d[5] : end;
         for (int c = d[3];;) {
             if (run.x0 < run.x1) {
                 const int blocks = BLOCKS - c;
@@ -985,7 +988,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     cuts.total_w = a.plan->total_cost;
     cuts.nw = a.plan->cuts;
     int w_first, w_last;
-    cuts.unit_waves((long long)r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
+    cuts.unit_spans(r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
     if (!a.plan->team) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
         w_first /= kWavesPerWg;
         w_last /= kWavesPerWg;

@@ -26,7 +26,7 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
 constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
 constexpr int kWavesPerWg = 4;
-constexpr int kDescInts = 32;            // ints per wave descriptor (19 in use)
+constexpr int kDescInts = 32;            // ints per wave descriptor (18 in use)
 constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
 constexpr int kChainRowBlocks = 2;       // up to here the spans of a workgroup can be combined in LDS
@@ -76,7 +76,7 @@ struct AttnReq {
     int32_t L, q0, q1;     // its kv_len, its query rows
     int32_t n, cls;        // pairs per KV head, class
     int32_t pre;           // pairs per KV head in front of it
-    uint32_t cpre;         // cost per KV head in front of it
+    int64_t cpre;          // cost per KV head in front of it
 };
 
 struct AttnArgs {
@@ -103,14 +103,13 @@ struct AttnArgs {
     AttnPlan *plan;
     AttnReq *req;          // [batch] the requests in the order of the flat sequence
     int2 *pair_addr;       // [batch*ceil(max_blocks/2)*kv_heads] flat pair list: per tile, physical block * kv_heads + kv head
-    int32_t *wave_desc;    // [launch_waves][kDescInts]: where each wave's span starts and what its first loads need
+    int32_t *wave_desc;    // [launch_waves + 1][kDescInts]: where each wave's span starts and what its first loads need
     float *part_o;         // [slots][rows_pad][head_dim]
     float *part_ml;        // [slots][rows_pad][2]  (log2-domain max, sum)
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
     int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts)
     int32_t auto_weight;   // unit_weight is the default: teams take the weights measured for their row blocks
-    int32_t plan_fits;     // the plan's prefixes fit LDS and 32 bits: the cuts are weighted, the requests laid out by class
     int32_t team_blocks;   // row blocks of the team kernel that is launched, 0 for the kernels of one or two
 };
 

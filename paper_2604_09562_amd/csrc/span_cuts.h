@@ -1,11 +1,11 @@
 // Where the flat sequence of KV tile pairs is cut into the spans of the streaming attention kernel.
 //
-// The pairs of all (request, KV head) units lie end to end, unit major: request b contributes hkv units of
-// n_b pairs each.  Spans are equal in a "weighted" coordinate in which every unit is preceded by `weight`
-// virtual pairs (what opening a unit costs a wavefront): unit u = b * hkv + g occupies the stretch
-// [ya, ya + weight + n_b), ya = (flat index of its first pair) + weight * u, and wave w starts at the cut
-// w * total_w / nw.  A cut inside a unit's virtual part starts the span at the unit's first pair.  The plan
-// kernel (which writes the spans) and the merge kernel (which has to know which waves hold a part of a unit)
+// The pairs of all (request, KV head) units lie end to end, unit major: the request at place p of the layout contributes
+// hkv units of n_p pairs each.  Spans are equal in a weighted coordinate in which every unit is preceded by
+// what opening it costs, and a pair is as long as it costs: the unit occupies the stretch
+// [ya, ya + weight + n * cost), and span w starts at the cut w * total_w / nw.  A cut inside the opening's part
+// starts the span at the unit's first pair; a span ends where the next one starts.  The plan
+// kernel (which writes the spans) and the merge kernel (which has to know which spans hold a part of a unit)
 // both use the functions below; they depend on nothing of the device, so that a host test can check
 // them against each other over many shapes: the same arithmetic, the division of `quotient` included.
 #pragma once
@@ -62,6 +62,7 @@ SS_HOST_DEVICE inline long long count_team_spans(long long total, int longest, l
 constexpr int kMaxClasses = 5;
 struct SpanClasses {
     int end[kMaxClasses];    // requests (in layout order) of class 0, classes 0 and 1, ...: the last one is the batch
+    int x[kMaxClasses];      // their pairs per KV head
     uint64_t cost, weight;   // of a pair (8 bits a class), of opening a unit (12 bits a class): packed, as arrays indexed by a
                              // variable would live in scratch memory
     SS_HOST_DEVICE SS_INLINE int of(int i) const
@@ -71,13 +72,28 @@ struct SpanClasses {
         for (int k = 0; k + 1 < kMaxClasses; ++k) c += i >= end[k];
         return c;
     }
-    SS_HOST_DEVICE SS_INLINE int end_of(int c) const { return c == 0 ? end[0] : c == 1 ? end[1] : c == 2 ? end[2] : c == 3 ? end[3] : end[4]; }
     SS_HOST_DEVICE SS_INLINE int cost_of(int c) const { return (int)(cost >> (8 * c)) & 0xff; }
     SS_HOST_DEVICE SS_INLINE int weight_of(int c) const { return (int)(weight >> (12 * c)) & 0xfff; }
+    // What the requests in front of place p cost per KV head: p is of class c, and `pre` pairs lie in front of it.
+    SS_HOST_DEVICE SS_INLINE long long start(int p, int pre, int c) const
+    {
+        long long y = 0;
+        int first = 0, x0 = 0;   // requests and pairs in front of class c
+#pragma unroll
+        for (int k = 0; k + 1 < kMaxClasses; ++k) {
+            if (k < c) {
+                y += (long long)(x[k] - x0) * cost_of(k) + (long long)(end[k] - first) * weight_of(k);
+                first = end[k];
+                x0 = x[k];
+            }
+        }
+        return y + (long long)(pre - x0) * cost_of(c) + (long long)(p - first) * weight_of(c);
+    }
+    SS_HOST_DEVICE SS_INLINE long long total() const { return start(end[kMaxClasses - 1], x[kMaxClasses - 1], kMaxClasses - 1); }
 };
 
 // a / b for 0 <= a < 2^62, b >= 1 and a quotient below 2^50: by a division in fp64 and one correction (the integer division is
-// about 150 instructions on the GPU, and a descriptor takes five of them).
+// about 150 instructions on the GPU).
 SS_HOST_DEVICE SS_INLINE inline long long quotient(long long a, long long b)
 {
     const long long q = (long long)((double)a / (double)b);   // off by less than one: 2^50 * 3 * 2^-53
@@ -86,82 +102,26 @@ SS_HOST_DEVICE SS_INLINE inline long long quotient(long long a, long long b)
 }
 
 struct SpanCuts {
-    const int32_t *prefix;    // [batch + 1] exclusive prefix of the pairs per KV head of the requests
-    int batch, hkv, weight;   // (weight: of every unit, without classes)
-    long long total;          // pairs of all units
-    long long total_w;        // the coordinate's end: what all units cost
-    long long nw;             // number of spans
-    const uint32_t *cprefix;  // [batch + 1] exclusive prefix of the units' costs, or nullptr: every pair costs one
-    SpanClasses classes;      // (with cprefix)
+    long long total_w;   // the coordinate's end: what all units cost
+    long long nw;        // number of spans
 
-    SS_HOST_DEVICE static SpanCuts make(const int32_t *prefix, int batch, int hkv, int weight, long long nw)
-    {
-        SpanCuts c;
-        c.prefix = prefix;
-        c.batch = batch;
-        c.hkv = hkv;
-        c.weight = weight;
-        c.total = (long long)prefix[batch] * hkv;
-        c.total_w = c.total + (long long)weight * batch * hkv;
-        c.nw = nw;
-        c.cprefix = nullptr;
-        return c;
-    }
-    // weighted coordinate of wave w's cut
-    SS_HOST_DEVICE long long cut(long long w) const { return quotient(w * total_w, nw); }
-    // where request i's stretch begins in the coordinate, per KV head; what opening a unit and a pair of it cost
-    SS_HOST_DEVICE SS_INLINE long long start(int i) const { return cprefix ? (long long)cprefix[i] : (long long)prefix[i] + (long long)weight * i; }
-    SS_HOST_DEVICE SS_INLINE int weight_of(int i) const { return cprefix ? classes.weight_of(classes.of(i)) : weight; }
-    SS_HOST_DEVICE SS_INLINE int cost_of(int i) const { return cprefix ? classes.cost_of(classes.of(i)) : 1; }
-    // flat index of unit (b, g)'s first pair, and the weighted coordinate where its stretch begins
-    SS_HOST_DEVICE long long unit_offset(int b, int g) const
-    {
-        return (long long)prefix[b] * hkv + (long long)g * (prefix[b + 1] - prefix[b]);
-    }
-    SS_HOST_DEVICE long long unit_coord(int b, int g) const { return start(b) * hkv + (long long)g * (start(b + 1) - start(b)); }
-    // the waves whose cut falls into the stretch [ya, ya + weight + n): w_lo <= w < w_hi (w_hi may exceed nw)
-    SS_HOST_DEVICE long long first_cut_at_or_after(long long y) const { return quotient(y * nw + total_w - 1, total_w); }
+    // weighted coordinate of span w's cut
+    SS_HOST_DEVICE SS_INLINE long long cut(long long w) const { return quotient(w * total_w, nw); }
+    // the first span whose cut lies at or behind y: those of a unit's stretch [ya, ye) are from this of ya to this of ye
+    SS_HOST_DEVICE SS_INLINE long long first_cut_at_or_after(long long y) const { return quotient(y * nw + total_w - 1, total_w); }
     // pair of the unit at which a span begins whose cut lies in the unit's stretch
-    SS_HOST_DEVICE static int first_pair(long long cut_y, long long ya, int weight, int cost)
+    SS_HOST_DEVICE SS_INLINE static int first_pair(long long cut_y, long long ya, int weight, int cost)
     {
         const long long in_unit = cut_y - ya - weight;
-        return in_unit > 0 ? (int)((uint32_t)in_unit / (uint32_t)cost) : 0;   // (a unit's stretch fits 32 bits)
+        return in_unit > 0 ? (int)quotient(in_unit, cost) : 0;
     }
-    SS_HOST_DEVICE int first_pair(long long cut_y, long long ya) const { return first_pair(cut_y, ya, weight, 1); }
-    // unit and pair that weighted coordinate y (< total_w) falls on; returns the flat pair index
-    SS_HOST_DEVICE SS_INLINE long long locate(long long y, int &b, int &g, int &pair) const
-    {
-        int lo = 0, hi = batch - 1;   // last request whose first unit starts at or before y
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (start(mid) * hkv <= y)
-                lo = mid;
-            else
-                hi = mid - 1;
-        }
-        b = lo;
-        const int n = prefix[b + 1] - prefix[b];
-        const long long r = y - start(b) * hkv, unit = start(b + 1) - start(b);
-        g = (int)quotient(r, unit);
-        pair = first_pair(r, (long long)g * unit, weight_of(b), cost_of(b));
-        return (long long)prefix[b] * hkv + (long long)g * n + pair;
-    }
-    // flat index one past wave w's last pair
-    SS_HOST_DEVICE SS_INLINE long long span_end(long long w) const
-    {
-        if (w + 1 >= nw) return total;
-        if (!cprefix && weight == 0) return (w + 1) * total / nw;
-        int b, g, t;
-        return locate(cut(w + 1), b, g, t);
-    }
-    // The waves that hold pairs of a unit with n >= 1 pairs whose stretch begins at ya: the last wave whose cut
-    // lies at or before the unit's first pair ... the last wave whose cut lies at or before its last pair.
-    SS_HOST_DEVICE void unit_waves(long long ya, int n, int weight, int cost, int &w_first, int &w_last) const
+    // The spans that hold pairs of a unit with n >= 1 pairs whose stretch begins at ya: the last one whose cut
+    // lies at or before the unit's first pair ... the last one whose cut lies at or before its last pair.
+    SS_HOST_DEVICE SS_INLINE void unit_spans(long long ya, int n, int weight, int cost, int &w_first, int &w_last) const
     {
         w_first = (int)quotient((ya + weight + cost) * nw - 1, total_w);
         w_last = (int)quotient((ya + weight + (long long)n * cost) * nw - 1, total_w);
     }
-    SS_HOST_DEVICE void unit_waves(long long ya, int n, int &w_first, int &w_last) const { unit_waves(ya, n, weight, 1, w_first, w_last); }
 };
 
 }  // namespace ss

@@ -16,41 +16,44 @@ SHIM = r"""
 using namespace ss;
 // out[w] = {unit, first pair, x0, x1} of every span, as the plan kernel finds them unit by unit; first/last: the merge's formula
 extern "C" long long spans(const int32_t *n, const int32_t *cls, int batch, int hkv, const int32_t *cost, const int32_t *weight, long long nw,
-                           int32_t *prefix, uint32_t *cprefix, long long *out, int *count, int *first, int *last)
+                           int32_t *prefix, long long *cprefix, long long *out, int *count, int *first, int *last)
 {
-    SpanCuts c = SpanCuts::make(prefix, batch, hkv, 0, nw);
-    c.classes.cost = c.classes.weight = 0;
-    for (int k = 0; k < kMaxClasses; ++k) {
-        c.classes.end[k] = 0;
-        for (int i = 0; i < batch; ++i) c.classes.end[k] += cls[i] <= k;
-        c.classes.cost |= (uint64_t)cost[k] << (8 * k);
-        c.classes.weight |= (uint64_t)weight[k] << (12 * k);
-    }
+    SpanClasses k5;
+    k5.cost = k5.weight = 0;
     prefix[0] = 0;
     cprefix[0] = 0;
     for (int i = 0; i < batch; ++i) {
-        if (c.classes.of(i) != cls[i]) return -1;
         prefix[i + 1] = prefix[i] + n[i];
-        cprefix[i + 1] = cprefix[i] + n[i] * c.classes.cost_of(cls[i]) + c.classes.weight_of(cls[i]);
+        cprefix[i + 1] = cprefix[i] + (long long)n[i] * cost[cls[i]] + weight[cls[i]];
     }
-    c.cprefix = cprefix;
-    c.total = (long long)prefix[batch] * hkv;
-    c.total_w = (long long)cprefix[batch] * hkv;
-    for (int p = 0; p < batch; ++p)
+    for (int k = 0; k < kMaxClasses; ++k) {
+        k5.end[k] = 0;
+        for (int i = 0; i < batch; ++i) k5.end[k] += cls[i] <= k;
+        k5.x[k] = prefix[k5.end[k]];
+        k5.cost |= (uint64_t)cost[k] << (8 * k);
+        k5.weight |= (uint64_t)weight[k] << (12 * k);
+    }
+    if (k5.total() != cprefix[batch]) return -1;
+    const SpanCuts c = {k5.total() * hkv, nw};
+    for (int p = 0; p < batch; ++p) {
+        const int co = k5.cost_of(cls[p]), we = k5.weight_of(cls[p]);
+        if (k5.of(p) != cls[p] || co != cost[cls[p]] || we != weight[cls[p]] || k5.start(p, prefix[p], cls[p]) != cprefix[p]) return -1;
         for (int g = 0; g < hkv; ++g) {
-            const int co = c.cost_of(p), we = c.weight_of(p);
-            const long long off = c.unit_offset(p, g), ya = c.unit_coord(p, g), ye = ya + we + (long long)n[p] * co;
-            for (long long w = c.first_cut_at_or_after(ya); w < c.first_cut_at_or_after(ye) && w < nw; ++w) {
+            const long long off = (long long)prefix[p] * hkv + (long long)g * n[p], stretch = we + (long long)n[p] * co,
+                            ya = k5.start(p, prefix[p], cls[p]) * hkv + g * stretch;
+            for (long long w = c.first_cut_at_or_after(ya); w < c.first_cut_at_or_after(ya + stretch) && w < nw; ++w) {
                 const int t0 = SpanCuts::first_pair(c.cut(w), ya, we, co);
                 out[4 * w] = (long long)p * hkv + g;
                 out[4 * w + 1] = t0;
                 out[4 * w + 2] = off + t0;
-                out[4 * w + 3] = c.span_end(w);
+                if (w) out[4 * w - 1] = off + t0;   // a span ends where the next one starts
                 ++count[w];
             }
-            c.unit_waves(ya, n[p], we, co, first[p * hkv + g], last[p * hkv + g]);
+            c.unit_spans(ya, n[p], we, co, first[p * hkv + g], last[p * hkv + g]);
         }
-    return c.total;
+    }
+    out[4 * nw - 1] = (long long)prefix[batch] * hkv;
+    return (long long)prefix[batch] * hkv;
 }
 extern "C" long long team_spans(long long total, int longest, long long most) { return count_team_spans(total, longest, most); }
 """
@@ -85,10 +88,10 @@ def test_spans_by_class(shim, seed):
         nw = int(min(rng.choice([1, 3, 16, 256]), max(1, total // 2)))
         out, count = np.full((nw, 4), -1, np.int64), np.zeros(nw, np.int32)
         first, last = np.zeros(batch * hkv, np.int32), np.zeros(batch * hkv, np.int32)
-        prefix, cprefix = np.zeros(batch + 1, np.int32), np.zeros(batch + 1, np.uint32)
+        prefix, cprefix = np.zeros(batch + 1, np.int32), np.zeros(batch + 1, np.int64)
         assert shim.spans(_p(n), _p(cls), batch, hkv, _p(cost), _p(weight), ctypes.c_longlong(nw), _p(prefix), _p(cprefix), _p(out),
                           _p(count), _p(first), _p(last)) == total
-        assert np.all(count == 1)
+        assert np.all(count == 1) and np.all(out[:, 1] >= 0)
         x0, x1 = out[:, 2], out[:, 3]
         assert x0[0] == 0 and x1[-1] == total and np.all(x1[:-1] == x0[1:]) and np.all(x1 >= x0)
         off = np.concatenate([[0], np.cumsum(np.repeat(n, hkv))])

@@ -1,10 +1,10 @@
 """Host check of the span-cut arithmetic shared by the plan kernel and the merge kernel of the attention path.
 
-`csrc/span_cuts.h` is plain integer code.  It is compiled here for the host; for many shapes (pair counts per
+`csrc/span_cuts.h` depends on nothing of the device.  It is compiled here for the host; for many shapes (pair counts per
 request, KV heads, span counts, unit weights) the spans are enumerated the way the plan kernel writes them
 (for every unit, the waves whose cut falls into the unit's stretch) and checked against what the streaming
 and merge kernels rely on:
-  * the spans tile the flat sequence: contiguous, in order, nothing lost, nothing twice;
+  * the spans (each ends where the next one starts) tile the flat sequence: in order, nothing lost, nothing twice;
   * every wave gets its descriptor from exactly one unit, and its span begins inside that unit;
   * the waves that hold pairs of a unit are exactly w_first .. w_last of the merge kernel's formula, so the
     partial slots it reads are the ones that were written (also after the division by four that the
@@ -25,25 +25,41 @@ SHIM = r"""
 #define SS_HOST_DEVICE
 #include "span_cuts.h"
 using ss::SpanCuts;
+using ss::SpanClasses;
+// One class, a pair costing one: the layout, and where unit (b, g)'s stretch begins.
+static SpanClasses one_class(const int32_t *prefix, int batch, int weight)
+{
+    SpanClasses c;
+    c.cost = 1;
+    c.weight = weight;
+    for (int k = 0; k < ss::kMaxClasses; ++k) c.end[k] = batch, c.x[k] = prefix[batch];
+    return c;
+}
+static long long unit_start(const SpanClasses &c, const int32_t *prefix, int b, int g, int hkv)
+{
+    return c.start(b, prefix[b], 0) * hkv + (long long)g * (c.weight_of(0) + prefix[b + 1] - prefix[b]);
+}
 // For every unit (b, g) in order: the waves the plan kernel would describe from it, with their first pair and
 // span (x0, x1).  out[w] = {unit, t0, x0, x1}; count[w] = how many units claimed wave w.
 extern "C" void plan_spans(const int32_t *prefix, int batch, int hkv, int weight, long long nw, long long *out, int *count)
 {
-    const SpanCuts c = SpanCuts::make(prefix, batch, hkv, weight, nw);
+    const SpanClasses classes = one_class(prefix, batch, weight);
+    const SpanCuts c = {classes.total() * hkv, nw};
     for (int b = 0; b < batch; ++b)
         for (int g = 0; g < hkv; ++g) {
             const int n = prefix[b + 1] - prefix[b];
-            const long long off = c.unit_offset(b, g), ya = c.unit_coord(b, g);
+            const long long off = (long long)prefix[b] * hkv + (long long)g * n, ya = unit_start(classes, prefix, b, g, hkv);
             const long long w_lo = c.first_cut_at_or_after(ya), w_hi = c.first_cut_at_or_after(ya + weight + n);
             for (long long w = w_lo; w < w_hi && w < nw; ++w) {
-                const int t0 = c.first_pair(c.cut(w), ya);
+                const int t0 = SpanCuts::first_pair(c.cut(w), ya, weight, 1);
                 out[4 * w + 0] = (long long)b * hkv + g;
                 out[4 * w + 1] = t0;
                 out[4 * w + 2] = off + t0;
-                out[4 * w + 3] = c.span_end(w);
+                if (w) out[4 * w - 1] = off + t0;   // a span ends where the next one starts
                 ++count[w];
             }
         }
+    out[4 * nw - 1] = (long long)prefix[batch] * hkv;
 }
 extern "C" long long count_spans(long long total, int longest, long long launch_waves, int can_chain, int *chain)
 {
@@ -57,10 +73,11 @@ extern "C" void quotients(const long long *a, const long long *b, int n, long lo
 }
 extern "C" void merge_waves(const int32_t *prefix, int batch, int hkv, int weight, long long nw, int *first, int *last)
 {
-    const SpanCuts c = SpanCuts::make(prefix, batch, hkv, weight, nw);
+    const SpanClasses classes = one_class(prefix, batch, weight);
+    const SpanCuts c = {classes.total() * hkv, nw};
     for (int b = 0; b < batch; ++b)
         for (int g = 0; g < hkv; ++g)
-            c.unit_waves(c.unit_coord(b, g), prefix[b + 1] - prefix[b], first[b * hkv + g], last[b * hkv + g]);
+            c.unit_spans(unit_start(classes, prefix, b, g, hkv), prefix[b + 1] - prefix[b], weight, 1, first[b * hkv + g], last[b * hkv + g]);
 }
 """
 
