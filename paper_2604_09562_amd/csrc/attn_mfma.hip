@@ -32,7 +32,6 @@ namespace {
 // 6.4 (two kernels), 1000 over two 25.4 -> 12.4, 4096 over one 177 -> 22.  (Without classes, cuts and layout by one prefix of the batch
 // took 6.5, 9.0, 10.7, 12.3 and 39.6.)
 // ---------------------------------------------------------------------------------------------
-static_assert(kSpansPerWg == kWavesPerWg, "one span per wavefront");
 constexpr int kPlanLanes = 256, kPlanGroups = 512;
 
 // Inclusive scan over a wavefront's lanes (values >= 0, 0 is neutral for `op`) by data-parallel moves: a scan by shuffles is six
@@ -60,11 +59,13 @@ __device__ __forceinline__ int wave_total(int x, Op op)
     return __builtin_amdgcn_readlane(wave_scan_int(x, op), 63);
 }
 
-// Costs for the cuts of a team kernel, in eighths of a pair of a unit with one row block: of a pair and of opening a unit, with
-// 1 .. 5 row blocks, for bf16 and e4m3 caches.  Measured by sweeps over nine bf16 and seven e4m3 batches (uniform and mixed row blocks, short
-// and long units); half or twice the opening costs are 1 to 4 % slower, pair costs between equal and 8 : 12 within 3 %.
+// Costs for the cuts of the class kernels, in eighths of a pair of a unit with one row block: of a pair and of opening a unit, with
+// 1 .. 5 row blocks, for bf16 and e4m3 caches.  For teams measured by sweeps over nine bf16 and seven e4m3 batches (uniform and mixed row blocks, short
+// and long units); half or twice the opening costs are 1 to 4 % slower, pair costs between equal and 8 : 12 within 3 %.  For wavefronts by
+// themselves over 90 batches of 80 to 256 requests: half of these opening costs 2 % slower, twice 1 %.
 constexpr int kPairCost[2][kMaxClasses] = {{8, 8, 8, 9, 9}, {8, 8, 9, 9, 10}};
 constexpr int kOpenCost[2][kMaxClasses] = {{32, 48, 80, 100, 128}, {64, 96, 160, 220, 280}};
+constexpr int kOpenCostAlone[kMaxClasses] = {24, 32, 44, 52, 68};
 // Packed for SpanClasses, class 0 being five row blocks.
 constexpr uint64_t pack_costs(const int (&v)[kMaxClasses], int bits)
 {
@@ -84,26 +85,28 @@ __device__ __forceinline__ void plan_request(const AttnArgs &a, int L, int q_len
 // How a call is cut: filled in from the classes' requests and pairs and the longest unit's pairs.
 struct Cut {
     SpanClasses classes;
-    SpanCount count;
     SpanCuts cuts;
     long long total;   // pairs of all units
-    int team;
+    int mode;
 
     __device__ __forceinline__ void choose(const AttnArgs &a, int longest)
     {
+        const bool kv8 = a.kv_dtype == SS_FP8_E4M3;
         total = (long long)classes.x[kMaxClasses - 1] * a.num_kv_heads;
-        count = count_spans(total, longest, a.launch_waves, a.team_blocks == 0);
-        team = a.team_blocks > 0 || count.spans < a.launch_waves;   // (kernels of one or two row blocks: when the chip is not full)
-        cuts.nw = team ? count_team_spans(total, longest, a.launch_waves / kWavesPerWg) : count.spans;
+        const SpanChoice c = choose_spans(total, longest, (long long)a.batch * a.num_kv_heads, a.launch_waves, a.team_blocks > 0, kv8);
+        mode = c.mode;
+        cuts.nw = c.spans;
+        constexpr uint64_t every = 0x001001001001001ull;   // one weight for all classes
         if (a.team_blocks) {
-            const bool kv8 = a.kv_dtype == SS_FP8_E4M3;
             const int skip = kMaxClasses - a.team_blocks;   // classes with more row blocks than the kernel has
             classes.cost = (kv8 ? pack_costs(kPairCost[1], 8) : pack_costs(kPairCost[0], 8)) >> (8 * skip);
-            classes.weight = a.auto_weight ? (kv8 ? pack_costs(kOpenCost[1], 12) : pack_costs(kOpenCost[0], 12)) >> (12 * skip)
-                                           : 0x001001001001001ull * (uint64_t)(a.unit_weight * kWavesPerWg * 8);
+            if (a.auto_weight)
+                classes.weight = (mode == kSpanAlone ? pack_costs(kOpenCostAlone, 12) : kv8 ? pack_costs(kOpenCost[1], 12) : pack_costs(kOpenCost[0], 12)) >> (12 * skip);
+            else
+                classes.weight = every * (uint64_t)(a.unit_weight * 8 * (mode == kSpanTeam ? kWavesPerWg : 1));
         } else {   // What a team pays for opening a unit: 4 to 8 pairs are level with one or two row blocks.
             classes.cost = 1;
-            classes.weight = (uint64_t)(team ? a.unit_weight * 2 : a.unit_weight);
+            classes.weight = (uint64_t)(mode == kSpanTeam ? a.unit_weight * 2 : a.unit_weight);
         }
         cuts.total_w = classes.total() * a.num_kv_heads;
     }
@@ -111,11 +114,8 @@ struct Cut {
     {
         AttnPlan &plan = *a.plan;
         plan.total_pairs = (int)total;
-        plan.num_waves = (int)count.spans;
-        plan.unit_weight = a.unit_weight;
-        plan.chain = count.chain;
-        plan.cuts = (int)cuts.nw;
-        plan.team = team;
+        plan.mode = mode;
+        plan.spans = (int)cuts.nw;
         plan.total_cost = cuts.total_w;
 #pragma unroll
         for (int c = 0; c < kMaxClasses; ++c) {
@@ -231,8 +231,8 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
         own = a.req[p];
         const AttnPlan &plan = *a.plan;
         cut.total = plan.total_pairs;
-        cut.team = plan.team;
-        cut.cuts.nw = plan.cuts;
+        cut.mode = plan.mode;
+        cut.cuts.nw = plan.spans;
         cut.cuts.total_w = plan.total_cost;
     } else {
         int L[N], q0[N], q1[N], n[N], c[N], place[N];
@@ -260,6 +260,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
         for (int k = 0; k < kMaxClasses; ++k) {
             if (k < classes) {
                 int pairs = 0;
+                const int before = end;
 #pragma unroll
                 for (int s = 0; s < N; ++s) {
                     const unsigned long long m = __ballot(c[s] == k);
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
                     }
                     end += __popcll(m);
                 }
-                x += wave_total(pairs, Add());
+                if (end > before) x += wave_total(pairs, Add());
             }
             cut.classes.end[k] = end;
             cut.classes.x[k] = x;
@@ -291,6 +292,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
             }
             if ((s & 3) == wave && place[s] >= 0) places[place[s]] = Place{s * 64 + lane, L[s], n[s]};
         }
+        __syncthreads();   // (`places`; nothing but LDS is on its way)
         own.pre = wave_total(pre, Add());
         own.cpre = cut.classes.start(p, own.pre, own.cls);
         if (g0 == 0 && tid == 0) {
@@ -298,7 +300,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
             if (p == a.batch - 1) cut.publish(a);
         }
     }
-    const int per = cut.team ? kWavesPerWg : 1;   // wavefronts that share a span
+    const int per = cut.mode == kSpanTeam ? kWavesPerWg : 1;   // wavefronts that share a span
     const int n = own.n;
     // (a pair whose second tile lies past the cache's end repeats the first; its slots are never visible)
     auto pair_at = [&](int b, int L, int t, int gg) {
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
         return make_int2(b0 * a.num_kv_heads + gg, b1 * a.num_kv_heads + gg);
     };
     const long long off0 = (long long)own.pre * a.num_kv_heads;   // the request's place in the flat list
-    for (int t = tid; t < n; t += 256) {
+    for (int t = 255 - tid; t < n; t += 256) {   // (from the last wavefront on: the first one has the descriptors)
         const int2 addr = pair_at(own.b, own.L, t, 0);
         for (int g = g0; g < g0 + heads; ++g) a.pair_addr[off0 + (long long)g * n + t] = make_int2(addr.x + g, addr.y + g);
     }
@@ -326,7 +328,6 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
 #pragma unroll
         for (int k = 0; k < kMaxClasses; ++k)
             if (k == own.cls) class_end = cut.classes.x[k] * a.num_kv_heads;
-        __syncthreads();   // (`places`)
     }
     for (int g = g0; g < g0 + heads; ++g) {
         const long long off = off0 + (long long)g * n;
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
             d[0] = p; d[1] = g; d[2] = t0; d[3] = own.cls;
             d[4] = (int)(off + t0); d[5] = class_end;
             d[6] = own.L; d[7] = own.q0; d[8] = own.q1;
-            d[15] = cut.team; d[16] = own.b; d[17] = n;
+            d[15] = cut.mode; d[16] = own.b; d[17] = n;
             // walk forward from (p, g, pair) over unit boundaries; past the last unit repeat the unit's pair
             Place at = {own.b, own.L, n};
             int pp = p, gg = g, tt = t0 + (int)(i - w * per);
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(AttnArgs a, int heads)
         for (long long w = cuts.nw * per + tid; w <= a.launch_waves; w += 256) {
             int32_t *d = a.wave_desc + w * kDescInts;
             d[4] = (int)cut.total;
-            d[15] = cut.team;   // (read before the span is seen to be empty)
+            d[15] = cut.mode;   // (read before the span is seen to be empty)
         }
     }
 }
@@ -424,7 +425,7 @@ int32_t attn_mfma_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, 
     AttnArgs p = a;
     p.q_win = (a.max_q_len + passes - 1) / passes;
     const int nb = (p.q_win * G + 15) / 16;   // row blocks of a pass's window
-    if (a.auto_weight) p.unit_weight = nb >= 4 ? kUnitWeightDeep : kUnitWeight;
+    if (a.auto_weight) p.unit_weight = kUnitWeight;
     p.team_blocks = nb > kChainRowBlocks ? attn_team_blocks(G) : 0;
     for (p.q_lo = 0; p.q_lo < a.max_q_len; p.q_lo += p.q_win) {
         if (!(a.reuse_plan && passes == 1)) {   // a stored plan describes one window only

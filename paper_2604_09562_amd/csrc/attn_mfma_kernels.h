@@ -11,20 +11,26 @@
 // of one unit, several whole units and the head of another; for every unit it touches there is
 // one partial result (softmax reference, sum, unnormalised output).
 //
-// A full chip and units of one or two row blocks only: a span per wavefront.  The four wavefronts of a workgroup, whose spans are
-// consecutive, hand the partials of a shared unit from right to left through LDS and combine them by their log-sum-exp; a unit that
+// Whose a span is (choose_spans says, from the batch's lengths):
+//
+// A wavefront's, handed over: units of one or two row blocks on a full chip, or many of them.  The four wavefronts of a workgroup, whose
+// spans are consecutive, hand the partials of a shared unit from right to left through LDS and combine them by their log-sum-exp; a unit that
 // lies inside one workgroup's spans is normalised, rounded and written by that workgroup.
 //
-// Otherwise a span per workgroup, whose wavefronts are a team and take its pairs in turn (every fourth), so that they reach the
+// A workgroup's, whose wavefronts are a team and take its pairs in turn (every fourth), so that they reach the
 // end of a unit together and add their results block by block through LDS.  One partial per workgroup instead of four: with five row
 // blocks a partial is 40 KB (52 MB of them and as much read again by the merge for 281 MB of keys and values, 32 requests of 256..4096
-// with trees of 8..16 nodes; the call 76.5 us with a span per wavefront, 72 with teams).  On a chip that is not full the team ends
-// sooner than a chain of hand-overs (one request of 8000 tokens 29.5 us and 27.3, four of 40..600 21.2 and 20.2), on a full one with one or
-// two row blocks the chain is ahead (64 requests of 256..4096: 108 and 112).  In the kernels for three row blocks and more the requests are
-// laid out by row blocks, and each run of units is walked by the code for its own number of them (see the plan kernel).
+// with trees of 8..16 nodes; the call 76.5 us with a span per wavefront, 69 with teams).  On a chip that is not full the team ends
+// sooner than a chain of hand-overs (one request of 8000 tokens 28.9 us and 23.9).
+//
+// A wavefront's by itself: many units of three row blocks and more, where opening and ending each of them with all four wavefronts would
+// be most of a team's time (256 requests of 48 tokens over 8 KV heads, five row blocks, e4m3: 95 us and 55).
+//
+// In the kernels for three row blocks and more the requests are laid out by row blocks, and each run of units is walked by the code for
+// its own number of them (see the plan kernel).
 //
 // What is left (a unit that crosses spans that are not combined) goes to device memory as a partial in slot
-// `workgroup + unit` (unique along the sequence), and a last
+// `workgroup + unit` (`wavefront + unit` for wavefronts by themselves; unique along the sequence), and a last
 // kernel merges those partials in span order and writes the rounded output.
 //
 // Per pair, with rows = (k+1) * (query heads per KV head) padded to a multiple of 16:
@@ -48,9 +54,9 @@
 // epilogue, more than the 64 KB instruction cache that two compute units share; now 14 to 28 KB per number of row blocks.
 //
 // Measured, a whole call: 96 requests of 512..8192 tokens, e4m3, 64 heads over 8, depth 2..8: 305 us as single tiles with 16-token output
-// products, 247 as pairs, 221 in teams by classes; 32 requests of 256..4096, trees of 8..16 nodes, 32 heads over 8: 98 / 76.5 / 72;
-// 128 requests of 128..16384, depth 0..8, 32 heads over 8: 292 / 291 / 279; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 /
-// 107.2 / 107.7; four requests of 40..600: 26.0 / 20.1 / 20.1.
+// products, 247 as pairs, 221 in teams by classes; 32 requests of 256..4096, trees of 8..16 nodes, 32 heads over 8: 98 / 76.5 / 69;
+// 128 requests of 128..16384, depth 0..8, 32 heads over 8: 292 / 291 / 278; 64 requests of 256..4096 at depth 4 (bound by memory): 108.4 /
+// 107.2 / 106.1; four requests of 40..600: 26.0 / 20.8 / 18.4.
 #pragma once
 
 #include <type_traits>
@@ -221,17 +227,17 @@ struct Run {
 // BLOCKS  those of the kernel
 // TREE    the new tokens of a request form a draft tree: a row's visibility among them comes from its
 //         mask word instead of the chain's "tokens up to my own"
-// TEAM    the run is the workgroup's: its wavefronts take the pairs in turn; else it is the wavefront's own
-template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool TEAM>
-__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, const Run &run, const int2 *__restrict__ pair_addr,
+// CHAIN   wavefronts' spans, handed over; else `team` says whether the run is the workgroup's or the wavefront's own
+template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool CHAIN>
+__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, const Run &run, bool team, const int2 *__restrict__ pair_addr,
                                      const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
                                      const float *__restrict__ v_scale)
 {
-    constexpr bool QLDS = kQueriesInLds<NB>, CHAIN = !TEAM;
+    constexpr bool QLDS = kQueriesInLds<NB>;
     const int lane = threadIdx.x & 63;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = lane & 15, jq = lane >> 4;
-    uint4 *qs = lds.q + (QLDS ? wslot * NB * 4 * 64 + lane : 0);
+    uint4 *qs = lds.q + (QLDS ? wslot * BLOCKS * 4 * 64 + lane : 0);   // (not NB: wavefronts may be at different classes)
     auto &o_lds = lds.o;
     auto &ml_lds = lds.ml;
     auto &dep_o = lds.dep_o;
@@ -247,8 +253,8 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     constexpr bool SINGLE = NB >= 4;
     // ---- state of the unit being computed ----
     // A team takes the pairs of its span in turn: wavefront w every fourth from the w-th on, whatever units they belong to.
-    constexpr int STRIDE = TEAM ? kWavesPerWg : 1;
-    int pos = x0 + (TEAM ? wslot : 0);   // flat index of this wave's next pair
+    const int step_log = team ? kWavesPerWgLog : 0, stride = 1 << step_log;
+    int pos = x0 + (team ? wslot : 0);   // flat index of this wave's next pair
     int seg_x0 = x0, seg_x1 = x0;     // the current segment (the part of the unit inside the span), flat
     int seg_left = 0;                 // this wave's pairs of it that are left
     int L = 0, q0 = 0, q_len = 0, rows = 0, nbu = 0;   // nbu: 16-row blocks the unit really has (for its partial)
@@ -284,7 +290,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
             }
         }
         seg_x1 = unit_x + nb_tiles < x1 ? unit_x + nb_tiles : x1;
-        seg_left = pos < seg_x1 ? (seg_x1 - pos + STRIDE - 1) / STRIDE : 0;
+        seg_left = pos < seg_x1 ? (seg_x1 - pos + stride - 1) >> step_log : 0;
         // All query loads go out before any of them is waited for: buffer loads over the request's rows, whose
         // offset is out of range (zeros) for a row the unit does not have, so there is no branch between them.  (Under a branch
         // per block the LDS instances waited for every block's loads in turn, 7 us at the start of a span.)
@@ -342,51 +348,67 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         }
     };
 
-    // Output row of the unit's row nn, and four of a finished row's values: normalised, rounded to bf16 (nearest even), 256 bytes
-    // per half-wavefront.
-    auto row_of = [&](int nn) __attribute__((always_inline)) {
-        return (long long)(q0 + a.q_lo + nn / G) * a.num_q_heads + g * G + nn % G;
-    };
-    auto write_row = [&](long long orow, float4v v, float inv) __attribute__((always_inline)) {
+    // The unit's row nn in the output, counted from the unit's first (in 32 bits: with 64-bit row numbers the addresses of a
+    // block's rows took longer than its values), and four of a finished row's values: normalised, rounded to bf16 (nearest even), 256
+    // bytes per half-wavefront.
+    auto row_of = [&](int nn) __attribute__((always_inline)) { return nn / G * a.num_q_heads + nn % G; };
+    auto first_row = [&]() __attribute__((always_inline)) { return (long long)(q0 + a.q_lo) * a.num_q_heads + g * G; };
+    auto write_row = [&](__bf16 *out, int row, float4v v, float inv) __attribute__((always_inline)) {
         const float2v lo2 = {v[0] * inv, v[1] * inv}, hi2 = {v[2] * inv, v[3] * inv};
         uint2 pk;
         pk.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo2, bf16x2));
         pk.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi2, bf16x2));
-        *reinterpret_cast<uint2 *>(static_cast<__bf16 *>(a.out) + orow * D + (lane & 31) * 4) = pk;
+        *reinterpret_cast<uint2 *>(out + (uint32_t)(row * D + (lane & 31) * 4)) = pk;
     };
 
-    // The end of a team's segment: the four wavefronts' results are brought to a common reference and added, block by block
-    // through LDS, each wavefront adding (in a fixed order) and writing four of a block's sixteen rows: as finished output if the
-    // segment is the `whole` unit, else as one partial of the workgroup.  The barriers wait for LDS only, not for the pairs in
+    // The end of a segment without a hand-over, block by block through LDS: as finished output if the segment is the `whole` unit, else
+    // as a partial.  A team's four wavefronts bring their results to a common reference and add them, each wavefront
+    // adding (in a fixed order) and writing four of a block's sixteen rows.  The barriers wait for LDS only, not for the pairs in
     // flight.  Two block buffers: a wavefront that writes block nb + 2 has passed the barrier of block nb + 1, which the others
-    // reach after reading block nb.
-    auto team_barrier = []() __attribute__((always_inline)) {
+    // reach after reading block nb.  A wavefront by itself takes the same way with its own results only and all sixteen rows: LDS
+    // serves a wave's requests in order.
+    auto team_barrier = [&]() __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-        __builtin_amdgcn_s_barrier();
+        if (team) __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
-    auto end_team = [&](bool whole, const float (&lsum)[NB]) __attribute__((always_inline)) {
+    auto end_blocks = [&](bool whole, const float (&lsum)[NB]) __attribute__((always_inline)) {
         if (nbu == 0) return;   // (a request without rows in this window)
-        if (jq == 0) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) ml_lds[wslot][nb * 16 + r16] = make_float2(m_run[nb], lsum[nb]);
-        }
-        team_barrier();
+        // (a copy that the compiler does not see through: what follows from it alone, the places of all rows, would be worked out
+        // at the start of the kernel and kept, 0.5 us of a short call)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
         float m_all[NB], l_all[NB];
+        if (team) {
+            if (jq == 0) {
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-            float2 ml[kWavesPerWg];
+                for (int nb = 0; nb < NB; ++nb) ml_lds[wslot][nb * 16 + r16] = make_float2(m_run[nb], lsum[nb]);
+            }
+            team_barrier();
 #pragma unroll
-            for (int w = 0; w < kWavesPerWg; ++w) ml[w] = ml_lds[w][nb * 16 + r16];
-            m_all[nb] = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
-            l_all[nb] = 0.f;
+            for (int nb = 0; nb < NB; ++nb) {
+                float2 ml[kWavesPerWg];
 #pragma unroll
-            for (int w = 0; w < kWavesPerWg; ++w) l_all[nb] += ml[w].y * __builtin_amdgcn_exp2f(ml[w].x - m_all[nb]);
+                for (int w = 0; w < kWavesPerWg; ++w) ml[w] = ml_lds[w][nb * 16 + r16];
+                m_all[nb] = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));
+                l_all[nb] = 0.f;
+#pragma unroll
+                for (int w = 0; w < kWavesPerWg; ++w) l_all[nb] += ml[w].y * __builtin_amdgcn_exp2f(ml[w].x - m_all[nb]);
+            }
+        } else {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+                m_all[nb] = m_run[nb];
+                l_all[nb] = lsum[nb];
+            }
         }
         auto deposit = [&](int nb) __attribute__((always_inline)) {
-            const float mine = __builtin_amdgcn_exp2f(m_run[nb] - m_all[nb]);   // (0 for a wave without a pair of this segment)
-            float4v *ol = o_lds[(TEAM ? nb & 1 : 0) * kWavesPerWg + wslot];
+            // (0 for a wave without a pair of this segment.  A wavefront by itself normalises finished rows here: a lane's accumulators
+            // are of one row, and behind LDS every row's factor would have to come from another lane.)
+            float mine = __builtin_amdgcn_exp2f(m_run[nb] - m_all[nb]);
+            if (!team) mine = whole ? 1.f / l_all[nb] : 1.f;
+            float4v *ol = o_lds[(nb & 1) * kWavesPerWg + wslot];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {   // accumulator row 4*jq+e of M-block mb is d = 8*(4*jq+e) + mb
 #pragma unroll
@@ -398,38 +420,55 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
                 }
             }
         };
-        const long long slot = (long long)blockIdx.x + (long long)p * a.num_kv_heads + g;
+        const long long slot = (long long)(team ? (int)blockIdx.x : (int)blockIdx.x * kWavesPerWg + wslot) + (long long)p * a.num_kv_heads + g;
         float *po = a.part_o + slot * a.rows_pad * D;
         float2 *pml = reinterpret_cast<float2 *>(a.part_ml) + slot * a.rows_pad;
+        __bf16 *out = static_cast<__bf16 *>(a.out) + first_row() * D;
+        float *lse = a.lse ? a.lse + first_row() : nullptr;
+        // The eight reads of a block: two rows of each of the four wavefronts' blocks, or all sixteen rows of the own one.
+        const float4v *from0 = o_lds[team ? 0 : wslot] + ((team ? wslot * 4 : 0) + (ln >> 5)) * kPartRowStride + (ln & 31);
         deposit(0);
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             if (nb < nbu) {
                 team_barrier();
                 float4v v[2][kWavesPerWg];
+                auto read = [&](int from_one_to_next) __attribute__((always_inline)) {
 #pragma unroll
-                for (int it = 0; it < 2; ++it)
+                    for (int it = 0; it < 2; ++it)
 #pragma unroll
-                    for (int w = 0; w < kWavesPerWg; ++w)
-                        v[it][w] = o_lds[(TEAM ? nb & 1 : 0) * kWavesPerWg + w][(wslot * 4 + it * 2 + (lane >> 5)) * kPartRowStride + (lane & 31)];
+                        for (int w = 0; w < kWavesPerWg; ++w)
+                            v[it][w] = from0[(nb & 1) * (kWavesPerWg * 16 * kPartRowStride) + w * from_one_to_next + it * 2 * kPartRowStride];
+                };
+                if (team) read(16 * kPartRowStride);   // (constant offsets cost no address arithmetic)
+                else read(4 * kPartRowStride);
                 if (nb + 1 < NB) deposit(nb + 1 < NB ? nb + 1 : 0);   // (under the latency of the reads)
-                const bool mine = jq == 0 && (r16 >> 2) == wslot && nb * 16 + r16 < rows;   // lanes that hold (m, l) of the rows written here
+                const int first = team ? wslot * 4 : 0, rows_here = team ? 4 : 16;   // of the block, written by this wavefront
+                const bool mine = jq == 0 && (unsigned)(r16 - first) < (unsigned)rows_here && nb * 16 + r16 < rows;   // lanes that hold their (m, l)
                 float inv = 1.f;
                 if (whole) {
-                    inv = 1.f / l_all[nb];
-                    if (mine && a.lse) a.lse[row_of(nb * 16 + r16)] = (m_all[nb] + log2f(l_all[nb])) * kLn2;
+                    if (team) inv = 1.f / l_all[nb];
+                    if (mine && lse) lse[row_of(nb * 16 + r16)] = (m_all[nb] + log2f(l_all[nb])) * kLn2;
                 } else if (mine) {
                     pml[nb * 16 + r16] = make_float2(m_all[nb], l_all[nb]);
                 }
+                auto write = [&](int row, const float4v &x) __attribute__((always_inline)) {
+                    const int nn = nb * 16 + row;
+                    if (whole) {
+                        const float iv = team ? __shfl(inv, row) : 1.f;
+                        if (nn < rows) write_row(out, row_of(nn), x, iv);
+                    } else if (nn < rows) {
+                        *reinterpret_cast<float4v *>(po + nn * D + (ln & 31) * 4) = x;
+                    }
+                };
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
-                    const int row = wslot * 4 + it * 2 + (lane >> 5), nn = nb * 16 + row;
-                    const float4v sum = ((v[it][0] + v[it][1]) + v[it][2]) + v[it][3];
-                    if (whole) {
-                        const float iv = __shfl(inv, row);
-                        if (nn < rows) write_row(row_of(nn), sum, iv);
-                    } else if (nn < rows) {
-                        *reinterpret_cast<float4v *>(po + nn * D + (lane & 31) * 4) = sum;
+                    const int row = first + it * 2 + (ln >> 5);
+                    if (team) v[it][0] = ((v[it][0] + v[it][1]) + v[it][2]) + v[it][3];
+                    write(row, v[it][0]);
+                    if (!team) {
+#pragma unroll
+                        for (int w = 1; w < kWavesPerWg; ++w) write(row + 4 * w, v[it][w]);
                     }
                 }
             }
@@ -451,8 +490,8 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
             l += __shfl_xor(l, 32);
             lsum[nb] = l;
         }
-        if constexpr (TEAM) {
-            end_team(starts && ends, lsum);
+        if constexpr (!CHAIN) {
+            end_blocks(starts && ends, lsum);
             return;
         }
         bool to_end = ends;   // does the result held here reach the unit's last tile?
@@ -528,13 +567,17 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         }
         // What is held here goes to memory: as the finished output if it covers the whole unit, else as a
         // partial in slot (workgroup, or wave without the hand-over) + unit, unique along the pair sequence.
-        const bool whole = CHAIN && starts && to_end;
+        const bool whole = starts && to_end;
         const long long slot = (long long)blockIdx.x + (long long)p * a.num_kv_heads + g;
         float *po = a.part_o + slot * a.rows_pad * D;
         float *pml = a.part_ml + slot * a.rows_pad * 2;
+        __bf16 *out = static_cast<__bf16 *>(a.out) + first_row() * D;
+        float *lse = a.lse ? a.lse + first_row() : nullptr;
         // A lane holds 32 consecutive d of one row (d = 32*jq + 8*e + mb), in registers that are 16 bytes
         // apart in memory: written directly, every store would scatter 16-byte pieces over 64 cache lines.
         // The block goes through LDS instead and leaves as whole rows, two per store.
+        int ln = lane;   // (as in end_blocks)
+        asm volatile("" : "+v"(ln));
         float4v *ol = o_lds[wslot];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
@@ -561,22 +604,22 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
                 float2 rowml[8];
 #pragma unroll
                 for (int it = 0; it < 8; ++it) {
-                    const int row = it * 2 + (lane >> 5);
+                    const int row = it * 2 + (ln >> 5);
                     rowv[it] = ol[row * kPartRowStride + (lane & 31)];
                     if (whole) rowml[it] = ml_lds[wslot][row];
                 }
 #pragma unroll
                 for (int it = 0; it < 8; ++it) {
-                    const int row = it * 2 + (lane >> 5), nn = nb * 16 + row;
+                    const int row = it * 2 + (ln >> 5), nn = nb * 16 + row;
                     const float4v v = rowv[it];
                     if (whole) {
                         const float2 ml = rowml[it];
                         if (nn < rows) {
-                            write_row(row_of(nn), v, 1.f / ml.y);
-                            if (a.lse && (lane & 31) == 0) a.lse[row_of(nn)] = (ml.x + log2f(ml.y)) * kLn2;
+                            write_row(out, row_of(nn), v, 1.f / ml.y);
+                            if (lse && (lane & 31) == 0) lse[row_of(nn)] = (ml.x + log2f(ml.y)) * kLn2;
                         }
                     } else if (nn < rows) {
-                        *reinterpret_cast<float4v *>(po + nn * D + (lane & 31) * 4) = v;
+                        *reinterpret_cast<float4v *>(po + nn * D + (ln & 31) * 4) = v;
                     }
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -599,7 +642,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     auto load_pair = [&](PairRegs<FP8> &t, int2 addr) __attribute__((always_inline)) {
         const bool live = next_x < x1;
         load_pair_tiles<FP8>(t, a, k_scale, v_scale, addr, live, lane);
-        next_x += STRIDE;
+        next_x += stride;
     };
     auto issue = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
         const int2 addr = next_addr;
@@ -858,7 +901,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         if constexpr (SINGLE) {
             for (; seg_left > 0; --seg_left) {
                 compute(buf[0], tile, std::true_type{});
-                tile += STRIDE;
+                tile += stride;
             }
         } else {
             // A segment of odd length begins with a step of its own, so that the loop takes both buffers in turn with one way
@@ -866,15 +909,15 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
             // newest, and drains the whole ring at the top, or spills.
             if (seg_left & 1) {
                 compute(buf[0], tile, std::false_type{});
-                tile += STRIDE;
+                tile += stride;
                 --seg_left;
                 buf[0] = buf[SINGLE ? 0 : 1];
                 issue(buf[SINGLE ? 0 : 1]);
             }
             for (; seg_left > 0; seg_left -= 2) {
                 compute(buf[0], tile, std::true_type{});
-                compute(buf[SINGLE ? 0 : 1], tile + STRIDE, std::true_type{});
-                tile += 2 * STRIDE;
+                compute(buf[SINGLE ? 0 : 1], tile + stride, std::true_type{});
+                tile += 2 * stride;
             }
         }
         pos = unit_x + tile;
@@ -886,15 +929,60 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     }
 }
 
-// BLOCKS  the most 16-row blocks of query rows a unit can have
+// A span of the class kernels, class by class: units of k row blocks are walked by the code for k.
+//   cls, class_end  class of the span's first unit, and where that class ends
 template <int G, int BLOCKS, bool FP8, bool TREE>
+__device__ __forceinline__ void walk_classes(const AttnArgs &a, StreamLds<BLOCKS> &lds, Run run, bool team, int cls, int class_end,
+                                             const AttnPlan *__restrict__ plan, const int2 *__restrict__ pair_addr,
+                                             const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
+                                             const float *__restrict__ v_scale)
+{
+    const int end = run.x1;
+    // (the first class's end comes with the descriptor: the plan's record would be one more read in a row before the
+    // first pair, 0.5 % of the whole call: 221.8 -> 220.5 us with 96 e4m3 requests, 278.8 -> 277.4 with 128 ragged ones)
+    run.x1 = class_end < end ? class_end : end;
+    for (int c = cls;;) {
+        if (run.x0 < run.x1) {
+            const int blocks = BLOCKS - c;
+            if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            else {
+                if constexpr (BLOCKS >= 5) {
+                    if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+                    else walk<G, 4, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+                }
+            }
+        }
+        if (run.x1 >= end) break;
+        // the next class begins with its first request
+        const int place = plan->class_req[c];
+        ++c;
+        if (place >= a.batch) break;
+        const AttnReq r = req[place];
+        run.p = place; run.g = 0; run.b = r.b; run.n = r.n;
+        run.x0 = run.unit_x = run.x1;
+        run.L = r.L; run.q0 = r.q0; run.q1 = r.q1;
+#pragma unroll
+        for (int j = 0; j < kDescPairs; ++j) {
+            const int x = run.x0 + (team ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + j * kWavesPerWg : j);
+            run.addr[j] = pair_addr[x < end ? x : end - 1];
+        }
+        const int next_end = plan->class_x[c];
+        run.x1 = next_end < end ? next_end : end;
+    }
+}
+
+// BLOCKS  the most 16-row blocks of query rows a unit can have
+// MIXED   more than two row blocks: the spans may be wavefronts' as well as teams' (with fewer than two units to a team they never
+//         are, and the code of a team alone is 0.5 to 0.8 us faster in a call of 16 us)
+template <int G, int BLOCKS, bool FP8, bool TREE, bool MIXED>
 __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     AttnArgs a, const AttnPlan *__restrict__ plan, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
     const AttnReq *__restrict__ req, const float *__restrict__ k_scale, const float *__restrict__ v_scale)
 {
     // The metadata arrays come in as separate no-alias arguments so that their wave-uniform reads
     // become scalar loads (own counter, no ordering against the vector KV loads).
-    constexpr bool CLASSES = BLOCKS > kChainRowBlocks;
     __shared__ StreamLds<BLOCKS> lds;
     const int wslot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // where this wave's span starts: written by the plan kernel (waves past the partition count start at the end of all pairs).  It
@@ -904,58 +992,29 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     run.p = d[0]; run.g = d[1]; run.b = d[16]; run.n = d[17];
     run.x0 = d[4];
     const int next_team = wave_desc[(long long)(blockIdx.x + 1) * kWavesPerWg * kDescInts + 4], next_wave = d[kDescInts + 4];
-    run.x1 = CLASSES || d[15] ? next_team : next_wave;
+    const bool team = !MIXED || __builtin_amdgcn_readfirstlane(d[15]) == kSpanTeam;   // (the same for the whole call)
+    run.x1 = team ? next_team : next_wave;
     run.unit_x = run.x0 - d[2];
     run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
 #pragma unroll
     for (int j = 0; j < kDescPairs; ++j) run.addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
-    if constexpr (!CLASSES) {
-        if (d[15]) {   // (the same for the whole workgroup)
+    // (In one trip to memory: left to the compiler, some of it is read behind the test for an empty span, and some again further down.)
+    int cls = d[3], class_end = d[5];
+    asm volatile("" : "+s"(run.p), "+s"(run.g), "+s"(run.b), "+s"(run.n), "+s"(run.x0), "+s"(run.unit_x), "+s"(run.L), "+s"(run.q0), "+s"(run.q1), "+s"(cls), "+s"(class_end));
+    asm volatile("" : "+s"(run.addr[0].x), "+s"(run.addr[0].y), "+s"(run.addr[1].x), "+s"(run.addr[1].y), "+s"(run.addr[2].x), "+s"(run.addr[2].y));
+    if constexpr (BLOCKS <= kChainRowBlocks) {
+        if (team) {
             if (run.x0 >= run.x1) return;
-            walk<G, BLOCKS, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, false>(a, lds, run, true, pair_addr, req, k_scale, v_scale);
         } else {
             if ((threadIdx.x & 63) == 0) lds.dep_flag[wslot] = 0;
             __syncthreads();   // every wave's flag is clear before any neighbour can look at it
             if (run.x0 >= run.x1) return;
-            walk<G, BLOCKS, BLOCKS, FP8, TREE, false>(a, lds, run, pair_addr, req, k_scale, v_scale);
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, true>(a, lds, run, false, pair_addr, req, k_scale, v_scale);
         }
     } else {
-        // The span of the workgroup, class by class: units of k row blocks are walked by the code for k.
         if (run.x0 >= run.x1) return;
-        const int end = run.x1;
-        // (the first class's end comes with the descriptor: the plan's record would be one more read in a row before the
-        // first pair, 0.5 % of the whole call: 221.8 -> 220.5 us with 96 e4m3 requests, 278.8 -> 277.4 with 128 ragged ones)
-        run.x1 = d[5] < end ? d[5] : end;
-        for (int c = d[3];;) {
-            if (run.x0 < run.x1) {
-                const int blocks = BLOCKS - c;
-                if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                else {
-                    if constexpr (BLOCKS >= 5) {
-                        if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                        else walk<G, 4, BLOCKS, FP8, TREE, true>(a, lds, run, pair_addr, req, k_scale, v_scale);
-                    }
-                }
-            }
-            if (run.x1 >= end) break;
-            // the next class begins with its first request
-            const int place = plan->class_req[c];
-            ++c;
-            if (place >= a.batch) break;
-            const AttnReq r = req[place];
-            run.p = place; run.g = 0; run.b = r.b; run.n = r.n;
-            run.x0 = run.unit_x = run.x1;
-            run.L = r.L; run.q0 = r.q0; run.q1 = r.q1;
-#pragma unroll
-            for (int j = 0; j < kDescPairs; ++j) {
-                const int x = run.x0 + wslot + j * kWavesPerWg;
-                run.addr[j] = pair_addr[x < end ? x : end - 1];
-            }
-            const int class_end = plan->class_x[c];
-            run.x1 = class_end < end ? class_end : end;
-        }
+        walk_classes<G, BLOCKS, FP8, TREE>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
     }
 }
 
@@ -986,10 +1045,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     const int cost = a.plan->class_cost[r.cls], weight = a.plan->class_weight[r.cls];
     SpanCuts cuts;
     cuts.total_w = a.plan->total_cost;
-    cuts.nw = a.plan->cuts;
+    cuts.nw = a.plan->spans;
     int w_first, w_last;
     cuts.unit_spans(r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
-    if (!a.plan->team) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
+    if (a.plan->mode == kSpanChain) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup
         w_first /= kWavesPerWg;
         w_last /= kWavesPerWg;
     }
@@ -1044,7 +1103,9 @@ int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hip
     // into a long tail.
     // When a profile is being taken the two events are attached to the dispatch itself, so that
     // their difference is the kernel's own duration on this stream (what a kernel trace shows).
-    hipExtLaunchKernelGGL((attn_stream_kernel<G, BLOCKS, FP8, TREE>), dim3((unsigned)(a.launch_waves / kWavesPerWg)),
+    const bool few = BLOCKS > kChainRowBlocks && (long long)a.batch * a.num_kv_heads < 2 * (a.launch_waves / kWavesPerWg);
+    const auto kernel = few ? attn_stream_kernel<G, BLOCKS, FP8, TREE, BLOCKS <= kChainRowBlocks> : attn_stream_kernel<G, BLOCKS, FP8, TREE, true>;
+    hipExtLaunchKernelGGL(kernel, dim3((unsigned)(a.launch_waves / kWavesPerWg)),
                           dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, a, a.plan, a.pair_addr, a.wave_desc, a.req, a.k_scale,
                           a.v_scale);
     SS_HIP_CHECK(hipGetLastError(), "launch attn_stream_kernel");

@@ -25,15 +25,15 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // ---- attention -----------------------------------------------------------------------------
 constexpr int kTile = SS_BLOCK_SIZE;     // tokens per KV tile = tokens per cache block
 constexpr int kPairTokens = 2 * kTile;   // the matrix-core kernel takes two tiles of a request at a time
-constexpr int kWavesPerWg = 4;
+constexpr int kWavesPerWg = kSpansPerWg, kWavesPerWgLog = 2;
 constexpr int kDescInts = 32;            // ints per wave descriptor (18 in use)
 constexpr int kDescPairs = 3;            // tile pairs whose addresses a descriptor carries for the span's first loads
 constexpr int kMfmaHeadDim = 128;        // head_dim the matrix-core kernel is written for
 constexpr int kChainRowBlocks = 2;       // up to here the spans of a workgroup can be combined in LDS
 constexpr int kMaxRowBlocks = 5;         // 16-row blocks of query rows one wavefront can keep accumulators for
-// What opening a unit is taken to cost a wavefront, in pairs, for the span cuts: with one or two row blocks 2 (1 to 3 are level).
-// The team kernels have costs of their own by row blocks (attn_mfma.hip); the plan's record still names 8 for four and five.
-constexpr int kUnitWeight = 2, kUnitWeightDeep = 8;
+// What opening a unit is taken to cost a wavefront, in pairs, for the span cuts of the kernels of one or two row blocks (1 to 3 are level).
+// The others have costs of their own by row blocks (attn_mfma.hip).
+constexpr int kUnitWeight = 2;
 
 // Query tokens of a request that fall into the pass's window, and the tile pairs its units stream in this
 // pass: a request without rows in the window keeps one pair so that no unit of the flat pair space is empty.
@@ -58,16 +58,15 @@ __host__ __device__ inline int window_pairs(int kv_len, int q_len, int q_lo)
 // Written by the plan kernel, read by the streaming and merge kernels.
 struct AttnPlan {
     int32_t total_pairs;   // sum over requests of ceil(kv_len/32) * num_kv_heads
-    int32_t num_waves;     // partitions actually used (<= launched wavefronts)
-    int32_t unit_weight;   // what opening a unit costs a wavefront, in pairs (0: spans of equal pair counts)
-    int32_t chain;         // count_spans' choice to combine the results of a workgroup in LDS
-    int32_t cuts;          // spans that were cut: num_waves, or a quarter of that where a workgroup shares a span
-    int32_t team;          // the spans are workgroups', whose wavefronts take the pairs in turn
+    int32_t mode;          // whose a span is (span_cuts.h)
+    int32_t spans;
+    int32_t pad;
     int64_t total_cost;                  // the end of the coordinate they were cut in
     int32_t class_req[kMaxClasses];      // requests, in layout order, before the end of each class
     int32_t class_x[kMaxClasses];        // pairs of the flat sequence before the end of each class
     int32_t class_cost[kMaxClasses], class_weight[kMaxClasses];
 };
+static_assert(kWavesPerWg == 1 << kWavesPerWgLog, "");
 static_assert(kMaxClasses >= kMaxRowBlocks, "a class per number of row blocks");
 static_assert(sizeof(AttnPlan) <= 256, "the plan record's place in the workspace");
 // One per request, in the order in which the flat sequence holds them.
@@ -109,7 +108,7 @@ struct AttnArgs {
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
     int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts)
-    int32_t auto_weight;   // unit_weight is the default: teams take the weights measured for their row blocks
+    int32_t auto_weight;   // unit_weight is the default: classes take the weights measured for their row blocks
     int32_t team_blocks;   // row blocks of the team kernel that is launched, 0 for the kernels of one or two
 };
 

@@ -19,42 +19,65 @@
 
 namespace ss {
 
-// How many spans, and whether the spans of a workgroup are combined in LDS (`can_chain`: the instance is able to).
-//
-// The spans of a call with one or two row blocks on a full chip are these, a wavefront's each, handed over in LDS.  A call that does not
-// fill the chip is served by teams instead (count_team_spans); what is counted here then only says so (fewer spans than
-// launched wavefronts) and stands in the plan's record.
-constexpr int kMinPairsPerSpan = 2, kMinPairsLongUnits = 4;
-constexpr int kMaxLooseSpans = 16, kMaxUnitPartials = 32;
+// Whose a span is: a wavefront's, its partials handed over inside the workgroup (kernels of one or two row blocks); a workgroup's,
+// whose wavefronts take its pairs in turn and leave one partial; a wavefront's by itself (kernels of more row blocks).
+enum { kSpanChain = 0, kSpanTeam = 1, kSpanAlone = 2 };
+
 constexpr int kSpansPerWg = 4;   // wavefronts of a workgroup
+// The merge adds a unit's partials one after the other: with more than kMaxUnitPartials for the longest unit the spans get longer.
+constexpr int kMaxUnitPartials = 32;
 
-struct SpanCount {
-    long long spans;
-    int chain;
+struct SpanChoice {
+    int mode;
+    long long spans;   // of all pairs, cut by cost
 };
-// total: pairs of all units (>= 1); longest: pairs of the longest unit; launch_waves: the most spans there can be.
-SS_HOST_DEVICE inline SpanCount count_spans(long long total, int longest, long long launch_waves, bool can_chain)
-{
-    auto bounded = [&](long long n) { return n < 1 ? 1 : n > launch_waves ? launch_waves : n; };
-    SpanCount c;
-    c.spans = bounded(total / kMinPairsPerSpan);
-    const long long of_longest = longest * c.spans;   // spans of the longest unit, times total
-    c.chain = can_chain && (c.spans == launch_waves || of_longest > kMaxLooseSpans * total);
-    if (of_longest > (c.chain ? kSpansPerWg : 1) * kMaxUnitPartials * total) c.spans = bounded(total / kMinPairsLongUnits);
-    return c;
-}
 
-// Spans of a team kernel, whose four wavefronts take a span's pairs in turn and write one partial: of two pairs as long as the chip
-// is not full (then half of the wavefronts have none, but the span is over sooner), of sixteen where a unit would leave more
-// than kMaxUnitPartials partials.  A whole call, in us, with a span per wavefront and no team / spans of 8 / 4 / 2 pairs:
+// Wavefronts' spans: of two pairs as long as the chip is not full, of four where a unit would leave too many partials (a hand-over leaves
+// one for four spans).
+SS_HOST_DEVICE inline long long count_wave_spans(long long total, int longest, long long waves, bool chain)
+{
+    auto bounded = [&](long long n) { return n < 1 ? 1 : n > waves ? waves : n; };
+    const long long n = bounded(total / 2);
+    return longest * n > (chain ? kSpansPerWg : 1) * kMaxUnitPartials * total ? bounded(total / 4) : n;
+}
+// Teams' spans: of two pairs as long as the chip is not full (then half of the wavefronts have none, but the span is over sooner), of
+// sixteen where a unit would leave too many partials.  A whole call, in us, with a span per wavefront and no team / spans of 8 / 4 / 2 pairs:
 //   24 requests of 30..200 tokens, 8 KV heads, three row blocks  24.1 / 31.9 / 26.5 / 23.7     4 of 40..600, four and five  25.7 / 28.9 / 24.6 / 23.6
 //   4 of 1000..3000, e4m3  27.8 / 26.5 / 24.7 / 24.7      one of 60000 over one KV head, five row blocks  108 / 53 (spans of 16) / 74 (spans of 8)
-constexpr int kMinTeamPairs = 2, kMinTeamPairsLongUnits = 16;
-SS_HOST_DEVICE inline long long count_team_spans(long long total, int longest, long long most)
+SS_HOST_DEVICE inline long long count_team_spans(long long total, int longest, long long teams)
 {
-    auto bounded = [&](long long n) { return n < 1 ? 1 : n > most ? most : n; };
-    const long long n = bounded(total / kMinTeamPairs);
-    return longest * n > kMaxUnitPartials * total ? bounded(total / kMinTeamPairsLongUnits) : n;
+    auto bounded = [&](long long n) { return n < 1 ? 1 : n > teams ? teams : n; };
+    const long long n = bounded(total / 2);
+    return longest * n > kMaxUnitPartials * total ? bounded(total / 16) : n;
+}
+
+// total: pairs of all units (>= 1); longest: pairs of the longest unit; waves: the most wavefronts' spans there can be; classes: a
+// kernel of more than two row blocks; kv8: e4m3 caches.
+//
+// Teams or wavefronts.  A team opens every unit of its span with all four wavefronts and ends it with an exchange: with many units to a
+// team that is most of its time, where four wavefronts by themselves open and end four units at once.  With few long units the teams are
+// ahead: a quarter of the partials, and the chip's ends closer together.  A whole call, in us, teams / wavefronts by themselves,
+// 8 KV heads:
+//   three row blocks, bf16, 256 requests of 48 tokens  70 / 42     64 of 200  38 / 34     64 of 400  45 / 43     64 of 800  62 / 63     128 of 1600  178 / 186
+//   five row blocks, e4m3   256 of 48  95 / 57     64 of 800  64 / 62     64 of 1600  85 / 85     96 of 512..8192  224 / 232
+// So from two units to a team on, and while a unit's pairs on average are not more than kAlonePairs times the units to a wavefront.
+// With one or two row blocks the exchange is small and wavefronts hand over: they serve a full chip (64 requests of 256..4096
+// tokens: 106 us, and 112 in teams), and calls of many short units (64 of 100 tokens: 24.6, and 26.8 in teams).
+constexpr int kAlonePairs = 27, kAlonePairsKv8 = 56;
+SS_HOST_DEVICE inline SpanChoice choose_spans(long long total, int longest, long long units, long long waves, bool classes, bool kv8)
+{
+    const long long teams = waves / kSpansPerWg;
+    SpanChoice c;
+    if (classes) {
+        const bool alone = units >= 2 * teams && (double)total * (double)waves <= (double)(kv8 ? kAlonePairsKv8 : kAlonePairs) * (double)units * (double)units;
+        c.mode = alone ? kSpanAlone : kSpanTeam;
+        c.spans = count_wave_spans(total, longest, waves, false);
+    } else {
+        c.spans = count_wave_spans(total, longest, waves, true);
+        c.mode = c.spans == waves || units >= 2 * teams ? kSpanChain : kSpanTeam;
+    }
+    if (c.mode == kSpanTeam) c.spans = count_team_spans(total, longest, teams);
+    return c;
 }
 
 // Requests of different row blocks in one call are laid out class by class (most row blocks first, so that a run of units

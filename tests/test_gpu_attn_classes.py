@@ -1,6 +1,6 @@
 """GPU parity of the matrix-core attention kernels whose workgroups are teams: requests of one to five row blocks in one call (laid out by
-class), spans that cross classes, units without a pair for some of the team's wavefronts, batches beyond one round of the plan's sort and
-beyond its LDS."""
+class), spans that cross classes, units without a pair for some of the team's wavefronts, batches of one and of several requests to a lane of the plan and those laid out by a
+kernel of their own."""
 import numpy as np
 import pytest
 import torch
@@ -37,15 +37,16 @@ def test_mixed_row_blocks(oracle, hq, top, kv, tree, waves):
         binding.ss_set_option("attn_waves", 0)
 
 
-@pytest.mark.parametrize("batch", [256, 257, 600, 4096, 4097])   # rounds of the sort; the largest sorted batch, one beyond
-def test_large_batches(oracle, batch):
+@pytest.mark.parametrize("hq,top", [(8, 9), (4, 8), (4, 12)])    # to five, three and four row blocks
+@pytest.mark.parametrize("batch", [256, 257, 600, 4096, 4097])   # the plan's largest batch by lanes, the smallest of the layout kernel
+def test_large_batches(oracle, batch, hq, top):
     rng = np.random.default_rng(batch)
-    depth = rng.integers(0, 10, batch)
+    depth = rng.integers(0, top + 1, batch)
     lens = np.maximum(depth + 1, rng.integers(1, 70, batch))
-    check(_inputs("bf16", 8, 1, lens, depth, seed=1), oracle, max_q_len=10, label=f"{batch} requests")
+    check(_inputs("bf16", hq, 1, lens, depth, seed=1), oracle, max_q_len=top + 1, label=f"{batch} requests, {hq} heads")
 
 
-@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])   # a request to a lane of the plan up to 64, loops from 65 on
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])   # a request to a lane of the plan up to 64, two from 65 on
 @pytest.mark.parametrize("hq,top", [(4, 3), (8, 9)])     # one row block (no classes); one to five
 def test_batches_of_a_lane_each(oracle, hq, top, batch):
     rng = np.random.default_rng(batch)

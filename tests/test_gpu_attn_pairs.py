@@ -31,22 +31,45 @@ def test_pairs(oracle, hq, depth, kv, tree, waves):
         binding.ss_set_option("attn_waves", 0)
 
 
-@pytest.mark.parametrize("weight,pairs,pairs_deep", [(0, 0, 0), (1, 1, 1), (4, 2, 2), (17, 9, 9), (64, 32, 32), (3, 2, 8)])
-def test_unit_weight_option(weight, pairs, pairs_deep):
-    """The plan record (four int32 at the start of the workspace: pairs, spans, unit weight, hand-over) carries the weight the
-    spans were cut with: as given, or by the row blocks for the default, also after the option had another value."""
-    for hq, depth, want in ((8, 4, pairs), (16, 9, pairs_deep)):
-        cfg = LLAMA8B.scaled(batch=4, num_q_heads=hq, num_kv_heads=2, depth=("fixed", depth))
-        d = binding.attention_to_device(synth.make_attention_inputs(cfg, seed=1, kv_len=np.full(4, 900, np.int32)))
-        out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=depth + 1)
-        binding.ss_set_option("attn_unit_weight", 64)
-        binding.ss_set_option("attn_unit_weight", weight)
-        try:
-            binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=depth + 1)
-        finally:
-            binding.ss_set_option("attn_unit_weight", 3)
-        torch.cuda.synchronize()
-        assert ws[:16].view(torch.int32)[2].item() == want, (hq, weight)
+# The plan record at the start of the workspace, int32: pairs, whose the spans are, spans, -, -, -, requests and pairs in front of the end of
+# each of five classes, what a pair and what opening a unit costs in each.
+CHAIN, TEAM, ALONE = 0, 1, 2
+
+
+def plan_of(inp, max_q_len):
+    d = binding.attention_to_device(inp)
+    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=max_q_len)
+    binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=max_q_len)
+    torch.cuda.synchronize()
+    rec = ws[:104].view(torch.int32).tolist()
+    return dict(pairs=rec[0], mode=rec[1], spans=rec[2], cost=rec[16:21], weight=rec[21:26])
+
+
+@pytest.mark.parametrize("weight", [0, 1, 4, 17, 64, 3])
+@pytest.mark.parametrize("batch,hq,depth,mode", [
+    (4, 8, 4, TEAM), (64, 8, 4, CHAIN),                                  # two row blocks, in pairs
+    (4, 16, 9, TEAM), (260, 16, 9, ALONE)])                              # five, in eighths of a pair
+def test_unit_weight_option(batch, hq, depth, mode, weight):
+    """What opening a unit is charged when the spans are cut: the option's value for a wavefront (tiles, rounded up to pairs) or the
+    default's, also after the option had another value."""
+    cfg = LLAMA8B.scaled(batch=batch, num_q_heads=hq, num_kv_heads=2, depth=("fixed", depth))
+    inp = synth.make_attention_inputs(cfg, seed=1, kv_len=np.full(batch, 900 if mode != ALONE else 200, np.int32))
+    binding.ss_set_option("attn_unit_weight", 64)
+    binding.ss_set_option("attn_unit_weight", weight)
+    try:
+        plan = plan_of(inp, depth + 1)
+    finally:
+        binding.ss_set_option("attn_unit_weight", 3)
+    assert plan["mode"] == mode
+    pairs = (weight + 1) // 2
+    if hq == 8:
+        assert plan["cost"][0] == 1
+        assert plan["weight"][0] == (2 if weight == 3 else pairs) * (2 if mode == TEAM else 1)
+    elif weight != 3:
+        assert plan["weight"] == [pairs * 8 * (4 if mode == TEAM else 1)] * 5
+    else:   # five row blocks ... one
+        assert plan["cost"] == [9, 9, 8, 8, 8]
+        assert plan["weight"] == ([128, 100, 80, 48, 32] if mode == TEAM else [68, 52, 44, 32, 24])
 
 
 @pytest.mark.parametrize("weight", [0, 3, 16, 64])
@@ -71,22 +94,38 @@ def test_many_short_units_over_weights(oracle, hq, depth, kv, tree, weight):
         binding.ss_set_option("attn_waves", 0)
 
 
-@pytest.mark.parametrize("tokens,hkv,hq,depth,spans,chain", [
-    (1000, 8, 32, 4, 128, 0), (1100, 8, 32, 4, 140, 1), (4000, 8, 32, 4, 500, 1),      # two row blocks: the hand-over comes in
-    (8200, 8, 32, 4, 1024, 1), (8100, 4, 16, 4, 508, 1),                               # (a full chip)
-    (8200, 4, 16, 4, 257, 1), (32000, 1, 4, 4, 250, 1),                                # then spans of four pairs
-    (2000, 8, 32, 8, 252, 0), (2200, 8, 32, 8, 138, 0), (20000, 1, 8, 8, 156, 0)])     # three and five row blocks
-def test_single_long_requests(oracle, tokens, hkv, hq, depth, spans, chain):
-    """One request: the plan record (pairs, spans, unit weight, hand-over) on both sides of its rules, and the result."""
+@pytest.mark.parametrize("tokens,hkv,hq,depth,spans,mode", [
+    (1000, 8, 32, 4, 128, TEAM), (4000, 8, 32, 4, 256, TEAM), (8100, 8, 32, 4, 256, TEAM),   # two row blocks: teams until the chip is full,
+    (8200, 8, 32, 4, 1024, CHAIN), (8200, 4, 16, 4, 64, TEAM), (32000, 1, 4, 4, 62, TEAM),  # of sixteen pairs in long units
+    (2000, 8, 32, 8, 252, TEAM), (20000, 8, 32, 8, 256, TEAM), (20000, 1, 8, 8, 39, TEAM)])  # three and five row blocks
+def test_single_long_requests(oracle, tokens, hkv, hq, depth, spans, mode):
+    """One request: whose the spans are and how many, on both sides of the rules, and the result."""
     cfg = LLAMA8B.scaled(batch=1, num_q_heads=hq, num_kv_heads=hkv)
     inp = synth.make_attention_inputs(cfg, seed=tokens, kv_len=np.array([tokens], np.int32), depth=np.array([depth], np.int32))
     check(inp, oracle, max_q_len=depth + 1, label=f"{tokens} tokens over {hkv} KV heads")
-    d = binding.attention_to_device(inp)
-    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=depth + 1)
-    binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=depth + 1)
-    torch.cuda.synchronize()
-    plan = ws[:16].view(torch.int32).tolist()
-    assert (plan[1], plan[3]) == (spans, chain), plan
+    plan = plan_of(inp, depth + 1)
+    assert (plan["spans"], plan["mode"]) == (spans, mode), plan
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("tree", [False, True])
+@pytest.mark.parametrize("batch,hkv,hq,depth,lo,hi,mode", [
+    (16, 2, 8, 10, 1, 256, TEAM), (128, 2, 8, 15, 1, 512, TEAM),
+    (255, 2, 16, 9, 1, 200, TEAM), (256, 2, 16, 9, 1, 200, ALONE),      # five row blocks: two units to a team
+    (256, 2, 8, 10, 1, 1300, TEAM),                                     # (their pairs too many)
+    (255, 2, 8, 4, 1, 100, TEAM), (256, 2, 8, 4, 1, 100, CHAIN)])       # two row blocks: many units
+def test_short_units(oracle, batch, hkv, hq, depth, lo, hi, mode, tree, kv):
+    """Requests of a few pairs, all row blocks up to the call's: teams and wavefronts by themselves."""
+    rng = np.random.default_rng(batch + hi)
+    lens = rng.integers(lo, hi + 1, batch).astype(np.int32)
+    lens[0] = hi
+    k = np.minimum(rng.integers(0, depth + 1, batch), lens - 1).astype(np.int32)
+    k[0] = depth
+    cfg = (LLAMA8B if kv == "bf16" else FP8_70B).scaled(batch=batch, num_q_heads=hq, num_kv_heads=hkv)
+    inp = synth.make_attention_inputs(cfg, seed=batch, kv_len=lens, depth=k, tree=tree, nan_tail=True)
+    check(inp, oracle, max_q_len=depth + 1, label=f"{batch} requests of up to {hi}")
+    plan = plan_of(inp, depth + 1)
+    assert plan["mode"] == (mode if kv == "bf16" or hi != 1300 else ALONE), plan
 
 
 @pytest.mark.parametrize("waves", [4, 0])

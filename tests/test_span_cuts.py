@@ -7,8 +7,8 @@ and merge kernels rely on:
   * the spans (each ends where the next one starts) tile the flat sequence: in order, nothing lost, nothing twice;
   * every wave gets its descriptor from exactly one unit, and its span begins inside that unit;
   * the waves that hold pairs of a unit are exactly w_first .. w_last of the merge kernel's formula, so the
-    partial slots it reads are the ones that were written (also after the division by four that the
-    instances with the in-workgroup hand-over apply);
+    partial slots it reads are the ones that were written (also after the division by four that applies where
+    wavefronts hand over inside their workgroup);
   * slot `wave + unit` (and `workgroup + unit`) is unique along the sequence.
 """
 import ctypes
@@ -61,10 +61,10 @@ extern "C" void plan_spans(const int32_t *prefix, int batch, int hkv, int weight
         }
     out[4 * nw - 1] = (long long)prefix[batch] * hkv;
 }
-extern "C" long long count_spans(long long total, int longest, long long launch_waves, int can_chain, int *chain)
+extern "C" long long choose_spans(long long total, int longest, long long units, long long waves, int classes, int kv8, int *mode)
 {
-    const ss::SpanCount c = ss::count_spans(total, longest, launch_waves, can_chain != 0);
-    *chain = c.chain;
+    const ss::SpanChoice c = ss::choose_spans(total, longest, units, waves, classes != 0, kv8 != 0);
+    *mode = c.mode;
     return c.spans;
 }
 extern "C" void quotients(const long long *a, const long long *b, int n, long long *out)
@@ -178,7 +178,7 @@ def test_random_shapes(shim):
         else:
             pairs = rng.integers(200, 1200, batch)                  # long
         total = int(pairs.sum()) * hkv
-        weight = int(rng.choice([0, 1, 2, 3, 8, 17, 32]))           # 2 and 8 are the defaults, 32 the largest the option gives
+        weight = int(rng.choice([0, 1, 2, 3, 8, 17, 32]))           # 2 is the default, 32 the largest the option gives
         nw_max = max(1, total // 2)                                 # the plan kernel's bound: two pairs per span on average
         nw = int(min(nw_max, rng.choice([1, 4, 8, 64, 256, 1024])))
         nw = max(4 * (nw // 4), 1) if nw >= 4 else nw
@@ -186,43 +186,68 @@ def test_random_shapes(shim):
 
 
 def test_bench_workload_shape(shim):
-    # 64 requests, contexts uniform on [256, 4096] + 5 new tokens, 8 KV heads, 1024 spans, both default weights
+    # 64 requests, contexts uniform on [256, 4096] + 5 new tokens, 8 KV heads, 1024 spans
     rng = np.random.default_rng(2)
     pairs = (rng.integers(256, 4097, 64) + 5 + 31) // 32
     for weight in (2, 8):
         _check(shim, pairs, 8, weight, 1024)
 
 
-@pytest.mark.parametrize("can_chain", [False, True])
-def test_the_merge_adds_few_partials(shim, can_chain):
-    """A unit's partials are added one after the other: at most about 32 of them, or what spans of four pairs leave (with the
-    hand-over, where the instance has it) on a call of long units.  One request, a few equal ones, one long among short ones."""
-    shim.count_spans.restype = ctypes.c_longlong
-    worst = 0
+CHAIN, TEAM, ALONE = 0, 1, 2
+WAVES = 1024
+
+
+def choose(shim, total, longest, units, classes, kv8):
+    mode = ctypes.c_int()
+    shim.choose_spans.restype = ctypes.c_longlong
+    n = shim.choose_spans(ctypes.c_longlong(total), int(longest), ctypes.c_longlong(units), ctypes.c_longlong(WAVES), int(classes),
+                          int(kv8), ctypes.byref(mode))
+    return n, mode.value
+
+
+@pytest.mark.parametrize("classes,kv8", [(False, False), (True, False), (True, True)])
+def test_the_merge_adds_few_partials(shim, classes, kv8):
+    """Over many shapes: there are never more spans than wavefronts (teams) or than half as many as pairs; and the
+    merge adds a unit's partials one after the other, so that these are at most about 32, or what the longer spans leave on a
+    call of long units.  One request, a few equal ones, one long among short ones."""
+    seen = set()
     for hkv in (1, 2, 8):
-        for batch in (1, 2, 4, 16, 64):
-            for n in (1, 2, 9, 31, 32, 33, 63, 64, 65, 125, 128, 129, 250, 500, 1000, 4000):
+        for batch in (1, 2, 4, 16, 64, 128, 512):
+            for n in (1, 2, 4, 5, 8, 9, 16, 17, 31, 33, 64, 125, 250, 500, 1000, 4000):
                 for rest in (n, 3):
                     pairs = np.array([n] + [min(rest, n)] * (batch - 1))
-                    total = int(pairs.sum()) * hkv
-                    chain = ctypes.c_int()
-                    nw = shim.count_spans(ctypes.c_longlong(total), n, ctypes.c_longlong(1024), int(can_chain),
-                                          ctypes.byref(chain))
-                    label = (hkv, batch, n, rest, nw, chain.value)
-                    assert 1 <= nw <= 1024 and (nw == 1 or total >= 2 * nw), label
-                    assert can_chain or not chain.value, label
-                    assert not can_chain or chain.value or nw < 1024, label    # a full chip hands over
+                    total, units = int(pairs.sum()) * hkv, batch * hkv
+                    nw, mode = choose(shim, total, n, units, classes, kv8)
+                    label = (hkv, batch, n, rest, nw, mode)
+                    seen.add(mode)
+                    most = WAVES if mode != TEAM else WAVES // 4
+                    assert 1 <= nw <= most and (nw == 1 or total >= 2 * nw), label
+                    assert mode == TEAM or mode == (ALONE if classes else CHAIN), label
+                    if units < 2 * (WAVES // 4) and (classes or total < 2 * WAVES):
+                        assert mode == TEAM, label                  # few units, or a chip that is not full
+                    if classes and units < 2 * (WAVES // 4):
+                        assert mode != ALONE, label                 # (such calls are launched without the code for it)
+                    if units * nw > 100000:
+                        continue   # (the check walks every unit's spans)
                     _check(shim, pairs, hkv, 2, nw)
                     prefix = np.concatenate([[0], np.cumsum(pairs)]).astype(np.int32)
-                    first, last = np.zeros(batch * hkv, np.int32), np.zeros(batch * hkv, np.int32)
+                    first, last = np.zeros(units, np.int32), np.zeros(units, np.int32)
                     as_int = lambda a: a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
                     shim.merge_waves(as_int(prefix), batch, hkv, 2, ctypes.c_longlong(nw), as_int(first), as_int(last))
-                    per = 4 if chain.value else 1
+                    per = 4 if mode == CHAIN else 1
                     partials = int((last // per - first // per).max()) + 1
-                    coarse = min(1024, max(1, total // 4))       # spans of four pairs
-                    before = -(-n * coarse // total) // (4 if can_chain else 1) + 2
-                    assert partials <= max(34, before), (label, partials, before)
-                    if not chain.value and can_chain:
-                        assert partials <= 18, label
-                    worst = max(worst, partials)
-    assert worst > 200 or can_chain
+                    longer = max(1, min(most, total // (16 if mode == TEAM else 4)))
+                    assert partials <= max(34, -(-n * longer // total) // per + 2), (label, partials)
+    assert seen == {TEAM, ALONE if classes else CHAIN}
+
+
+@pytest.mark.parametrize("units,mean,longest,classes,kv8,want", [
+    (511, 2, 4, True, False, TEAM), (512, 2, 4, True, False, ALONE),                 # two units to a team
+    (512, 13, 30, True, False, ALONE), (512, 14, 30, True, False, TEAM),             # 27 pairs per unit to a wavefront
+    (1024, 27, 60, True, False, ALONE), (1024, 28, 60, True, False, TEAM), (1024, 28, 60, True, True, ALONE),
+    (768, 42, 99, True, True, ALONE), (768, 43, 99, True, True, TEAM),               # 56 with e4m3 caches
+    (511, 2, 4, False, False, TEAM), (512, 2, 4, False, False, CHAIN),               # one or two row blocks: many units,
+    (64, 31, 40, False, False, TEAM), (64, 32, 40, False, False, CHAIN), (1, 4000, 4000, False, False, TEAM),
+    (1, 4096, 4096, False, False, CHAIN)])                                           # or a full chip (spans of four pairs in a long unit)
+def test_whose_the_spans_are(shim, units, mean, longest, classes, kv8, want):
+    assert choose(shim, units * mean, longest, units, classes, kv8)[1] == want
