@@ -97,7 +97,10 @@ struct Cut {
         mode = c.mode;
         cuts.nw = c.spans;
         constexpr uint64_t every = 0x001001001001001ull;   // one weight for all classes
-        if (a.team_blocks) {
+        if (c.whole) {   // a unit counts one, whatever its pairs
+            classes.cost = 0;
+            classes.weight = every;
+        } else if (a.team_blocks) {
             const int skip = kMaxClasses - a.team_blocks;   // classes with more row blocks than the kernel has
             classes.cost = (kv8 ? pack_costs(kPairCost[1], 8) : pack_costs(kPairCost[0], 8)) >> (8 * skip);
             if (a.auto_weight)

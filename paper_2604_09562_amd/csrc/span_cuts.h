@@ -30,6 +30,7 @@ constexpr int kMaxUnitPartials = 32;
 struct SpanChoice {
     int mode;
     long long spans;   // of all pairs, cut by cost
+    bool whole;        // instead: a span per unit
 };
 
 // Wavefronts' spans: of two pairs as long as the chip is not full, of four where a unit would leave too many partials (a hand-over leaves
@@ -63,11 +64,19 @@ SS_HOST_DEVICE inline long long count_team_spans(long long total, int longest, l
 // So from two units to a team on, and while a unit's pairs on average are not more than kAlonePairs times the units to a wavefront.
 // With one or two row blocks the exchange is small and wavefronts hand over: they serve a full chip (64 requests of 256..4096
 // tokens: 106 us, and 112 in teams), and calls of many short units (64 of 100 tokens: 24.6, and 26.8 in teams).
-constexpr int kAlonePairs = 27, kAlonePairsKv8 = 56;
+//
+// Whole units.  A team walks four pairs at once and a chip that is not full has teams to spare, so units up to a few rounds of it get a
+// team each: no unit waits behind another's in one span, none is split (before, cuts of equal cost gave one team two units and
+// the next none).  A whole call, in us, cuts by cost / whole units: 4 requests of 28..40 tokens, 8 KV heads, three row blocks 23.9 / 18.0,
+// five 28.6 / 20.8; 100 of 30..60 over one, five 31.0 / 21.8; two of 20..100 over two, three 23.0 / 18.0; longest unit of 11 pairs, one request 18.4
+// / 19.6, 16 requests 22.9 / 20.8, 31 requests 30.0 / 22.7; of 22 pairs level.  With one or two row blocks splitting costs less: 4 requests of
+// up to 8 pairs 16.0 / 16.6, 31 of them 23.1 / 19.1.
+constexpr int kAlonePairs = 27, kAlonePairsKv8 = 56, kWholePairs = 8;
 SS_HOST_DEVICE inline SpanChoice choose_spans(long long total, int longest, long long units, long long waves, bool classes, bool kv8)
 {
     const long long teams = waves / kSpansPerWg;
     SpanChoice c;
+    c.whole = false;
     if (classes) {
         const bool alone = units >= 2 * teams && (double)total * (double)waves <= (double)(kv8 ? kAlonePairsKv8 : kAlonePairs) * (double)units * (double)units;
         c.mode = alone ? kSpanAlone : kSpanTeam;
@@ -76,7 +85,13 @@ SS_HOST_DEVICE inline SpanChoice choose_spans(long long total, int longest, long
         c.spans = count_wave_spans(total, longest, waves, true);
         c.mode = c.spans == waves || units >= 2 * teams ? kSpanChain : kSpanTeam;
     }
-    if (c.mode == kSpanTeam) c.spans = count_team_spans(total, longest, teams);
+    if (c.mode == kSpanTeam) {
+        c.spans = count_team_spans(total, longest, teams);
+        if (units <= teams && longest <= kWholePairs * (2 * units >= teams ? 2 : 1) / (classes ? 1 : 2)) {
+            c.whole = true;
+            c.spans = units;
+        }
+    }
     return c;
 }
 
@@ -128,10 +143,10 @@ struct SpanCuts {
     long long total_w;   // the coordinate's end: what all units cost
     long long nw;        // number of spans
 
-    // weighted coordinate of span w's cut
-    SS_HOST_DEVICE SS_INLINE long long cut(long long w) const { return quotient(w * total_w, nw); }
+    // weighted coordinate of span w's cut  (a span per unit of the coordinate: no division, a third of a short call's plan)
+    SS_HOST_DEVICE SS_INLINE long long cut(long long w) const { return nw == total_w ? w : quotient(w * total_w, nw); }
     // the first span whose cut lies at or behind y: those of a unit's stretch [ya, ye) are from this of ya to this of ye
-    SS_HOST_DEVICE SS_INLINE long long first_cut_at_or_after(long long y) const { return quotient(y * nw + total_w - 1, total_w); }
+    SS_HOST_DEVICE SS_INLINE long long first_cut_at_or_after(long long y) const { return nw == total_w ? y : quotient(y * nw + total_w - 1, total_w); }
     // pair of the unit at which a span begins whose cut lies in the unit's stretch
     SS_HOST_DEVICE SS_INLINE static int first_pair(long long cut_y, long long ya, int weight, int cost)
     {
@@ -142,6 +157,10 @@ struct SpanCuts {
     // lies at or before the unit's first pair ... the last one whose cut lies at or before its last pair.
     SS_HOST_DEVICE SS_INLINE void unit_spans(long long ya, int n, int weight, int cost, int &w_first, int &w_last) const
     {
+        if (cost == 0) {   // (cuts fall between units only)
+            w_first = w_last = 0;
+            return;
+        }
         w_first = (int)quotient((ya + weight + cost) * nw - 1, total_w);
         w_last = (int)quotient((ya + weight + (long long)n * cost) * nw - 1, total_w);
     }

@@ -109,13 +109,15 @@ def test_single_long_requests(oracle, tokens, hkv, hq, depth, spans, mode):
 
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 @pytest.mark.parametrize("tree", [False, True])
-@pytest.mark.parametrize("batch,hkv,hq,depth,lo,hi,mode", [
-    (16, 2, 8, 10, 1, 256, TEAM), (128, 2, 8, 15, 1, 512, TEAM),
-    (255, 2, 16, 9, 1, 200, TEAM), (256, 2, 16, 9, 1, 200, ALONE),      # five row blocks: two units to a team
-    (256, 2, 8, 10, 1, 1300, TEAM),                                     # (their pairs too many)
-    (255, 2, 8, 4, 1, 100, TEAM), (256, 2, 8, 4, 1, 100, CHAIN)])       # two row blocks: many units
-def test_short_units(oracle, batch, hkv, hq, depth, lo, hi, mode, tree, kv):
-    """Requests of a few pairs, all row blocks up to the call's: teams and wavefronts by themselves."""
+@pytest.mark.parametrize("batch,hkv,hq,depth,lo,hi,spans,mode", [
+    (16, 2, 8, 10, 1, 256, 32, TEAM), (16, 2, 8, 10, 1, 290, None, TEAM),        # whole units of up to eight pairs
+    (128, 2, 8, 15, 1, 512, 256, TEAM), (128, 2, 8, 10, 1, 540, None, TEAM),     # of up to sixteen in half as many units as teams
+    (255, 2, 16, 9, 1, 200, None, TEAM), (256, 2, 16, 9, 1, 200, None, ALONE),   # five row blocks: two units to a team
+    (256, 2, 8, 10, 1, 1300, None, TEAM),                                        # (their pairs too many)
+    (16, 2, 8, 4, 1, 128, 32, TEAM), (16, 2, 8, 4, 1, 160, None, TEAM),          # two row blocks: whole units of up to four pairs
+    (255, 2, 8, 4, 1, 100, None, TEAM), (256, 2, 8, 4, 1, 100, None, CHAIN)])    # many units
+def test_short_units(oracle, batch, hkv, hq, depth, lo, hi, spans, mode, tree, kv):
+    """Requests of a few pairs, all row blocks up to the call's: a span per unit, teams and wavefronts by themselves."""
     rng = np.random.default_rng(batch + hi)
     lens = rng.integers(lo, hi + 1, batch).astype(np.int32)
     lens[0] = hi
@@ -126,6 +128,8 @@ def test_short_units(oracle, batch, hkv, hq, depth, lo, hi, mode, tree, kv):
     check(inp, oracle, max_q_len=depth + 1, label=f"{batch} requests of up to {hi}")
     plan = plan_of(inp, depth + 1)
     assert plan["mode"] == (mode if kv == "bf16" or hi != 1300 else ALONE), plan
+    assert plan["cost"][0] == 0 if spans else plan["cost"][0] > 0
+    assert spans is None or plan["spans"] == spans
 
 
 @pytest.mark.parametrize("waves", [4, 0])

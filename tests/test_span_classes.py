@@ -80,12 +80,15 @@ def test_spans_by_class(shim, seed):
         batch, hkv = int(rng.integers(1, 50)), int(rng.choice([1, 2, 8]))
         cls = np.sort(rng.integers(0, 5, batch)).astype(np.int32)
         n = (np.exp(rng.uniform(0, np.log(rng.choice([4, 60, 700])), batch)).astype(np.int32) + 1).astype(np.int32)
-        if rng.random() < 0.5:
+        kind = rng.integers(0, 3)
+        if kind == 0:   # whole units
+            cost, weight = np.zeros(5, np.int32), np.ones(5, np.int32)
+        elif kind == 1:
             cost, weight = np.array([10, 9, 9, 8, 8], np.int32), np.array([280, 220, 160, 96, 64], np.int32)
         else:
             cost, weight = rng.integers(1, 17, 5).astype(np.int32), rng.integers(0, 1025, 5).astype(np.int32)
         total = int(n.sum()) * hkv
-        nw = int(min(rng.choice([1, 3, 16, 256]), max(1, total // 2)))
+        nw = int(min(rng.choice([1, 3, 16, 256]), max(1, total // 2))) if kind else batch * hkv
         out, count = np.full((nw, 4), -1, np.int64), np.zeros(nw, np.int32)
         first, last = np.zeros(batch * hkv, np.int32), np.zeros(batch * hkv, np.int32)
         prefix, cprefix = np.zeros(batch + 1, np.int32), np.zeros(batch + 1, np.int64)
@@ -97,7 +100,10 @@ def test_spans_by_class(shim, seed):
         off = np.concatenate([[0], np.cumsum(np.repeat(n, hkv))])
         for u in range(batch * hkv):
             holders = [w for w in range(nw) if max(x0[w], off[u]) < min(x1[w], off[u + 1])]
-            assert holders == list(range(first[u], last[u] + 1)), (u, holders, first[u], last[u])
+            if kind:
+                assert holders == list(range(first[u], last[u] + 1)), (u, holders, first[u], last[u])
+            else:   # the merge has to see that every unit lies in one span, which is its own
+                assert holders == [u] and first[u] == last[u], (u, holders)
 
 
 def test_team_spans(shim):

@@ -61,10 +61,11 @@ extern "C" void plan_spans(const int32_t *prefix, int batch, int hkv, int weight
         }
     out[4 * nw - 1] = (long long)prefix[batch] * hkv;
 }
-extern "C" long long choose_spans(long long total, int longest, long long units, long long waves, int classes, int kv8, int *mode)
+extern "C" long long choose_spans(long long total, int longest, long long units, long long waves, int classes, int kv8, int *mode, int *whole)
 {
     const ss::SpanChoice c = ss::choose_spans(total, longest, units, waves, classes != 0, kv8 != 0);
     *mode = c.mode;
+    *whole = c.whole;
     return c.spans;
 }
 extern "C" void quotients(const long long *a, const long long *b, int n, long long *out)
@@ -198,16 +199,16 @@ WAVES = 1024
 
 
 def choose(shim, total, longest, units, classes, kv8):
-    mode = ctypes.c_int()
+    mode, whole = ctypes.c_int(), ctypes.c_int()
     shim.choose_spans.restype = ctypes.c_longlong
     n = shim.choose_spans(ctypes.c_longlong(total), int(longest), ctypes.c_longlong(units), ctypes.c_longlong(WAVES), int(classes),
-                          int(kv8), ctypes.byref(mode))
-    return n, mode.value
+                          int(kv8), ctypes.byref(mode), ctypes.byref(whole))
+    return n, mode.value, whole.value
 
 
 @pytest.mark.parametrize("classes,kv8", [(False, False), (True, False), (True, True)])
 def test_the_merge_adds_few_partials(shim, classes, kv8):
-    """Over many shapes: there are never more spans than wavefronts (teams) or than half as many as pairs; and the
+    """Over many shapes: there are never more spans than wavefronts (teams) or, but for whole units, than half as many as pairs; and the
     merge adds a unit's partials one after the other, so that these are at most about 32, or what the longer spans leave on a
     call of long units.  One request, a few equal ones, one long among short ones."""
     seen = set()
@@ -217,10 +218,13 @@ def test_the_merge_adds_few_partials(shim, classes, kv8):
                 for rest in (n, 3):
                     pairs = np.array([n] + [min(rest, n)] * (batch - 1))
                     total, units = int(pairs.sum()) * hkv, batch * hkv
-                    nw, mode = choose(shim, total, n, units, classes, kv8)
-                    label = (hkv, batch, n, rest, nw, mode)
-                    seen.add(mode)
+                    nw, mode, whole = choose(shim, total, n, units, classes, kv8)
+                    label = (hkv, batch, n, rest, nw, mode, whole)
+                    seen.add((mode, whole))
                     most = WAVES if mode != TEAM else WAVES // 4
+                    if whole:
+                        assert mode == TEAM and nw == units <= most and n <= 16, label
+                        continue
                     assert 1 <= nw <= most and (nw == 1 or total >= 2 * nw), label
                     assert mode == TEAM or mode == (ALONE if classes else CHAIN), label
                     if units < 2 * (WAVES // 4) and (classes or total < 2 * WAVES):
@@ -238,7 +242,7 @@ def test_the_merge_adds_few_partials(shim, classes, kv8):
                     partials = int((last // per - first // per).max()) + 1
                     longer = max(1, min(most, total // (16 if mode == TEAM else 4)))
                     assert partials <= max(34, -(-n * longer // total) // per + 2), (label, partials)
-    assert seen == {TEAM, ALONE if classes else CHAIN}
+    assert seen == ({(TEAM, 0), (TEAM, 1), (ALONE, 0)} if classes else {(TEAM, 0), (TEAM, 1), (CHAIN, 0)})
 
 
 @pytest.mark.parametrize("units,mean,longest,classes,kv8,want", [
@@ -251,3 +255,12 @@ def test_the_merge_adds_few_partials(shim, classes, kv8):
     (1, 4096, 4096, False, False, CHAIN)])                                           # or a full chip (spans of four pairs in a long unit)
 def test_whose_the_spans_are(shim, units, mean, longest, classes, kv8, want):
     assert choose(shim, units * mean, longest, units, classes, kv8)[1] == want
+
+
+@pytest.mark.parametrize("classes,few,many", [(True, 8, 16), (False, 4, 8)])
+def test_whole_units(shim, classes, few, many):
+    """A span per unit for units of a few pairs: of more where they are at least half as many as teams."""
+    for units, longest, want in ((1, few, 1), (1, few + 1, 0), (127, few, 1), (127, few + 1, 0), (128, many, 1), (128, many + 1, 0),
+                                 (256, many, 1), (257, 2, 0)):
+        n, mode, whole = choose(shim, units * 2 + longest - 2, longest, units, classes, False)
+        assert (mode, whole) == (TEAM, want) and (not whole or n == units), (units, longest)
