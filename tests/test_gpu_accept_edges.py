@@ -160,3 +160,47 @@ def test_more_workgroups_than_a_grid_holds():
     assert np.array_equal(acc.cpu().numpy(), n)
     last = toks.cpu().numpy()[np.arange(B), n]
     assert np.array_equal(last, hot.cpu().numpy()[q_indptr[:-1].cpu().numpy() + n])
+
+
+def rejected_at_once(inp, dtype, target, draft):
+    """Both logit arrays as given; every request's first draft is the token that its target row likes least against its draft row."""
+    inp["target_logits"][:] = synth.store(target, dtype)
+    inp["draft_logits"][:] = synth.store(draft, dtype)
+    t, d = (synth.decode_storage(inp[k], dtype).astype(np.float64) for k in ("target_logits", "draft_logits"))
+    for b in range(inp["batch"]):
+        r, rd = int(inp["q_indptr"][b]), int(inp["q_indptr"][b]) - b
+        dd, tt = d[rd, :inp["vocab"]], t[r, :inp["vocab"]]
+        inp["draft_tokens"][rd] = int(np.argmax((dd - dd.max()) - (tt - tt.max())))
+    inp["u_accept"][:] = np.float32(0.999999)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [3000, 20000])   # entries at the boundary of p and q listed, and more of them than the list holds
+@pytest.mark.parametrize("temperature", [1.0, 0.05])
+@pytest.mark.parametrize("offset", [1e3, -1e3, 1e5, -1e5, 1e6])
+def test_rows_offset_against_each_other(oracle, offset, temperature, vocab, dtype):
+    """Rows that differ by a large constant and a little noise: where p > q is decided by a difference of logits that is far from 0, with
+    much of the vocabulary at the boundary, and the residual is spread over thousands of entries."""
+    cfg = TINY.scaled(batch=12, vocab=vocab, logit_dtype=dtype, temperature=temperature, depth=("fixed", 2))
+    inp = make(False, cfg, 3)
+    rng = np.random.default_rng(7)
+    R, Rd = inp["target_logits"].shape[0], inp["draft_logits"].shape[0]
+    target = rng.standard_normal((R, vocab)).astype(np.float32) * np.float32(2.0 * temperature)
+    judge = np.array([inp["q_indptr"][b] + i for b in range(12) for i in range(2)])
+    draft = target[judge] + rng.standard_normal((Rd, vocab)).astype(np.float32) * np.float32(0.3 * temperature)
+    rejected_at_once(inp, dtype, target + np.float32(offset), draft)
+    assert np.all(oracle.spec_accept(inp)["accepted_len"] == 0)
+    check(False, inp, oracle, f"offset {offset} T {temperature} {dtype}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("vocab", [3000, 20000])
+def test_draft_rows_of_the_lowest_value(oracle, vocab, dtype):
+    """A draft row that holds the type's lowest finite value throughout is the uniform distribution; every entry lies at the boundary."""
+    cfg = TINY.scaled(batch=12, vocab=vocab, logit_dtype=dtype, depth=("fixed", 1))
+    inp = make(False, cfg, 5)
+    target = synth.decode_storage(inp["target_logits"], dtype).astype(np.float32)
+    lowest = np.float32(np.finfo(np.float32).min if dtype == "f32" else -3.3895313892515355e38)
+    rejected_at_once(inp, dtype, target, np.full(inp["draft_logits"].shape, lowest, np.float32))
+    assert np.all(oracle.spec_accept(inp)["accepted_len"] == 0)
+    check(False, inp, oracle, f"lowest draft rows {dtype}")
