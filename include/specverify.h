@@ -376,10 +376,11 @@ int32_t ss_route_select(const ss_worker_metrics *workers, int32_t n, const doubl
  * Options (process-wide, not thread-safe; meant for tests and measurement).
  *   "attn_path"     0 = automatic, 1 = force the fp32 kernel, 2 = require the MFMA kernel
  *   "attn_waves"    number of KV stream partitions (wavefronts) of the MFMA kernel, 0 = automatic
- *   "attn_unit_weight"  what opening a (request, KV head) unit is taken to cost a wavefront, in KV tiles, when the
- *                   KV stream is cut into partitions.  3 (the default) = automatic: 3, or 16 where a KV head has more
- *                   than 48 query rows; any other value in 0..64 is used as given, rounded up to whole pairs of tiles
- *                   (0 = partitions of equal tile counts)
+ *   "attn_unit_weight"  what opening a (request, KV head) unit is taken to cost a wavefront, in KV tiles (rounded up to whole
+ *                   pairs), when the KV stream is cut into partitions; 0..64.  Where a workgroup's four wavefronts open a
+ *                   unit together it counts four times (twice up to 32 query rows per KV head); 0 = partitions of equal
+ *                   cost of the tiles alone.  3 (the default) = automatic: two pairs of tiles up to 32 query rows per KV head, costs
+ *                   measured by row blocks and cache type above that.  Not used where every unit is a partition (few short units)
  *   "validate"      1 = before launching, ss_spec_verify_attn, ss_kv_append and ss_spec_accept check the
  *                   device-resident metadata with a small kernel (row offsets, lengths against block counts,
  *                   block ids, draft tokens, temperatures, uniforms), synchronise the stream and return

@@ -29,7 +29,7 @@ int32_t hip_fail(hipError_t e, const char *what)
 static int64_t g_attn_path = 0;
 static int64_t g_attn_waves = 0;
 static int64_t g_validate = 0;
-constexpr int64_t kUnitWeightAuto = 3;    // the option's default: by the instance's row blocks (3 or 16 tiles)
+constexpr int64_t kUnitWeightAuto = 3;    // the option's default: what was measured for the kernel and the row blocks
 static int64_t g_unit_weight = kUnitWeightAuto;
 static std::vector<hipEvent_t> g_events;  // pairs
 static int g_prof_cap = 0, g_prof_used = 0;
