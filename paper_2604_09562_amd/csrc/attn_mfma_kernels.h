@@ -998,10 +998,6 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
 #pragma unroll
     for (int j = 0; j < kDescPairs; ++j) run.addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
-    // (In one trip to memory: left to the compiler, some of it is read behind the test for an empty span, and some again further down.)
-    int cls = d[3], class_end = d[5];
-    asm volatile("" : "+s"(run.p), "+s"(run.g), "+s"(run.b), "+s"(run.n), "+s"(run.x0), "+s"(run.unit_x), "+s"(run.L), "+s"(run.q0), "+s"(run.q1), "+s"(cls), "+s"(class_end));
-    asm volatile("" : "+s"(run.addr[0].x), "+s"(run.addr[0].y), "+s"(run.addr[1].x), "+s"(run.addr[1].y), "+s"(run.addr[2].x), "+s"(run.addr[2].y));
     if constexpr (BLOCKS <= kChainRowBlocks) {
         if (team) {
             if (run.x0 >= run.x1) return;
@@ -1013,6 +1009,11 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
             walk<G, BLOCKS, BLOCKS, FP8, TREE, true>(a, lds, run, false, pair_addr, req, k_scale, v_scale);
         }
     } else {
+        // (In one trip to memory: left to the compiler, some of it is read behind the test for an empty span, and some again further
+        // down: 0.3 us of a short call.  The kernels above read it so by themselves.)
+        int cls = d[3], class_end = d[5];
+        asm volatile("" : "+s"(run.p), "+s"(run.g), "+s"(run.b), "+s"(run.n), "+s"(run.x0), "+s"(run.unit_x), "+s"(run.L), "+s"(run.q0), "+s"(run.q1), "+s"(cls), "+s"(class_end));
+        asm volatile("" : "+s"(run.addr[0].x), "+s"(run.addr[0].y), "+s"(run.addr[1].x), "+s"(run.addr[1].y), "+s"(run.addr[2].x), "+s"(run.addr[2].y));
         if (run.x0 >= run.x1) return;
         walk_classes<G, BLOCKS, FP8, TREE>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
     }
@@ -1037,15 +1038,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a)
     const int q0 = r.q0;
     const int rows = window_q_len(r.q1 - q0, a.q_lo, a.q_win) * G;   // rows of this pass's window
     const int n = slab * (8 * PER) + (threadIdx.x >> 5), d4 = threadIdx.x & 31;
-    if (n >= rows) return;
-    // The spans were cut at w*total_cost/cuts in the weighted coordinate (every unit: what opening it costs, then its
-    // pairs); the last wave whose cut lies at or before coordinate t is ((t+1)*cuts - 1) / total_cost.  A cut
-    // inside the opening's part starts at the unit's first pair, so the unit's first wave is the last one at
-    // or before the end of that part and the first pair, its last wave the last one before the next unit's stretch.
-    const int cost = a.plan->class_cost[r.cls], weight = a.plan->class_weight[r.cls];
     SpanCuts cuts;
     cuts.total_w = a.plan->total_cost;
     cuts.nw = a.plan->spans;
+    if ((n >= rows) | (cuts.nw == cuts.total_w)) return;   // (a span per unit: nothing is left; read together with the request's record)
+    // The spans were cut at w*total_cost/spans in the weighted coordinate (every unit: what opening it costs, then its
+    // pairs); the last wave whose cut lies at or before coordinate t is ((t+1)*spans - 1) / total_cost.  A cut
+    // inside the opening's part starts at the unit's first pair, so the unit's first wave is the last one at
+    // or before the end of that part and the first pair, its last wave the last one before the next unit's stretch.
+    const int cost = a.plan->class_cost[r.cls], weight = a.plan->class_weight[r.cls];
     int w_first, w_last;
     cuts.unit_spans(r.cpre * a.num_kv_heads + (long long)g * (weight + (long long)r.n * cost), r.n, weight, cost, w_first, w_last);
     if (a.plan->mode == kSpanChain) {   // the streaming kernel has combined the spans of each workgroup: one partial per workgroup

@@ -157,10 +157,6 @@ struct SpanCuts {
     // lies at or before the unit's first pair ... the last one whose cut lies at or before its last pair.
     SS_HOST_DEVICE SS_INLINE void unit_spans(long long ya, int n, int weight, int cost, int &w_first, int &w_last) const
     {
-        if (cost == 0) {   // (cuts fall between units only)
-            w_first = w_last = 0;
-            return;
-        }
         w_first = (int)quotient((ya + weight + cost) * nw - 1, total_w);
         w_last = (int)quotient((ya + weight + (long long)n * cost) * nw - 1, total_w);
     }
