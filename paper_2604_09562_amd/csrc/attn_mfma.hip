@@ -25,14 +25,17 @@ namespace {
 // a call took 238 us with every unit walked by the code for five, 221 this way; 128 requests of 128..16384, 32 heads over 8, depth 0..8
 // (one to three): 280 either way (bound by memory); decode step of two layers of trees of 4..8 nodes, e4m3: 145 and 132.
 //
-// What a unit's place needs to know of the other requests: up to kPlanLanes requests every wavefront reads all of them, up to
-// four to a lane, and sums for itself, with one barrier for what the descriptors look up; a larger batch is laid out by a kernel of one
-// workgroup in front (attn_layout_kernel), where every workgroup of the plan would walk the whole batch.  Measured with three row
-// blocks, against a sort in rounds of 256 requests by every workgroup: 65 requests over 8 KV heads 9.2 -> 7.3 us, 256 13.2 -> 8.3, 300 18.7 -> 4.7 and
-// 6.4 (two kernels), 1000 over two 25.4 -> 12.4, 4096 over one 177 -> 22.  (Without classes, cuts and layout by one prefix of the batch
-// took 6.5, 9.0, 10.7, 12.3 and 39.6.)
+// What a unit's place needs to know of the other requests: up to kPlanLanes requests every wavefront reads all of them, up to eight
+// to a lane (four with classes), and sums for itself, with one barrier for what the descriptors look up; a larger batch is laid out
+// by a kernel of one workgroup in front (attn_layout_kernel), where every workgroup of the plan would walk the whole batch.  Measured
+// with three row blocks, against a sort in rounds of 256 requests by every workgroup: 65 requests over 8 KV heads 9.2 -> 7.3 us, 256
+// 13.2 -> 8.3, 300 18.7 -> 4.7 and 6.4 (two kernels), 1000 over two 25.4 -> 12.4, 4096 over one 177 -> 22.  (Without classes, cuts
+// and layout by one prefix of the batch took 6.5, 9.0, 10.7, 12.3 and 39.6.)  Where the layout kernel begins to pay, eight to a lane
+// against layout and plan: without classes 257 requests over one KV head 7.6 / 4.2 + 5.9 us, 400 over one 6.4 / 4.2 + 4.6, 257 over
+// eight 10.7 / 4.8 + 8.1, 512 over eight 10.9 / 4.7 + 8.8, and a launch less; with classes 300 over eight 12.4 / 4.8 + 7.6, 400 over
+// two 10.9 / 4.7 + 4.9 (the call 36.1 / 35.0).
 // ---------------------------------------------------------------------------------------------
-constexpr int kPlanLanes = 256, kPlanGroups = 512;
+constexpr int kPlanLanes = 512, kPlanLanesClasses = 256, kPlanGroups = 512;
 
 // Inclusive scan over a wavefront's lanes (values >= 0, 0 is neutral for `op`) by data-parallel moves: a scan by shuffles is six
 // LDS round trips, 0.3 us of the plan's 5.
@@ -130,8 +133,8 @@ struct Cut {
     }
 };
 
-// The layout of a batch beyond kPlanLanes: one workgroup, each wavefront a run of the requests.  One pass counts the classes, the other
-// finds the places (stable, class by class) and writes the records.
+// The layout of a batch beyond kPlanLanes (kPlanLanesClasses with classes): one workgroup, each wavefront a run of the requests.  One
+// pass counts the classes, the other finds the places (stable, class by class) and writes the records.
 constexpr int kLayoutWaves = 16;
 __global__ __launch_bounds__(64 * kLayoutWaves) void attn_layout_kernel(AttnArgs a)
 {
@@ -442,8 +445,10 @@ int32_t attn_mfma_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, 
                 hipLaunchKernelGGL(attn_plan_kernel<1>, grid, dim3(256), 0, stream, p, heads);
             } else if (a.batch <= 128) {
                 hipLaunchKernelGGL(attn_plan_kernel<2>, grid, dim3(256), 0, stream, p, heads);
-            } else if (a.batch <= kPlanLanes) {
+            } else if (a.batch <= kPlanLanesClasses) {
                 hipLaunchKernelGGL(attn_plan_kernel<4>, grid, dim3(256), 0, stream, p, heads);
+            } else if (a.batch <= kPlanLanes && !p.team_blocks) {
+                hipLaunchKernelGGL(attn_plan_kernel<8>, grid, dim3(256), 0, stream, p, heads);
             } else {
                 hipLaunchKernelGGL(attn_layout_kernel, dim3(1), dim3(64 * kLayoutWaves), 0, stream, p);
                 SS_HIP_CHECK(hipGetLastError(), "launch attn_layout_kernel");

@@ -38,7 +38,7 @@ def test_mixed_row_blocks(oracle, hq, top, kv, tree, waves):
 
 
 @pytest.mark.parametrize("hq,top", [(8, 9), (4, 8), (4, 12)])    # to five, three and four row blocks
-@pytest.mark.parametrize("batch", [256, 257, 600, 4096, 4097])   # the plan's largest batch by lanes, the smallest of the layout kernel
+@pytest.mark.parametrize("batch", [256, 257, 600, 4096, 4097])   # the largest batch by lanes with classes, the smallest of the layout kernel
 def test_large_batches(oracle, batch, hq, top):
     rng = np.random.default_rng(batch)
     depth = rng.integers(0, top + 1, batch)
@@ -46,7 +46,8 @@ def test_large_batches(oracle, batch, hq, top):
     check(_inputs("bf16", hq, 1, lens, depth, seed=1), oracle, max_q_len=top + 1, label=f"{batch} requests, {hq} heads")
 
 
-@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65])   # a request to a lane of the plan up to 64, two from 65 on
+# a request to a lane of the plan up to 64, two from 65 on, eight from 257 to 512 without classes
+@pytest.mark.parametrize("batch", [1, 2, 63, 64, 65, 257, 512, 513])
 @pytest.mark.parametrize("hq,top", [(4, 3), (8, 9)])     # one row block (no classes); one to five
 def test_batches_of_a_lane_each(oracle, hq, top, batch):
     rng = np.random.default_rng(batch)

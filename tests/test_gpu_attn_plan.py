@@ -30,7 +30,7 @@ def plan_of(inp, max_q_len):
     return plan, raw[16:24].view(np.int64)[0], req, pairs
 
 
-@pytest.mark.parametrize("batch", [1, 63, 64, 65, 128, 255, 256, 257, 1024, 1025, 4097])
+@pytest.mark.parametrize("batch", [1, 63, 64, 65, 128, 255, 256, 257, 511, 512, 513, 1024, 1025, 4097])
 @pytest.mark.parametrize("hq,hkv,top", [(8, 2, 3), (8, 2, 10), (16, 2, 9)])   # one row block; one to three; one to five
 def test_plan(batch, hq, hkv, top):
     rng = np.random.default_rng(batch + top)
