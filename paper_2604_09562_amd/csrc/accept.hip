@@ -308,12 +308,14 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
 }
 
 // ---- pass 2a: fp64 sums per block -------------------------------------------------------------
-// One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  Bound by the fp64 instructions
-// (26 per pair of entries and the 32-bit ones around them), so the sums cross the lanes by data-parallel moves, once.  Measured for
-// 64 requests of 128256 entries: 22.7 us with shuffles through LDS and ldexp, 20.3 with data-parallel moves and 32 fp64 instructions per
-// pair, 19.0 this way; two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5 against 4.9 us for 8 requests of 32000: a wavefront that
-// walks a block alone is a long chain); all 32 entries of a lane as straight-line code 27 us (instruction fetch).  Exponentials of bf16
-// logits by a table of all values in LDS (64 KB, 1024-lane workgroups): 17.3 us, 58.0 -> 56.7 for the call; not kept for its size.
+// One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  Bound by the instructions of an entry (25 fp64 ones
+// and 14 others per pair): the four sums cross the lanes together and by data-parallel moves, the power of two goes into the table's
+// exponent, and which lanes are near the boundary stays in scalar registers.  Measured for 64 requests of 128256 entries: 22.7 us with
+// shuffles through LDS and ldexp, 20.3 with data-parallel moves and 32 fp64 instructions per pair, 19.2 with 26 of them, a scan per sum and
+// the boundary test in vector registers, 17.5 this way (the call 56.8 -> 55.3); two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5
+// against 4.9 us for 8 requests of 32000: a wavefront that walks a block alone is a long chain); all 32 entries of a lane as
+// straight-line code 27 us (instruction fetch).  Exponentials of bf16 logits by a table of all values in LDS (64 KB, 1024-lane workgroups)
+// saved 2 us of the 19; not kept for its size.
 template <int DT>
 __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Workspace w)
 {
@@ -339,16 +341,17 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
     // exponentials of all entries (zp, zq) and of those whose residual p - q is positive for certain (pp, qq): the difference of an
     // entry's logits decides that in 32 bits (before, two fp64 instructions and two fp64 comparisons did)
     double zp = 0.0, zq = 0.0, pp = 0.0, qq = 0.0;
-    const float theta = pk.theta, width = pk.width;
-    unsigned near = 0;   // entries of this lane that are too close to call before Zp/Zq are exact
-    auto pair = [&](double ep, double eq, float d, unsigned bit) __attribute__((always_inline)) {
-        const float t = d - theta;
+    // clearly above or below the boundary, and else too close to call before Zp/Zq are exact
+    const float above = pk.theta + pk.width, below = pk.theta - pk.width;
+    unsigned long long close = 0;   // lanes with such an entry
+    auto pair = [&](double ep, double eq, float d) __attribute__((always_inline)) {
         zp += ep;
         zq += eq;
-        const double sure = t > width ? 1.0 : 0.0;   // (a factor costs fewer instructions than two selects of doubles)
+        const bool up = d > above;
+        const double sure = up ? 1.0 : 0.0;   // (a factor costs fewer instructions than two selects of doubles)
         pp = fma(ep, sure, pp);
         qq = fma(eq, sure, qq);
-        if (fabsf(t) <= width && __double2hiint(ep) != 0) near |= bit;   // (an entry without mass is not worth a place)
+        close |= __ballot(d >= below) ^ __ballot(up);
     };
     float xp[8], xq[8];
     unpack8<DT>(rp, xp);
@@ -372,22 +375,20 @@ __global__ __launch_bounds__(kThreads) void accept_norm_kernel(AcceptArgs a, Wor
         }
     } else if (normal) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) pair(ex.normal(ap.fma_form(xp[s])), ex.normal(aq.fma_form(xq[s])), xp[s] - xq[s], 1u << s);
+        for (int s = 0; s < 8; ++s) pair(ex.normal(ap.fma_form(xp[s])), ex.normal(aq.fma_form(xq[s])), xp[s] - xq[s]);
     } else {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), xp[s] - xq[s], 1u << s);
+        for (int s = 0; s < 8; ++s) pair(ex(ap(xp[s])), ex(aq(xq[s])), xp[s] - xq[s]);
     }
-    zp = wave_scan(zp);
-    if (residual) {
-        zq = wave_scan(zq);
-        pp = wave_scan(pp);
-        qq = wave_scan(qq);
-    }
-    if (lane == 63) {
-        sum_sh[wave][0] = zp;
-        sum_sh[wave][1] = zq;
-        sum_sh[wave][2] = pp;
-        sum_sh[wave][3] = qq;
+    const double sum = wave_sum4(zp, zq, pp, qq);
+    if ((lane & 15) == 15) sum_sh[wave][sum4_index(lane)] = sum;
+    unsigned near = 0;   // entries of this lane that go to the list (one without mass is not worth a place)
+    if (close) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const float d = xp[s] - xq[s];
+            if (d >= below && d <= above && ap(xp[s]) >= kExpMass) near |= 1u << s;
+        }
     }
     // The boundary entries of a block go to the request's list as one contiguous run, in wavefront, lane and entry
     // order (so their later additions have a fixed order); one counter update per block.

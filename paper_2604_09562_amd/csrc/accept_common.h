@@ -252,8 +252,9 @@ __device__ __forceinline__ T block_sum(T v, T *sh)
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_add(double x)
 {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+    constexpr bool all = ROWS == 0xf;   // lanes without a source read 0 by the instruction itself, not from a register cleared for them
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, all);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, all);
     return x + __hiloint2double(hi, lo);
 }
 // Inclusive running sums of x over the lanes; lane 63 holds the total.  A fixed association.
@@ -267,6 +268,33 @@ __device__ __forceinline__ double wave_scan(double x)
     x = dpp_add<0x143, 0xc>(x);   // row_bcast 31: the sum of rows 0 and 1 to rows 2 and 3
     return x;
 }
+// Lanes 0..31: x of the lane and of the lane 32 further; lanes 32..63: y of the lane and of the lane 32 in front.
+__device__ __forceinline__ double fold32(double x, double y)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(y), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Rows of 16 lanes in pairs: even rows get x of both rows of their pair, odd rows y.
+__device__ __forceinline__ double fold16(double x, double y)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(x), __double2loint(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(x), __double2hiint(y), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// Sums of four values over the wavefront, in a fixed association: lanes 0..15 hold that of a, then c, b and d, each in its
+// row's last lane (15, 31, 47, 63).  Every step halves the values that a lane still carries: a third of the instructions of
+// four scans, which were a quarter of what a block of the fp64 passes issues.
+__device__ __forceinline__ double wave_sum4(double a, double b, double c, double d)
+{
+    double x = fold16(fold32(a, b), fold32(c, d));
+    x = dpp_add<0x111, 0xf>(x);
+    x = dpp_add<0x112, 0xf>(x);
+    x = dpp_add<0x114, 0xf>(x);
+    return dpp_add<0x118, 0xf>(x);
+}
+// Which of the four values the caller's row of lanes holds.
+__device__ __forceinline__ int sum4_index(int lane) { return ((lane >> 4) & 1) * 2 + (lane >> 5); }
 __device__ __forceinline__ double lane_value(double x, int lane)
 {
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane), __builtin_amdgcn_readlane(__double2loint(x), lane));
@@ -299,16 +327,21 @@ static __device__ const double kExp2Sixtyfourths[64] = {
 
 constexpr double kExpSteps = 92.33248261689366;   // 64 / ln2
 constexpr double kExpNormal = -700.0 * kExpSteps;   // from here up ExpTable::normal may be used
+constexpr double kExpMass = -722.0 * kExpSteps;     // from here down an exponential (2^-1041) is not worth a place in a list of boundary entries
 
 struct ExpTable {
+    // 2^(j/64) with j << 14 taken from its upper word: k << 14, k = 64 e + j, added to that makes it 2^(e + j/64)
     double t[64];
     __device__ void init()
     {
-        if (threadIdx.x < 64) t[threadIdx.x] = kExp2Sixtyfourths[threadIdx.x];
+        if (threadIdx.x < 64) {
+            const double v = kExp2Sixtyfourths[threadIdx.x];
+            t[threadIdx.x] = __hiloint2double(__double2hiint(v) - ((int)threadIdx.x << 14), __double2loint(v));
+        }
         __syncthreads();
     }
-    // the significand of exp, in [0.99, 2), and k with exp = significand * 2^(k >> 6)
-    __device__ __forceinline__ double significand(double y, int &k) const
+    // 2^(f/64), f in steps of the table, and k, the nearest integer to y
+    __device__ __forceinline__ double fraction(double y, int &k) const
     {
         // y to the nearest integer: added to 1.5 * 2^52 it lands in the low bits of the significand
         constexpr double magic = 0x1.8p52, step = 0.010830424696249145;   // ln2 / 64
@@ -317,21 +350,22 @@ struct ExpTable {
         const double f = y - (kd - magic);
         constexpr double c1 = step, c2 = step * step / 2, c3 = step * step * step / 6, c4 = step * step * step * step / 24,
                          c5 = step * step * step * step * step / 120;
-        const double p = fma(fma(fma(fma(fma(f, c5, c4), f, c3), f, c2), f, c1), f, 1.0);
-        return t[k & 63] * p;
+        return fma(fma(fma(fma(fma(f, c5, c4), f, c3), f, c2), f, c1), f, 1.0);
     }
     __device__ __forceinline__ double operator()(double y) const
     {
         int k;
-        const double s = significand(fmax(y, -746.0 * kExpSteps), k);   // exp underflows to 0 from there on (also covers -inf)
-        return ldexp(s, k >> 6);
+        const double p = fraction(fmax(y, -746.0 * kExpSteps), k);   // exp underflows to 0 from there on (also covers -inf)
+        const double v = t[k & 63];
+        return ldexp(__hiloint2double(__double2hiint(v) + ((k & 63) << 14), __double2loint(v)) * p, k >> 6);
     }
-    // the same bits for -700 <= x <= 1, where the result is normal and the power of two is an addition to its exponent
+    // the same bits for -700 <= x <= 1, where the result is normal and the power of two goes into the table's exponent
     __device__ __forceinline__ double normal(double y) const
     {
         int k;
-        const double s = significand(y, k);
-        return __hiloint2double(__double2hiint(s) + ((k & ~63) << 14), __double2loint(s));
+        const double p = fraction(y, k);
+        const double v = t[k & 63];
+        return __hiloint2double(__double2hiint(v) + (k << 14), __double2loint(v)) * p;
     }
 };
 
