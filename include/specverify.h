@@ -259,9 +259,9 @@ int32_t ss_spec_accept_tree_greedy(int32_t batch, int32_t vocab, int64_t row_str
  *   out_tokens, accepted_len, accepted_nodes   as for ss_spec_accept_tree_greedy
  *   ratio_out   device float [total_rows-batch] or NULL: r[x]/q[x] of every node that was offered, NaN elsewhere
  *   workspace   >= ss_spec_accept_tree_sample_workspace(...) bytes (it holds two fp64 vocabulary vectors
- *               per request besides the row statistics)
+ *               per request, and lists of entries at the boundary of r and q, besides the row statistics)
  *   max_q_len   also bounds the number of rejections a request can have, hence the number of rounds the
- *               call enqueues (block sums, whose kernel walks on first, and a residual pass per round): a tight bound saves launches
+ *               call enqueues (one launch each, which walks on first): a tight bound saves launches
  * Children are judged from two gathered logits and the row statistics (fp32 chunk sums, relative error
  * below 1e-6, as in ss_spec_accept); residuals, their normalisers and the draw are fp64 with fixed reduction
  * orders.  Other arguments and errors as for ss_spec_accept.
