@@ -66,9 +66,8 @@ static int32_t check_attn_shape(const ss_paged_kv *kv, const ss_batch *b, int32_
     return SS_OK;
 }
 
-int attn_default_waves()
+int attn_chip_waves()
 {
-    if (g_attn_waves > 0) return (int)g_attn_waves;
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
         int v = 0;
@@ -78,6 +77,8 @@ int attn_default_waves()
     }
     return cus * 4;  // one wavefront per SIMD
 }
+
+int attn_default_waves() { return g_attn_waves > 0 ? (int)g_attn_waves : attn_chip_waves(); }
 
 // The checks and the launch behind ss_spec_accept; ss_spec_accept_static calls it with its own buffer and
 // without the optional metadata check (which synchronises and owns a pinned host record).
@@ -214,6 +215,7 @@ int32_t ss_spec_verify_attn(const ss_paged_kv *kv, const ss_batch *batch, const 
     a.q = q; a.out = out; a.lse = lse; a.q_dtype = q_dtype; a.num_q_heads = num_q_heads; a.total_rows = total_rows;
     a.sm_scale = sm_scale;
     a.launch_waves = launch_waves;
+    a.default_waves = g_attn_waves == 0 || launch_waves == attn_chip_waves();
     const int G = num_q_heads / kv->num_kv_heads;
     a.rows_pad = attn_rows_pad(max_q_len, G);
     a.max_q_len = max_q_len;

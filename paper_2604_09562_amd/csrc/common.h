@@ -107,6 +107,7 @@ struct AttnArgs {
     float *part_ml;        // [slots][rows_pad][2]  (log2-domain max, sum)
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
+    int32_t default_waves; // launch_waves is one wavefront per SIMD of this GPU, given or not
     int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts)
     int32_t auto_weight;   // unit_weight is the default: classes take the weights measured for their row blocks
     int32_t team_blocks;   // row blocks of the team kernel that is launched, 0 for the kernels of one or two
@@ -126,8 +127,15 @@ int32_t attn_mfma_launch_g1(const AttnArgs &a, hipStream_t stream, hipEvent_t ev
 int32_t attn_mfma_launch_g2(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);   // after the plan kernel
 int32_t attn_mfma_launch_g4(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 int32_t attn_mfma_launch_g8(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
+// Calls whose units are all short: a workgroup (or `splits` of them, of `team` wavefronts) per unit, without a plan (attn_unit.hip).
+struct AttnUnitChoice {
+    int splits, team;   // splits 0: the call is not one of them
+};
+AttnUnitChoice attn_unit_choose(const AttnArgs &a);
+int32_t attn_unit_launch(const AttnArgs &a, const AttnUnitChoice &choice, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 int32_t attn_generic_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
-int attn_default_waves();
+int attn_default_waves();   // the option's, or one per SIMD
+int attn_chip_waves();      // one per SIMD
 
 // ---- accept --------------------------------------------------------------------------------
 constexpr int kChunk = 8192;  // vocabulary entries per chunk of the row statistics (two chunks to a workgroup)
