@@ -139,12 +139,16 @@ def _check(rc: int) -> None:
         raise SpecVerifyError(f"specverify error {rc}: {lib().ss_last_error().decode()}")
 
 
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+# Addresses go to ctypes as plain integers, which the declared argument types take as they are: an object per argument and torch's stream object
+# were 3 of a call's 6.5 us in Python.
+def _ptr(t: Optional[torch.Tensor]) -> int:
+    return 0 if t is None else t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    if torch.cuda.is_initialized():   # (the current stream of the current device, without an object around it)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def ss_version() -> int:
@@ -236,8 +240,8 @@ def ss_spec_verify_attn(d: Dict[str, object], out: torch.Tensor, lse: Optional[t
     """Enqueue verify attention for a device batch; `out`/`lse`/`workspace` are caller-owned device tensors."""
     kv, bt = _descriptors(d, max_q_len, SS_BATCH_REUSE_PLAN if reuse_plan else 0)
     _check(lib().ss_spec_verify_attn(ctypes.byref(kv), ctypes.byref(bt), _ptr(d["q"]), _DT[d["q_dtype"]],
-                                     d["num_q_heads"], d["total_rows"], ctypes.c_float(d["sm_scale"]), _ptr(out),
-                                     _ptr(lse), _ptr(workspace), workspace.numel() * workspace.element_size(),
+                                     d["num_q_heads"], d["total_rows"], d["sm_scale"], _ptr(out),
+                                     _ptr(lse), _ptr(workspace), workspace.nbytes,
                                      _stream()))
 
 
@@ -311,8 +315,8 @@ def ss_spec_accept(d: Dict[str, object], accepted_len: torch.Tensor, out_tokens:
     _check(lib().ss_spec_accept(d["batch"], d["vocab"], d["row_stride"], _DT[d["logit_dtype"]], d["total_rows"],
                                 max_q_len, _ptr(d["q_indptr"]), _ptr(d["target_logits"]), _ptr(d["draft_logits"]),
                                 _ptr(d["draft_tokens"]), _ptr(d["u_accept"]), _ptr(d["u_sample"]), _ptr(temp),
-                                ctypes.c_float(t_scalar), g, _ptr(accepted_len), _ptr(out_tokens), _ptr(ratio_out),
-                                _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()))
+                                t_scalar, g, _ptr(accepted_len), _ptr(out_tokens), _ptr(ratio_out),
+                                _ptr(workspace), workspace.nbytes, _stream()))
 
 
 def ss_spec_accept_static(d: Dict[str, object], accepted_len: torch.Tensor, out_tokens: torch.Tensor,
@@ -325,7 +329,7 @@ def ss_spec_accept_static(d: Dict[str, object], accepted_len: torch.Tensor, out_
     _check(lib().ss_spec_accept_static(d["batch"], d["vocab"], d["row_stride"], _DT[d["logit_dtype"]], d["total_rows"],
                                        max_q_len, _ptr(d["q_indptr"]), _ptr(d["target_logits"]), _ptr(d["draft_logits"]),
                                        _ptr(d["draft_tokens"]), _ptr(d["u_accept"]), _ptr(d["u_sample"]), _ptr(temp),
-                                       ctypes.c_float(t_scalar), g, _ptr(accepted_len), _ptr(out_tokens), _ptr(ratio_out),
+                                       t_scalar, g, _ptr(accepted_len), _ptr(out_tokens), _ptr(ratio_out),
                                        _stream()))
 
 
@@ -339,7 +343,7 @@ def ss_spec_accept_tree_greedy(d: Dict[str, object], accepted_len: torch.Tensor,
                                             d["total_rows"], max_q_len, _ptr(d["q_indptr"]), _ptr(d["tree_parent"]),
                                             _ptr(d["target_logits"]), _ptr(d["draft_tokens"]), _ptr(accepted_len),
                                             _ptr(out_tokens), _ptr(accepted_nodes), _ptr(workspace),
-                                            workspace.numel() * workspace.element_size(), _stream()))
+                                            workspace.nbytes, _stream()))
 
 
 def ss_spec_accept_tree_sample(d: Dict[str, object], accepted_len: torch.Tensor, out_tokens: torch.Tensor,
@@ -349,9 +353,9 @@ def ss_spec_accept_tree_sample(d: Dict[str, object], accepted_len: torch.Tensor,
                                             d["total_rows"], max_q_len, _ptr(d["q_indptr"]), _ptr(d["tree_parent"]),
                                             _ptr(d["target_logits"]), _ptr(d["draft_logits"]), _ptr(d["draft_tokens"]),
                                             _ptr(d["u_accept"]), _ptr(d["u_sample"]), _ptr(d["temperature"]),
-                                            ctypes.c_float(0.0), _ptr(accepted_len), _ptr(out_tokens),
+                                            0.0, _ptr(accepted_len), _ptr(out_tokens),
                                             _ptr(accepted_nodes), _ptr(ratio_out), _ptr(workspace),
-                                            workspace.numel() * workspace.element_size(), _stream()))
+                                            workspace.nbytes, _stream()))
 
 
 def tree_sample_workspace(d: Dict[str, object], device="cuda:0") -> torch.Tensor:

@@ -3,6 +3,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <atomic>
 #include <vector>
 
 #include "common.h"
@@ -68,10 +69,18 @@ static int32_t check_attn_shape(const ss_paged_kv *kv, const ss_batch *b, int32_
 
 int attn_chip_waves()
 {
+    // (asked for once per GPU; a thread that finds it unknown asks again and stores the same)
+    static std::atomic<int> known[64];
     int dev = 0, cus = 256;
     if (hipGetDevice(&dev) == hipSuccess) {
+        const bool slot = dev >= 0 && dev < 64;
+        if (slot && (cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus * 4;
         int v = 0;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
+        cus = 256;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) {
+            cus = v;
+            if (slot) known[dev].store(v, std::memory_order_relaxed);
+        }
     } else {
         (void)hipGetLastError();
     }
