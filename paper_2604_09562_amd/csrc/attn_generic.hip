@@ -10,9 +10,10 @@
 // many wavefronts per workgroup with the next block's tile in flight; long ones the fp32 matrix rate (D/2
 // instructions of 32 cycles per block and 16 rows) where there are workgroups enough to fill the chip.  The cache of a
 // request is not split over workgroups: one request of 65536 tokens, 32 heads of 64 over 8, is 8 to 24 workgroups at depth
-// 0 to 8 and takes 0.67 ms at any of them (4.0 to 8.6 ms with one workgroup per (row, head) and one token per lane); its
-// bytes alone would take about 0.04 ms.  4 requests of 64..512 tokens, 8 heads of 64, depth 4: 57 us with that form, 12 us
-// (a pass among others, as the host enqueues it) with this one.
+// 0 to 8 and takes 0.65 ms at any of them (4.0 to 8.6 ms with one workgroup per (row, head) and one token per lane); its
+// bytes alone would take about 0.04 ms.  4 requests of 64..512 tokens, 8 heads of 64, depth 4: 57 us with that form, 10.5 us
+// with this one (12.2 with each lane's quarter of a key in one piece, the block ids read behind the lengths, and the weights of the
+// wavefronts' parts worked out by every lane for itself); 64 requests of 1000 tokens, 56 heads over 8, e4m3, depth 4: 174 us (190).
 #include "common.h"
 
 namespace ss {
@@ -60,17 +61,35 @@ __device__ __forceinline__ void load_run(const void *base, int64_t i, float (&x)
     }
 }
 
+// A lane's quarter of a row for the score product: pieces of 16 bytes of the cache's type, those of the four lanes of a token side by side, so that
+// a read takes 64 bytes of a row (with a quarter in one piece it takes 16 bytes of each of 64 places, and a compute unit gets 15 GB/s
+// out of memory instead of 24).  The queries, of either type, are taken in the same order: base + piece * 4 * PIECE + jq * PIECE.
+template <int DT, int D, int PIECE>
+__device__ __forceinline__ void load_quarter(const void *base, int64_t row, int jq, float (&x)[D / 4])
+{
+#pragma unroll
+    for (int j = 0; j < D / 4 / PIECE; ++j) {
+        float part[PIECE];
+        load_run<DT>(base, row * D + j * 4 * PIECE + jq * PIECE, part);
+#pragma unroll
+        for (int c = 0; c < PIECE; ++c) x[j * PIECE + c] = part[c];
+    }
+}
+
 template <int D>
 struct GenericTile {
-    float k[D / 4];         // key of token (lane & 15) at d = (lane >> 4) * D/4 ..
+    float k[D / 4];         // of the key of token (lane & 15), as load_quarter lays it out
     float v[4][D / 16];     // values of tokens 4 * (lane >> 4) + i at d = (lane & 15) * D/16 ..
     float ks, vs;
 };
 
 template <int D, int KV, int QDT>
-__global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(AttnArgs a, int row_blocks)
+__global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(AttnArgs a, int row_blocks, const int32_t *__restrict__ q_indptr, const int32_t *__restrict__ kv_len,
+                                                                         const int32_t *__restrict__ block_table)
 {
+    // (the offsets come in as no-alias arguments of their own, so that they are scalar loads)
     constexpr int NW = kGenericWaves<D>, MB = D / 16;
+    constexpr int PIECE = KV == SS_F32 ? 4 : KV == SS_BF16 ? 8 : 16;   // elements of 16 bytes
     __shared__ float part_o[NW][16][D + 4];
     __shared__ float part_m[NW][16], part_l[NW][16];
 
@@ -79,9 +98,13 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n16 = lane & 15, jq = lane >> 4;
     const int G = a.num_q_heads / a.num_kv_heads;
-    const int q0 = a.q_indptr[b], q_len = a.q_indptr[b + 1] - q0, rows = q_len * G;
+    const int q0 = q_indptr[b], q_len = q_indptr[b + 1] - q0, rows = q_len * G;
+    // This wavefront's tiles are wave, wave + NW, ..: their block ids are read 64 at a time, one per lane; the first ones together with the lengths
+    // (inside the request's row of the table, whose entries past the cache's end may hold anything and are not used).
+    const int32_t *bt = block_table + (int64_t)b * a.max_blocks;
+    int ids = bt[min(wave + lane * NW, a.max_blocks - 1)];
     if (rb * 16 >= rows) return;
-    const int L = a.kv_len[b], ctx = L - q_len;
+    const int L = kv_len[b], ctx = L - q_len;
     const int n = rb * 16 + n16, qi = min(n, rows - 1) / G, hh = n % G;   // this lane's query row (padding rows: the last one's mask)
     // Visible cache positions: everything before this step's new tokens, then the new tokens the
     // row's mask word names (its own node and its ancestors); for a chain those are tokens 0..i.
@@ -90,12 +113,11 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
     const int qi_last = min(rb * 16 + 15, rows - 1) / G;
     const int end = a.tree_mask ? L : ctx + qi_last + 1;
     const int tiles = (end + kTile - 1) / kTile;
-    const int32_t *bt = a.block_table + (int64_t)b * a.max_blocks;
 
-    float q[D / 4];   // B operand: lane holds its row's D/4 values at d = jq * D/4 ..
+    float q[D / 4];   // B operand: the lane's quarter of its row, in the order of the keys
 #pragma unroll
     for (int j = 0; j < D / 4; ++j) q[j] = 0.f;
-    if (n < rows) load_run<QDT>(a.q, ((int64_t)(q0 + qi) * a.num_q_heads + g * G + hh) * D + jq * (D / 4), q);
+    if (n < rows) load_quarter<QDT, D, PIECE>(a.q, (int64_t)(q0 + qi) * a.num_q_heads + g * G + hh, jq, q);
 
     float m = kNoRef, l = 0.f;
     float4v acc[MB];
@@ -107,7 +129,7 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
     GenericTile<D> t;
     auto load_k = [&](int phys) __attribute__((always_inline)) {
         const int64_t addr = (int64_t)phys * a.num_kv_heads + g;
-        load_run<KV>(a.k, (addr * kTile + n16) * D + jq * (D / 4), t.k);
+        load_quarter<KV, D, PIECE>(a.k, addr * kTile + n16, jq, t.k);
         t.ks = KV == SS_FP8_E4M3 ? a.k_scale[addr] : 1.f;
     };
     auto load_v = [&](int phys) __attribute__((always_inline)) {
@@ -119,19 +141,19 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
     // tile ti, whose keys and values are in t; `next` is the block of the wavefront's next tile, or -1
     auto compute = [&](int ti, int next) __attribute__((always_inline)) {
         const int tok0 = ti * kTile + 4 * jq;   // first of this lane's four positions
-        float4v s = {0.f, 0.f, 0.f, 0.f}, s2 = {0.f, 0.f, 0.f, 0.f};   // (two chains: the instruction's latency is long)
+        float4v chain[4];   // (four chains: the instruction's latency is long, and short sums round less)
 #pragma unroll
-        for (int j = 0; j < D / 4; j += 2) {
-            s = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[j], q[j], s, 0, 0, 0);
-            s2 = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[j + 1], q[j + 1], s2, 0, 0, 0);
-        }
+        for (int c = 0; c < 4; ++c) chain[c] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < D / 4; ++j) chain[j & 3] = __builtin_amdgcn_mfma_f32_16x16x4f32(t.k[j], q[j], chain[j & 3], 0, 0, 0);
+        const float4v s = (chain[0] + chain[1]) + (chain[2] + chain[3]);
         const float kscale = t.ks * a.sm_scale;
         if (next >= 0) load_k(next);
         const bool tail = ti * kTile + kTile > ctx;   // holds new tokens or slots past the end
         float p[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            p[i] = (s[i] + s2[i]) * kscale;
+            p[i] = s[i] * kscale;
             if (tail) {
                 const int pos = tok0 + i - ctx;
                 const bool see = pos < 0 || (pos < 32 && ((newmask >> pos) & 1u));
@@ -189,10 +211,8 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
         }
     };
 
-    // This wavefront's tiles are wave, wave + NW, ..: their block ids are read 64 at a time, one per lane.
     for (int base = wave; base < tiles; base += 64 * NW) {
-        const int mine = base + lane * NW;
-        const int ids = bt[mine < tiles ? mine : base];
+        if (base != wave) ids = bt[min(base + lane * NW, a.max_blocks - 1)];
         const int count = min(64, (tiles - base + NW - 1) / NW);
         int cur = __builtin_amdgcn_readlane(ids, 0);
         load_k(cur);
@@ -216,17 +236,27 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) part_o[wave][n16][(4 * jq + e) * MB + mb] = acc[mb][e];
     __syncthreads();
-    const int used = min(NW, tiles);   // the other wavefronts had no tile
+    const int used = min(NW, tiles);
     for (int i = tid; i < 16 * D; i += 64 * NW) {
-        const int r = i / D, d = i % D, nn = rb * 16 + r;
+        const int r = __builtin_amdgcn_readfirstlane(i / D), d = i % D, nn = rb * 16 + r;   // (a wavefront's 64 elements are of one row)
         if (nn >= rows) continue;
-        float gm = part_m[0][r];
-        for (int w = 1; w < used; ++w) gm = fmaxf(gm, part_m[w][r]);
+        // lane w has what wavefront w's part weighs
+        const float pm = part_m[min(lane, used - 1)][r], pl = part_l[min(lane, used - 1)][r];
+        float gm = pm;
+#pragma unroll
+        for (int x = 1; x < NW; x *= 2) gm = fmaxf(gm, __shfl_xor(gm, x));   // (every lane group of NW holds all of them)
+        const float sc = expf(pm - gm);
         float ls = 0.f, o = 0.f;
-        for (int w = 0; w < used; ++w) {
-            const float sc = expf(part_m[w][r] - gm);
-            ls = fmaf(part_l[w][r], sc, ls);
-            o = fmaf(part_o[w][r][d], sc, o);
+        float po[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) po[w] = part_o[w][r][d];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            if (w < used) {   // (the others had no tile)
+                const float f = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, sc), w));
+                ls = fmaf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, pl), w)), f, ls);
+                o = fmaf(po[w], f, o);
+            }
         }
         const int64_t orow = (int64_t)(q0 + nn / G) * a.num_q_heads + g * G + nn % G;
         if (a.q_dtype == SS_F32)
@@ -242,9 +272,9 @@ void launch_generic(const AttnArgs &a, int row_blocks, hipStream_t stream)
 {
     const dim3 grid((unsigned)a.batch * a.num_kv_heads * row_blocks), wg(64 * kGenericWaves<D>);
     if (a.q_dtype == SS_F32)
-        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_F32>), grid, wg, 0, stream, a, row_blocks);
+        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_F32>), grid, wg, 0, stream, a, row_blocks, a.q_indptr, a.kv_len, a.block_table);
     else
-        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_BF16>), grid, wg, 0, stream, a, row_blocks);
+        hipLaunchKernelGGL((attn_generic_kernel<D, KV, SS_BF16>), grid, wg, 0, stream, a, row_blocks, a.q_indptr, a.kv_len, a.block_table);
 }
 
 template <int D>
