@@ -83,6 +83,7 @@ constexpr float kSlack = 8.0f;       // log2 headroom of the lagging softmax ref
 constexpr float kNoMax = -1.0e30f;   // reference before any score was seen (finite, so that -inf - ref stays -inf)
 constexpr int kMaxFlagPolls = 1 << 23;   // polls of a neighbour's deposit flag before giving up (each at least 128 cycles)
 constexpr int kPartRowStride = 33;   // float4 per staged partial row in LDS (32 of data + 1 of padding)
+constexpr int kBlockStride = 16 * kPartRowStride;   // float4 from one staged 16-row block to the next (more than a pair of e4m3 key tiles takes)
 template <int NB>
 constexpr bool kQueriesInLds = NB >= 4;        // for many row blocks the registers are needed for the accumulators
 
@@ -136,6 +137,7 @@ template <bool FP8>
 struct TileRegs {
     // bf16: k[ks] = 8 bf16 of token (lane&15) at d = 32*ks + 8*(lane>>4)
     // fp8 : k[kk] = 16 bytes of token (lane&15) at d = 64*kk + 16*(lane>>4)   (kk = 0,1)
+    // STAGE: k[i] = the tile's bytes 1024 i + 16 lane .. + 15: whole kilobytes in the order of memory, not yet an operand (see stage_keys)
     u32x4 k[FP8 ? 2 : 4];
     // bf16: v[e] = 8 bf16 of token 4*(lane>>4)+e at d = 8*(lane&15)
     // fp8 : v[e] = 8 bytes of the same
@@ -155,13 +157,12 @@ struct PairRegs {
 // displacing what is reused (partials, queries, the pair list) in the caches.
 // The keys of both tiles come first: they are used first.
 constexpr int kNonTemporal = 2;
-template <bool FP8>
-__device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs &a, const float *__restrict__ k_scale,
-                                                const float *__restrict__ v_scale, int2 addr, bool live, int lane)
+template <bool FP8, bool STAGE>
+__device__ __forceinline__ void load_pair_keys(PairRegs<FP8> &p, const AttnArgs &a, int2 addr, bool live, int lane)
 {
     constexpr int ES = FP8 ? 1 : 2, BYTES = kTile * D * ES;
     const int bytes = live ? BYTES : 0;
-    const int ko = (lane & 15) * (D * ES) + (lane >> 4) * 16, vo = (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
+    const int ko = STAGE ? lane * 16 : (lane & 15) * (D * ES) + (lane >> 4) * 16;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int64_t blk = (int64_t)(h ? addr.y : addr.x) * BYTES;
@@ -169,8 +170,16 @@ __device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs
             const_cast<char *>(static_cast<const char *>(a.k)) + blk, 0, bytes, 0x00020000);
 #pragma unroll
         for (int i = 0; i < (FP8 ? 2 : 4); ++i)
-            p.t[h].k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, ko + i * 64, 0, kNonTemporal);
+            p.t[h].k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, ko + i * (STAGE ? 1024 : 64), 0, kNonTemporal);
     }
+}
+template <bool FP8>
+__device__ __forceinline__ void load_pair_values(PairRegs<FP8> &p, const AttnArgs &a, const float *__restrict__ k_scale,
+                                                 const float *__restrict__ v_scale, int2 addr, bool live, int lane)
+{
+    constexpr int ES = FP8 ? 1 : 2, BYTES = kTile * D * ES;
+    const int bytes = live ? BYTES : 0;
+    const int vo = (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int ad = h ? addr.y : addr.x;
@@ -197,7 +206,7 @@ __device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs
 // A workgroup's LDS.  BLOCKS: the most row blocks of the kernel.
 //   q    query operands, in operand order, one 1 KB line per row block and k-step of each wavefront (kQueriesInLds)
 //   o    one 16-row block of a partial per wavefront, rows 33 float4 apart (the odd stride spreads the rows over the banks); teams
-//        exchange blocks through it: two buffers, one barrier per block
+//        exchange blocks through it: two buffers, one barrier per block.  Between the ends of units, the keys of a pair
 //   ml   references and sums of the rows
 //   dep  CHAIN: the deposits.  The wavefronts of a workgroup own consecutive spans, so a unit that runs on from one span into the next
 //        is combined inside the workgroup: the right-hand wave leaves the result of its part in its deposit slot, the left-hand one
@@ -207,7 +216,7 @@ template <int BLOCKS>
 struct StreamLds {
     static constexpr bool CHAIN = BLOCKS <= kChainRowBlocks;
     uint4 q[kQueriesInLds<BLOCKS> ? kWavesPerWg * BLOCKS * 4 * 64 : 1];
-    float4v o[2 * kWavesPerWg][16 * kPartRowStride];
+    float4v o[2 * kWavesPerWg][kBlockStride];
     float2 ml[kWavesPerWg][BLOCKS * 16];
     float4v dep_o[CHAIN ? kWavesPerWg : 1][CHAIN ? BLOCKS * 16 * kPartRowStride : 1];
     float2 dep_ml[CHAIN ? kWavesPerWg : 1][CHAIN ? BLOCKS * 16 : 1];
@@ -220,6 +229,7 @@ struct Run {
     int unit_x;           // flat index of the unit's first pair
     int x0, x1;           // the run, flat
     int L, q0, q1;        // kv_len and query rows of the request
+    int free_block;       // which of the wavefront's two block buffers in LDS nobody reads
     int2 addr[kDescPairs];   // of the wave's first pairs
 };
 
@@ -227,9 +237,10 @@ struct Run {
 // BLOCKS  those of the kernel
 // TREE    the new tokens of a request form a draft tree: a row's visibility among them comes from its
 //         mask word instead of the chain's "tokens up to my own"
+// STAGE   the keys are read in the order of memory and turned in LDS (see stage_keys)
 // CHAIN   wavefronts' spans, handed over; else `team` says whether the run is the workgroup's or the wavefront's own
-template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool CHAIN>
-__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, const Run &run, bool team, const int2 *__restrict__ pair_addr,
+template <int G, int NB, int BLOCKS, bool FP8, bool TREE, bool CHAIN, bool STAGE>
+__device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, Run &run, bool team, const int2 *__restrict__ pair_addr,
                                      const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
                                      const float *__restrict__ v_scale)
 {
@@ -265,6 +276,9 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     float m_run[NB], l_run[NB];
     float4v acc[8][NB];
     const float sc2 = a.sm_scale * kLog2e;
+    // The keys' place in LDS: the wavefront's block buffer that nobody reads.  At a team's unit end the others may still be reading this
+    // wavefront's last block when it goes on; its buffer before that one has been read by all.
+    u32x4 *stage = STAGE ? reinterpret_cast<u32x4 *>(o_lds[run.free_block * kWavesPerWg + wslot]) : nullptr;
 
     u32x4 qw[NB][4];   // a unit's queries on their way (between begin_unit_issue and begin_unit_wait)
     // (the metadata of the unit after the current one is fetched a unit ahead)
@@ -438,9 +452,9 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
                     for (int it = 0; it < 2; ++it)
 #pragma unroll
                         for (int w = 0; w < kWavesPerWg; ++w)
-                            v[it][w] = from0[(nb & 1) * (kWavesPerWg * 16 * kPartRowStride) + w * from_one_to_next + it * 2 * kPartRowStride];
+                            v[it][w] = from0[(nb & 1) * (kWavesPerWg * kBlockStride) + w * from_one_to_next + it * 2 * kPartRowStride];
                 };
-                if (team) read(16 * kPartRowStride);   // (constant offsets cost no address arithmetic)
+                if (team) read(kBlockStride);   // (constant offsets cost no address arithmetic)
                 else read(4 * kPartRowStride);
                 if (nb + 1 < NB) deposit(nb + 1 < NB ? nb + 1 : 0);   // (under the latency of the reads)
                 const int first = team ? wslot * 4 : 0, rows_here = team ? 4 : 16;   // of the block, written by this wavefront
@@ -641,13 +655,47 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     int2 next_addr = run.addr[0];    // its addresses
     auto load_pair = [&](PairRegs<FP8> &t, int2 addr) __attribute__((always_inline)) {
         const bool live = next_x < x1;
-        load_pair_tiles<FP8>(t, a, k_scale, v_scale, addr, live, lane);
+        load_pair_keys<FP8, STAGE>(t, a, addr, live, lane);
+        load_pair_values<FP8>(t, a, k_scale, v_scale, addr, live, lane);
         next_x += stride;
     };
     auto issue = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
         const int2 addr = next_addr;
         load_pair(t, addr);
         next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
+    };
+    // in two halves, where the keys' registers are free before the values' (STAGE)
+    auto issue_keys = [&](PairRegs<FP8> &t) __attribute__((always_inline)) { load_pair_keys<FP8, STAGE>(t, a, next_addr, next_x < x1, lane); };
+    auto issue_values = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
+        load_pair_values<FP8>(t, a, k_scale, v_scale, next_addr, next_x < x1, lane);
+        next_x += stride;
+        next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
+    };
+
+    // Keys as operands.  An operand register wants 16 bytes of sixteen tokens' rows in sixteen consecutive lanes, and reading memory
+    // that way takes four times as long as reading whole lines (a compute unit 38 GB/s and 145 out of L2; the chip 6.0 and 7.1 TB/s out of
+    // memory), with the wavefront standing still while its loads are accepted.  With STAGE the tiles are read in the order of memory and turned
+    // here, through the wavefront's own place in LDS.  Rows stand one 16-byte word further apart than they are long, so that neither
+    // side meets a bank twice.
+    // Where it pays: e4m3 caches, three row blocks and more, batches that may be served by wavefronts' spans (96 requests of 512..8192 tokens, 64 heads
+    // over 8, depth 2..8: 221 -> 213 us, depth 2..4 193 -> 175; 96 trees of 8..16 nodes, 32 heads 213 -> 207).  With fewer units the
+    // round trip through LDS costs what the reads gain (20 requests 58.6 / 58.7, trees 58.0 / 59.2), with one or two row blocks more (159.1 / 160.5).
+    // bf16 keys are twice the LDS traffic: 64 requests of 256..4096 105.5 / 106.6, 128 of 128..16384 276.4 / 277.3 at best.
+    constexpr int KROW = (FP8 ? 8 : 16) + 1, KSEG = FP8 ? 8 : 16;   // 16-byte words of a row in LDS, in memory
+    static_assert(!STAGE || 2 * 16 * KROW <= kBlockStride, "a pair's keys fit a block buffer");
+    auto stage_keys = [&](const PairRegs<FP8> &t, u32x4 (&kw)[2][FP8 ? 2 : 4]) __attribute__((always_inline)) {
+        u32x4 *to = stage + lane / KSEG * KROW + lane % KSEG;
+        const u32x4 *from = stage + r16 * KROW + jq;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < (FP8 ? 2 : 4); ++i) to[h * 16 * KROW + i * (64 / KSEG) * KROW] = t.t[h].k[i];
+        __builtin_amdgcn_wave_barrier();   // (LDS serves a wavefront's requests in order; this keeps the compiler to it)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < (FP8 ? 2 : 4); ++i) kw[h][i] = from[h * 16 * KROW + i * 4];
+        __builtin_amdgcn_wave_barrier();
     };
 
     // One pair: S^T = K Q^T for both tiles and all row blocks, softmax, O^T += V^T P^T.  Row blocks beyond the
@@ -666,27 +714,32 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         const float kscale[2] = {sc2 * t.t[0].ks, sc2 * t.t[1].ks}, vscale[2] = {t.t[0].vs, t.t[1].vs};
 
         bf16x8 kop[2][4];
+        auto widen_keys = [&](int h, const u32x4 *k) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const TileRegs<FP8> &tt = t.t[h];
-            if constexpr (FP8) {
-                kop[h][0] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[0].x, tt.k[0].y));
-                kop[h][1] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[0].z, tt.k[0].w));
-                kop[h][2] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[1].x, tt.k[1].y));
-                kop[h][3] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(tt.k[1].z, tt.k[1].w));
-            } else {
+            for (int ks = 0; ks < 4; ++ks) kop[h][ks] = __builtin_bit_cast(bf16x8, fp8x8_to_bf16x8(k[ks >> 1][(ks & 1) * 2], k[ks >> 1][(ks & 1) * 2 + 1]));
+        };
+        u32x4 kw[2][FP8 ? 2 : 4];
+        if constexpr (STAGE) {
+            stage_keys(t, kw);
+        } else {
 #pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    u32x4 w = tt.k[ks];
-                    if constexpr (SINGLE) {   // a copy, so that the registers it came in are free for the refill
+            for (int h = 0; h < 2; ++h) {
+                if constexpr (FP8) {
+                    widen_keys(h, t.t[h].k);
+                } else {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            uint32_t x;
-                            asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(w[c]));
-                            w[c] = x;
+                    for (int ks = 0; ks < 4; ++ks) {
+                        u32x4 w = t.t[h].k[ks];
+                        if constexpr (SINGLE) {   // a copy, so that the registers it came in are free for the refill
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                uint32_t x;
+                                asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(w[c]));
+                                w[c] = x;
+                            }
                         }
+                        kop[h][ks] = __builtin_bit_cast(bf16x8, w);
                     }
-                    kop[h][ks] = __builtin_bit_cast(bf16x8, w);
                 }
             }
         }
@@ -714,11 +767,21 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
                 }
             }
         };
+        if constexpr (STAGE) {
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (decltype(refill)::value) issue_keys(t);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         if constexpr (SINGLE) {
             pack_values();
             __builtin_amdgcn_sched_barrier(0);
-            issue(t);
+            if constexpr (STAGE) issue_values(t);
+            else issue(t);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (STAGE) {   // (e4m3)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) widen_keys(h, kw[h]);
         }
 
         float4v s[NB][2];
@@ -758,7 +821,10 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
             if constexpr (!SINGLE) {
                 pack_values();
                 __builtin_amdgcn_sched_barrier(0);
-                if constexpr (decltype(refill)::value) issue(t);
+                if constexpr (decltype(refill)::value) {
+                    if constexpr (STAGE) issue_values(t);
+                    else issue(t);
+                }
                 __builtin_amdgcn_sched_barrier(0);
             }
             // Slots at or past kv_len may hold anything (NaN, inf): they are cleared so that 0 * garbage cannot
@@ -922,6 +988,10 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         }
         pos = unit_x + tile;
         end_unit(seg_x0 == unit_x, seg_x1 == unit_x + nb_tiles);
+        if constexpr (STAGE) {
+            if (team && nbu) run.free_block = nbu & 1;
+            stage = reinterpret_cast<u32x4 *>(o_lds[run.free_block * kWavesPerWg + wslot]);
+        }
         if (seg_x1 >= x1) break;
         next_unit();
         begin_unit_issue();
@@ -931,7 +1001,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
 
 // A span of the class kernels, class by class: units of k row blocks are walked by the code for k.
 //   cls, class_end  class of the span's first unit, and where that class ends
-template <int G, int BLOCKS, bool FP8, bool TREE>
+template <int G, int BLOCKS, bool FP8, bool TREE, bool STAGE>
 __device__ __forceinline__ void walk_classes(const AttnArgs &a, StreamLds<BLOCKS> &lds, Run run, bool team, int cls, int class_end,
                                              const AttnPlan *__restrict__ plan, const int2 *__restrict__ pair_addr,
                                              const AttnReq *__restrict__ req, const float *__restrict__ k_scale,
@@ -944,13 +1014,13 @@ __device__ __forceinline__ void walk_classes(const AttnArgs &a, StreamLds<BLOCKS
     for (int c = cls;;) {
         if (run.x0 < run.x1) {
             const int blocks = BLOCKS - c;
-            if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
-            else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
-            else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            if (blocks == 1) walk<G, 1, BLOCKS, FP8, TREE, false, STAGE>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            else if (blocks == 2) walk<G, 2, BLOCKS, FP8, TREE, false, STAGE>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+            else if (blocks == 3) walk<G, 3, BLOCKS, FP8, TREE, false, STAGE>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
             else {
                 if constexpr (BLOCKS >= 5) {
-                    if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
-                    else walk<G, 4, BLOCKS, FP8, TREE, false>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+                    if (blocks == 5) walk<G, 5, BLOCKS, FP8, TREE, false, STAGE>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
+                    else walk<G, 4, BLOCKS, FP8, TREE, false, STAGE>(a, lds, run, team, pair_addr, req, k_scale, v_scale);
                 }
             }
         }
@@ -996,17 +1066,18 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     run.x1 = team ? next_team : next_wave;
     run.unit_x = run.x0 - d[2];
     run.L = d[6]; run.q0 = d[7]; run.q1 = d[8];
+    run.free_block = 1;   // (wavefronts that hand over write finished blocks through the other one)
 #pragma unroll
     for (int j = 0; j < kDescPairs; ++j) run.addr[j] = make_int2(d[9 + 2 * j], d[10 + 2 * j]);
     if constexpr (BLOCKS <= kChainRowBlocks) {
         if (team) {
             if (run.x0 >= run.x1) return;
-            walk<G, BLOCKS, BLOCKS, FP8, TREE, false>(a, lds, run, true, pair_addr, req, k_scale, v_scale);
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, false, false>(a, lds, run, true, pair_addr, req, k_scale, v_scale);
         } else {
             if ((threadIdx.x & 63) == 0) lds.dep_flag[wslot] = 0;
             __syncthreads();   // every wave's flag is clear before any neighbour can look at it
             if (run.x0 >= run.x1) return;
-            walk<G, BLOCKS, BLOCKS, FP8, TREE, true>(a, lds, run, false, pair_addr, req, k_scale, v_scale);
+            walk<G, BLOCKS, BLOCKS, FP8, TREE, true, false>(a, lds, run, false, pair_addr, req, k_scale, v_scale);
         }
     } else {
         // (In one trip to memory: left to the compiler, some of it is read behind the test for an empty span, and some again further
@@ -1015,7 +1086,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         asm volatile("" : "+s"(run.p), "+s"(run.g), "+s"(run.b), "+s"(run.n), "+s"(run.x0), "+s"(run.unit_x), "+s"(run.L), "+s"(run.q0), "+s"(run.q1), "+s"(cls), "+s"(class_end));
         asm volatile("" : "+s"(run.addr[0].x), "+s"(run.addr[0].y), "+s"(run.addr[1].x), "+s"(run.addr[1].y), "+s"(run.addr[2].x), "+s"(run.addr[2].y));
         if (run.x0 >= run.x1) return;
-        walk_classes<G, BLOCKS, FP8, TREE>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
+        walk_classes<G, BLOCKS, FP8, TREE, FP8 && MIXED>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
     }
 }
 
