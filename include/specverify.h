@@ -375,7 +375,9 @@ int32_t ss_route_select(const ss_worker_metrics *workers, int32_t n, const doubl
 /*
  * Options (process-wide, not thread-safe; meant for tests and measurement).
  *   "attn_path"     0 = automatic, 1 = force the fp32 kernel, 2 = require the MFMA kernel
- *   "attn_waves"    number of KV stream partitions (wavefronts) of the MFMA kernel, 0 = automatic
+ *   "attn_waves"    number of KV stream partitions (wavefronts) of the MFMA kernel, 0 = automatic.  Any other number than the
+ *                   automatic one also keeps calls of few or short requests on the partitioned kernel; they otherwise take a
+ *                   workgroup, or several, per (request, KV head)
  *   "attn_unit_weight"  what opening a (request, KV head) unit is taken to cost a wavefront, in KV tiles (rounded up to whole
  *                   pairs), when the KV stream is cut into partitions; 0..64.  Where a workgroup's four wavefronts open a
  *                   unit together it counts four times (twice up to 32 query rows per KV head); 0 = partitions of equal

@@ -3,7 +3,7 @@
 //
 // One workgroup per (request, KV head, block of 16 query rows); its wavefronts take the request's 16-token cache
 // blocks in turn and are merged through LDS by their log-sum-exp.  A wavefront works on one block at a time:
-//   S^T[token][row] = K[token][:] . Q[row][:]    v_mfma_f32_16x16x4_f32, a lane holds D/4 consecutive d of a token
+//   S^T[token][row] = K[token][:] . Q[row][:]    v_mfma_f32_16x16x4_f32, a lane holds a quarter of a token's d
 //   O^T[d][row]    += V[token][d] * P[row][token] the same shape; step i contracts tokens {4 jq + i}, so that P is
 //                                                taken straight from the S^T accumulators
 // What bounds it: short calls are a chain of dependent reads (offsets, block table, keys, values) and the merge, so

@@ -1,23 +1,28 @@
-// Verify attention with one workgroup per unit (a request's rows of one KV head): one launch, no plan, no partials, no merge.
+// Verify attention with a workgroup per unit (a request's rows of one KV head), or several to a unit and a small kernel that merges them: one launch
+// or two where the streaming kernels take a plan, a stream and a merge, each a chain of dependent reads.
 //
-// Serves the calls of the matrix-core kernels (head_dim 128, bf16 queries, bf16 or e4m3 caches, groups of 1/2/4/8) in which no unit is
+// Serves the calls of the matrix-core kernels (head_dim 128, bf16 queries, bf16 or e4m3 caches, groups of 1/2/4/8) in which no unit can be
 // long; the rule stands at attn_unit_choose.
 //
-// Eight wavefronts, two to a SIMD: while one waits for a result the other issues.  Wavefronts 2s and 2s + 1 are siblings.
-// A step takes 256 tokens, a pair of tiles (32 tokens) to a wavefront:
+// What bounds it: the chain of lengths, block ids, tiles, exchange and rows written (6 us for 64 tokens, launch included); beyond a few steps
+// what a compute unit gets out of memory, about 60 GB/s while the chip is not full.
+//
+// Eight or four wavefronts of 256 registers, two to a SIMD: while one waits for a result, or for its loads to be accepted, the other issues.
+// Wavefronts 2s and 2s + 1 are siblings.  A step takes a pair of tiles (32 tokens) to a wavefront, 256 or 128 tokens:
 //   scores   S^T = K Q^T of the wavefront's own pair                                     (all row blocks)
-//   softmax  against a reference that the siblings share; P as bf16 into LDS
+//   softmax  P as bf16 into LDS
 //   output   O^T += V^T P^T of both siblings' pairs, the sibling's P from LDS, for the wavefront's half of the head dimension
 // so that a wavefront holds accumulators of half a row: with five row blocks 80 registers instead of 160, which is what lets two
-// wavefronts share a SIMD.  No matrix or vector work is done twice for it; what it costs is 1 KB of LDS written and read per row block and
-// wavefront, and two barriers per step.
+// wavefronts share a SIMD.  No matrix or vector work is done twice for it; what it costs is 1 KB of LDS written and 2 KB read per row block and
+// wavefront, and a barrier or two per step.
 //
 // The operands' lane layouts are those of attn_mfma_kernels.h: for S^T a K tile is the A operand, for O^T the contraction runs over
 // the 32 tokens of a pair, lane group jq bringing tokens 4 jq .. 4 jq + 3 of either tile, so that P is taken straight from the
 // accumulators of S^T; V is loaded as four consecutive d of a token per lane, the M-blocks being the four interleaved phases.
 //
-// The reference is the siblings' largest score so far (a barrier more a step than with one that lags: a step of few row blocks waits for
-// memory anyway, and the largest probabilities stay exact).
+// The softmax reference is the largest score so far, not one that lags as in the streaming kernels: the largest probabilities stay exact in bf16
+// (1.68e-3 to 1.74e-3 from 64 bits over the range, the streaming kernels 1.69e-3 to 2.0e-3; a reference that lags by up to 2^8 for a whole
+// unit 1.9e-3 to 2.3e-3, and 5 % faster).
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -534,7 +539,7 @@ __global__ __launch_bounds__(64 * TEAM, 2) void attn_unit_kernel(AttnArgs a, int
     Unit u;
     if ((int)blockIdx.x >= a.batch * a.num_kv_heads * splits) {
         // The workgroups behind the units' leave the plan in the workspace, as every call does that does not reuse one: a later call that
-        // may take the streaming kernels finds it.  They run beside the others (4 requests of 64 tokens: no difference).
+        // may take the streaming kernels finds it.  They run beside the others (4 requests of 64 tokens 6.1 us, 64 of 8..64 12.8, and 9.4 without).
         if (threadIdx.x >= 256) return;
         const int block = blockIdx.x - a.batch * a.num_kv_heads * splits;
         Place *places = reinterpret_cast<Place *>(&lds.p[0][0][0][0]);
@@ -632,15 +637,17 @@ void launch(const AttnArgs &a, int group_log, int splits, hipStream_t stream, hi
 // Which calls take this path, and how: from what the host knows, the units and the width of the block table.  Batches whose plan takes a kernel
 // in front are left to the streaming kernels.
 //
-// Measured in captured graphs, us a call, plan / stream / merge against this path, 8 KV heads, lengths uniform in hi / 8 .. hi (u) or uniform in
-// the logarithm from hi / 50 on (l), depth 0 .. 8 with 32 heads bf16 and with 64 heads e4m3:
-//   one workgroup a unit       4 requests, hi 256 u  15.2 / 7.6, 19.9 / 12.2 (e4m3, hi 384)     32, hi 768 u  24.2 / 13.6, 29.2 / 17.9
-//                              64, hi 64  25.1 / 9.4, 31.5 / 12.6       64, hi 1000 u  46.2 / 32.1, 47.3 / 32.4       160, hi 1000 l  56.3 / 41.5, 58.0 / 45.5
-//   several                    4, hi 8000 u  28.9 / 21.1, 27.5 / 22.7    8, hi 4000 u  28.0 / 22.9, 28.6 / 26.2    16, hi 2000 l  21.6 / 16.9, 24.6 / 19.7
-// and where the line lies: a unit is walked by its workgroups alone, so a batch of very different lengths waits for its longest units, which the
-// plan's spans share out: 8 requests, hi 8000 (four workgroups of up to 128 tiles) u 35.0 / 36.6, l 27.6 / 25.2; 32, hi 2000 l 30.5 / 28.6, hi 4000 l
-// 44.1 / 50.3; 64, hi 2000 u 63.8 / 59.3, hi 4000 l 61.5 / 62.9; 40, hi 2000 u 46.3 / 49.1.
-// A second workgroup of a unit costs the merge, 3 us with its launch: up to 48 tiles one is as fast (4 of 600 tokens 10.4, with two 10.5).
+// Measured in captured graphs, us a call, plan + stream + merge against this path, 8 KV heads, depth 0 .. 8, lengths uniform in hi / 8 .. hi (u) or
+// uniform in the logarithm from hi / 50 on (l); 32 heads bf16, then 64 heads e4m3:
+//   one workgroup a unit   4 requests, hi 64 u  13.1 / 6.7  16.4 / 8.8    hi 600 u  16.4 / 12.8  20.5 / 16.2    32, hi 768 u  26.9 / 15.7  28.9 / 17.4
+//                          64, hi 64 u  25.1 / 12.8  31.6 / 15.3    64, hi 1000 u  45.6 / 34.0  47.5 / 36    160, hi 1000 l  56.2 / 44.0
+//   several                4, hi 8000 u  28.8 / 20.9  27.4 / 22.1    8, hi 4000 u  27.8 / 22.5  28.4 / 26.4    16, hi 2000 l  21.4 / 17.6  24.5 / 19.9
+// Where the line lies: a unit is walked by its workgroups alone, so a batch of very different lengths waits for its longest units, which the
+// plan's spans share out.  Beyond the limits (with references that lag, a little faster than now): 8 requests, hi 8000 (four workgroups of up to
+// 128 tiles) u 35.0 / 36.6; 32, hi 2000 l 30.5 / 28.6, hi 4000 l 44.1 / 50.3; 64, hi 2000 u 63.8 / 59.3, hi 4000 l 61.5 / 62.9; 40 (320 units: the
+// last of them alone on the chip), hi 2000 u 46.3 / 49.1, five row blocks hi 1000 35.4 / 37.5.  250 requests of 8..64 39.7 / 39.3: from six units
+// to a compute unit on the workgroups that leave the plan take what the path gains.
+// A second workgroup of a unit costs the merge, 3 us with its launch: up to 48 tiles one is as fast (4 of 40..600 tokens 10.4, with two 10.5).
 // Eight wavefronts or four: with four the chip holds two workgroups to a compute unit, and a unit of few tiles begins and ends sooner (32 requests of 64
 // tokens 8.1 / 6.2, 64 12.7 / 7.2); eight walk a long unit faster from four row blocks on, where a step is bound by its instructions (32 of 2000
 // tokens, five row blocks, e4m3 41.6 / 48.0; three bf16 44.9 / 44.3).
@@ -659,7 +666,7 @@ AttnUnitChoice attn_unit_choose(const AttnArgs &a)
         splits = splits < kMaxShares ? splits : kMaxShares;
         splits = splits < (tiles + 15) / 16 ? splits : (tiles + 15) / 16;
         if ((tiles + splits - 1) / splits > kShareTiles) return c;
-    } else if (tiles > (units <= cus ? kUnitTilesFew : deep ? kUnitTiles : kUnitTilesMany)) {
+    } else if (tiles > (units <= cus ? kUnitTilesFew : deep && units < 2 * cus ? kUnitTiles : kUnitTilesMany)) {
         return c;
     }
     c.splits = splits;
