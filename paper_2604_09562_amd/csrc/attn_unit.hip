@@ -650,7 +650,8 @@ void launch(const AttnArgs &a, int group_log, int splits, hipStream_t stream, hi
 // A second workgroup of a unit costs the merge, 3 us with its launch: up to 48 tiles one is as fast (4 of 40..600 tokens 10.4, with two 10.5).
 // Eight wavefronts or four: with four the chip holds two workgroups to a compute unit, and a unit of few tiles begins and ends sooner (32 requests of 64
 // tokens 8.1 / 6.2, 64 12.7 / 7.2); eight walk a long unit faster from four row blocks on, where a step is bound by its instructions (32 of 2000
-// tokens, five row blocks, e4m3 41.6 / 48.0; three bf16 44.9 / 44.3).
+// tokens, five row blocks, e4m3 41.6 / 48.0; three bf16 44.9 / 44.3).  The same with several workgroups to a unit (eight / four, the merge included: two row
+// blocks bf16, 4 requests of 500..4000 16.4 / 14.6, 8 of 187..1500 15.8 / 14.1, 16 of 250..2000 22.7 / 22.9; five e4m3 22.7 / 25.9, 18.2 / 19.1, 31.3 / 37.6).
 constexpr int kUnitTiles = 48, kUnitTilesFew = 80, kUnitTilesMany = 64, kShareTiles = 64, kUnitsPerCu = 6;
 AttnUnitChoice attn_unit_choose(const AttnArgs &a)
 {
@@ -670,7 +671,7 @@ AttnUnitChoice attn_unit_choose(const AttnArgs &a)
         return c;
     }
     c.splits = splits;
-    c.team = units <= cus && (splits > 1 || (tiles > 16 && deep) || (tiles > kUnitTiles && a.kv_dtype == SS_FP8_E4M3)) ? 8 : 4;
+    c.team = units <= cus && ((tiles > 16 && deep) || (tiles > kUnitTiles && a.kv_dtype == SS_FP8_E4M3)) ? 8 : 4;
     return c;
 }
 
