@@ -78,3 +78,29 @@ def test_same_bits_every_time():
         torch.cuda.synchronize()
         first = first or (out, lse)
         assert torch.equal(out, first[0]) and torch.equal(lse, first[1])
+
+
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+@pytest.mark.parametrize("longest,batch,hkv", [(700, 14, 2), (4000, 4, 8), (1024, 40, 8)])   # one workgroup a unit, several and the merge, many units
+def test_captured_calls_replay_exactly(longest, batch, hkv, kv):
+    inp = inputs(kv, 4 * hkv, hkv, (EDGES * 6)[:batch - 1] + [longest], 8, seed=longest, tree=False)
+    d = binding.attention_to_device(inp)
+    out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=9)
+    binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=9)
+    torch.cuda.synchronize()
+    want = out.clone(), lse.clone()
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=9)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        out.fill_(0)
+        lse.fill_(0)
+        ws.fill_(0xFF)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want[0]) and torch.equal(lse, want[1])
