@@ -391,6 +391,15 @@ struct RowArg {
     __device__ __forceinline__ double fma_form(float x) const { return fma((double)x, inv_t, c); }   // the same bits if `fused`
 };
 
+// What is left of r where q is taken from it (nothing, if that is no number), of two products of an exponential and a reciprocal.  Both are
+// rounded before they are subtracted: a fused multiply-add, which rounds one of them only, leaves 1e-17 of two equal ones, and a
+// residual that has vanished would have mass.
+__device__ __forceinline__ double residual_of(double r, double q)
+{
+#pragma clang fp contract(off)
+    return fmax(r - q, 0.0);
+}
+
 // The smaller of two logits, NaN if either is (one instruction for three operands): the tests that admit a wavefront to
 // ExpTable::normal must see a NaN, which the general form takes as no mass.
 __device__ __forceinline__ float min_or_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }

@@ -296,14 +296,14 @@ struct TreeResidual {
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             r[t] *= inv_src;
-            if (form) r[t] = r[t] > q[t] * inv_prev ? r[t] - q[t] * inv_prev : 0.0;
+            if (form) r[t] = residual_of(r[t], q[t] * inv_prev);
             r[t] *= inv_norm;
         }
         load8<DT>(qrow, vocab, i, raw);
         unpack8<DT>(raw, x);
         exp8(ex, aq, x, q);
 #pragma unroll
-        for (int t = 0; t < 8; ++t) r[t] = r[t] > q[t] * inv_q ? r[t] - q[t] * inv_q : 0.0;
+        for (int t = 0; t < 8; ++t) r[t] = residual_of(r[t], q[t] * inv_q);
     }
 };
 
@@ -315,11 +315,7 @@ __device__ __forceinline__ bool too_many(uint64_t cnt)
 }
 
 // What is left of a block's sums, and of an entry that was set aside: scale_r is the exact 1 / Zp at level 0, else 1.
-__device__ __forceinline__ double clipped(double r, double q, double scale_r, double inv_q)
-{
-    const double d = r * scale_r - q * inv_q;
-    return d > 0.0 ? d : 0.0;
-}
+__device__ __forceinline__ double clipped(double r, double q, double scale_r, double inv_q) { return residual_of(r * scale_r, q * inv_q); }
 
 // What a block's entries that were set aside add to its mass, in their stored order.
 __device__ __forceinline__ double boundary_mass(const TreeBlock &v, const ZonePair *run, double scale_r, double inv_q)
@@ -459,8 +455,9 @@ __global__ __launch_bounds__(kThreads, DT == SS_BF16 ? 4 : 3) void tree_round_ke
         if (wave == 0) {
             const TreeScalars before = s;
             if (t.norm > 0.0) {   // r takes the rejected child in
-                const double from = s.level ? r / s.norm : ex(RowArg(inv_t, s.mp)(lp)) / t.zp, q = ex(RowArg(inv_t, s.mq)(lq)) / t.zq;
-                r = from > q ? from - q : 0.0;
+                // (by reciprocals, as in the passes: what vanishes there vanishes here)
+                const double from = s.level ? r * (1.0 / s.norm) : ex(RowArg(inv_t, s.mp)(lp)) * (1.0 / t.zp);
+                r = residual_of(from, ex(RowArg(inv_t, s.mq)(lq)) * (1.0 / t.zq));
                 if (s.level && s.more) s.which ^= 1;
                 ++s.level;
                 s.degenerate = 0;
@@ -608,7 +605,7 @@ __global__ __launch_bounds__(kThreads, DT == SS_BF16 ? 4 : 3) void tree_round_ke
             if (j + 1 < count) rqp.load(qprow, V, i + kSub);
             exp8(ex, aqp, x, q);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) e[t] = fmax(e[t] * inv_src - q[t] * inv_prev, 0.0);
+            for (int t = 0; t < 8; ++t) e[t] = residual_of(e[t] * inv_src, q[t] * inv_prev);
             if (s.more && whole) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) __builtin_memcpy(dst + i + t * 2 * kThreads, &e[2 * t], 16);

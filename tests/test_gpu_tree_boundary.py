@@ -72,3 +72,64 @@ def test_equal_bf16_logits_on_the_boundary(oracle, vocab, moved):
             r /= r.sum()
     ref = compare(inp, oracle, f"{moved} moved, vocab {vocab}")
     assert np.all(ref["ratio"][0::2] < 0.999)   # every first child rejected
+
+
+def few_live(batch, siblings, vocab, live, logit_dtype, seed):
+    """Requests whose target row at the root has `live` logits and -inf for the others; every child of the root has that row for a
+    proposal.  Returns the batch and the live tokens of each request, in ascending order, each but the last with a free one behind it."""
+    cfg = TINY.scaled(batch=batch, vocab=vocab, logit_dtype=logit_dtype, temperature=1.0, depth=("fixed", siblings))
+    inp = synth.make_tree_sample_inputs(cfg, seed=seed, row_pad=(-vocab) % 8)
+    inp["tree_parent"] = np.tile(np.concatenate([[-1], np.zeros(siblings)]), batch).astype(np.int32)
+    inp["u_accept"][:] = np.float32(0.5)
+    rng = np.random.default_rng(seed)
+    none = synth.store(np.full(1, -np.inf, np.float32), logit_dtype)[0]
+    tokens = []
+    for b in range(batch):
+        at = np.sort(rng.choice(vocab // 8, live, replace=False)) * 8 + rng.integers(0, 6, live)
+        row = inp["target_logits"][b * (siblings + 1), :vocab]
+        keep = row[at].copy()
+        row[:] = none
+        row[at] = keep
+        inp["draft_logits"][b * siblings:(b + 1) * siblings, :vocab] = row
+        tokens.append(at)
+    return inp, tokens, none
+
+
+@pytest.mark.parametrize("logit_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("live", [1, 3, 40, 120])
+@pytest.mark.parametrize("vocab", [1000, 9001])
+def test_no_residual_of_equal_rows(oracle, vocab, live, logit_dtype):
+    """Target row and proposals alike, a first child that neither gives any mass: nothing is left, so r stays what it was, and the second
+    child, which r and q weigh alike, is accepted.  (A product that is rounded on one side only leaves 1e-17 of each entry.)"""
+    B, siblings = 8, 2
+    inp, tokens, _ = few_live(B, siblings, vocab, live, logit_dtype, seed=live)
+    for b in range(B):
+        inp["draft_tokens"][b * siblings] = tokens[b][0] + 1
+        inp["draft_tokens"][b * siblings + 1] = tokens[b][b % live]
+    ref = compare(inp, oracle, f"{live} live of {vocab}")
+    assert np.all(ref["accepted_nodes"][:, 0] == 2)
+    # without the second child: the arg-maximum of the target row
+    inp, tokens, _ = few_live(B, 1, vocab, live, logit_dtype, seed=live)
+    for b in range(B):
+        inp["draft_tokens"][b] = tokens[b][0] + 1
+    ref = compare(inp, oracle, f"{live} live of {vocab}, one child")
+    assert np.all(ref["accepted_len"] == 0)
+
+
+@pytest.mark.parametrize("logit_dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("live", [3, 40, 120])
+def test_no_residual_after_a_second_rejection(oracle, live, logit_dtype):
+    """The first proposal has one live logit moved to the token behind it: what is left of the target row is all at that logit's token.  The
+    second proposal has only that one, its draft another: nothing is left, r stays, and the third child, that token, is accepted."""
+    B, siblings, vocab = 8, 3, 1000
+    inp, tokens, none = few_live(B, siblings, vocab, live, logit_dtype, seed=10 + live)
+    for b in range(B):
+        hot = int(tokens[b][b % live])
+        first, second = inp["draft_logits"][b * siblings, :vocab], inp["draft_logits"][b * siblings + 1, :vocab]
+        first[hot + 1], first[hot] = first[hot], none     # (in its neighbour's place: the sums of both rows round alike)
+        keep = second[hot]
+        second[:] = none
+        second[hot] = keep
+        inp["draft_tokens"][b * siblings:(b + 1) * siblings] = hot + 1, int(tokens[b][(b + 1) % live]), hot
+    ref = compare(inp, oracle, f"{live} live, second rejection")
+    assert np.all(ref["accepted_nodes"][:, 0] == 3)
