@@ -157,48 +157,46 @@ struct PairRegs {
 // displacing what is reused (partials, queries, the pair list) in the caches.
 // The keys of both tiles come first: they are used first.
 constexpr int kNonTemporal = 2;
-template <bool FP8, bool STAGE>
-__device__ __forceinline__ void load_pair_keys(PairRegs<FP8> &p, const AttnArgs &a, int2 addr, bool live, int lane)
+enum { kKeys = 1, kValues = 2 };   // what of a pair
+template <bool FP8, bool STAGE, int WHAT>
+__device__ __forceinline__ void load_pair_tiles(PairRegs<FP8> &p, const AttnArgs &a, const float *__restrict__ k_scale,
+                                                const float *__restrict__ v_scale, int2 addr, bool live, int lane)
 {
     constexpr int ES = FP8 ? 1 : 2, BYTES = kTile * D * ES;
     const int bytes = live ? BYTES : 0;
-    const int ko = STAGE ? lane * 16 : (lane & 15) * (D * ES) + (lane >> 4) * 16;
+    const int ko = STAGE ? lane * 16 : (lane & 15) * (D * ES) + (lane >> 4) * 16, vo = (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
+    if constexpr (WHAT & kKeys) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int64_t blk = (int64_t)(h ? addr.y : addr.x) * BYTES;
-        const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char *>(static_cast<const char *>(a.k)) + blk, 0, bytes, 0x00020000);
+        for (int h = 0; h < 2; ++h) {
+            const int64_t blk = (int64_t)(h ? addr.y : addr.x) * BYTES;
+            const __amdgpu_buffer_rsrc_t kr = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(static_cast<const char *>(a.k)) + blk, 0, bytes, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < (FP8 ? 2 : 4); ++i)
-            p.t[h].k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, ko + i * (STAGE ? 1024 : 64), 0, kNonTemporal);
-    }
-}
-template <bool FP8>
-__device__ __forceinline__ void load_pair_values(PairRegs<FP8> &p, const AttnArgs &a, const float *__restrict__ k_scale,
-                                                 const float *__restrict__ v_scale, int2 addr, bool live, int lane)
-{
-    constexpr int ES = FP8 ? 1 : 2, BYTES = kTile * D * ES;
-    const int bytes = live ? BYTES : 0;
-    const int vo = (lane >> 4) * (4 * D * ES) + (lane & 15) * (8 * ES);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int ad = h ? addr.y : addr.x;
-        const int64_t blk = (int64_t)ad * BYTES;
-        const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<char *>(static_cast<const char *>(a.v)) + blk, 0, bytes, 0x00020000);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            if constexpr (FP8)
-                p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b64(vr, vo + e * (D * ES), 0, kNonTemporal);
-            else
-                p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b128(vr, vo + e * (D * ES), 0, kNonTemporal);
+            for (int i = 0; i < (FP8 ? 2 : 4); ++i)
+                p.t[h].k[i] = __builtin_amdgcn_raw_buffer_load_b128(kr, ko + i * (STAGE ? 1024 : 64), 0, kNonTemporal);
         }
-        if constexpr (FP8) {
-            p.t[h].ks = k_scale[ad];   // wave-uniform: scalar loads
-            p.t[h].vs = v_scale[ad];
-        } else {
-            p.t[h].ks = 1.f;
-            p.t[h].vs = 1.f;
+    }
+    if constexpr (WHAT & kValues) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ad = h ? addr.y : addr.x;
+            const int64_t blk = (int64_t)ad * BYTES;
+            const __amdgpu_buffer_rsrc_t vr = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(static_cast<const char *>(a.v)) + blk, 0, bytes, 0x00020000);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (FP8)
+                    p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b64(vr, vo + e * (D * ES), 0, kNonTemporal);
+                else
+                    p.t[h].v[e] = __builtin_amdgcn_raw_buffer_load_b128(vr, vo + e * (D * ES), 0, kNonTemporal);
+            }
+            if constexpr (FP8) {
+                p.t[h].ks = k_scale[ad];   // wave-uniform: scalar loads
+                p.t[h].vs = v_scale[ad];
+            } else {
+                p.t[h].ks = 1.f;
+                p.t[h].vs = 1.f;
+            }
         }
     }
 }
@@ -655,8 +653,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     int2 next_addr = run.addr[0];    // its addresses
     auto load_pair = [&](PairRegs<FP8> &t, int2 addr) __attribute__((always_inline)) {
         const bool live = next_x < x1;
-        load_pair_keys<FP8, STAGE>(t, a, addr, live, lane);
-        load_pair_values<FP8>(t, a, k_scale, v_scale, addr, live, lane);
+        load_pair_tiles<FP8, STAGE, kKeys | kValues>(t, a, k_scale, v_scale, addr, live, lane);
         next_x += stride;
     };
     auto issue = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
@@ -665,9 +662,11 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
         next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
     };
     // in two halves, where the keys' registers are free before the values' (STAGE)
-    auto issue_keys = [&](PairRegs<FP8> &t) __attribute__((always_inline)) { load_pair_keys<FP8, STAGE>(t, a, next_addr, next_x < x1, lane); };
+    auto issue_keys = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
+        load_pair_tiles<FP8, STAGE, kKeys>(t, a, k_scale, v_scale, next_addr, next_x < x1, lane);
+    };
     auto issue_values = [&](PairRegs<FP8> &t) __attribute__((always_inline)) {
-        load_pair_values<FP8>(t, a, k_scale, v_scale, next_addr, next_x < x1, lane);
+        load_pair_tiles<FP8, STAGE, kValues>(t, a, k_scale, v_scale, next_addr, next_x < x1, lane);
         next_x += stride;
         next_addr = pair_addr[next_x < x1 ? next_x : x1 - 1];
     };
@@ -677,8 +676,7 @@ __device__ __forceinline__ void walk(const AttnArgs &a, StreamLds<BLOCKS> &lds, 
     // memory), with the wavefront standing still while its loads are accepted.  With STAGE the tiles are read in the order of memory and turned
     // here, through the wavefront's own place in LDS.  Rows stand one 16-byte word further apart than they are long, so that neither
     // side meets a bank twice.
-    // Where it pays: e4m3 caches, three row blocks and more, batches that may be served by wavefronts' spans (96 requests of 512..8192 tokens, 64 heads
-    // over 8, depth 2..8: 221 -> 213 us, depth 2..4 193 -> 175; 96 trees of 8..16 nodes, 32 heads 213 -> 207).  With fewer units the
+    // Where it pays: e4m3 caches and batches that may be served by wavefronts' spans; the rule stands at launch_stream.  With fewer units the
     // round trip through LDS costs what the reads gain (20 requests 58.6 / 58.7, trees 58.0 / 59.2), with one or two row blocks more (159.1 / 160.5).
     // bf16 keys are twice the LDS traffic: 64 requests of 256..4096 105.5 / 106.6, 128 of 128..16384 276.4 / 277.3 at best.
     constexpr int KROW = (FP8 ? 8 : 16) + 1, KSEG = FP8 ? 8 : 16;   // 16-byte words of a row in LDS, in memory
@@ -1046,7 +1044,8 @@ __device__ __forceinline__ void walk_classes(const AttnArgs &a, StreamLds<BLOCKS
 // BLOCKS  the most 16-row blocks of query rows a unit can have
 // MIXED   more than two row blocks: the spans may be wavefronts' as well as teams' (with fewer than two units to a team they never
 //         are, and the code of a team alone is 0.5 to 0.8 us faster in a call of 16 us)
-template <int G, int BLOCKS, bool FP8, bool TREE, bool MIXED>
+// STAGE   keys turned through LDS (see stage_keys)
+template <int G, int BLOCKS, bool FP8, bool TREE, bool MIXED, bool STAGE>
 __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
     AttnArgs a, const AttnPlan *__restrict__ plan, const int2 *__restrict__ pair_addr, const int32_t *__restrict__ wave_desc,
     const AttnReq *__restrict__ req, const float *__restrict__ k_scale, const float *__restrict__ v_scale)
@@ -1086,7 +1085,7 @@ __global__ __launch_bounds__(64 * kWavesPerWg, 1) void attn_stream_kernel(
         asm volatile("" : "+s"(run.p), "+s"(run.g), "+s"(run.b), "+s"(run.n), "+s"(run.x0), "+s"(run.unit_x), "+s"(run.L), "+s"(run.q0), "+s"(run.q1), "+s"(cls), "+s"(class_end));
         asm volatile("" : "+s"(run.addr[0].x), "+s"(run.addr[0].y), "+s"(run.addr[1].x), "+s"(run.addr[1].y), "+s"(run.addr[2].x), "+s"(run.addr[2].y));
         if (run.x0 >= run.x1) return;
-        walk_classes<G, BLOCKS, FP8, TREE, FP8 && MIXED>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
+        walk_classes<G, BLOCKS, FP8, TREE, STAGE>(a, lds, run, team, cls, class_end, plan, pair_addr, req, k_scale, v_scale);
     }
 }
 
@@ -1176,7 +1175,18 @@ int32_t launch_stream(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hip
     // When a profile is being taken the two events are attached to the dispatch itself, so that
     // their difference is the kernel's own duration on this stream (what a kernel trace shows).
     const bool few = BLOCKS > kChainRowBlocks && (long long)a.batch * a.num_kv_heads < 2 * (a.launch_waves / kWavesPerWg);
-    const auto kernel = few ? attn_stream_kernel<G, BLOCKS, FP8, TREE, BLOCKS <= kChainRowBlocks> : attn_stream_kernel<G, BLOCKS, FP8, TREE, true>;
+    // Keys turned through LDS or read as operands, where a call may have two units to a team (direct / turned, 64 heads over 8 unless said; the
+    // two forms in turn).  Up to three row blocks from 24 tiles on: 300 requests of 20..100 tokens, depth 2..4, 49.8 / 50.2 us, of 50..500 76.0 /
+    // 73.6, of 100..1000 114.3 / 106.8, 96 of 512..8192 196.7 / 179.3.  With four and five the turn costs what the reads gain while a call is
+    // short (depth 2..8: 160 of 20..1300 61.9 / 63.2, 300 of 50..500 89.9 / 91.4, 80 of 300..3000 97.0 / 97.7) and pays from 256 tiles of table to a
+    // wavefront on (64 of 512..8192 159.8 / 154.1, 96 223.5 / 216.9, 500 of 100..1500 242.9 / 232.3; 96 trees of 8..16 nodes, 32 heads, 213.5 / 208.4;
+    // all requests at depth 8, every unit of five row blocks, 230.8 / 233.9 and 266.2 / 266.7, which the bound of the rows does not tell).
+    constexpr bool CLASSES = BLOCKS > kChainRowBlocks;
+    const bool deep = a.q_win * G > 48;
+    const bool stage = FP8 && CLASSES && !few && (deep ? (long long)a.batch * a.num_kv_heads * a.max_blocks >= 256ll * a.launch_waves : a.max_blocks >= 24);
+    const auto kernel = few     ? attn_stream_kernel<G, BLOCKS, FP8, TREE, !CLASSES, false>
+                        : stage ? attn_stream_kernel<G, BLOCKS, FP8, TREE, true, FP8 && CLASSES>
+                                : attn_stream_kernel<G, BLOCKS, FP8, TREE, true, false>;
     hipExtLaunchKernelGGL(kernel, dim3((unsigned)(a.launch_waves / kWavesPerWg)),
                           dim3(64 * kWavesPerWg), 0, stream, ev0, ev1, 0, a, a.plan, a.pair_addr, a.wave_desc, a.req, a.k_scale,
                           a.v_scale);

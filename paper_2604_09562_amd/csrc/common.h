@@ -107,10 +107,10 @@ struct AttnArgs {
     float *part_ml;        // [slots][rows_pad][2]  (log2-domain max, sum)
     int32_t rows_pad;      // query rows per (request, kv head), padded to 16
     int32_t launch_waves;  // upper bound of streaming wavefronts (sizes the partial slots)
-    int32_t default_waves; // launch_waves is one wavefront per SIMD of this GPU, given or not
     int32_t unit_weight;   // what opening a unit costs a wave, in pairs (weights the span cuts; 0 = equal pair counts)
     int32_t auto_weight;   // unit_weight is the default: classes take the weights measured for their row blocks
     int32_t team_blocks;   // row blocks of the team kernel that is launched, 0 for the kernels of one or two
+    int32_t default_waves; // launch_waves is one wavefront per SIMD of this GPU, given or not
 };
 
 size_t attn_workspace_bytes(int batch, int max_blocks, int num_q_heads, int num_kv_heads, int head_dim,

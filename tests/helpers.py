@@ -31,3 +31,10 @@ def softmax64(logits, T):
     z = np.asarray(logits, dtype=np.float64) / float(T)
     w = np.exp(z - z.max())
     return w / w.sum()
+
+
+def wider(inp, columns):
+    """The same batch with a block table of more columns; what stands there may be anything."""
+    table = np.full((inp["batch"], columns), 0x7FFFFFFF, np.int32)
+    table[:, :inp["block_table"].shape[1]] = inp["block_table"]
+    return dict(inp, block_table=table, max_blocks_per_seq=columns)
