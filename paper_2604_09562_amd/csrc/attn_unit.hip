@@ -2,7 +2,7 @@
 // or two where the streaming kernels take a plan, a stream and a merge, each a chain of dependent reads.
 //
 // Serves the calls of the matrix-core kernels (head_dim 128, bf16 queries, bf16 or e4m3 caches, groups of 1/2/4/8) in which no unit can be
-// long; the rule stands at attn_unit_choose.
+// long; the rule stands in unit_rule.h.
 //
 // What bounds it: the chain of lengths, block ids, tiles, exchange and rows written (6 us for 64 tokens, launch included); beyond a few steps
 // what a compute unit gets out of memory, about 60 GB/s while the chip is not full.
@@ -44,7 +44,6 @@ constexpr int D = kMfmaHeadDim;
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr float kNoMax = -1.0e30f;   // reference before any score was seen, as in attn_mfma_kernels.h
 constexpr int kNonTemporal = 2;                     // tiles are read once
-constexpr int kMaxShares = 16;                      // workgroups of a unit
 constexpr int kRowStride = 17;                      // 16-byte words from one bf16 row to the next in LDS (16 and one of padding)
 constexpr int kHalfRow = 17;                        // float4 from one row of a staged half block to the next (16 and one of padding)
 
@@ -538,8 +537,9 @@ __global__ __launch_bounds__(64 * TEAM, 2) void attn_unit_kernel(AttnArgs a, int
     __shared__ UnitLds<TEAM> lds;
     Unit u;
     if ((int)blockIdx.x >= a.batch * a.num_kv_heads * splits) {
-        // The workgroups behind the units' leave the plan in the workspace, as every call does that does not reuse one: a later call that
-        // may take the streaming kernels finds it.  They run beside the others (4 requests of 64 tokens 6.1 us, 64 of 8..64 12.8, and 9.4 without).
+        // The workgroups behind the units' leave the plan in the workspace, as every call does that does not reuse one.  (A call that reuses it has
+        // the same sizes, so it takes this path again and does not read it.)  They run beside the others (4 requests of 64 tokens 6.1 us, 64 of
+        // 8..64 12.8, and 9.4 without).
         if (threadIdx.x >= 256) return;
         const int block = blockIdx.x - a.batch * a.num_kv_heads * splits;
         Place *places = reinterpret_cast<Place *>(&lds.p[0][0][0][0]);
@@ -634,45 +634,13 @@ void launch(const AttnArgs &a, int group_log, int splits, hipStream_t stream, hi
 
 }  // namespace
 
-// Which calls take this path, and how: from what the host knows, the units and the width of the block table.  Batches whose plan takes a kernel
-// in front are left to the streaming kernels.
-//
-// Measured in captured graphs, us a call, plan + stream + merge against this path, 8 KV heads, depth 0 .. 8, lengths uniform in hi / 8 .. hi (u) or
-// uniform in the logarithm from hi / 50 on (l); 32 heads bf16, then 64 heads e4m3:
-//   one workgroup a unit   4 requests, hi 64 u  13.1 / 6.7  16.4 / 8.8    hi 600 u  16.4 / 12.8  20.5 / 16.2    32, hi 768 u  26.9 / 15.7  28.9 / 17.4
-//                          64, hi 64 u  25.1 / 12.8  31.6 / 15.3    64, hi 1000 u  45.6 / 34.0  47.5 / 36    160, hi 1000 l  56.2 / 44.0
-//   several                4, hi 8000 u  28.8 / 20.9  27.4 / 22.1    8, hi 4000 u  27.8 / 22.5  28.4 / 26.4    16, hi 2000 l  21.4 / 17.6  24.5 / 19.9
-// Where the line lies: a unit is walked by its workgroups alone, so a batch of very different lengths waits for its longest units, which the
-// plan's spans share out.  Beyond the limits (with references that lag, a little faster than now): 8 requests, hi 8000 (four workgroups of up to
-// 128 tiles) u 35.0 / 36.6; 32, hi 2000 l 30.5 / 28.6, hi 4000 l 44.1 / 50.3; 64, hi 2000 u 63.8 / 59.3, hi 4000 l 61.5 / 62.9; 40 (320 units: the
-// last of them alone on the chip), hi 2000 u 46.3 / 49.1, five row blocks hi 1000 35.4 / 37.5.  250 requests of 8..64 39.7 / 39.3: from six units
-// to a compute unit on the workgroups that leave the plan take what the path gains.
-// A second workgroup of a unit costs the merge, 3 us with its launch: up to 48 tiles one is as fast (4 of 40..600 tokens 10.4, with two 10.5).
-// Eight wavefronts or four: with four the chip holds two workgroups to a compute unit, and a unit of few tiles begins and ends sooner (32 requests of 64
-// tokens 8.1 / 6.2, 64 12.7 / 7.2); eight walk a long unit faster from four row blocks on, where a step is bound by its instructions (32 of 2000
-// tokens, five row blocks, e4m3 41.6 / 48.0; three bf16 44.9 / 44.3).  The same with several workgroups to a unit (eight / four, the merge included: two row
-// blocks bf16, 4 requests of 500..4000 16.4 / 14.6, 8 of 187..1500 15.8 / 14.1, 16 of 250..2000 22.7 / 22.9; five e4m3 22.7 / 25.9, 18.2 / 19.1, 31.3 / 37.6).
-constexpr int kUnitTiles = 48, kUnitTilesFew = 80, kUnitTilesMany = 64, kShareTiles = 64, kUnitsPerCu = 6;
+// Batches whose plan takes a kernel in front are left to the streaming kernels; the rule itself is in unit_rule.h.
 AttnUnitChoice attn_unit_choose(const AttnArgs &a)
 {
-    AttnUnitChoice c = {0, 0};
     const long long units = (long long)a.batch * a.num_kv_heads;
-    const int cus = a.launch_waves / kWavesPerWg, group = a.num_q_heads / a.num_kv_heads;
-    if (!a.default_waves || a.max_q_len * group > 16 * kMaxRowBlocks || plan_laid_out(a) || units > kUnitsPerCu * cus) return c;
-    const int tiles = a.max_blocks;
-    const bool deep = a.max_q_len * group > 48;   // four or five row blocks
-    int splits = 1;
-    if (tiles > kUnitTiles && 2 * units <= cus) {
-        splits = (int)(cus / units);
-        splits = splits < kMaxShares ? splits : kMaxShares;
-        splits = splits < (tiles + 15) / 16 ? splits : (tiles + 15) / 16;
-        if ((tiles + splits - 1) / splits > kShareTiles) return c;
-    } else if (tiles > (units <= cus ? kUnitTilesFew : deep && units < 2 * cus ? kUnitTiles : kUnitTilesMany)) {
-        return c;
-    }
-    c.splits = splits;
-    c.team = units <= cus && ((tiles > 16 && deep) || (tiles > kUnitTiles && a.kv_dtype == SS_FP8_E4M3)) ? 8 : 4;
-    return c;
+    const int cus = a.launch_waves / kWavesPerWg, rows = a.max_q_len * (a.num_q_heads / a.num_kv_heads);
+    if (!a.default_waves || rows > 16 * kMaxRowBlocks || plan_laid_out(a) || units > kUnitsPerCu * cus) return {0, 0};
+    return attn_unit_rule(units, a.max_blocks, rows, a.kv_dtype == SS_FP8_E4M3, cus);
 }
 
 int32_t attn_unit_launch(const AttnArgs &a, const AttnUnitChoice &choice, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1)

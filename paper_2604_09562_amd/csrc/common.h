@@ -7,6 +7,7 @@
 
 #include "specverify.h"
 #include "span_cuts.h"
+#include "unit_rule.h"
 
 namespace ss {
 
@@ -128,9 +129,6 @@ int32_t attn_mfma_launch_g2(const AttnArgs &a, hipStream_t stream, hipEvent_t ev
 int32_t attn_mfma_launch_g4(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 int32_t attn_mfma_launch_g8(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 // Calls whose units are all short: a workgroup (or `splits` of them, of `team` wavefronts) per unit, without a plan (attn_unit.hip).
-struct AttnUnitChoice {
-    int splits, team;   // splits 0: the call is not one of them
-};
 AttnUnitChoice attn_unit_choose(const AttnArgs &a);
 int32_t attn_unit_launch(const AttnArgs &a, const AttnUnitChoice &choice, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);
 int32_t attn_generic_launch(const AttnArgs &a, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1);

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from paper_2604_09562_amd import binding, synth
+from tests.helpers import STREAM_COLUMNS, unit_choice, wider
 from tests.test_gpu_attn import check
 
 pytestmark = pytest.mark.gpu
@@ -22,15 +23,8 @@ def inputs(kv, hq, hkv, lens, top, seed, tree):
     return synth.make_attention_inputs(cfg, seed=seed, kv_len=lens, depth=depth.astype(np.int32), tree=tree, nan_tail=True)
 
 
-def wider(inp, columns):
-    """The same batch with a block table of more columns; what stands there may be anything."""
-    table = np.full((inp["batch"], columns), 0x7FFFFFFF, np.int32)
-    table[:, :inp["block_table"].shape[1]] = inp["block_table"]
-    return dict(inp, block_table=table, max_blocks_per_seq=columns)
-
-
-# longest request, batch, KV heads (256 compute units): one workgroup a unit up to 48 tiles, several beyond it as long as there are twice as many
-# compute units, up to 64 tiles each; one for 80 tiles beside many units, for 64 (48 with four row blocks) in more units than compute units
+# longest request, batch, KV heads (256 compute units), on both sides of where the rule (unit_rule.h) takes another number of workgroups to a
+# unit, other teams or the streaming kernels; the batches' row bounds move some of the lines
 SHAPES = [(700, 14, 2), (769, 14, 2), (900, 14, 2), (1025, 1, 8), (4000, 4, 8), (9000, 14, 1), (16400, 2, 8), (1280, 33, 8), (1281, 33, 8),
           (768, 40, 8), (1024, 40, 8), (1025, 40, 8), (300, 65, 8)]
 
@@ -46,15 +40,30 @@ def test_shapes(oracle, longest, batch, hkv, group, top, kv, tree):
     check(inp, oracle, requests=some, max_q_len=top + 1, label=f"{longest} x {batch} over {hkv}")
 
 
+@pytest.mark.parametrize("kv,tree", [("bf16", False), ("fp8", True)])
+@pytest.mark.parametrize("group,top", [(4, 3), (8, 9)])                  # one and five row blocks
+@pytest.mark.parametrize("longest,batch,hkv,shares", [                   # (bf16, e4m3), one and five row blocks
+    (384, 4, 8, (1, 1, 1, 1)), (400, 4, 8, (4, 4, 1, 1)), (512, 4, 8, (4, 4, 1, 1)), (528, 4, 8, (5, 5, 5, 5)),      # 24, 25, 32, 33 tiles
+    (1024, 4, 8, (8, 8, 8, 8)), (1040, 4, 8, (5, 5, 5, 5)), (768, 8, 8, (3, 1, 1, 1)), (784, 8, 8, (4, 4, 4, 4)),    # 64, 65; 48, 49
+    (1024, 12, 8, (2, 2, 1, 1)), (1056, 12, 8, (2, 0, 2, 0)), (6160, 4, 8, (8, 0, 8, 0))])
+def test_lines_of_the_rule(oracle, longest, batch, hkv, shares, group, top, kv, tree):
+    lens = (EDGES * 6)[:batch - 1] + [longest]
+    inp = inputs(kv, group * hkv, hkv, lens, top, seed=longest + top, tree=tree)
+    assert unit_choice(inp, top + 1)[0] == shares[2 * (kv == "fp8") + (group == 8)]
+    check(inp, oracle, max_q_len=top + 1, label=f"{longest} x {batch} over {hkv}")
+
+
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 @pytest.mark.parametrize("group,top", [(4, 4), (4, 10), (8, 9)])
-@pytest.mark.parametrize("longest,batch,hkv", [(700, 14, 2), (3000, 6, 4), (1000, 40, 8)])
+@pytest.mark.parametrize("longest,batch,hkv", [(700, 14, 2), (3000, 6, 4), (1000, 40, 8), (1000, 66, 8)])
 def test_against_the_streaming_kernels(longest, batch, hkv, group, top, kv):
     """Two correct results: bf16 outputs of which each is within a rounding or two of the other's, 32-bit lse."""
-    lens = (EDGES * 3)[:batch - 1] + [longest]
+    lens = (EDGES * 5)[:batch - 1] + [longest]
     inp = inputs(kv, group * hkv, hkv, lens, top, seed=1, tree=False)
     got = []
-    for i in (inp, wider(inp, 1100 if 2 * batch * hkv <= 256 else 90)):
+    # (320 units of five row blocks are left to the streaming kernels either way)
+    assert bool(unit_choice(inp, top + 1)[0]) == ((batch, group) != (40, 8)) and not unit_choice(wider(inp, STREAM_COLUMNS), top + 1)[0]
+    for i in (inp, wider(inp, STREAM_COLUMNS)):
         d = binding.attention_to_device(i)
         out, lse, ws = binding.alloc_attention_outputs(d, max_q_len=top + 1)
         binding.ss_spec_verify_attn(d, out, lse, ws, max_q_len=top + 1)
