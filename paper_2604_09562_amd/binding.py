@@ -147,7 +147,10 @@ def _ptr(t: Optional[torch.Tensor]) -> int:
 
 def _stream() -> int:
     if torch.cuda.is_initialized():   # (the current stream of the current device, without an object around it)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:        # (neither is part of torch's public interface)
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 

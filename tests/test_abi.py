@@ -107,3 +107,15 @@ def test_options(L):
     assert L.ss_set_option(b"attn_unit_weight", 3) == 0    # back to the default
     assert L.ss_set_option(b"no_such_option", 1) == 1
     assert L.ss_set_option(None, 1) == 1
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_stream_without_torch_private_functions(monkeypatch, missing):
+    """The stream handle comes from torch's public interface where the private one lacks a function."""
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=1234))
+    assert binding._stream() == 1234
