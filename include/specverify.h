@@ -25,7 +25,8 @@
  *   - "device" pointers are HIP device memory on the current device, "host"
  *     pointers ordinary host memory.  The caller owns every buffer, including
  *     the workspace; the library allocates no device memory, frees nothing and
- *     keeps no state between calls (except the optional profiling events).
+ *     keeps no state between calls (except the optional profiling events and the
+ *     number of compute units of each GPU).
  *   - Work is enqueued on `stream` (a hipStream_t passed as void*, NULL = the
  *     default stream) and the call returns without synchronising.
  *   - Return value: SS_OK or an ss_status error; ss_last_error() gives the
@@ -88,6 +89,11 @@ typedef struct ss_paged_kv {
  * One decode-lane batch.
  *   block_table  device int32 [batch][max_blocks_per_seq]: logical block j of request b
  *                is physical block block_table[b][j]; entries past ceil(kv_len/16) are ignored.
+ *   max_blocks_per_seq  host value: the table's width, and the only bound of the lengths that the library knows on
+ *                the host.  Verify attention serves batches of few or short requests with other kernels,
+ *                chosen from this width (with 8 KV heads up to 80 blocks, for few requests more) and up to
+ *                twice as fast; a table as wide as the longest request of the step takes them, one as
+ *                wide as the longest context that could come never does.
  *   kv_len       device int32 [batch]: valid cache positions of each request, INCLUDING the
  *                q_len new tokens of this step, whose K/V the caller has already appended.
  *   q_indptr     device int32 [batch+1]: request b owns query rows q_indptr[b]..q_indptr[b+1]-1

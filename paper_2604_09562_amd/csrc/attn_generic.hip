@@ -240,11 +240,12 @@ __global__ __launch_bounds__(64 * kGenericWaves<D>) void attn_generic_kernel(Att
     for (int i = tid; i < 16 * D; i += 64 * NW) {
         const int r = __builtin_amdgcn_readfirstlane(i / D), d = i % D, nn = rb * 16 + r;   // (a wavefront's 64 elements are of one row)
         if (nn >= rows) continue;
-        // lane w has what wavefront w's part weighs
-        const float pm = part_m[min(lane, used - 1)][r], pl = part_l[min(lane, used - 1)][r];
+        // lane w of every NW has what wavefront w's part weighs
+        const int part = min(lane & (NW - 1), used - 1);
+        const float pm = part_m[part][r], pl = part_l[part][r];
         float gm = pm;
 #pragma unroll
-        for (int x = 1; x < NW; x *= 2) gm = fmaxf(gm, __shfl_xor(gm, x));   // (every lane group of NW holds all of them)
+        for (int x = 1; x < NW; x *= 2) gm = fmaxf(gm, __shfl_xor(gm, x));   // (every group of NW lanes holds all of them)
         const float sc = expf(pm - gm);
         float ls = 0.f, o = 0.f;
         float po[NW];

@@ -71,16 +71,13 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y)
     const float2v v = {x, y};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-// The maximum over the four rows of 16 lanes.  (Written out: from the compiler's builtins for these exchanges the second result comes back as a
-// copy of the first, ROCm 7.2.0.  The wait states are those it puts in front of them itself.)
+// The maximum over the four rows of 16 lanes.
 __device__ __forceinline__ float max_over_rows(float x)
 {
-    float y = x;
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y));
-    x = fmaxf(x, y);
-    y = x;
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y));
-    return fmaxf(x, y);
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1]));
+    const auto rows = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(rows[0]), __uint_as_float(rows[1]));
 }
 // Waits for this wavefront's LDS accesses only (not for the tiles in flight), then for the others.
 __device__ __forceinline__ void team_barrier()
