@@ -308,9 +308,10 @@ __global__ __launch_bounds__(kThreads) void accept_decide_kernel(AcceptArgs a, W
 }
 
 // ---- pass 2a: fp64 sums per block -------------------------------------------------------------
-// One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  Bound by the instructions of an entry (25 fp64 ones
-// and 14 others per pair): the four sums cross the lanes together and by data-parallel moves, the power of two goes into the table's
-// exponent, and which lanes are near the boundary stays in scalar registers.  Measured for 64 requests of 128256 entries: 22.7 us with
+// One 256-lane workgroup per 2048-entry block, eight entries of each row per lane.  The instructions of an entry (25 fp64 ones and 14
+// others per pair) are 8 to 11 of the 17.5 us below at 4 to 5.5 cycles each; the rest is not issue: each workgroup waits for its request's record, then
+// its rows and the table, before it computes.  The four sums cross the lanes together and by data-parallel moves, the power of two goes into
+// the table's exponent, and which lanes are near the boundary stays in scalar registers.  Measured for 64 requests of 128256 entries: 22.7 us with
 // shuffles through LDS and ldexp, 20.3 with data-parallel moves and 32 fp64 instructions per pair, 19.2 with 26 of them, a scan per sum and
 // the boundary test in vector registers, 17.5 this way (the call 56.8 -> 55.3); two wavefronts per block 22.3, one 21.5 (and 6.8, 11.5
 // against 4.9 us for 8 requests of 32000: a wavefront that walks a block alone is a long chain); all 32 entries of a lane as
