@@ -114,7 +114,7 @@ def test_keys_turned_through_lds(oracle, hq, top, lo, hi, mode, tree):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
-def test_short_and_wide_tables_agree_on_replays():
+def test_replays_with_a_wide_table():
     """Captured calls of the streaming kernels at a size the short-unit kernels would serve replay to the eager bits."""
     inp = wide_inputs("bf16", 32, 8, [40, 300, 2000, 3900], 8, seed=3)
     d = binding.attention_to_device(inp)
